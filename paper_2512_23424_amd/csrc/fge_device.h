@@ -54,6 +54,17 @@ __device__ __forceinline__ void lds_dma16(const void *base, uint32_t lane_off, u
     default: asm volatile("global_load_lds_dwordx4 %0, %1 offset:3072" :: "v"(lane_off), "s"(base) : "memory"); break;
     }
 }
+// The same for the lanes of `mask` only (a wave-uniform value; all 64 lanes must be active here).  An
+// empty mask moves nothing, but the instruction is issued and counted all the same.
+__device__ __forceinline__ void lds_dma16_masked(const void *base, uint32_t lane_off, uint32_t lds_addr, int step, bool set_base, uint64_t mask) {
+    if (set_base) asm volatile("s_mov_b32 m0, %0" :: "s"(lds_addr) : "memory");
+    if (step == 0)
+        asm volatile("s_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                     :: "v"(lane_off), "s"(base), "s"(mask) : "memory");
+    else
+        asm volatile("s_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\ts_mov_b64 exec, -1"
+                     :: "v"(lane_off), "s"(base), "s"(mask) : "memory");
+}
 __device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---------------------------------------------------------------- storage conversion

@@ -139,6 +139,11 @@ void tile_kernel(const TileArgs a) {
     // give a CU no second workgroup to hide the latency with.
     static_assert(STAGES == 0 || (STAGES > 2 && !SPLIT && !GATED), "extra stage buffers: plain 16- and 8-bit tiles");
     constexpr bool DEEP = STAGES > 2 || (BM == 64 && BN == 64 && !SPLIT && !COOP);
+    // QUAD: the mainloop by output quadrants (see there); A buffers first, then B buffers, so that
+    // every fragment read is a lane address plus an immediate offset
+    constexpr bool QUAD = BM == 256 && BN == 256 && NT == 512 && MB == 4 && NB == 2 && !SPLIT && STAGES == 0;
+    constexpr int A_STEP = QUAD ? BM * ROWB : STAGE, B_STEP = QUAD ? BN * ROWB : STAGE;    // bytes between stage buffers
+    constexpr int B_AT = QUAD ? 2 * BM * ROWB : BM * ROWB;                                 // first B buffer
     constexpr int NST = STAGES > 2 ? STAGES : DEEP ? 4 : 2;
 
     __shared__ __attribute__((aligned(16))) unsigned char smem[NST * STAGE];
@@ -203,25 +208,27 @@ void tile_kernel(const TileArgs a) {
 
     // ---------------- global -> LDS staging plan
     // A copy instruction of a wave fills 1024 contiguous LDS bytes = 8 panel rows (lane l lands at
-    // base + 16*l).  Wave w stages the 8*A_LD rows of the A panel from row w*8*A_LD on and the
-    // 8*B_LD rows of the B panel from row w*8*B_LD on, copy i the rows 8i .. 8i+7 of those: the
-    // copies of an operand land 1024 bytes apart, which the instruction's own 12-bit offset
-    // reaches - it moves the LDS address and the global address alike, so the lane offset of copy
-    // i is lowered by the same amount -, and one write of the LDS base register serves four
-    // copies.  Rows past the end of X / W are clamped to the last valid row: they only feed
-    // outputs that are never stored or counted.  Only a partial last K tile needs zero fill; it
-    // goes through registers.
+    // base + 16*l), and copy i of an operand lands 1024 bytes behind copy i - 1 within a run of RUN
+    // copies: the instruction's own 12-bit offset moves the LDS address and the global address
+    // alike, so the lane offset of copy i is lowered by the same amount and one write of the LDS
+    // base register serves the run.  Rows past the end of X / W are clamped to the last valid
+    // row: they only feed outputs that are never stored or counted.  Only a partial last K tile
+    // needs zero fill; it goes through registers.
+    // Which rows a wave stages: rows w*8*A_LD .. of the A panel and w*8*B_LD .. of the B panel; QUAD:
+    // 16 rows of each half of either panel.  A half of the A panel holds the upper (lower) 64 of
+    // each wave's 128 rows, a half of the B panel the first (second) 32 of each wave's 64 columns -
+    // gated: 32 columns of the first product, the same 32 of the second.
     // The lane at (row, physical chunk c) of the panel fetches global chunk c ^ swizzle(row): the
     // LDS image of a wave's 64 chunks is then the 1024 contiguous bytes a copy writes.
     const int ld_r = (tid & 63) >> 3, ld_c = tid & 7;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int PRE = 3072;                         // bytes the scalar bases start early (keeps lane offsets >= 0)
-    static_assert(!GATED || BNO % (8 * B_LD) == 0, "a wave's B rows come from one matrix");
-    // gated: the waves whose B rows lie at or beyond BNO stage the same rows of W2
-    const bool second = GATED && wave_id * 8 * B_LD >= BNO;
+    constexpr int RUN = QUAD ? 2 : 4;
+    static_assert(!GATED || QUAD, "the gated form runs on the quadrant mainloop");
     const unsigned char *Xt = reinterpret_cast<const unsigned char *>(X + (int64_t)m0 * a.ldx) - PRE;
-    const unsigned char *Wt = reinterpret_cast<const unsigned char *>(
-                                  (second ? reinterpret_cast<const InT *>(a.W2) + (int64_t)z * a.bsw : W) + (int64_t)n0 * a.ldw) - PRE;
+    const unsigned char *Wt = reinterpret_cast<const unsigned char *>(W + (int64_t)n0 * a.ldw) - PRE;
+    const unsigned char *W2t = GATED ? reinterpret_cast<const unsigned char *>(
+                                           reinterpret_cast<const InT *>(a.W2) + (int64_t)z * a.bsw + (int64_t)n0 * a.ldw) - PRE : Wt;
     // A copy's global address is a scalar base (first row of the tile, current k) plus the lane's
     // byte offset from it, which does not change along K: 32 bits (the host keeps tiles whose
     // rows span 2 GB or more off this kernel).
@@ -229,16 +236,20 @@ void tile_kernel(const TileArgs a) {
     int rowA[A_LD], rowB[B_LD], gcA[A_LD], gcB[B_LD];  // panel row and global chunk of this lane per copy
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        rowA[i] = wave_id * 8 * A_LD + i * 8 + ld_r;
+        const int in_half = wave_id * 16 + (i & 1) * 8 + ld_r;
+        rowA[i] = QUAD ? (i >> 1) * 128 + in_half : wave_id * 8 * A_LD + i * 8 + ld_r;
+        const int row = QUAD ? (in_half >> 6) * 128 + (i >> 1) * 64 + (in_half & 63) : rowA[i];     // row of the tile
         gcA[i] = ld_c ^ swz(rowA[i]);
-        oA[i] = (uint32_t)((int64_t)(min(m0 + rowA[i], a.M - 1) - m0) * a.ldx + gcA[i] * CW) * (uint32_t)sizeof(InT) + PRE - (i & 3) * 1024;
+        oA[i] = (uint32_t)((int64_t)(min(m0 + row, a.M - 1) - m0) * a.ldx + gcA[i] * CW) * (uint32_t)sizeof(InT) + PRE - (i % RUN) * 1024;
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
-        rowB[i] = wave_id * 8 * B_LD + i * 8 + ld_r;
+        const int in_half = wave_id * 16 + (i & 1) * 8 + ld_r;
+        rowB[i] = QUAD ? (i >> 1) * 128 + in_half : wave_id * 8 * B_LD + i * 8 + ld_r;
+        const int row = GATED ? in_half                                                             // row of W (or of W2)
+                        : QUAD ? (in_half >> 5) * 64 + (i >> 1) * 32 + (in_half & 31) : rowB[i];
         gcB[i] = ld_c ^ swz(rowB[i]);
-        const int prow = rowB[i] - (second ? BNO : 0);   // row of W (gated: or of W2) in the tile
-        oB[i] = (uint32_t)((int64_t)(min(n0 + prow, a.w_rows - 1) - n0) * a.ldw + gcB[i] * CW) * (uint32_t)sizeof(InT) + PRE - (i & 3) * 1024;
+        oB[i] = (uint32_t)((int64_t)(min(n0 + row, a.w_rows - 1) - n0) * a.ldw + gcB[i] * CW) * (uint32_t)sizeof(InT) + PRE - (i % RUN) * 1024;
     }
 
     // full tile: asynchronous global -> LDS, no registers involved; completion is tracked by
@@ -277,10 +288,7 @@ void tile_kernel(const TileArgs a) {
     };
 
     // ---------------- fragment read plan
-    // B fragment of column block j sits FB_STEP panel rows below block 0's (gated: the second
-    // product's rows start BNO rows down)
-    constexpr int FB_STEP = GATED ? BNO : 32;
-    const int fa_row = wave_m * WTM + l32, fb_row = wave_n * (GATED ? 32 : WTN) + l32;
+    const int fa_row = wave_m * (QUAD ? 64 : WTM) + l32, fb_row = wave_n * (QUAD ? 32 : WTN) + l32;
     // chunk pair u (0..3) of a panel row: lanes 0-31 take chunk 2u, lanes 32-63 chunk 2u+1.
     // A k-step consumes FR pairs.  Which k land in which lane and slot does not matter as long
     // as both operands use the same assignment - the sum over k is complete either way.
@@ -413,6 +421,165 @@ void tile_kernel(const TileArgs a) {
     }
     compute.template operator()<false>(kt & 1);
     __syncthreads();                                  // the epilogue reuses the panel memory
+    } else if constexpr (QUAD) {
+    // ---------------- mainloop by output quadrants (256x256 tiles)
+    // A wave's 128 x 64 outputs are multiplied as four quadrants of 64 x 32, each over the whole
+    // K tile: (A0,P) (A0,Q) (A1,Q) (A1,P), where A0 / A1 are the upper / lower half of its rows and P
+    // / Q its two column blocks.  Half a panel then is read by all waves within one quadrant's
+    // time instead of throughout the K tile, its buffer is free again as soon as that quadrant
+    // is multiplied, and the copy that refills it (two K tiles ahead) has a whole K tile's time
+    // to arrive - with the k-steps running over the whole tile it had half of that, every copy was
+    // issued and awaited inside one K tile, and the waits for them took a third of the loop.
+    // Fragments: one register set per operand half.  The next half's fragments are read into the
+    // registers of the current one, each right behind the last MFMA that uses it, and are needed
+    // a quadrant later; P and Q swap roles every K tile (the block multiplied last, next to an A
+    // half that is about to change, frees its registers last), so a quadrant issues 4 or 8
+    // reads, never 12.
+    // Two barriers per K tile, each in front of a quadrant's last k-step, when the fragments of
+    // the halves it releases have all arrived (they have been waited for by the MFMAs so far) and
+    // MFMAs with ready operands are left to issue right behind it:
+    //   beta  in (A0,P): releases A0 and P of this tile  -> copies of A0, P of tile kt+2 issue behind it
+    //   alpha in (A1,Q): releases A1 and Q of this tile  -> copies of A1, Q of tile kt+2 issue behind it
+    // What is read between beta(kt) and alpha(kt) - A1 of kt, the first column block of kt+1 - was
+    // issued no later than beta(kt-1), what is read between alpha(kt) and beta(kt+1) - A0 and the
+    // second block of kt+1 - no later than alpha(kt-1): three pairs of copies are younger in both
+    // cases, so the wait in front of a barrier is for all but the last six copies of the wave.
+    // Against the k-step order: 8192 x 4096 x 4096 SiLU + RMSNorm bf16 235.6 -> 224.8 us, 8-bit 131 ->
+    // 123 us, 16 x 2048 x 512 x 2048 softmax 148.9 -> 142.3 us, logits 2048 x 4096 x 50257 990 -> 922 us.
+    // What bounds it now is power: without copies, without barriers or without fragment reads the
+    // launch takes the same 365 K cycles, only at 1.8 to 2.3 GHz instead of 1.73.
+    constexpr int NMQ = 2 * KS;                       // MFMAs per quadrant: k-steps x two row blocks
+    constexpr int LASTK = NMQ - 2;                    // first MFMA of the last k-step
+    const unsigned char *baseA = smem + fa_row * ROWB, *baseB = smem + B_AT + fb_row * ROWB;
+    const unsigned char *pA[4], *pB[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { pA[u] = baseA + fsw[u]; pB[u] = baseB + fsw[u]; }
+    u32x4 fA[2][4], fB[2][4];                         // [row block of the half][chunk pair], [column block set][chunk pair]
+    auto read_a = [&](int par, int half, int i, int u) __attribute__((always_inline)) {
+        fA[i][u] = *reinterpret_cast<const u32x4 *>(pA[u] + par * A_STEP + half * 128 * ROWB + i * 32 * ROWB);
+    };
+    auto read_b = [&](int par, int col, int set, int u) __attribute__((always_inline)) {
+        fB[set][u] = *reinterpret_cast<const u32x4 *>(pB[u] + par * B_STEP + col * 128 * ROWB);
+    };
+    const uint32_t ldsA = lds_address(smem) + (uint32_t)(wave_id * 2048);
+    const uint32_t ldsB = ldsA + B_AT;
+    // K tiles: KF whole ones and, if K is not a multiple of BK, a partial one (KT in all).  Copies run
+    // under a lane mask: all lanes for a whole tile, the lanes whose chunk lies inside K for the partial
+    // one (the others' LDS chunks are zeroed by hand), none past the last tile - the instruction
+    // is still issued and counted then, so the waits in front of the barriers hold for every tile.
+    const int KF = a.K / BK, KT = (a.K + BK - 1) / BK;
+    const uint64_t part[2] = {__ballot(KF * BK + gcA[0] * CW < a.K), __ballot(KF * BK + gcA[1] * CW < a.K)};
+    auto lanes = [&](int kt, int i) __attribute__((always_inline)) -> uint64_t { return kt < KF ? ~0ull : kt < KT ? part[i] : 0ull; };
+    // copies of half `half` of the A panel / of column block `col` of the B panel of tile kt
+    auto copy_a = [&](int par, int half, int kt, int i) __attribute__((always_inline)) {
+        lds_dma16_masked(Xt + (int64_t)kt * ROWB, oA[half * 2 + i], ldsA + par * A_STEP + half * 128 * ROWB, i, i == 0, lanes(kt, i));
+    };
+    auto copy_b = [&](int par, int col, int kt, int i) __attribute__((always_inline)) {
+        lds_dma16_masked((col ? W2t : Wt) + (int64_t)kt * ROWB, oB[col * 2 + i], ldsB + par * B_STEP + col * 128 * ROWB, i, i == 0, lanes(kt, i));
+    };
+    auto zero_fill = [&](int par) __attribute__((always_inline)) {      // this wave's share of the chunks past K
+        const u32x4 none = {0u, 0u, 0u, 0u};
+        unsigned char *dst = smem + wave_id * 2048 + lane * 16;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (KF * BK + gcA[i] * CW >= a.K)
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    *reinterpret_cast<u32x4 *>(dst + par * A_STEP + half * 128 * ROWB + i * 1024) = none;
+                    *reinterpret_cast<u32x4 *>(dst + B_AT + par * B_STEP + half * 128 * ROWB + i * 1024) = none;
+                }
+    };
+    auto mma = [&](int half, int col, int set, int m) __attribute__((always_inline)) {
+        const int t = m >> 1, i = m & 1;
+        floatx16 &c = acc[half * 2 + i][col];
+        if constexpr (F8) {
+            const u32x4 av[2] = {fA[i][2 * t], fA[i][2 * t + 1]}, bv[2] = {fB[set][2 * t], fB[set][2 * t + 1]};
+            Mma<InT>::run(av, bv, c);
+        } else {
+            Mma<InT>::run(fA[i][t], fB[set][t], c);
+        }
+    };
+    // One K tile.  PAR: parity of the tile: its buffer, and the column block / register set P.  The
+    // last tile reads fragments of a tile that does not exist (whatever its buffer holds) and
+    // never uses them.
+    auto tile_body = [&]<int PAR>(int kt) __attribute__((always_inline)) {
+        constexpr int P = PAR, Q = PAR ^ 1;
+#pragma unroll
+        for (int m = 0; m < NMQ; ++m) {               // (A0, P); reads Q of this tile
+            if (m == LASTK) {
+                asm volatile("s_waitcnt vmcnt(6) lgkmcnt(4)" ::: "memory");
+                __builtin_amdgcn_s_barrier();         // beta
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            mma(0, P, P, m);
+            if (F8 ? m < 2 : m < 4) {
+                if constexpr (F8) { read_b(PAR, Q, Q, 2 * m); read_b(PAR, Q, Q, 2 * m + 1); }
+                else              read_b(PAR, Q, Q, m);
+            }
+            if (m >= LASTK) copy_b(PAR, P, kt + 2, m - LASTK);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int m = 0; m < NMQ; ++m) {               // (A0, Q); reads A1 of this tile behind A0's last uses
+            mma(0, Q, Q, m);
+            if constexpr (F8) { read_a(PAR, 1, m & 1, m & ~1); read_a(PAR, 1, m & 1, m | 1); }
+            else              read_a(PAR, 1, m & 1, m >> 1);
+            if (m == NMQ / 4) copy_a(PAR, 0, kt + 2, 0);
+            if (m == NMQ / 4 * 2) copy_a(PAR, 0, kt + 2, 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int m = 0; m < NMQ; ++m) {               // (A1, Q); reads the next tile's first column block behind Q's last uses
+            if (m == LASTK) {
+                asm volatile("s_waitcnt vmcnt(6) lgkmcnt(%0)" ::"n"(F8 ? 2 : 3) : "memory");
+                __builtin_amdgcn_s_barrier();         // alpha
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            mma(1, Q, Q, m);
+            if (m & 1) {
+                if constexpr (F8) { read_b(PAR ^ 1, Q, Q, m - 1); read_b(PAR ^ 1, Q, Q, m); }
+                else              read_b(PAR ^ 1, Q, Q, m >> 1);
+            }
+            if (m >= LASTK) copy_b(PAR, Q, kt + 2, m - LASTK);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (KF < KT && kt + 2 == KF) zero_fill(PAR);
+#pragma unroll
+        for (int m = 0; m < NMQ; ++m) {               // (A1, P); reads A0 of the next tile behind A1's last uses
+            mma(1, P, P, m);
+            if constexpr (F8) { read_a(PAR ^ 1, 0, m & 1, m & ~1); read_a(PAR ^ 1, 0, m & 1, m | 1); }
+            else              read_a(PAR ^ 1, 0, m & 1, m >> 1);
+            if (m == NMQ / 4) copy_a(PAR, 1, kt + 2, 0);
+            if (m == NMQ / 4 * 2) copy_a(PAR, 1, kt + 2, 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // tiles 0 and 1, in the order the loop would have issued them (a tile's first column block is
+    // that of its parity)
+    static_for<0, 2>([&]<int t>() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) copy_b(t, t, t, i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) copy_a(t, 0, t, i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) copy_b(t, t ^ 1, t, i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) copy_a(t, 1, t, i);
+        if (KF < KT && t == KF) zero_fill(t);
+    });
+    asm volatile("s_waitcnt vmcnt(10)" ::: "memory");     // all but A1 of tile 0 and tile 1
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { read_b(0, 0, 0, u); read_a(0, 0, 0, u); read_a(0, 0, 1, u); }
+    __builtin_amdgcn_s_waitcnt(0xC07F);               // lgkmcnt(0): or the compiler's waits inside the loop provide for this entry
+    __builtin_amdgcn_sched_barrier(0);
+    for (int kt = 0;;) {
+        tile_body.template operator()<0>(kt);
+        if (++kt == KT) break;
+        tile_body.template operator()<1>(kt);
+        if (++kt == KT) break;
+    }
+    __syncthreads();                                  // the epilogue reuses the panel memory
     } else {
     // ---------------- mainloop
     // Per staged tile: KS k-steps of NM MFMAs.  Fragments of the next k-step are read from LDS
@@ -437,7 +604,7 @@ void tile_kernel(const TileArgs a) {
                 if constexpr (F8) fa1[q][c] = v;
                 else              fr[t & 1][q][c] = v;
             } else {
-                fr[t & 1][q][c] = *reinterpret_cast<const u32x4 *>(sB + (q - MB) * FB_STEP * ROWB + off);
+                fr[t & 1][q][c] = *reinterpret_cast<const u32x4 *>(sB + (q - MB) * 32 * ROWB + off);
             }
         }
     };
