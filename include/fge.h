@@ -122,6 +122,8 @@ typedef enum {
  *   schedule) before scale, bias and activation; a row operation then runs over that fp32
  *   result.  Taken only when the workspace has the room fge_workspace_bytes reports; with a
  *   smaller workspace (or none, where none is needed otherwise) the problem runs unsliced.
+ *   Products of at most 64 rows of 16- or 8-bit operands (K of 1024 bytes and more) normally share
+ *   out K inside a workgroup instead and need no slices; the flag keeps them on the tile kernels.
  *   FGE_FLAG_TILE(t) : run the tile kernels with tile configuration t (an fge_tile) instead of
  *   the library's own choice - for tuning and tests.  A configuration without kernels for the
  *   operand type (or the narrow-K kernel outside K <= 64, N <= 512, fp32) yields
@@ -262,8 +264,9 @@ int fge_fused_finish(int act, int norm, const fge_params *p, void *out, void *st
  * Depends on the arguments only (not on the stream or the device). */
 int fge_fused_needs_finish(int act, int norm, const fge_params *p);
 /* Slices of K that fused_gemm_epilogue cuts these arguments into when the workspace has the
- * room (1: none; see FGE_FLAG_NO_SPLIT_K), negative on bad args.  The stage entry points
- * fge_fused_tiles / fge_fused_finish never slice. */
+ * room (1: none; see FGE_FLAG_NO_SPLIT_K), negative on bad args; for a product the few-row kernel
+ * takes, the slices it would be cut into otherwise.  The stage entry points fge_fused_tiles /
+ * fge_fused_finish never slice. */
 int fge_fused_k_slices(int act, int norm, const fge_params *p);
 
 /* Unfused K1: Y (rows x N, out_dtype, row stride ldo) = post_scale * (alpha * X.W^T + b). */
@@ -280,7 +283,8 @@ const char *fge_status_string(int status);
 /* hipError_t (as int) recorded by the calling thread's last FGE_ERR_HIP, else 0. */
 int fge_last_hip_error(void);
 /* Name of the tile configuration the fused path picks for these arguments (static string,
- * e.g. "256x256_w2x4"); NULL on invalid arguments.  For reports and tests. */
+ * e.g. "256x256_w2x4"); NULL on invalid arguments.  For reports and tests.  (Of a product the few-row
+ * kernel takes: the configuration it would run on otherwise.) */
 const char *fge_tile_name(int fused, int act, int norm, const fge_params *p);
 
 #ifdef __cplusplus

@@ -2,6 +2,7 @@
 // launched), tile selection, workspace layout and the kernel launches on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 
@@ -10,6 +11,7 @@
 
 #include "fge_launch.h"
 #include "fge_rowops.h"
+#include "fge_skinny.h"
 #include "fge_tile_table.h"
 
 using namespace fge;
@@ -374,6 +376,55 @@ KSplit k_split(const fge_params *p, int norm, const Plan &pl) {
     return ks;
 }
 
+// Few-row products (see fge_skinny.h): at most 64 rows of 16- or 8-bit operands that can be staged
+// where they lie, K of at least eight 128-byte tiles (one per wave of a workgroup); results of any
+// width and stride.  A row operation needs room for the fp32 rows and the arrival marks; without it -
+// or with a tile configuration or an uncut K asked for - the tile kernels run as before, and so they do
+// for a row op over more columns than one workgroup's registers hold.
+struct Skinny {
+    bool use;
+    Problem pr;
+    int64_t ld_mid;
+    size_t ws_mid, ws_marks;     // fp32 rows; arrival marks and, in their last 256 bytes, the fault word
+    size_t bytes() const { return ws_mid + ws_marks; }
+};
+
+// Whether the product's own workgroups run the row op: rows they can hold (logsumexp needs only their
+// pairs), unless told otherwise.
+bool skinny_in_kernel(const fge_params *p, int norm) {
+    return !(p->flags & FGE_FLAG_TWO_PASS) && (norm == FGE_NORM_LOGSUMEXP || p->N <= SKINNY_ROW_N);
+}
+
+Skinny plan_skinny(const fge_params *p, int norm, bool gated) {
+    Skinny k{};
+    const Plan pl = make_plan(p, FGE_NORM_NONE, true, TILE_64x64);      // for the folded problem only
+    k.pr = pl.pr;
+    if (p->in_dtype == FGE_F32 || forced_tile(p) >= 0 || (p->flags & FGE_FLAG_NO_SPLIT_K)) return k;
+    if (k.pr.batch != 1 || k.pr.M > SKINNY_ROWS || (int64_t)k.pr.K * (int64_t)esize(p->in_dtype) < 128 * SKINNY_WAVES) return k;
+    if (!operand_ok(p, k.pr.ldx, 0) || !operand_ok(p, k.pr.ldw, 0)) return k;
+    if (norm != FGE_NORM_NONE && norm != FGE_NORM_LOGSUMEXP && k.pr.N > SKINNY_WIDE_N) return k;
+    // Every workgroup reads all of X.  More than 32 rows of it cost more than W does once there are more
+    // than two workgroups per CU (64 x 4096 x 11008: 33 us against 27 us in K slices; 64 x 8192 x 8192 33.6
+    // against 39.5 us) - the gated form, which reads twice the weights for it, excepted -, and a
+    // long K with a few columns leaves too few workgroups to read it (64 x 8192 x 1024 15.1 against 13.9 us,
+    // with softmax 32 rows 14.5 against
+    // 12.2, 16 rows 12.0 against 11.8 us; 64 x 8192 x 2048 with softmax 20.1 against 18.2 us).
+    const int rows16 = (k.pr.M + 15) / 16 * 16, groups = (k.pr.N + 15) / 16;
+    if (!gated) {
+        if (rows16 > 32 && groups > 2 * num_cu()) return k;
+        const int64_t x_bytes = (int64_t)rows16 * k.pr.K * (int64_t)esize(p->in_dtype);
+        if (groups * 4 <= num_cu() && x_bytes > (norm == FGE_NORM_NONE ? 512 << 10 : 256 << 10)) return k;
+        if (groups * 2 <= num_cu() && norm != FGE_NORM_NONE && x_bytes > 512 << 10) return k;
+    }
+    k.use = true;
+    if (norm != FGE_NORM_NONE) {
+        k.ld_mid = (k.pr.N + 63) / 64 * 64;
+        k.ws_mid = round256((size_t)k.pr.M * k.ld_mid * sizeof(float));
+        k.ws_marks = round256((size_t)((k.pr.N + 15) / 16) * sizeof(unsigned)) + 256;
+    }
+    return k;
+}
+
 struct Repack {
     bool use;
     bool odd_out;                // the result is not storable in 16-byte units either
@@ -391,12 +442,12 @@ Repack plan_repack(const fge_params *p, int norm);
 // K-split where the one-call entry point would take it.
 size_t fused_workspace(const fge_params *p, int norm) {
     const Plan p1 = make_plan(p, norm, false), p2 = make_plan(p, norm, true);
+    const size_t few = plan_skinny(p, norm, false).bytes();
     if (p1.generic) {                // room for the repacked operands where the problem is worth repacking
         const Repack rp = plan_repack(p, norm);
-        return rp.use && rp.bytes > p1.ws_generic ? rp.bytes : p1.ws_generic;
+        return std::max({rp.use ? rp.bytes : 0, p1.ws_generic, few});
     }
-    const size_t a = p1.ws_stats + p1.ws_marks, b = p2.ws_stats + p2.ws_marks, c = k_split(p, norm, p1).bytes();
-    return a > b ? (a > c ? a : c) : (b > c ? b : c);
+    return std::max({p1.ws_stats + p1.ws_marks, p2.ws_stats + p2.ws_marks, k_split(p, norm, p1).bytes(), few});
 }
 
 // What the tile kernels need of it (the K-split is optional: without the room it is not taken).
@@ -614,6 +665,33 @@ int run_k_split(const void *X, const void *W, const float *b, int act, int norm,
     return finish_partials(part, nullptr, b, nullptr, act, norm, p, pl, S, slice, part + ks.ws_part, out, s);
 }
 
+// A few-row product (W2: of the gated form, else null): one launch, or - where a launch may not wait
+// for its own workgroups - two.
+int run_skinny(const void *X, const void *W, const void *W2, const float *b, const float *b2, int act, int norm,
+               const fge_params *p, const Skinny &k, void *out, hipStream_t s) {
+    SkinnyArgs a{};
+    a.X = X; a.W = W; a.W2 = W2; a.b = b; a.b2 = b2; a.gamma = p->gamma; a.beta = p->beta; a.out = out; a.aux = p->aux_out;
+    a.M = k.pr.M; a.N = k.pr.N; a.K = k.pr.K; a.ldx = k.pr.ldx; a.ldw = k.pr.ldw; a.ldo = k.pr.ldo; a.ld_mid = k.ld_mid;
+    a.alpha = p->alpha; a.post = p->post_scale; a.lo = clamp_low(p); a.hi = p->clamp_hi; a.eps = p->eps;
+    a.act = act; a.norm = norm; a.out_f32 = p->out_dtype == FGE_F32;
+    if (norm != FGE_NORM_NONE) {
+        char *ws = static_cast<char *>(p->workspace);
+        a.mid = reinterpret_cast<float *>(ws);
+        a.in_kernel = skinny_in_kernel(p, norm) && !capturing(s);
+        if (a.in_kernel) {
+            a.arrive = reinterpret_cast<unsigned *>(ws + k.ws_mid);
+            a.fault = reinterpret_cast<int *>(ws + k.bytes() - 256);
+            a.gen = g_generation.fetch_add(1) + 1;
+            const bool expire = (p->flags & FGE_FLAG_TEST_EXPIRE_WAIT) != 0;
+            a.spin_limit = expire ? 1u : WAIT_POLLS;
+            a.withhold = expire ? 1 : 0;
+        }
+    }
+    const int rc = hip_status(launch_skinny(p->in_dtype, W2 != nullptr, num_cu(), s, a));
+    if (rc || norm == FGE_NORM_NONE || a.in_kernel) return rc;
+    return hip_status(launch_skinny_rows(p->in_dtype, W2 != nullptr, num_cu(), s, a));
+}
+
 int run_fused(const void *X, const void *W, const float *b, int act, int norm, const fge_params *p, void *out,
               hipStream_t s);
 
@@ -726,6 +804,11 @@ int do_fused_tiles(const void *X, const void *W, const float *b, int act, int no
     if (!X || !W || !out) return FGE_ERR_NULL;
     if (!aligned16(X) || !aligned16(W) || !aligned16(out) || !aligned16(b)) return FGE_ERR_ALIGN;
     if (norm == FGE_NORM_LOGSUMEXP && !p->aux_out) return FGE_ERR_NULL;
+    if (one_call && g_w_rows == 0) {
+        const Skinny k = plan_skinny(p, norm, false);
+        if (k.use && (k.bytes() == 0 || (p->workspace && p->workspace_bytes >= k.bytes())))
+            return run_skinny(X, W, nullptr, b, nullptr, act, norm, p, k, out, s);
+    }
     const Plan pl = make_plan(p, norm, !one_call || capturing(s));
     if (plan_out) *plan_out = pl;
     if (pl.generic) {
@@ -955,8 +1038,8 @@ int fused_gemm_epilogue_static(const void *X, const void *W, const float *b, int
     fge_params q = *p;
     q.workspace = nullptr;
     q.workspace_bytes = 0;
-    // (the K slices are optional: taken when their partial products fit the array as well)
-    if (need > 0 || k_split(p, norm, pl).slices > 1) {
+    // (the K slices and the fp32 rows of few-row products are optional: taken when their partial products fit the array as well)
+    if (need > 0 || k_split(p, norm, pl).slices > 1 || plan_skinny(p, norm, false).bytes() > 0) {
         void *sp = nullptr;
         if ((rc = static_scratch(&sp))) return rc;
         q.workspace = sp;
@@ -1064,6 +1147,9 @@ int fused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, con
         return FGE_ERR_ALIGN;
     if (norm == FGE_NORM_LOGSUMEXP && !p->aux_out) return FGE_ERR_NULL;
     hipStream_t s = (hipStream_t)stream;
+    const Skinny few = plan_skinny(p, norm, true);
+    if (few.use && (few.bytes() == 0 || (p->workspace && p->workspace_bytes >= few.bytes())))
+        return run_skinny(X, W1, W2, b1, b2, act, norm, p, few, out, s);
     const GatedSmall gs = gated_small(p, norm);
     if (gs.use && p->workspace && p->workspace_bytes >= gs.bytes()) {
         const int S = gs.ks.slices;
@@ -1101,9 +1187,8 @@ int fused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, con
 size_t fge_gated_workspace_bytes(int fused, int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return (size_t)-1;
     if (!fused || !gated_fast(p, norm)) return 2 * make_plan(p, norm).ws_buf;
-    const size_t a = gated_workspace(p, norm);
     const GatedSmall gs = gated_small(p, norm);
-    return gs.use && gs.bytes() > a ? gs.bytes() : a;
+    return std::max({gated_workspace(p, norm), gs.use ? gs.bytes() : 0, plan_skinny(p, norm, true).bytes()});
 }
 
 const char *fge_gated_tile_name(int act, int norm, const fge_params *p) {
@@ -1114,6 +1199,8 @@ const char *fge_gated_tile_name(int act, int norm, const fge_params *p) {
 
 size_t fge_fault_word_offset(int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return (size_t)-1;
+    const Skinny few = plan_skinny(p, norm, false);
+    if (few.use) return few.bytes() && skinny_in_kernel(p, norm) ? few.bytes() - 256 : (size_t)-1;
     const Plan pl = make_plan(p, norm);
     return pl.coop ? pl.ws_stats + pl.ws_marks - 256 : (size_t)-1;
 }

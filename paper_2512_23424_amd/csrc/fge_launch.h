@@ -249,6 +249,12 @@ hipError_t launch_gated_bf16(int out_dtype, dim3 grid, hipStream_t s, const Tile
 hipError_t launch_gated_f16(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 hipError_t launch_gated_f8(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 
+// Defined in fge_skinny.hip: products of at most 64 rows (16- and 8-bit operands), and the row
+// operation behind one as a kernel of its own.  cus: compute units of the device.
+struct SkinnyArgs;
+hipError_t launch_skinny(int in_dtype, bool gated, int cus, hipStream_t s, const SkinnyArgs &a);
+hipError_t launch_skinny_rows(int in_dtype, bool gated, int cus, hipStream_t s, const SkinnyArgs &a);
+
 // Whether launch_tile_any has a cooperative kernel for this tile and operand type.
 inline bool tile_has_coop(int tile, int in_dtype) {
     if (tile == TILE_GATED) return true;
