@@ -27,6 +27,15 @@ thread_local int g_last_hip = 0;
 // Rows of W that exist when that is fewer than the problem's N (set around the inner call of the
 // repacked path, see run_repacked; 0: N)
 thread_local int g_w_rows = 0;
+// Results whose rows start and end at any element (set around the inner plans and calls of the repacked
+// path): OUT_ANY, the caller's rows; OUT_PADDED, fp32 rows of the workspace, padded to whole groups
+enum { OUT_ALIGNED = 0, OUT_ANY = 1, OUT_PADDED = 2 };
+thread_local int g_out_rows = OUT_ALIGNED;
+struct OutRows {
+    const int before;
+    explicit OutRows(int kind) : before(g_out_rows) { g_out_rows = kind; }
+    ~OutRows() { g_out_rows = before; }
+};
 
 // Launch counter: its value marks "arrived" in the cooperative form, so marks left in a
 // workspace by earlier launches (or by whatever the memory held before) never match.
@@ -142,8 +151,10 @@ bool operand_ok(const fge_params *p, int64_t ld, int64_t bs) {
 
 bool vectorisable(const fge_params *p, int norm, bool need_in) {
     const size_t os = esize(p->out_dtype);
-    if ((p->N * os) % 16 || (p->ldo * os) % 16) return false;
-    if (p->batch > 1 && (p->batch_stride_o * os) % 16) return false;
+    if (g_out_rows == OUT_ALIGNED) {
+        if ((p->N * os) % 16 || (p->ldo * os) % 16) return false;
+        if (p->batch > 1 && (p->batch_stride_o * os) % 16) return false;
+    }
     if (need_in && (!operand_ok(p, p->ldx, p->batch > 1 ? p->batch_stride_x : 0) || !operand_ok(p, p->ldw, 0))) return false;
     if (norm != FGE_NORM_NONE && !need_in && p->N > MAX_ROWOP_N) return false;
     return true;
@@ -294,6 +305,7 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
     if (pl.tile == TILE_128x128 && p->in_dtype != FGE_F32 &&
         (int64_t)((pr.M + 127) / 128) * ((pr.N + 127) / 128) * pr.batch <= num_cu())
         pl.tile = TILE_128x128_S3;
+    if (g_out_rows != OUT_ALIGNED) pl.tile = any_tile(pl.tile, p->in_dtype, (p->flags & FGE_FLAG_IEEE_FP32) != 0);
     const TileInfo &ti = tile_info(pl.tile);
     pl.tiles_m = (pr.M + ti.bm - 1) / ti.bm;
     pl.tiles_n = (pr.N + ti.bn - 1) / ti.bn;
@@ -312,7 +324,7 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
     bool table_two_pass = false;
     if (force_tile < 0 && forced_tile(p) < 0 && !(p->flags & FGE_FLAG_NO_TABLE))
         if (const TileTableEntry *e = table_entry(pr, p->in_dtype, norm)) table_two_pass = e->tile == pl.tile && e->two_pass;
-    pl.coop = pl.split && !two_pass && !table_two_pass && !(p->flags & FGE_FLAG_TWO_PASS) && tile_has_coop(pl.tile, p->in_dtype) &&
+    pl.coop = pl.split && !two_pass && g_out_rows == OUT_ALIGNED && !table_two_pass && !(p->flags & FGE_FLAG_TWO_PASS) && tile_has_coop(pl.tile, p->in_dtype) &&
               capacity >= pl.tiles_n && pl.tiles_n <= coop_max_tiles;
     if (pl.coop) {
         const int64_t total = (int64_t)pl.tiles_m * pl.tiles_n * pr.batch;
@@ -357,6 +369,7 @@ struct KSplit {
 
 KSplit k_split(const fge_params *p, int norm, const Plan &pl) {
     KSplit ks{1, 0, 0};
+    if (g_out_rows != OUT_ALIGNED) return ks;                           // its kernels store whole groups into aligned rows
     if (pl.generic || pl.tile != TILE_64x64 || pl.pr.batch != 1 || (p->flags & FGE_FLAG_NO_SPLIT_K)) return ks;
     if (norm != FGE_NORM_NONE && pl.pr.N > MAX_ROWOP_N) return ks;      // its row kernel holds a row in registers
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
@@ -375,6 +388,9 @@ KSplit k_split(const fge_params *p, int norm, const Plan &pl) {
     ks.ws_mid = norm == FGE_NORM_NONE ? 0 : one;
     return ks;
 }
+
+constexpr double REPACK_MIN_FLOP = 3.0e7;   // below this the element-granular product is as fast as four launches
+bool worth_repacking(const fge_params *p) { return 2.0 * (double)p->M * p->batch * p->N * p->K >= REPACK_MIN_FLOP; }
 
 // Few-row products (see fge_skinny.h): at most 64 rows of 16- or 8-bit operands that can be staged
 // where they lie, K of at least eight 128-byte tiles (one per wave of a workgroup); results of any
@@ -403,12 +419,15 @@ Skinny plan_skinny(const fge_params *p, int norm, bool gated) {
     if (k.pr.batch != 1 || k.pr.M > SKINNY_ROWS || (int64_t)k.pr.K * (int64_t)esize(p->in_dtype) < 128 * SKINNY_WAVES) return k;
     if (!operand_ok(p, k.pr.ldx, 0) || !operand_ok(p, k.pr.ldw, 0)) return k;
     if (norm != FGE_NORM_NONE && norm != FGE_NORM_LOGSUMEXP && k.pr.N > SKINNY_WIDE_N) return k;
+    // (8-bit operands that would otherwise be multiplied by fp32 FMAs stay there: the 8-bit matrix
+    // instruction sums less exactly)
+    if (p->in_dtype == FGE_F8E4M3 && !vectorisable(p, norm, true) && !worth_repacking(p)) return k;
     // Every workgroup reads all of X.  More than 32 rows of it cost more than W does once there are more
     // than two workgroups per CU (64 x 4096 x 11008: 33 us against 27 us in K slices; 64 x 8192 x 8192 33.6
     // against 39.5 us) - the gated form, which reads twice the weights for it, excepted -, and a
     // long K with a few columns leaves too few workgroups to read it (64 x 8192 x 1024 15.1 against 13.9 us,
-    // with softmax 32 rows 14.5 against
-    // 12.2, 16 rows 12.0 against 11.8 us; 64 x 8192 x 2048 with softmax 20.1 against 18.2 us).
+    // with softmax 32 rows 14.5 against 12.2, 16 rows 12.0 against 11.8 us; 64 x 8192 x 2048 with softmax
+    // 20.1 against 18.2 us).
     const int rows16 = (k.pr.M + 15) / 16 * 16, groups = (k.pr.N + 15) / 16;
     if (!gated) {
         if (rows16 > 32 && groups > 2 * num_cu()) return k;
@@ -433,6 +452,11 @@ struct Repack {
     int64_t rows, w_rows;        // rows of the padded X / W
     size_t off_w, off_b, off_mid, off_inner, bytes;      // workspace layout; the padded X sits at 0
     fge_params inner;            // the padded problem (workspace still to be filled in)
+    bool any;                    // odd_out: the tile kernels store straight into `out`
+    fge_params any_p;            // ... that problem; its workspace starts at off_b
+    bool parked;                 // odd_out: the tile kernels park fp32 rows and their statistics, a second pass finishes them
+    fge_params parked_p;         // ... that problem; the rows lie at off_b, its workspace at off_parked
+    size_t off_parked;
 };
 
 Repack plan_repack(const fge_params *p, int norm);
@@ -533,6 +557,7 @@ TileArgs tile_args(const void *X, const void *W, const float *b, int act, int no
     // the tiles share (batched K = 512 workload, 128 MiB of output: 3.7 % faster; the headline
     // workload's 64 MiB: no difference either way)
     a.stream_out = (size_t)pl.pr.M * pl.pr.batch * pl.pr.N * esize(p->out_dtype) >= ((size_t)128 << 20);
+    a.any_row = g_out_rows == OUT_ANY;
     a.coop = 0;
     if (pl.coop && norm != FGE_NORM_NONE) {
         char *base = static_cast<char *>(p->workspace) + pl.ws_stats;
@@ -562,6 +587,12 @@ int launch_tiles(const TileArgs &a, const fge_params *p, const Plan &pl, hipStre
     }
     const dim3 grid(a.coop ? (unsigned)pl.coop_grid : (unsigned)(pl.tiles_m * pl.tiles_n), 1,
                     a.coop ? 1u : (unsigned)pl.pr.batch);
+    if (g_out_rows != OUT_ALIGNED)
+        return hip_status(p->in_dtype == FGE_BF16     ? launch_any_bf16(pl.tile, p->out_dtype, grid, s, a)
+                          : p->in_dtype == FGE_F16    ? launch_any_f16(pl.tile, p->out_dtype, grid, s, a)
+                          : p->in_dtype == FGE_F8E4M3 ? launch_any_f8(pl.tile, p->out_dtype, grid, s, a)
+                          : (p->flags & FGE_FLAG_IEEE_FP32) ? launch_any_f32(pl.tile, p->out_dtype, grid, s, a)
+                                                            : launch_any_f32s(pl.tile, p->out_dtype, grid, s, a));
     if (pl.tile == TILE_128x256 || pl.tile == TILE_256x128)
         return hip_status(p->in_dtype == FGE_BF16  ? launch_half_bf16(pl.tile, p->out_dtype, grid, s, a)
                           : p->in_dtype == FGE_F16 ? launch_half_f16(pl.tile, p->out_dtype, grid, s, a)
@@ -701,20 +732,29 @@ int run_fused(const void *X, const void *W, const float *b, int act, int norm, c
 // fused_gemm_epilogue repacks them instead of leaving the product to the element-granular
 // kernel: X and W are copied into dense workspace buffers with K padded by zeros to a whole
 // chunk (the extra terms of every sum are exact zeros), and the padded problem runs on the
-// tile kernels.  When the result's own extents or strides are odd as well, the tile kernel
-// applies the activation and writes fp32 rows of padded width into the workspace (a copied W
-// gets zero rows, b zero entries for the padding columns), and a row kernel that stores
-// element by element and never looks at the padding columns turns them into `out`
-// (launch_generic_row: one workgroup per row, since these rows start on 16-byte boundaries).
+// tile kernels.  When the result's own extents or strides are odd as well, there are three ways:
+//   any     the tile kernels store rows that start and end at any element themselves: no row op,
+//           logsumexp, rows one tile spans (2048 x 4096 x 50257 bf16 with logsumexp: 1018 -> 752 us);
+//   parked  other split rows are parked in fp32 in the workspace - in `out` they would be rounded twice -
+//           with their statistics, and one pass finishes them (finish_any_kernel; 2048 x 1360 x 45363
+//           fp16 softmax: 552 -> 488 us);
+//   else (K cut into slices) the tile kernel applies the activation and writes fp32 rows of padded width
+//           into the workspace (a copied W gets zero rows, b zero entries for the padding columns),
+//           and a row kernel that stores element by element and never looks at the padding
+//           columns turns them into `out` (launch_generic_row: one workgroup per row, since these
+//           rows start on 16-byte boundaries).
 // The stage entry points and the unfused sequence keep the element-granular product.
-constexpr double REPACK_MIN_FLOP = 3.0e7;   // below this the element-granular product is as fast as four launches
+// The tiles a product without row op would take: nothing is exchanged between them in this form.
+Plan plan_parked(const fge_params *q, int norm) {
+    return make_plan(q, norm, true, make_plan(q, FGE_NORM_NONE, true).tile);
+}
 
 Repack plan_repack(const fge_params *p, int norm) {
     Repack r{};
     if (vectorisable(p, norm, true)) return r;
     const size_t is = esize(p->in_dtype), os = esize(p->out_dtype);
     const int64_t rows = (int64_t)p->M * p->batch;
-    if (2.0 * (double)rows * p->N * p->K < REPACK_MIN_FLOP || rows > INT32_MAX / 2) return r;
+    if (!worth_repacking(p) || rows > INT32_MAX / 2) return r;
     const int cw = (int)(16 / is);
     r.Kp = (p->K + cw - 1) / cw * cw;
     r.odd_out = (p->N * os) % 16 || (p->ldo * os) % 16 || (p->batch > 1 && (p->batch_stride_o * os) % 16);
@@ -751,7 +791,64 @@ Repack plan_repack(const fge_params *p, int norm) {
     r.off_inner = r.off_mid + (r.odd_out ? round256((size_t)rows * r.Np * sizeof(float)) : 0);
     r.bytes = r.off_inner + fused_workspace(&r.inner, r.odd_out ? FGE_NORM_NONE : norm);
     r.use = true;
+    if (!r.odd_out || k_split(&r.inner, FGE_NORM_NONE, make_plan(&r.inner, FGE_NORM_NONE)).slices > 1) return r;
+    const bool final_at_once = norm == FGE_NORM_NONE || norm == FGE_NORM_LOGSUMEXP;
+    r.any_p = *p;
+    r.any_p.K = r.Kp;
+    if (r.copy_x) { r.any_p.ldx = r.Kp; r.any_p.batch_stride_x = (int64_t)p->M * r.Kp; }
+    if (r.copy_w) r.any_p.ldw = r.Kp;
+    r.any_p.workspace = nullptr;
+    r.any_p.workspace_bytes = 0;
+    size_t need = 0;
+    {
+        const OutRows scope(OUT_ANY);
+        const Plan pl = make_plan(&r.any_p, norm);
+        r.any = !pl.generic && pl.strips <= MAX_SPLIT && (final_at_once || !pl.split);
+        if (r.any) need = r.off_b + fused_workspace(&r.any_p, norm);
+    }
+    if (!r.any && !final_at_once) {
+        const int ld = (p->N + 7) / 8 * 8;
+        r.parked_p = r.any_p;
+        r.parked_p.M = (int32_t)rows;
+        r.parked_p.batch = 1;
+        r.parked_p.ldo = ld;
+        r.parked_p.batch_stride_x = r.parked_p.batch_stride_o = 0;
+        r.parked_p.out_dtype = FGE_F32;
+        r.off_parked = r.off_b + round256((size_t)rows * ld * sizeof(float));
+        const OutRows scope(OUT_PADDED);
+        const Plan pl = plan_parked(&r.parked_p, norm);
+        r.parked = !pl.generic && pl.split && pl.strips <= MAX_SPLIT;
+        if (r.parked) need = r.off_parked + pl.ws_stats;
+    }
+    r.bytes = std::max(r.bytes, need);
     return r;
+}
+
+int run_parked(const void *X, const void *W, const float *b, int act, int norm, const fge_params *p, const Repack &rp,
+               void *out, hipStream_t s) {
+    char *ws = static_cast<char *>(p->workspace);
+    fge_params q = rp.parked_p;
+    q.workspace = ws + rp.off_parked;
+    q.workspace_bytes = p->workspace_bytes - rp.off_parked;
+    const OutRows scope(OUT_PADDED);
+    const Plan pl = plan_parked(&q, norm);
+    const int rc = launch_tiles(tile_args(X, W, b, act, norm, &q, pl, ws + rp.off_b), &q, pl, s);
+    if (rc) return rc;
+    FinishAnyArgs f{row_args(ws + rp.off_b, out, act, norm, &q, pl), q.ldo};
+    f.r.M = p->M; f.r.batch = p->batch; f.r.ldo = p->ldo; f.r.bso = p->batch > 1 ? p->batch_stride_o : 0;
+    const int64_t rows = (int64_t)p->M * p->batch;
+    const bool wide = p->N >= 2048 || rows < 4 * num_cu();            // a workgroup per row, or a wave
+    const dim3 grid((unsigned)(wide ? rows : (rows + 3) / 4)), block(256);
+#define FGE_FINISH(OT)                                                                              \
+    do {                                                                                            \
+        if (wide) hipLaunchKernelGGL((finish_any_kernel<OT, 4>), grid, block, 0, s, f);             \
+        else      hipLaunchKernelGGL((finish_any_kernel<OT, 1>), grid, block, 0, s, f);             \
+    } while (0)
+    if (p->out_dtype == FGE_BF16)     FGE_FINISH(bf16_t);
+    else if (p->out_dtype == FGE_F16) FGE_FINISH(f16_t);
+    else                              FGE_FINISH(float);
+#undef FGE_FINISH
+    return hip_status(hipGetLastError());
 }
 
 int run_repacked(const void *X, const void *W, const float *b, int act, int norm, const fge_params *p,
@@ -773,6 +870,14 @@ int run_repacked(const void *X, const void *W, const float *b, int act, int norm
     q.workspace = ws + rp.off_inner;
     q.workspace_bytes = p->workspace_bytes - rp.off_inner;
     if (!rp.odd_out) return run_fused(Xi, Wi, b, act, norm, &q, out, s);
+    if (rp.any) {
+        fge_params a = rp.any_p;
+        a.workspace = ws + rp.off_b;
+        a.workspace_bytes = p->workspace_bytes - rp.off_b;
+        const OutRows scope(OUT_ANY);
+        return run_fused(Xi, Wi, b, act, norm, &a, out, s);
+    }
+    if (rp.parked) return run_parked(Xi, Wi, b, act, norm, p, rp, out, s);
     const float *bp = nullptr;
     if (b != nullptr) {
         float *dst = reinterpret_cast<float *>(ws + rp.off_b);

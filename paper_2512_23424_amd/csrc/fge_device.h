@@ -86,6 +86,7 @@ __device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi) {
 template <typename T> struct Store;
 template <> struct Store<float> {
     static constexpr int CW = 4;                       // elements per 16-byte chunk
+    typedef u32x4 any16 __attribute__((aligned(4)));   // a 16-byte chunk that starts at any element
     __device__ static __forceinline__ void put(float *p, float v) { *p = v; }
     __device__ static __forceinline__ float get(const float *p) { return *p; }
     // one 16-byte chunk <-> CW floats
@@ -100,6 +101,7 @@ template <> struct Store<float> {
 };
 template <> struct Store<bf16_t> {
     static constexpr int CW = 8;
+    typedef u32x4 any16 __attribute__((aligned(2)));
     __device__ static __forceinline__ void put(bf16_t *p, float v) { p->bits = f32_to_bf16(v); }
     __device__ static __forceinline__ float get(const bf16_t *p) { return bf16_to_f32(p->bits); }
     __device__ static __forceinline__ void unpack(const uint4 &u, float *v) {
@@ -121,6 +123,7 @@ template <> struct Store<bf16_t> {
 
 template <> struct Store<f16_t> {
     static constexpr int CW = 8;
+    typedef u32x4 any16 __attribute__((aligned(2)));
     typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     // fp32 -> fp16 rounds to nearest even (the conversion instruction under the default mode)

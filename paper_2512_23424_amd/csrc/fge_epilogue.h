@@ -47,6 +47,7 @@ struct TileArgs {
     unsigned *arrive;           // [batch * tiles_m][tiles_n] arrival marks
     int *fault;                 // set to 1 if a wait ran out (the rows of that tile are then stored as NaN)
     int stream_out;             // store `out` with the streaming hint
+    int any_row;                // rows of `out` start and end at any element (stored 16 bytes at a time all the same, unaligned)
     int stagger, stagger_mask;  // cooperative form: row block rb of the first round starts (rb & mask) * stagger * 1024 clocks late
     unsigned spin_limit;        // polls after which a wait gives up
     int withhold;               // tests only: column tile 0 never marks itself as arrived
@@ -69,9 +70,11 @@ struct TileArgs {
 // uniform branches; BOUNDED_CT says which softmax / logsumexp variant (see `bounded`) that is.
 // PLAIN_ACC: the caller's accumulators already hold post*(alpha*x.w + b) (scale folded into an
 // operand, bias into the initial accumulator value), so no scale + bias step is applied.
+// ANY: N is any number - columns are guarded one by one instead of in groups of four, which costs the
+// fp32 kernels 3 to 7 % - and the rows of `out` may start anywhere (a.any_row).  Ordinary launches only.
 template <typename OutT, int MB, int NB, int WAVES_N, int PATCH_ROWS, bool JOINT, bool WAIT_VM, bool COOP = false,
           bool FULL_TILE = false, bool STREAM_OUT = false, int ACT_CT = -1, int NORM_CT = -1, bool BOUNDED_CT = false,
-          bool PLAIN_ACC = false>
+          bool PLAIN_ACC = false, bool ANY = false>
 struct TileEpilogue {
     static constexpr int WTN = NB * 32;               // columns of a wave strip
     // Patch layout.  A patch row is written 32 columns at a time by the lanes 0-31 (row R) and
@@ -116,7 +119,7 @@ struct TileEpilogue {
     int sub;                    // lane index inside its row segment
     int wsel[2];                // patch layout: column of this lane in a 32-column write, by (block ^ row bit 0)
     int rsel[2];                // ... and first column of its two 4-column read groups
-    bool ok4[2];                // columns gcol..+3 / gcol+4..+7 lie inside N (N is a multiple of 4)
+    bool okv[ANY ? VEC : 2];    // columns of this lane that lie inside N (not ANY: gcol..+3 / gcol+4..+7, N being a multiple of 4)
     int xch_par;                // which exchange buffer the next exchange uses
     float scale, bias[NB];      // y = scale * acc + bias  (scale = post*alpha, bias = post*b)
     bool whole_row;
@@ -138,8 +141,8 @@ struct TileEpilogue {
         sub = lane % LPR;
         pcol = sub * SUBW;
         gcol = n0 + wave_n * WTN + pcol;
-        ok4[0] = gcol < a.N;
-        ok4[1] = gcol + G4STEP < a.N;
+#pragma unroll
+        for (int e = 0; e < VEC; e += ANY ? 1 : 4) okv[ANY ? e : e >> 2] = gcol + (e >> 2) * G4STEP + (e & 3) < a.N;
         if constexpr (XORP) {                              // halves swapped where row bits 0 and 2 differ
             const int f = (prow ^ (prow >> 2)) & 1;
             wsel[0] = (h << 5) + l32;        wsel[1] = ((h ^ 1) << 5) + l32;
@@ -152,6 +155,15 @@ struct TileEpilogue {
         whole_row = a.tiles_n == 1;
         // (not in the cooperative form, whose registers are too scarce for two more variants)
         bounded = !COOP && a.act == FGE_ACT_CLAMP && a.hi - a.lo <= 64.0f;
+    }
+
+    // four neighbouring values of gamma / beta from column c on (inside N), the ones past N being zero
+    template <bool FULL> __device__ __forceinline__ floatx4 affine4(const float *p, int c) const {
+        if (FULL || !ANY || c + 3 < a.N) return *reinterpret_cast<const floatx4 *>(p + c);
+        floatx4 r = {p[c], 0.0f, 0.0f, 0.0f};
+        if (c + 1 < a.N) r[1] = p[c + 1];
+        if (c + 2 < a.N) r[2] = p[c + 2];
+        return r;
     }
 
     // valid columns of strip w of this tile
@@ -226,7 +238,7 @@ struct TileEpilogue {
     // small, so hi serves as the reference of the exponentials and no maximum is searched.
     template <int NORM, bool FULL, bool BOUNDED>
     __device__ __forceinline__ void norm_group(float (&v)[NPG][VEC], int grow0, float (&mkeep)[NPG]) {
-        auto okc = [&](int e) __attribute__((always_inline)) { return FULL || ok4[e >> 2]; };
+        auto okc = [&](int e) __attribute__((always_inline)) { return FULL || okv[ANY ? e : e >> 2]; };
         float s0[NPG], s1[NPG];
         if constexpr (NORM == FGE_NORM_SOFTMAX || NORM == FGE_NORM_LOGSUMEXP) {
             float ml[NPG];                            // strip maxima (or the common bound)
@@ -299,8 +311,8 @@ struct TileEpilogue {
         for (int e = 0; e < VEC; e += 4) {
             floatx4 g = {1.0f, 1.0f, 1.0f, 1.0f}, b = {0.0f, 0.0f, 0.0f, 0.0f};
             const int c = gcol + (e >> 2) * G4STEP;
-            if (whole_row && okc(e) && a.gamma != nullptr) g = *reinterpret_cast<const floatx4 *>(a.gamma + c);
-            if (whole_row && okc(e) && a.beta != nullptr) b = *reinterpret_cast<const floatx4 *>(a.beta + c);
+            if (whole_row && okc(e) && a.gamma != nullptr) g = affine4<FULL>(a.gamma, c);
+            if (whole_row && okc(e) && a.beta != nullptr) b = affine4<FULL>(a.beta, c);
             gam[e] = g[0]; gam[e + 1] = g[1]; gam[e + 2] = g[2]; gam[e + 3] = g[3];
             bet[e] = b[0]; bet[e + 1] = b[1]; bet[e + 2] = b[2]; bet[e + 3] = b[3];
         }
@@ -437,17 +449,41 @@ struct TileEpilogue {
             *reinterpret_cast<uint4 *>(o) = u;
         }
     }
+    // N values from column c on of a row that starts anywhere: one unaligned 16-byte store where all lie
+    // inside the row (the memory system takes any alignment; 2048 x 4096 x 50257 bf16 against fp32 rows of
+    // padded width and a kernel that copies them out: 1018 -> 752 us), else one by one
+    template <int N> __device__ __forceinline__ void put_any(OutT *o, const float *v, const bool *ok) const {
+        typedef typename Store<OutT>::any16 u32x4_any;
+        if (ok[N - 1]) {
+            const uint4 u = Store<OutT>::pack(v);
+            const u32x4 w = {u.x, u.y, u.z, u.w};
+            if (a.stream_out) __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any *>(o));
+            else              *reinterpret_cast<u32x4_any *>(o) = w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < N - 1; ++e)
+                if (ok[e]) Store<OutT>::put(o + e, v[e]);
+        }
+    }
     template <bool FULL> __device__ __forceinline__ void store_group(float (&v)[NPG][VEC], int grow0) {
 #pragma unroll
         for (int q = 0; q < NPG; ++q) {
             const int grow = m0 + qrow(grow0, q);
             if (FULL || grow < a.M) {
                 OutT *o = out + (int64_t)grow * a.ldo + gcol;
-                if constexpr (sizeof(OutT) == 2) {     // N is a multiple of 8: all or nothing
-                    if (FULL || ok4[0]) put16(o, Store<OutT>::pack(v[q]));
+                if (ANY && a.any_row) {
+                    if constexpr (!ANY) {
+                    } else if constexpr (sizeof(OutT) == 2) {
+                        put_any<8>(o, v[q], okv);
+                    } else {
+                        put_any<4>(o, v[q], okv);
+                        put_any<4>(o + G4STEP, v[q] + 4, okv + 4);
+                    }
+                } else if constexpr (sizeof(OutT) == 2) {   // whole 16-byte groups: all or nothing
+                    if (FULL || okv[0]) put16(o, Store<OutT>::pack(v[q]));
                 } else {
-                    if (FULL || ok4[0]) put16(o, Store<OutT>::pack(v[q]));
-                    if (FULL || ok4[1]) put16(o + G4STEP, Store<OutT>::pack(v[q] + 4));
+                    if (FULL || okv[0]) put16(o, Store<OutT>::pack(v[q]));
+                    if (FULL || okv[ANY ? 4 : 1]) put16(o + G4STEP, Store<OutT>::pack(v[q] + 4));
                 }
             }
         }
@@ -604,9 +640,9 @@ struct TileEpilogue {
         for (int e = 0; e < VEC; e += 4) {
             floatx4 g = {1.0f, 1.0f, 1.0f, 1.0f}, b = {0.0f, 0.0f, 0.0f, 0.0f};
             const int c = gcol + (e >> 2) * G4STEP;
-            const bool ok = FULL || ok4[e >> 2];
-            if (a.norm != FGE_NORM_SOFTMAX && ok && a.gamma != nullptr) g = *reinterpret_cast<const floatx4 *>(a.gamma + c);
-            if (a.norm == FGE_NORM_LAYERNORM && ok && a.beta != nullptr) b = *reinterpret_cast<const floatx4 *>(a.beta + c);
+            const bool ok = FULL || okv[ANY ? e : e >> 2];
+            if (a.norm != FGE_NORM_SOFTMAX && ok && a.gamma != nullptr) g = affine4<FULL>(a.gamma, c);
+            if (a.norm == FGE_NORM_LAYERNORM && ok && a.beta != nullptr) b = affine4<FULL>(a.beta, c);
             gam[e] = g[0]; gam[e + 1] = g[1]; gam[e + 2] = g[2]; gam[e + 3] = g[3];
             bet[e] = b[0]; bet[e + 1] = b[1]; bet[e + 2] = b[2]; bet[e + 3] = b[3];
         }

@@ -242,6 +242,46 @@ inline hipError_t launch_half_any(int tile, int out_dtype, dim3 grid, hipStream_
 #undef FGE_HALF
     return hipGetLastError();
 }
+// Results of any width and row alignment (ANY): ordinary launches of the tiles any_tile() leaves; defined in
+// fge_tiles_any_*.hip.
+template <typename InT, bool SPLIT>
+inline hipError_t launch_any_rows(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
+    typedef typename NarrowOut<InT>::type NarrowT;
+    constexpr bool BF = sizeof(InT) <= 2;
+#define FGE_ANY(BM, BN, WM, WN, STAGES)                                                                                \
+    do {                                                                                                               \
+        if (out_dtype != FGE_F32)                                                                                      \
+            hipLaunchKernelGGL((tile_kernel<InT, NarrowT, BM, BN, WM, WN, false, false, SPLIT, false, STAGES, true>),  \
+                               grid, dim3(64 * WM * WN), 0, s, a);                                                     \
+        else                                                                                                           \
+            hipLaunchKernelGGL((tile_kernel<InT, float, BM, BN, WM, WN, false, false, SPLIT, false, STAGES, true>),    \
+                               grid, dim3(64 * WM * WN), 0, s, a);                                                     \
+    } while (0)
+    if (tile == TILE_64x64) FGE_ANY(64, 64, 2, 2, 0);
+    else if (tile == TILE_128x128 && (BF || SPLIT)) { if constexpr (BF || SPLIT) FGE_ANY(128, 128, 2, 2, 0); }
+    else if (tile == TILE_128x128_W8 && SPLIT)      { if constexpr (SPLIT) FGE_ANY(128, 128, 2, 4, 0); }
+    else if (tile == TILE_128x128_S3 && BF)         { if constexpr (BF) FGE_ANY(128, 128, 2, 4, 3); }
+    else if (tile == TILE_256x256 && BF)            { if constexpr (BF) FGE_ANY(256, 256, 2, 4, 0); }
+    else return hipErrorInvalidValue;
+#undef FGE_ANY
+    return hipGetLastError();
+}
+hipError_t launch_any_f32(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
+hipError_t launch_any_f32s(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
+hipError_t launch_any_bf16(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
+hipError_t launch_any_f16(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
+hipError_t launch_any_f8(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
+// The tile that stands in for one that has no kernel of that form.
+inline int any_tile(int tile, int in_dtype, bool ieee_fp32) {
+    const bool small_only = in_dtype == FGE_F32 && ieee_fp32;
+    switch (tile) {
+    case TILE_128x256: case TILE_256x128:          return TILE_256x256;
+    case TILE_PANEL:                               return TILE_128x128;
+    case TILE_64x512: case TILE_64x128:            return small_only ? TILE_64x64 : TILE_128x128;
+    default:                                       return tile;
+    }
+}
+
 hipError_t launch_half_bf16(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 hipError_t launch_half_f16(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 hipError_t launch_half_f8(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);

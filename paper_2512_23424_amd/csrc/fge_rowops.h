@@ -617,4 +617,95 @@ __global__ __launch_bounds__(256) void finish_kernel(const RowArgs a) {
     }
 }
 
+// The same second pass for rows the tile kernel parked in fp32 (`in`, dense rows a.ldi apart, 16-byte
+// aligned, padded to whole groups of eight) because `out` has rows that start and end at any element and
+// its own type would round the parked values: eight columns per thread and step - two 16-byte loads, one unaligned
+// 16-byte store (32-bit results: two).  Softmax, LayerNorm, RMSNorm.  Bound by memory (6 bytes per value
+// with 16-bit results); WAVES as in finish_kernel.
+struct FinishAnyArgs {
+    RowArgs r;
+    int64_t ldi;
+};
+template <typename OutT, int WAVES>
+__global__ __launch_bounds__(256) void finish_any_kernel(const FinishAnyArgs f) {
+    const RowArgs &a = f.r;
+    constexpr int TEAM = 64 * WAVES;                      // threads per row
+    const int lane = threadIdx.x & 63;
+    const int member = WAVES == 1 ? lane : (int)threadIdx.x;
+    const int64_t rowg = WAVES == 1 ? (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6) : (int64_t)blockIdx.x;
+    if (rowg >= (int64_t)a.batch * a.M) return;           // wave-uniform
+    const float *in = reinterpret_cast<const float *>(a.in) + rowg * f.ldi;
+    OutT *out = reinterpret_cast<OutT *>(a.out) + (rowg / a.M) * a.bso + (rowg % a.M) * a.ldo;
+    const int S = a.tiles_n, SW = a.bn;                   // (SW: a multiple of 32)
+    const float2 *wr = a.ws + rowg * S;
+    const float inv_n = 1.0f / (float)a.N;
+    float shift = 0.0f, scale, ref = 0.0f;
+    if (a.norm == FGE_NORM_SOFTMAX) {
+        float m = OpMax::ident();
+#pragma unroll 8
+        for (int t = lane; t < S; t += 64) m = max_nc(m, wr[t].x);
+        ref = allreduce64<OpMax>(m);
+        float s = 0.0f;
+#pragma unroll 8
+        for (int t = lane; t < S; t += 64) s += wr[t].y * fast_exp(wr[t].x - ref);
+        scale = fast_rcp(allreduce64<OpSum>(s));
+    } else if (a.norm == FGE_NORM_LAYERNORM) {
+        float sm = 0.0f;
+#pragma unroll 8
+        for (int t = lane; t < S; t += 64) sm += (float)max(0, min(SW, a.N - t * SW)) * wr[t].x;
+        shift = allreduce64<OpSum>(sm) * inv_n;
+        float m2 = 0.0f;
+#pragma unroll 8
+        for (int t = lane; t < S; t += 64) {
+            const float d = wr[t].x - shift;
+            m2 += wr[t].y + (float)max(0, min(SW, a.N - t * SW)) * d * d;
+        }
+        scale = rsqrtf(allreduce64<OpSum>(m2) * inv_n + a.eps);
+    } else {
+        float ss = 0.0f;
+#pragma unroll 8
+        for (int t = lane; t < S; t += 64) ss += wr[t].x;
+        scale = rsqrtf(allreduce64<OpSum>(ss) * inv_n + a.eps);
+    }
+    const bool use_beta = a.norm == FGE_NORM_LAYERNORM && a.beta != nullptr;
+    typedef typename Store<OutT>::any16 u32x4_any;
+#pragma unroll 4
+    for (int c = member * 8; c < a.N; c += TEAM * 8) {
+        const bool whole = c + 8 <= a.N;
+        float v[8];
+        Store<float>::unpack(*reinterpret_cast<const uint4 *>(in + c), v);
+        Store<float>::unpack(*reinterpret_cast<const uint4 *>(in + c + 4), v + 4);
+        if (a.norm == FGE_NORM_SOFTMAX) {
+            const float k = fast_exp(wr[c / SW].x - ref) * scale;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] *= k;
+        } else {
+            float g[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f}, b[8] = {};
+            if (whole) {
+                if (a.gamma) { Store<float>::unpack(*reinterpret_cast<const uint4 *>(a.gamma + c), g); Store<float>::unpack(*reinterpret_cast<const uint4 *>(a.gamma + c + 4), g + 4); }
+                if (use_beta) { Store<float>::unpack(*reinterpret_cast<const uint4 *>(a.beta + c), b); Store<float>::unpack(*reinterpret_cast<const uint4 *>(a.beta + c + 4), b + 4); }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 7; ++e) {
+                    if (a.gamma && c + e < a.N) g[e] = a.gamma[c + e];
+                    if (use_beta && c + e < a.N) b[e] = a.beta[c + e];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (v[e] - shift) * scale * g[e] + b[e];
+        }
+        if (whole) {
+#pragma unroll
+            for (int g = 0; g < 8; g += Store<OutT>::CW) {
+                const uint4 u = Store<OutT>::pack(v + g);
+                *reinterpret_cast<u32x4_any *>(out + c + g) = u32x4{u.x, u.y, u.z, u.w};
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 7; ++e)
+                if (c + e < a.N) Store<OutT>::put(out + c + e, v[e]);
+        }
+    }
+}
+
 }  // namespace fge

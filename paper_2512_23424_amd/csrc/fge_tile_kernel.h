@@ -108,8 +108,9 @@ template <> struct Mma<float> {
 // than a fifth of its matrix-pipe time (3 x 8 passes per 16 k instead of 8 x 16 passes).  The
 // split product has a mainloop of its own (operands are split on their way into LDS).
 // STAGES: 0 for the tile's usual number of stage buffers, else that many (see DEEP below).
+// ANY: N and the rows of the result are any number of elements (see TileEpilogue).
 template <typename InT, typename OutT, int BM, int BN, int WAVES_M, int WAVES_N, bool COOP = false, bool FULL = false,
-          bool SPLIT = false, bool GATED = false, int STAGES = 0>
+          bool SPLIT = false, bool GATED = false, int STAGES = 0, bool ANY = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (BM * BN <= 64 * 128 ? 2 : 1))
 void tile_kernel(const TileArgs a) {
     static_assert(!SPLIT || sizeof(InT) == 4, "only fp32 operands are split");
@@ -756,7 +757,7 @@ void tile_kernel(const TileArgs a) {
                 wave_n, lane);
         epi.template tile<NT>(gated, wave_m * WTM, rowblock, tid);
     } else {
-        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL>;
+        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, -1, false, false, ANY>;
         static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= 2 * STAGE, "store patches fit the panels");
         Epi epi(a, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
                 wave_n, lane);

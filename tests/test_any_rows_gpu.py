@@ -1,0 +1,58 @@
+"""Results whose rows start and end at any element, stored by the tile kernels themselves (no row op,
+logsumexp, rows one tile spans) or parked in fp32 and finished by one pass (softmax, LayerNorm,
+RMSNorm over several tiles): widths around the tiles' edges and the stores' groups of eight, row
+strides that are odd or leave padding, which must stay untouched."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_23424_amd import binding as B
+from paper_2512_23424_amd import inputs as I
+from tests import _harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(w, d, pad, flags=0):
+    buf = torch.full((w.M, w.N + pad), float("nan"), dtype=H.tdtype(w.out_dtype), device="cuda")
+    out = buf[:, :w.N]
+    aux = torch.full((w.M,), float("nan"), device="cuda") if w.norm == I.NORM_LOGSUMEXP else None
+    p = B.make_params(d["X"], d["W"], out, alpha=w.alpha, post_scale=w.post_scale, eps=w.eps, gamma=d["gamma"], beta=d["beta"],
+                      aux_out=aux, flags=flags)
+    assert B.fge_tile_name(True, w.act, w.norm, p) == "repacked_operands"
+    ws = torch.empty(B.fge_workspace_bytes(True, w.act, w.norm, p), dtype=torch.uint8, device="cuda")
+    p.workspace, p.workspace_bytes = ws.data_ptr(), ws.numel()
+    B.fused_gemm_epilogue(d["X"], d["W"], d["b"], w.act, w.norm, p, out)
+    torch.cuda.synchronize()
+    assert pad == 0 or bool(torch.isnan(buf[:, w.N:]).all())
+    return H.to_host_f64(out.contiguous()), None if aux is None else H.to_host_f64(aux)
+
+
+@pytest.mark.parametrize("dt,out", [(I.BF16, I.BF16), (I.F16, I.F32), (I.F8E4M3, I.BF16), (I.F32, I.F32), (I.F32, I.BF16)])
+@pytest.mark.parametrize("tile", [0, 2, 3, 9, 10])
+def test_exact_values_at_the_edges_of_tiles_and_stores(dt, out, tile):
+    if (tile == 9) != (dt == I.F32) and tile in (3, 9, 10):
+        pytest.skip("no such tile for these operands")
+    for M, N, pad in ((300, 511, 0), (517, 257, 3), (330, 520, 1), (301, 1029, 5), (400, 770, 0)):
+        w = I.Workload(name="any", M=M, K=272, N=N, in_dtype=dt, out_dtype=out,
+                       dist={"X": ("int", -2, 2), "W": ("int", -2, 2), "b": ("int", -3, 3)})
+        t = I.generate(w)
+        ref, _ = H.oracle_chain(w, t)
+        ref = I.as_f64(I.f64_to_bf16_bits(ref)) if out == I.BF16 else ref
+        got, _ = _run(w, {k: H.to_device(v) for k, v in t.items()}, pad, (tile + 1) << 8)
+        assert np.array_equal(got, ref), f"M={M} N={N} pad={pad}: {int((got != ref).sum())} mismatches"
+
+
+@pytest.mark.parametrize("dt,out", [(I.BF16, I.BF16), (I.F16, I.F16), (I.F8E4M3, I.BF16), (I.F32, I.F32)])
+@pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LAYERNORM, I.NORM_RMSNORM, I.NORM_LOGSUMEXP])
+def test_row_operations_on_rows_of_any_width(dt, out, norm):
+    for M, K, N, pad in ((700, 1024, 61, 0), (300, 272, 515, 2), (260, 1040, 1544, 3), (130, 272, 9001, 0)):
+        w = I.Workload(name=f"any{norm}", M=M, K=K, N=N, in_dtype=dt, out_dtype=out, act=I.ACT_SILU, norm=norm,
+                       alpha=1.0 / K ** 0.5, post_scale=1.5, eps=1e-5,
+                       dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, 1.0), "b": ("uniform", -0.5, 0.5),
+                             "gamma": ("normal", 1.0, 0.1), "beta": ("normal", 0.0, 0.1)})
+        t = I.generate(w)
+        d = {k: H.to_device(v) for k, v in t.items()}
+        ref, raux = H.oracle_chain(w, t)
+        got, gaux = _run(w, d, pad)
+        H.check(w, got, gaux, ref, raux, f"any rows {M}x{K}x{N}+{pad}")
