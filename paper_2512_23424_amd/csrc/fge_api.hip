@@ -71,6 +71,7 @@ struct Plan {
     Problem pr;
     int tile;
     int tiles_m, tiles_n;
+    int waves_n;                 // wave strips across a tile
     int strips;                  // statistics slots per row: column tiles x waves across a tile
     bool split;                  // rows split over several column tiles and a row op is requested
     bool coop;                   // ... and the tiles finish their rows themselves (one kernel)
@@ -307,6 +308,7 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
         pl.tile = TILE_128x128_S3;
     if (g_out_rows != OUT_ALIGNED) pl.tile = any_tile(pl.tile, p->in_dtype, (p->flags & FGE_FLAG_IEEE_FP32) != 0);
     const TileInfo &ti = tile_info(pl.tile);
+    pl.waves_n = tile_strips(pl.tile, pr.K, esize(p->in_dtype), g_out_rows != OUT_ALIGNED);
     pl.tiles_m = (pr.M + ti.bm - 1) / ti.bm;
     pl.tiles_n = (pr.N + ti.bn - 1) / ti.bn;
     pl.split = norm != FGE_NORM_NONE && pl.tiles_n > 1;
@@ -333,14 +335,14 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
     }
     pl.needs_finish = pl.split && !pl.coop;
     // pairs per row: one per wave strip for the second pass, one per tile in the cooperative form
-    pl.strips = pl.coop ? pl.tiles_n : pl.tiles_n * ti.waves_n;
+    pl.strips = pl.coop ? pl.tiles_n : pl.tiles_n * pl.waves_n;
     pl.ws_stats = pl.split ? round256((size_t)pr.M * pr.batch * pl.strips * sizeof(float2)) : 0;
     pl.ws_marks = pl.coop ? round256((size_t)pl.tiles_m * pr.batch * pl.tiles_n * sizeof(unsigned)) + 256 : 0;
     const size_t extent = (size_t)(pr.batch - 1) * pr.bso + (size_t)(pr.M - 1) * pr.ldo + pr.N;
     pl.ws_buf = round256(extent * esize(p->out_dtype));
     // K2 writes straight into `out` when the row op leaves the activated values in place
     pl.n_bufs = (norm == FGE_NORM_NONE || norm == FGE_NORM_LOGSUMEXP) ? 1 : 2;
-    pl.generic = !vectorisable(p, norm, true) || (pl.split && pl.tiles_n * ti.waves_n > MAX_SPLIT);
+    pl.generic = !vectorisable(p, norm, true) || (pl.split && pl.tiles_n * pl.waves_n > MAX_SPLIT);
     if (pl.generic) {                // no tiles, no statistics: GEMM + activation to fp32, then the row op
         pl.split = pl.coop = pl.needs_finish = false;
         pl.ws_stats = pl.ws_marks = 0;
@@ -611,7 +613,7 @@ RowArgs row_args(const void *in, void *out, int act, int norm, const fge_params 
     r.ws = reinterpret_cast<const float2 *>(p->workspace);
     r.M = pl.pr.M; r.N = pl.pr.N; r.batch = pl.pr.batch; r.ldo = pl.pr.ldo; r.bso = pl.pr.bso;
     r.lo = clamp_low(p); r.hi = p->clamp_hi; r.eps = p->eps; r.act = act; r.norm = norm;
-    r.tiles_n = pl.strips; r.bn = tile_info(pl.tile).bn / tile_info(pl.tile).waves_n;
+    r.tiles_n = pl.strips; r.bn = tile_info(pl.tile).bn / pl.waves_n;
     return r;
 }
 

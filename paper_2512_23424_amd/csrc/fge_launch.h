@@ -34,10 +34,20 @@ inline const TileInfo &tile_info(int id) {
         // 16- and 8-bit operands, at most one 128x128 tile per CU: eight waves of 64x32 and three
         // stage buffers (no second workgroup shares the CU, so a second K-tile copy in flight and a
         // second wave per SIMD hide the latencies instead); the plan puts it in the place of
-        // 128x128_w2x2 wherever that tile is chosen for such a problem
+        // 128x128_w2x2 wherever that tile is chosen for such a problem.  With a long K: four stage
+        // buffers, the waves sharing out K, and two strips of 64 columns instead of four (tile_strips)
         {128, 128, 512, 4, 1, "128x128_w2x4_s3", nullptr},
     };
     return t[id];
+}
+
+// K from which the 64x64 and the 128x128_s3 tile run their K-sharing mainloop: 2 KB of K, the line where its
+// slower start and end are paid for (6144 x 304 x 528 bf16: 9.4 us without, 10.2 with it; 2048 x 624 x 1544
+// RMSNorm 16.5 / 17.3, 2048 x 1024 x 1544 18.4 / 18.0, 2048 x 2048 x 1544 26.1 / 24.3 us).
+inline bool long_k(int K, size_t esize) { return (size_t)K * esize >= 2048; }
+// Wave strips across a tile.  any_rows: the forms for results of any width, which share out K always.
+inline int tile_strips(int tile, int K, size_t esize, bool any_rows) {
+    return tile == TILE_128x128_S3 && (any_rows || long_k(K, esize)) ? 2 : tile_info(tile).waves_n;
 }
 
 // Defined in fge_tiles_f32.hip / fge_tiles_f32s.hip / fge_tiles_bf16.hip (separate units so they
@@ -136,22 +146,34 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
         if (out_dtype != FGE_F32)  FGE_LAUNCH_COOP1(BM, BN, WM, WN, NarrowT);                   \
         else                       FGE_LAUNCH_COOP1(BM, BN, WM, WN, float);                     \
     } while (0)
-    // 128x128 tiles on eight waves with three stage buffers (one workgroup per CU), ordinary and cooperative launch
-#define FGE_LAUNCH_DEEP128(OT)                                                                  \
+    // 128x128 tiles on eight waves with more stage buffers (one workgroup per CU), ordinary and cooperative launch
+#define FGE_LAUNCH_DEEP128(OT, WM, WN, STAGES)                                                  \
     do {                                                                                        \
         if (a.coop) {                                                                           \
-            auto kern = tile_kernel<InT, OT, 128, 128, 2, 4, true, false, false, false, 3>;     \
+            auto kern = tile_kernel<InT, OT, 128, 128, WM, WN, true, false, false, false, STAGES>; \
             static const int resident = resident_workgroups(reinterpret_cast<const void *>(kern), 512); \
             if ((int)grid.x > resident) return hipErrorCooperativeLaunchTooLarge;               \
             hipLaunchKernelGGL(kern, grid, dim3(512), 0, s, a);                                 \
         } else {                                                                                \
-            hipLaunchKernelGGL((tile_kernel<InT, OT, 128, 128, 2, 4, false, false, false, false, 3>), grid, \
+            hipLaunchKernelGGL((tile_kernel<InT, OT, 128, 128, WM, WN, false, false, false, false, STAGES>), grid, \
                                dim3(512), 0, s, a);                                             \
         }                                                                                       \
     } while (0)
+    const bool long_row = long_k(a.K, sizeof(InT));
     constexpr bool BF = sizeof(InT) <= 2;
     switch (tile) {
-    case TILE_64x64:   FGE_LAUNCH(64, 64, 2, 2); break;
+    case TILE_64x64:
+        if constexpr (BF) {
+            if (long_row) {
+                if (out_dtype != FGE_F32)
+                    hipLaunchKernelGGL((tile_kernel<InT, NarrowT, 64, 64, 2, 2, false, false, false, false, 4>), grid, dim3(256), 0, s, a);
+                else
+                    hipLaunchKernelGGL((tile_kernel<InT, float, 64, 64, 2, 2, false, false, false, false, 4>), grid, dim3(256), 0, s, a);
+                break;
+            }
+        }
+        FGE_LAUNCH(64, 64, 2, 2);
+        break;
     case TILE_64x512:  FGE_LAUNCH(64, 512, 1, 4); break;
     case TILE_128x128:
         if constexpr (BF || SPLIT) {
@@ -162,8 +184,8 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
         return hipErrorInvalidValue;
     case TILE_128x128_S3:
         if constexpr (BF && !SPLIT) {
-            if (out_dtype != FGE_F32) FGE_LAUNCH_DEEP128(NarrowT);
-            else                      FGE_LAUNCH_DEEP128(float);
+            if (out_dtype != FGE_F32) { if (long_row) FGE_LAUNCH_DEEP128(NarrowT, 4, 2, 4); else FGE_LAUNCH_DEEP128(NarrowT, 2, 4, 3); }
+            else                      { if (long_row) FGE_LAUNCH_DEEP128(float, 4, 2, 4);   else FGE_LAUNCH_DEEP128(float, 2, 4, 3); }
             break;
         }
         return hipErrorInvalidValue;
@@ -257,10 +279,10 @@ inline hipError_t launch_any_rows(int tile, int out_dtype, dim3 grid, hipStream_
             hipLaunchKernelGGL((tile_kernel<InT, float, BM, BN, WM, WN, false, false, SPLIT, false, STAGES, true>),    \
                                grid, dim3(64 * WM * WN), 0, s, a);                                                     \
     } while (0)
-    if (tile == TILE_64x64) FGE_ANY(64, 64, 2, 2, 0);
+    if (tile == TILE_64x64) FGE_ANY(64, 64, 2, 2, (BF ? 4 : 0));
     else if (tile == TILE_128x128 && (BF || SPLIT)) { if constexpr (BF || SPLIT) FGE_ANY(128, 128, 2, 2, 0); }
     else if (tile == TILE_128x128_W8 && SPLIT)      { if constexpr (SPLIT) FGE_ANY(128, 128, 2, 4, 0); }
-    else if (tile == TILE_128x128_S3 && BF)         { if constexpr (BF) FGE_ANY(128, 128, 2, 4, 3); }
+    else if (tile == TILE_128x128_S3 && BF)         { if constexpr (BF) FGE_ANY(128, 128, 4, 2, 4); }
     else if (tile == TILE_256x256 && BF)            { if constexpr (BF) FGE_ANY(256, 256, 2, 4, 0); }
     else return hipErrorInvalidValue;
 #undef FGE_ANY

@@ -135,17 +135,22 @@ void tile_kernel(const TileArgs a) {
     constexpr int STAGE = (BM + BN) * ROWB;
     // DEEP: a K tile of a small tile is multiplied in a fraction of the time its copy takes to
     // arrive, so one tile of lookahead leaves the loop waiting on memory latency.  The 64x64 tile
-    // always runs with four stage buffers (three copies in flight, two workgroups per CU); the
+    // runs with four stage buffers (three copies in flight, two workgroups per CU); the
     // 128x128 tile has a variant with three (STAGES = 3, one workgroup per CU) for launches that
     // give a CU no second workgroup to hide the latency with.
-    static_assert(STAGES == 0 || (STAGES > 2 && !SPLIT && !GATED), "extra stage buffers: plain 16- and 8-bit tiles");
-    constexpr bool DEEP = STAGES > 2 || (BM == 64 && BN == 64 && !SPLIT && !COOP);
+    // KSHARE (STAGES = 4): the same tiles for a longer K, with a mainloop of their own.  It starts and
+    // ends more slowly (more copies in front of the first tile, the groups' sums behind the last), so the
+    // launcher takes it from 2 KB of K on (see long_k).
+    static_assert(STAGES == 0 || ((STAGES == 3 || STAGES == 4) && !SPLIT && !GATED), "extra stage buffers: plain 16- and 8-bit tiles");
+    constexpr bool KSHARE = STAGES == 4;
+    constexpr bool DEEP = STAGES == 3 || (STAGES == 0 && BM == 64 && BN == 64 && !SPLIT && !COOP);
     // QUAD: the mainloop by output quadrants (see there); A buffers first, then B buffers, so that
     // every fragment read is a lane address plus an immediate offset
     constexpr bool QUAD = BM == 256 && BN == 256 && NT == 512 && MB == 4 && NB == 2 && !SPLIT && STAGES == 0;
     constexpr int A_STEP = QUAD ? BM * ROWB : STAGE, B_STEP = QUAD ? BN * ROWB : STAGE;    // bytes between stage buffers
     constexpr int B_AT = QUAD ? 2 * BM * ROWB : BM * ROWB;                                 // first B buffer
-    constexpr int NST = STAGES > 2 ? STAGES : DEEP ? 4 : 2;
+    constexpr int NST = KSHARE || (DEEP && STAGES == 0) ? 4 : DEEP ? STAGES : 2;
+    constexpr int OWN = NST * STAGE / (WAVES_M * WAVES_N);   // panel memory per wave behind the mainloop
 
     __shared__ __attribute__((aligned(16))) unsigned char smem[NST * STAGE];
     __shared__ __attribute__((aligned(16))) float2 xch[2 * BM * WAVES_N];
@@ -304,6 +309,38 @@ void tile_kernel(const TileArgs a) {
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    // Two groups of waves have shared out K (wave_m % 2: the group): of the 2*MB*NB blocks both have summed for the same part of
+    // the tile, group 0 keeps the first half and group 1 the second.  Every wave leaves what it does not keep
+    // in the part of the panel memory that belongs to the wave that keeps it - its store patch lies
+    // there as well, so one barrier is enough - and adds what was left for it, group 0's sum first.
+    auto join_groups = [&](floatx16 (&part)[2 * MB * NB]) __attribute__((always_inline)) {
+        constexpr int NK = MB * NB;
+        static_assert(!KSHARE || NK * 4096 <= OWN, "sums through the panel memory");
+        const int other = wave ^ WAVES_N;             // same blocks, the other group
+        auto slot = [&](int w, int k) __attribute__((always_inline)) { return reinterpret_cast<floatx4 *>(smem + w * OWN) + k * 256 + lane; };
+        __syncthreads();                              // the panels are free
+        static_for<0, 2>([&]<int G>() __attribute__((always_inline)) {
+            if (wave_m % 2 == G) {
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    const floatx16 &v = part[(G ^ 1) * NK + k];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) slot(other, k)[r * 64] = floatx4{v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]};
+                    acc[k / NB][k % NB] = part[G * NK + k];
+                }
+            }
+        });
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const floatx4 v = slot(wave, k)[r * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[k / NB][k % NB][4 * r + e] += v[e];
+            }
+    };
 
     if constexpr (SPLIT) {
     // ---------------- mainloop, split product
@@ -581,6 +618,118 @@ void tile_kernel(const TileArgs a) {
         if (++kt == KT) break;
     }
     __syncthreads();                                  // the epilogue reuses the panel memory
+    } else if constexpr (KSHARE) {
+    // ---------------- mainloop, small tiles with a long K: waves share out K, copies run three K tiles ahead, fragments one
+    // What bounds these tiles is LDS: every operand value is read once per wave that multiplies it.  So the
+    // waves do not cut the tile into ever smaller pieces but the K tile: KG groups of waves each multiply
+    // their part of every K tile into (all or a large part of) the tile, and the groups' sums meet
+    // in LDS behind the loop.  128x128 on eight waves: 64 KB of fragments per K tile (two groups, 64x64
+    // per wave) instead of 96 KB (64x32 per wave); 64x64 on four: 24 KB instead of 32 KB (four groups would
+    // read 16 KB, and measured no better).
+    // A wave holds the fragments of a K tile twice: while tile kt is multiplied, those of tile
+    // kt+1 are read behind its first MFMAs and have the rest of them to arrive.
+    // One barrier per K tile, behind its first MFMA: in front of it the copies of tile kt+1
+    // (issued three tiles ago) and the fragment reads of tile kt have been waited for, so behind it
+    // tile kt+1 is visible to every wave and buffer kt % 4 is free for the copy of tile kt+4.
+    // 1000 x 4096 x 4096 fp16 46.3 -> 41.6 us, 256 x 4096 x 4096 bf16 21.0 -> 16.2 us; what is left is the copies'
+    // rate (L2 to LDS, about 85 GB/s per CU) and power: the MFMAs alone, without copies, reads or barriers,
+    // take 30 us of the former.
+    static_assert(A_LD == 2 && B_LD == 2, "pairs of copies");
+    constexpr int KG = 2;                             // K groups
+    constexpr int WNG = 2, WMG = WAVES_M / KG;        // waves of a group across / down the tile
+    static_assert(KG * WNG * WMG == WAVES_M * WAVES_N && KS % KG == 0, "groups of waves");
+    constexpr int MBG = BM / WMG / 32, NBG = BN / WNG / 32, NK = MBG * NBG / KG;   // blocks of a wave; those it keeps
+    constexpr int NU = 4 / KG, KSG = KS / KG;         // chunk pairs and k-steps of a K tile per wave
+    static_assert(NK == MB * NB && KG == 2, "blocks of a wave");
+    const int g = wave_m % KG, wmg = wave_m / KG, wng = wave_n;
+    constexpr int NM = MBG * NBG, NMT = NM * KSG;     // MFMAs per k-step / per K tile
+    constexpr int NRT = (MBG + NBG) * NU;             // fragment chunks per K tile
+    constexpr int RSPAN = (NMT + 1) / 2;              // ... read behind this many MFMAs
+    const unsigned char *pA[NU], *pB[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int sw = ((2 * (g * NU + u) + h) ^ swz(l32)) << 4;
+        pA[u] = smem + (wmg * MBG * 32 + l32) * ROWB + sw;
+        pB[u] = smem + (BM + wng * NBG * 32 + l32) * ROWB + sw;
+    }
+    floatx16 part[MBG * NBG];
+#pragma unroll
+    for (int q = 0; q < MBG * NBG; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[q][r] = 0.0f;
+    u32x4 fa[2][MBG][NU], fb[2][NBG][NU];
+    const int KF = a.K / BK, KT = (a.K + BK - 1) / BK;    // whole K tiles; with the partial one
+    uint64_t partA[2], partB[2];                      // lanes whose chunk of the partial tile lies inside K
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        partA[i] = __ballot(KF * BK + gcA[i] * CW < a.K);
+        partB[i] = __ballot(KF * BK + gcB[i] * CW < a.K);
+    }
+    // copy w (A 0, A 1, B 0, B 1) of tile kt; past the last tile it moves nothing but is counted all the same
+    auto copy = [&](int kt, int w) __attribute__((always_inline)) {
+        const int i = w & 1, buf = kt & 3;
+        const uint64_t mask = kt < KF ? ~0ull : kt < KT ? (w < 2 ? partA[i] : partB[i]) : 0ull;
+        if (w < 2) lds_dma16_masked(Xt + (int64_t)kt * ROWB, oA[i], lds_waveA + buf * STAGE, i, i == 0, mask);
+        else       lds_dma16_masked(Wt + (int64_t)kt * ROWB, oB[i], lds_waveB + buf * STAGE, i, i == 0, mask);
+    };
+    auto zero_fill = [&](int kt) __attribute__((always_inline)) {        // this wave's chunks past K of the partial tile
+        unsigned char *sA = smem + (kt & 3) * STAGE + (ld_c << 4), *sB = sA + BM * ROWB;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (kt * BK + gcA[i] * CW >= a.K) *reinterpret_cast<u32x4 *>(sA + rowA[i] * ROWB) = u32x4{0u, 0u, 0u, 0u};
+            if (kt * BK + gcB[i] * CW >= a.K) *reinterpret_cast<u32x4 *>(sB + rowB[i] * ROWB) = u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    auto read = [&]<int SET>(int kt, int r) __attribute__((always_inline)) {          // fragment chunk r of tile kt
+        const int q = r / NU, u = r % NU, at = (kt & 3) * STAGE;
+        if (q < MBG) fa[SET][q][u] = *reinterpret_cast<const u32x4 *>(pA[u] + at + q * 32 * ROWB);
+        else         fb[SET][q - MBG][u] = *reinterpret_cast<const u32x4 *>(pB[u] + at + (q - MBG) * 32 * ROWB);
+    };
+    auto mma = [&]<int SET>(int m) __attribute__((always_inline)) {
+        const int t = m / NM, i = (m % NM) / NBG, j = m % NBG;
+        if constexpr (F8) {
+            const u32x4 av[2] = {fa[SET][i][2 * t], fa[SET][i][2 * t + 1]}, bv[2] = {fb[SET][j][2 * t], fb[SET][j][2 * t + 1]};
+            Mma<InT>::run(av, bv, part[i * NBG + j]);
+        } else {
+            Mma<InT>::run(fa[SET][i][t], fb[SET][j][t], part[i * NBG + j]);
+        }
+    };
+    // one K tile; behind the last one the fragments of a tile that does not exist are read and never used
+    auto tile_body = [&]<int SET>(int kt) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): the fragments of tile kt
+#pragma unroll
+        for (int m = 0; m < NMT; ++m) {
+            mma.template operator()<SET>(m);
+            if (m == 0) {
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * NS) : "memory");
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int r = (m * NRT) / RSPAN; r < ((m + 1) * NRT) / RSPAN && r < NRT; ++r) read.template operator()<SET ^ 1>(kt + 1, r);
+#pragma unroll
+            for (int w = (m * NS) / NMT; w < ((m + 1) * NS) / NMT; ++w) copy(kt + 4, w);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (KF < KT && kt + 4 == KF) zero_fill(KF);
+    };
+    static_for<0, 4>([&]<int t>() __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < NS; ++w) copy(t, w);
+        if (KF < KT && t == KF) zero_fill(t);
+    });
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NS) : "memory");
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < NRT; ++r) read.template operator()<0>(0, r);
+    for (int kt = 0;;) {
+        tile_body.template operator()<0>(kt);
+        if (++kt == KT) break;
+        tile_body.template operator()<1>(kt);
+        if (++kt == KT) break;
+    }
+    lds_dma_wait();
+    join_groups(part);
     } else {
     // ---------------- mainloop
     // Per staged tile: KS k-steps of NM MFMAs.  Fragments of the next k-step are read from LDS
@@ -752,14 +901,15 @@ void tile_kernel(const TileArgs a) {
         TileArgs ag = a;
         ag.act = FGE_ACT_NONE; ag.alpha = 1.0f; ag.post = 1.0f; ag.b = nullptr;
         using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false>;
-        static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= 2 * STAGE, "store patches fit the panels");
+        static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= NST * STAGE, "store patches fit the panels");
         Epi epi(ag, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
                 wave_n, lane);
         epi.template tile<NT>(gated, wave_m * WTM, rowblock, tid);
     } else {
         using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, -1, false, false, ANY>;
-        static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= 2 * STAGE, "store patches fit the panels");
-        Epi epi(a, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
+        constexpr int PATCH_BYTES = KSHARE ? OWN : Epi::PATCH_FLOATS * 4;
+        static_assert(WAVES_M * WAVES_N * PATCH_BYTES <= NST * STAGE && Epi::PATCH_FLOATS * 4 <= PATCH_BYTES, "store patches fit the panels");
+        Epi epi(a, out, xch, reinterpret_cast<float *>(smem + wave * PATCH_BYTES), BM, z, m0, n0, tn,
                 wave_n, lane);
         epi.template tile<NT>(acc, wave_m * WTM, rowblock, tid);
     }
