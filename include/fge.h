@@ -106,7 +106,10 @@ typedef enum {
  *   does not, the two-pass form is taken.  A tile whose wait runs out all the same (its row block's
  *   other tiles did not arrive within about 2^20 polls) stores NaN for its rows - and NaN in
  *   aux_out for LOGSUMEXP - and sets the fault word (fge_fault_word_offset): the kernel always
- *   terminates and never stores values normalised with incomplete statistics.  The stage entry
+ *   terminates and never stores values normalised with incomplete statistics.  (Products of at most
+ *   64 rows finish their rows in the launch's last workgroups, which wait in the same bounded way
+ *   for workgroups that started before them, so other launches cannot keep those from arriving;
+ *   the flag moves the row operation to a second kernel there as well.)  The stage entry
  *   points fge_fused_tiles / fge_fused_finish always take the two-pass form.
  *   FGE_FLAG_IEEE_FP32 : multiply fp32 operands with the fp32 matrix instruction.  Without it
  *   fp32 operands are multiplied on the bf16 matrix instruction after a split of each operand
