@@ -255,7 +255,8 @@ struct TileEpilogue {
             }
 #pragma unroll
             for (int q = 0; q < NPG; ++q) {
-                const float c = -ml[q] * LOG2E;
+                // (a strip of masked columns only - every value -inf - has exponentials of zero, not of -inf + inf)
+                const float c = ANY && ml[q] == OpMax::ident() ? 0.0f : -ml[q] * LOG2E;
                 float s = 0.0f;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {

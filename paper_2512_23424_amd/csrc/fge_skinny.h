@@ -132,7 +132,7 @@ __device__ __forceinline__ void skinny_row(const SkinnyArgs &a, int row, int gro
             for (int j = 0; j < NP; ++j) mn = max_nc(mn, e[j].x);
             s = m == OpMax::ident() ? 0.0f : s * fast_exp(m - mn);
 #pragma unroll
-            for (int j = 0; j < NP; ++j) s += e[j].y * fast_exp(e[j].x - mn);
+            for (int j = 0; j < NP; ++j) s += e[j].x == OpMax::ident() ? 0.0f : e[j].y * fast_exp(e[j].x - mn);
             m = mn;
         }
         const float mt = m;
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(64 * SKINNY_WAVES) void skinny_kernel(const SkinnyA
         if (a.norm == FGE_NORM_LOGSUMEXP) {           // maximum and sum of exponentials over this workgroup's columns
             const float v1 = col + 1 < a.N ? v[1] : OpMax::ident();
             const float m = allreduce_lanes<OpMax, COLS / 2>(col < a.N ? max_nc(v[0], v1) : OpMax::ident());
-            const float c = -m * LOG2E;
+            const float c = m == OpMax::ident() ? 0.0f : -m * LOG2E;      // (masked columns only: a sum of zero)
             const float s = allreduce_lanes<OpSum, COLS / 2>(col < a.N ? exp_rel(v[0], c) + (col + 1 < a.N ? exp_rel(v[1], c) : 0.0f) : 0.0f);
             if (cc == 0) skinny_put2(a.mid + row * a.ld_mid + 2 * blockIdx.x, m, s);
         } else if (a.norm != FGE_NORM_NONE && col < a.N) {

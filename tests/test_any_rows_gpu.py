@@ -56,3 +56,30 @@ def test_row_operations_on_rows_of_any_width(dt, out, norm):
         ref, raux = H.oracle_chain(w, t)
         got, gaux = _run(w, d, pad)
         H.check(w, got, gaux, ref, raux, f"any rows {M}x{K}x{N}+{pad}")
+
+
+@pytest.mark.parametrize("M", [7, 300])
+@pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LOGSUMEXP])
+def test_masked_columns_contribute_nothing(M, norm):
+    """A bias of -inf masks columns, whole strips of a tile among them: probabilities of zero and a
+    finite logsumexp, for few rows and for rows of odd width."""
+    K, N = 1024, 2051
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    W = (torch.randn(N, K, generator=g, device="cuda") / K ** 0.5).bfloat16()
+    b = torch.zeros(N, device="cuda")
+    b[64:330] = b[1000:1016] = b[1800:] = float("-inf")
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    aux = torch.full((M,), float("nan"), device="cuda") if norm == I.NORM_LOGSUMEXP else None
+    p = B.make_params(X, W, out, aux_out=aux)
+    ws = torch.empty(B.fge_workspace_bytes(True, I.ACT_NONE, norm, p), dtype=torch.uint8, device="cuda")
+    p.workspace, p.workspace_bytes = ws.data_ptr(), ws.numel()
+    B.fused_gemm_epilogue(X, W, b, I.ACT_NONE, norm, p, out)
+    torch.cuda.synchronize()
+    ref = X.double().cpu() @ W.double().cpu().T + b.double().cpu()
+    if norm == I.NORM_LOGSUMEXP:
+        assert torch.allclose(aux.double().cpu(), torch.logsumexp(ref, 1), rtol=1e-5)      # fp32 sums
+        assert bool((out[:, 1800:] == float("-inf")).all())
+    else:
+        assert torch.allclose(out.double().cpu(), torch.softmax(ref, 1), rtol=2 ** -7, atol=1e-9)   # one bf16 rounding
+        assert bool((out[:, 64:330] == 0).all())
