@@ -415,10 +415,10 @@ bool skinny_in_kernel(const fge_params *p, int norm) {
 
 Skinny plan_skinny(const fge_params *p, int norm, bool gated) {
     Skinny k{};
-    const Plan pl = make_plan(p, FGE_NORM_NONE, true, TILE_64x64);      // for the folded problem only
-    k.pr = pl.pr;
     if (p->in_dtype == FGE_F32 || forced_tile(p) >= 0 || (p->flags & FGE_FLAG_NO_SPLIT_K)) return k;
-    if (k.pr.batch != 1 || k.pr.M > SKINNY_ROWS || (int64_t)k.pr.K * (int64_t)esize(p->in_dtype) < 128 * SKINNY_WAVES) return k;
+    if ((int64_t)p->M * p->batch > SKINNY_ROWS) return k;
+    k.pr = make_plan(p, FGE_NORM_NONE, true, TILE_64x64).pr;            // the folded problem
+    if (k.pr.batch != 1 || (int64_t)k.pr.K * (int64_t)esize(p->in_dtype) < 128 * SKINNY_WAVES) return k;
     if (!operand_ok(p, k.pr.ldx, 0) || !operand_ok(p, k.pr.ldw, 0)) return k;
     if (norm != FGE_NORM_NONE && norm != FGE_NORM_LOGSUMEXP && k.pr.N > SKINNY_WIDE_N) return k;
     // (8-bit operands that would otherwise be multiplied by fp32 FMAs stay there: the 8-bit matrix
