@@ -169,6 +169,10 @@ __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcp
 constexpr float LOG2E = 1.4426950408889634f;
 // exp(x - m) as one multiply-add and one exponential: c = -m * LOG2E is formed once per row
 __device__ __forceinline__ float exp_rel(float x, float c) { return __builtin_amdgcn_exp2f(fmaf(x, LOG2E, c)); }
+// exp(x - m) with the difference formed first, for references that may be the value of a mask: a product
+// -m * LOG2E of -1e10 and beyond is off by more than the exponents fp32 has, and that of the lowest finite
+// values overflows, where x == m has to give 1.
+__device__ __forceinline__ float exp_diff(float x, float m) { return __builtin_amdgcn_exp2f((x - m) * LOG2E); }
 // max / clamp as single median-of-three instructions (the compiler wraps fmaxf / fminf of
 // values it cannot prove canonical - anything that came through LDS or a select - in an extra
 // canonicalising instruction each)
@@ -235,6 +239,9 @@ struct OpSum { __device__ static __forceinline__ float f(float a, float b) { ret
                static constexpr float ident() { return 0.0f; } };
 struct OpMax { __device__ static __forceinline__ float f(float a, float b) { return max_nc(a, b); }
                static constexpr float ident() { return -__builtin_inff(); } };
+// The reference exponentials are taken against, for a maximum m: of values that are all -inf (masked
+// columns) any finite one serves, and their exponentials are zero.
+__device__ __forceinline__ float exp_ref(float m) { return m == OpMax::ident() ? 0.0f : m; }
 
 template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(

@@ -360,8 +360,8 @@ __global__ __launch_bounds__(64 * SKINNY_WAVES) void skinny_kernel(const SkinnyA
         if (a.norm == FGE_NORM_LOGSUMEXP) {           // maximum and sum of exponentials over this workgroup's columns
             const float v1 = col + 1 < a.N ? v[1] : OpMax::ident();
             const float m = allreduce_lanes<OpMax, COLS / 2>(col < a.N ? max_nc(v[0], v1) : OpMax::ident());
-            const float c = m == OpMax::ident() ? 0.0f : -m * LOG2E;      // (masked columns only: a sum of zero)
-            const float s = allreduce_lanes<OpSum, COLS / 2>(col < a.N ? exp_rel(v[0], c) + (col + 1 < a.N ? exp_rel(v[1], c) : 0.0f) : 0.0f);
+            const float r = exp_ref(m);               // (the columns may all be masked, by any value)
+            const float s = allreduce_lanes<OpSum, COLS / 2>(col < a.N ? exp_diff(v[0], r) + (col + 1 < a.N ? exp_diff(v[1], r) : 0.0f) : 0.0f);
             if (cc == 0) skinny_put2(a.mid + row * a.ld_mid + 2 * blockIdx.x, m, s);
         } else if (a.norm != FGE_NORM_NONE && col < a.N) {
             skinny_put2(a.mid + row * a.ld_mid + col, v[0], v[1]);
