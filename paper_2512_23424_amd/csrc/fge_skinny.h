@@ -130,14 +130,16 @@ __device__ __forceinline__ void skinny_row(const SkinnyArgs &a, int row, int gro
             float mn = m;
 #pragma unroll
             for (int j = 0; j < NP; ++j) mn = max_nc(mn, e[j].x);
-            s = m == OpMax::ident() ? 0.0f : s * fast_exp(m - mn);
+            // (exp(-inf) = 0 drops a group of masked columns, but not the NaN its sum may be)
+            const float r = exp_ref(mn);
+            s *= fast_exp(m - r);
 #pragma unroll
-            for (int j = 0; j < NP; ++j) s += e[j].x == OpMax::ident() ? 0.0f : e[j].y * fast_exp(e[j].x - mn);
+            for (int j = 0; j < NP; ++j) s += e[j].y * fast_exp(e[j].x - r);
             m = mn;
         }
         const float mt = m;
         m = block_reduce(OpMax{}, mt);
-        s = block_reduce(OpSum{}, mt == OpMax::ident() ? 0.0f : s * fast_exp(mt - m)) + bad;
+        s = block_reduce(OpSum{}, s * fast_exp(mt - exp_ref(m))) + bad;
         if (tid == 0) a.aux[row] = m + __logf(s);
         return;
     }

@@ -57,3 +57,20 @@ def test_masks_of_any_size_contribute_nothing(case, norm):
             tol = {"f32": 1e-3, "f8": 2e-2, "f16": 2 ** -9}.get(dt, 2 ** -7)
             assert torch.allclose(out, torch.softmax(ref, 1), rtol=tol, atol=1e-7), f"mask {mask}"
             assert bool((out[:, masked] == 0).all()), f"mask {mask}"
+
+
+@pytest.mark.parametrize("case", [("bf16", 7, 1024, 1025, 0), ("f16", 17, 1024, 4097, 0), ("bf16", 7, 1024, 1025, B.FLAG_TWO_PASS),
+                                  ("bf16", 300, 1024, 2049, 0), ("bf16", 300, 256, 2056, tile(0))], ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LOGSUMEXP])
+def test_a_nan_column_reaches_the_result(case, norm):
+    """One NaN in a row makes its logsumexp and its probabilities NaN - alone in the last strip, or among
+    masked columns that have no maximum of their own."""
+    dt, M, K, N, flags = case
+    for columns_masked, at in (([], N - 1), ([(N - 400, N)], N - 1), ([(0, 300)], 5)):
+        b = torch.zeros(N, device="cuda")
+        for lo, hi in columns_masked:
+            b[lo:hi] = float("-inf")
+        b[at] = float("nan")
+        out, aux, _ = call(dt, M, K, N, flags, norm, b)
+        assert bool(torch.isnan(out[:, at]).all())
+        assert bool(torch.isnan(out if norm == I.NORM_SOFTMAX else aux).all()), f"masked {columns_masked}"
