@@ -124,6 +124,9 @@ struct TileEpilogue {
     float scale, bias[NB];      // y = scale * acc + bias  (scale = post*alpha, bias = post*b)
     bool whole_row;
     bool bounded;               // clamp activation with a narrow range feeds softmax / logsumexp
+    bool masked;                // the bias may mask columns of the wave: a strip may have no other, and its exponentials
+                                // are taken of differences formed first, see exp_diff - one more operation per value,
+                                // so only here and with ANY
     bool defer_lse = false;     // whole-row logsumexp: park the strip pairs, the caller merges them later
     int lse_par = 0;            // exchange buffer the parked pairs of this tile go to
 
@@ -155,6 +158,10 @@ struct TileEpilogue {
         whole_row = a.tiles_n == 1;
         // (not in the cooperative form, whose registers are too scarce for two more variants)
         bounded = !COOP && a.act == FGE_ACT_CLAMP && a.hi - a.lo <= 64.0f;
+        bool far = false;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) far = far || fabsf(bias[j]) > 1024.0f;
+        masked = __any(far);
     }
 
     // four neighbouring values of gamma / beta from column c on (inside N), the ones past N being zero
@@ -232,6 +239,48 @@ struct TileEpilogue {
         }
     }
 
+    // Softmax / logsumexp, first step: every strip's maximum and the sum of its exponentials against
+    // that maximum (softmax: the exponentials take the values' place).  BOUNDED: see norm_group.  MASKED:
+    // columns may be masked, see `masked`; where the values are not needed any more (softmax; the cooperative
+    // form's logsumexp has stored them) the differences are formed in place instead, a small branch in a kernel
+    // that a second copy of this code slows down (16 x 2048 x 512 x 2048 softmax 150.6 -> 156.5 us).
+    template <int NORM, bool FULL, bool BOUNDED, bool MASKED>
+    __device__ __forceinline__ void strip_sums(float (&v)[NPG][VEC], float (&ml)[NPG], float (&sum)[NPG]) {
+        auto okc = [&](int e) __attribute__((always_inline)) { return FULL || okv[ANY ? e : e >> 2]; };
+#pragma unroll
+        for (int q = 0; q < NPG; ++q) {
+            if constexpr (BOUNDED) {
+                ml[q] = a.hi;
+            } else {
+                float m = OpMax::ident();
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) m = max_nc(m, okc(e) ? v[q][e] : OpMax::ident());
+                ml[q] = allreduce_lanes<OpMax, LPR>(m);
+            }
+        }
+        constexpr bool IN_PLACE = !BOUNDED && !MASKED && (COOP || NORM == FGE_NORM_SOFTMAX);
+        if (IN_PLACE && masked) {
+#pragma unroll
+            for (int q = 0; q < NPG; ++q) {
+                const float r = exp_ref(ml[q]);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[q][e] -= r;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NPG; ++q) {
+            const float r = MASKED ? exp_ref(ml[q]) : IN_PLACE && masked ? 0.0f : -ml[q] * LOG2E;
+            float s = 0.0f;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const float x = MASKED ? exp_diff(v[q][e], r) : exp_rel(v[q][e], r);
+                if constexpr (NORM == FGE_NORM_SOFTMAX) v[q][e] = x;
+                s += okc(e) ? x : 0.0f;
+            }
+            sum[q] = allreduce_lanes<OpSum, LPR>(s);
+        }
+    }
+
     // Row operation on one group in the row-wise layout: v[q][e] is column gcol + (e/4)*G4STEP + e%4 of tile row
     // qrow(grow0, q).  Whole rows are normalised in place; split rows keep the parked value.
     // BOUNDED (softmax / logsumexp after a clamp): every value lies in [lo, hi] with hi - lo
@@ -242,32 +291,10 @@ struct TileEpilogue {
         float s0[NPG], s1[NPG];
         if constexpr (NORM == FGE_NORM_SOFTMAX || NORM == FGE_NORM_LOGSUMEXP) {
             float ml[NPG];                            // strip maxima (or the common bound)
+            if (!BOUNDED && !ANY && !COOP && NORM == FGE_NORM_LOGSUMEXP && masked) strip_sums<NORM, FULL, false, true>(v, ml, s1);
+            else                                                                   strip_sums<NORM, FULL, BOUNDED, ANY>(v, ml, s1);
 #pragma unroll
-            for (int q = 0; q < NPG; ++q) {
-                if constexpr (BOUNDED) {
-                    ml[q] = a.hi;
-                } else {
-                    float m = OpMax::ident();
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) m = max_nc(m, okc(e) ? v[q][e] : OpMax::ident());
-                    ml[q] = allreduce_lanes<OpMax, LPR>(m);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < NPG; ++q) {
-                // (a strip of masked columns only - every value -inf - has exponentials of zero, not of -inf + inf)
-                const float c = ANY && ml[q] == OpMax::ident() ? 0.0f : -ml[q] * LOG2E;
-                float s = 0.0f;
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    const float x = exp_rel(v[q][e], c);
-                    if constexpr (NORM == FGE_NORM_SOFTMAX) v[q][e] = x;
-                    s += okc(e) ? x : 0.0f;
-                }
-                s0[q] = ml[q];
-                s1[q] = allreduce_lanes<OpSum, LPR>(s);
-                mkeep[q] = ml[q];
-            }
+            for (int q = 0; q < NPG; ++q) s0[q] = mkeep[q] = ml[q];
             if (!whole_row) {
                 // softmax parks exp(a - m_strip); the second pass rescales by exp(m_strip - m)/s
 #pragma unroll
@@ -397,6 +424,15 @@ struct TileEpilogue {
             if constexpr (NORM_CT != FGE_NORM_NONE) norm_group<NORM_CT, FULL, BOUNDED_CT>(v, grow0, mkeep);
             return;
         }
+        if constexpr (COOP) {
+            switch (a.norm) {
+            case FGE_NORM_SOFTMAX:       norm_group<FGE_NORM_SOFTMAX, FULL, false>(v, grow0, mkeep); break;
+            case FGE_NORM_LOGSUMEXP:     norm_group<FGE_NORM_LOGSUMEXP, FULL, false>(v, grow0, mkeep); break;
+            case FGE_NORM_LAYERNORM:     norm_group<FGE_NORM_LAYERNORM, FULL, false>(v, grow0, mkeep); break;
+            default:                     norm_group<FGE_NORM_RMSNORM, FULL, false>(v, grow0, mkeep); break;
+            }
+            return;
+        }
         switch (a.norm + (bounded ? 8 : 0)) {
         case FGE_NORM_NONE: case FGE_NORM_NONE + 8: break;
         case FGE_NORM_SOFTMAX:       norm_group<FGE_NORM_SOFTMAX, FULL, false>(v, grow0, mkeep); break;
@@ -512,7 +548,7 @@ struct TileEpilogue {
 #pragma unroll
             for (int w = 1; w < WAVES_N; ++w) o0 = max_nc(o0, e[w].x);
 #pragma unroll
-            for (int w = 0; w < WAVES_N; ++w) o1 += e[w].y * fast_exp(e[w].x - o0);   // empty strips: 0 * exp(-inf)
+            for (int w = 0; w < WAVES_N; ++w) o1 += e[w].y * fast_exp(e[w].x - exp_ref(o0));   // empty and masked strips: 0 * exp(-inf)
         } else if (a.norm == FGE_NORM_LAYERNORM) {
             const int nt = max(1, min(WAVES_N * WTN, a.N - n0));
             float sm = 0.0f;
@@ -583,14 +619,14 @@ struct TileEpilogue {
                 float mc = e[0].x;
 #pragma unroll
                 for (int i = 1; i < CH; ++i) mc = max_nc(mc, e[i].x);
-                const float mn = max_nc(m, mc);            // finite: slot t0 exists and every tile has columns
-                sum *= fast_exp(m - mn);
+                const float mn = max_nc(m, mc), r = exp_ref(mn);   // (-inf: every column so far is masked)
+                sum *= fast_exp(m - r);
 #pragma unroll
-                for (int i = 0; i < CH; ++i) sum += e[i].y * fast_exp(e[i].x - mn);
+                for (int i = 0; i < CH; ++i) sum += e[i].y * fast_exp(e[i].x - r);
                 m = mn;
             }
             o0 = allreduce_lanes<OpMax, TPR>(m);
-            const float sden = allreduce_lanes<OpSum, TPR>(m == OpMax::ident() ? 0.0f : sum * fast_exp(m - o0));
+            const float sden = allreduce_lanes<OpSum, TPR>(sum * fast_exp(m - exp_ref(o0)));
             if (a.norm == FGE_NORM_SOFTMAX) o1 = fast_rcp(sden);
             else if (part == 0 && tn == 0 && grow < a.M) a.aux[row_base + grow] = waited_ok ? o0 + __logf(sden) : __builtin_nanf("");
         } else if (a.norm == FGE_NORM_LAYERNORM) {
@@ -657,7 +693,7 @@ struct TileEpilogue {
         for (int q = 0; q < NPG; ++q) {
             const float2 r = fin[qrow(grow0, q)];
             if constexpr (NORM == FGE_NORM_SOFTMAX) {      // v holds exp(a - mkeep)
-                const float f = exp_rel(mkeep[q], -r.x * LOG2E) * r.y;
+                const float f = fast_exp(mkeep[q] - r.x) * r.y;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) v[q][e] *= f;
             } else if constexpr (NORM == FGE_NORM_LAYERNORM) {
@@ -683,8 +719,8 @@ struct TileEpilogue {
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
                 static_for<0, G>([&]<int b>() __attribute__((always_inline)) { to_rows<b>(acc[g * G + b], vall[g]); });
                 const int grow0 = trow0 + g * G * 32;
-                norm_dispatch<FULL_TILE>(vall[g], grow0, mkeep[g]);
                 if (a.norm == FGE_NORM_LOGSUMEXP) store_group<FULL_TILE>(vall[g], grow0);
+                norm_dispatch<FULL_TILE>(vall[g], grow0, mkeep[g]);
             });
             // the affine vectors are the same for every group: fetched once, behind the wait
             float gam[VEC], bet[VEC];

@@ -18,6 +18,12 @@ def tile(t, flags=0):
 
 # (type of the operands, M, K, N, flags): what runs
 FEW = [("bf16", 7, 1024, 2051, 0), ("f16", 40, 1032, 2048, 0), ("f8", 17, 1024, 4098, 0), ("bf16", 16, 1024, 1500, B.FLAG_TWO_PASS)]
+ANY = [("bf16", 300, 1024, 2051, 0), ("f8", 300, 272, 2050, tile(3)), ("f32", 300, 272, 2051, 0), ("f32", 300, 272, 2051, B.FLAG_IEEE_FP32),
+       ("f16", 300, 272, 2049, tile(10))]
+ALIGNED = [("bf16", 300, 256, 2048, tile(0)), ("f32", 300, 256, 2048, tile(0)),                        # second pass
+           ("bf16", 2000, 256, 2048, tile(3)), ("f8", 700, 1024, 2048, tile(2)), ("f16", 700, 1024, 2048, tile(10)),     # one kernel
+           ("bf16", 700, 256, 2048, tile(7)), ("f32", 700, 256, 2048, tile(5)), ("f32", 700, 256, 2048, tile(9)),
+           ("bf16", 300, 256, 448, tile(1)), ("f32", 300, 256, 448, tile(1)), ("f32", 4200, 64, 448, 0)]               # whole rows
 
 
 def call(dt, M, K, N, flags, norm, b, W=None, gated=False):
@@ -38,7 +44,7 @@ def call(dt, M, K, N, flags, norm, b, W=None, gated=False):
 
 
 @pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LOGSUMEXP])
-@pytest.mark.parametrize("case", FEW, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("case", FEW + ANY + ALIGNED, ids=lambda c: "-".join(map(str, c)))
 def test_masks_of_any_size_contribute_nothing(case, norm):
     dt, M, K, N, flags = case
     for mask in MASKS:
@@ -60,7 +66,8 @@ def test_masks_of_any_size_contribute_nothing(case, norm):
 
 
 @pytest.mark.parametrize("case", [("bf16", 7, 1024, 1025, 0), ("f16", 17, 1024, 4097, 0), ("bf16", 7, 1024, 1025, B.FLAG_TWO_PASS),
-                                  ("bf16", 300, 1024, 2049, 0), ("bf16", 300, 256, 2056, tile(0))], ids=lambda c: "-".join(map(str, c)))
+                                  ("bf16", 300, 1024, 2049, 0), ("bf16", 300, 256, 2056, tile(0)), ("bf16", 2000, 256, 2056, tile(3)),
+                                  ("f32", 300, 256, 448, tile(1)), ("f32", 4200, 64, 456, 0)], ids=lambda c: "-".join(map(str, c)))
 @pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LOGSUMEXP])
 def test_a_nan_column_reaches_the_result(case, norm):
     """One NaN in a row makes its logsumexp and its probabilities NaN - alone in the last strip, or among
