@@ -203,25 +203,26 @@ __global__ __launch_bounds__(256) void aligned_src_row_kernel(const GenArgs a) {
             s = block_reduce(OpSum{}, s);
         } else {
             // a row that is read from memory every time: maximum and sum in one pass - every thread
-            // keeps a running maximum and rescales its sum so far whenever the maximum rises
-            // (a thread without elements ends with 0 * exp2(-inf) = 0)
+            // keeps a running maximum and rescales its sum so far whenever the maximum rises (the values
+            // so far may all be masked, by any value: see exp_diff; a thread without elements ends with
+            // 0 * exp2(-inf) = 0)
 #pragma unroll 4
             for (int q = tid; q < n4; q += 256) {
                 const floatx4 v = *reinterpret_cast<const floatx4 *>(src + 4 * q);
                 const float mn = max_nc(max_nc(max_nc(v[0], v[1]), max_nc(v[2], v[3])), m);
-                const float cn = -mn * LOG2E;
-                s = s * exp_rel(m, cn) + ((exp_rel(v[0], cn) + exp_rel(v[1], cn)) + (exp_rel(v[2], cn) + exp_rel(v[3], cn)));
+                const float r = exp_ref(mn);
+                s = s * exp_diff(m, r) + ((exp_diff(v[0], r) + exp_diff(v[1], r)) + (exp_diff(v[2], r) + exp_diff(v[3], r)));
                 m = mn;
             }
             if (const int j = 4 * n4 + tid; j < a.N) {
-                const float v = src[j], mn = max_nc(v, m), cn = -mn * LOG2E;
-                s = s * exp_rel(m, cn) + exp_rel(v, cn);
+                const float v = src[j], mn = max_nc(v, m), r = exp_ref(mn);
+                s = s * exp_diff(m, r) + exp_diff(v, r);
                 m = mn;
             }
             const float mt = m;
             m = block_reduce(OpMax{}, mt);
             c = -m * LOG2E;
-            s = block_reduce(OpSum{}, s * exp_rel(mt, c));
+            s = block_reduce(OpSum{}, s * exp_diff(mt, exp_ref(m)));
         }
         if (a.norm == FGE_NORM_SOFTMAX) {
             const float inv = 1.0f / s;

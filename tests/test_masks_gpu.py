@@ -24,13 +24,13 @@ ALIGNED = [("bf16", 300, 256, 2048, tile(0)), ("f32", 300, 256, 2048, tile(0)), 
            ("bf16", 2000, 256, 2048, tile(3)), ("f8", 700, 1024, 2048, tile(2)), ("f16", 700, 1024, 2048, tile(10)),     # one kernel
            ("bf16", 700, 256, 2048, tile(7)), ("f32", 700, 256, 2048, tile(5)), ("f32", 700, 256, 2048, tile(9)),
            ("bf16", 300, 256, 448, tile(1)), ("f32", 300, 256, 448, tile(1)), ("f32", 4200, 64, 448, 0)]               # whole rows
+SLICED = [("bf16", 70, 4096, 2048, 0), ("f32", 40, 4096, 2051, 0), ("f32", 20, 2048, 16381, 0), ("f32", 3, 64, 2051, 0)]
 
 
-def call(dt, M, K, N, flags, norm, b, W=None, gated=False):
+def call(dt, M, K, N, flags, norm, b):
     g = torch.Generator(device="cuda").manual_seed(5)
     X = torch.randn(M, K, generator=g, device="cuda").to(DT[dt])
-    if W is None:
-        W = (torch.randn(N, K, generator=g, device="cuda") / (1.0 if dt == "f8" else K ** 0.5)).to(DT[dt])
+    W = (torch.randn(N, K, generator=g, device="cuda") / (1.0 if dt == "f8" else K ** 0.5)).to(DT[dt])
     alpha = 1.0 / K ** 0.5 if dt == "f8" else 1.0
     out = torch.full((M, N), float("nan"), dtype=torch.bfloat16 if dt == "f8" else DT[dt], device="cuda")
     aux = torch.full((M,), float("nan"), device="cuda") if norm == I.NORM_LOGSUMEXP else None
@@ -44,7 +44,7 @@ def call(dt, M, K, N, flags, norm, b, W=None, gated=False):
 
 
 @pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LOGSUMEXP])
-@pytest.mark.parametrize("case", FEW + ANY + ALIGNED, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("case", FEW + ANY + ALIGNED + SLICED, ids=lambda c: "-".join(map(str, c)))
 def test_masks_of_any_size_contribute_nothing(case, norm):
     dt, M, K, N, flags = case
     for mask in MASKS:
