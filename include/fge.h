@@ -255,8 +255,8 @@ const char *fge_gated_tile_name(int act, int norm, const fge_params *p);
 
 /* ---- the individual stages, callable on their own (the two paths above are built from them) */
 
-/* Fused stage 1: the tile kernel, always in the two-pass form.  When the chosen tile spans N it
- * produces the final out; otherwise the tiles park their values in out and publish per-strip row
+/* Fused stage 1: the tile kernel, always in the two-pass form.  When the chosen tile spans N - and for
+ * shapes off the 16-byte grid - it produces the final out; otherwise the tiles park their values in out and publish per-strip row
  * statistics to the workspace (split rows, paper Fig. 2: statistics first, normalise second). */
 int fge_fused_tiles(const void *X, const void *W, const float *b, int act, int norm,
                     const fge_params *p, void *out, void *stream);

@@ -452,13 +452,18 @@ struct Repack {
     bool copy_x, copy_w;         // which operands are copied (one that the tile kernels can stage where it lies is not)
     int Kp, Np;                  // padded contraction length / padded width of the fp32 rows
     int64_t rows, w_rows;        // rows of the padded X / W
-    size_t off_w, off_b, off_mid, off_inner, bytes;      // workspace layout; the padded X sits at 0
+    size_t off_w, off_b, off_mid, off_inner;             // workspace layout; the padded X sits at 0
+    size_t need, bytes;          // bytes of it in use / the figure callers are told
     fge_params inner;            // the padded problem (workspace still to be filled in)
     bool any;                    // odd_out: the tile kernels store straight into `out`
     fge_params any_p;            // ... that problem; its workspace starts at off_b
     bool parked;                 // odd_out: the tile kernels park fp32 rows and their statistics, a second pass finishes them
     fge_params parked_p;         // ... that problem; the rows lie at off_b, its workspace at off_parked
     size_t off_parked;
+    // Whether the stage entry points run it as well, whole in stage 1 (nothing in it waits for another
+    // workgroup): their element-granular product would need fp32 rows that the tile kernels have no use for
+    // (2048 x 4096 x 50257 with logsumexp: 412 MB, against 13 MB of statistics).  Few rows may take the few-row kernel, which waits.
+    bool staged() const { return (any || parked) && !copy_x && !copy_w && rows > SKINNY_ROWS; }
 };
 
 Repack plan_repack(const fge_params *p, int norm);
@@ -471,6 +476,7 @@ size_t fused_workspace(const fge_params *p, int norm) {
     const size_t few = plan_skinny(p, norm, false).bytes();
     if (p1.generic) {                // room for the repacked operands where the problem is worth repacking
         const Repack rp = plan_repack(p, norm);
+        if (rp.use && rp.staged()) return rp.bytes;
         return std::max({rp.use ? rp.bytes : 0, p1.ws_generic, few});
     }
     return std::max({p1.ws_stats + p1.ws_marks, p2.ws_stats + p2.ws_marks, k_split(p, norm, p1).bytes(), few});
@@ -745,7 +751,8 @@ int run_fused(const void *X, const void *W, const float *b, int act, int norm, c
 //           and a row kernel that stores element by element and never looks at the padding
 //           columns turns them into `out` (launch_generic_row: one workgroup per row, since these
 //           rows start on 16-byte boundaries).
-// The stage entry points and the unfused sequence keep the element-granular product.
+// The unfused sequence keeps the element-granular product, and so do the stage entry points but for the
+// first two ways without copies (see Repack::staged).
 // The tiles a product without row op would take: nothing is exchanged between them in this form.
 Plan plan_parked(const fge_params *q, int norm) {
     return make_plan(q, norm, true, make_plan(q, FGE_NORM_NONE, true).tile);
@@ -791,7 +798,7 @@ Repack plan_repack(const fge_params *p, int norm) {
     r.off_b = r.off_w + wp;
     r.off_mid = r.off_b + (r.odd_out ? round256((size_t)r.Np * sizeof(float)) : 0);
     r.off_inner = r.off_mid + (r.odd_out ? round256((size_t)rows * r.Np * sizeof(float)) : 0);
-    r.bytes = r.off_inner + fused_workspace(&r.inner, r.odd_out ? FGE_NORM_NONE : norm);
+    r.need = r.bytes = r.off_inner + fused_workspace(&r.inner, r.odd_out ? FGE_NORM_NONE : norm);
     r.use = true;
     if (!r.odd_out || k_split(&r.inner, FGE_NORM_NONE, make_plan(&r.inner, FGE_NORM_NONE)).slices > 1) return r;
     const bool final_at_once = norm == FGE_NORM_NONE || norm == FGE_NORM_LOGSUMEXP;
@@ -822,7 +829,12 @@ Repack plan_repack(const fge_params *p, int norm) {
         r.parked = !pl.generic && pl.split && pl.strips <= MAX_SPLIT;
         if (r.parked) need = r.off_parked + pl.ws_stats;
     }
-    r.bytes = std::max(r.bytes, need);
+    // The padded fp32 rows of the third way are not touched then.  (Where operands are copied, the figure
+    // callers ask for has stayed that of the third way; what they bring may be as small as `need`.)
+    if (r.any || r.parked) {
+        r.need = need;
+        r.bytes = r.copy_x || r.copy_w ? std::max(r.bytes, need) : need;
+    }
     return r;
 }
 
@@ -919,10 +931,9 @@ int do_fused_tiles(const void *X, const void *W, const float *b, int act, int no
     const Plan pl = make_plan(p, norm, !one_call || capturing(s));
     if (plan_out) *plan_out = pl;
     if (pl.generic) {
-        if (one_call) {
-            const Repack rp = plan_repack(p, norm);
-            if (rp.use && p->workspace && p->workspace_bytes >= rp.bytes) return run_repacked(X, W, b, act, norm, p, rp, out, s);
-        }
+        const Repack rp = plan_repack(p, norm);
+        if (rp.use && (one_call || rp.staged()) && (rp.need == 0 || (p->workspace && p->workspace_bytes >= rp.need)))
+            return run_repacked(X, W, b, act, norm, p, rp, out, s);
         // GEMM + activation straight into out, or into an fp32 rows x N intermediate that the row
         // kernel then reads (several passes) and turns into out
         GenArgs g = gen_args(p);

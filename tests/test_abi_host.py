@@ -262,6 +262,19 @@ def test_tile_choice_reads_the_search_table_and_respects_its_limits():
     assert B.fge_tile_name(True, 4, 3, f32) == B.fge_tile_name(True, 4, 3, _params(M=2048, N=4096, K=4096, ldx=4096, ldw=4096, ldo=4096, flags=B.FLAG_NO_TABLE))
 
 
+def test_workspace_of_results_of_odd_width():
+    """Odd-width results that the tile kernels store themselves, over operands they can stage where they lie, need
+    room for the statistics of split rows, not for a copy of the result; parked rows need the fp32 rows beside them."""
+    def prm(M, K, N, ldx=None):
+        return _params(M=M, N=N, K=K, ldx=ldx or K, ldw=K, ldo=N, in_dtype=1, out_dtype=1)
+    def size(norm, p):
+        return B.lib().fge_workspace_bytes(1, 0, norm, ctypes.byref(p))
+    strips = (50257 + 255) // 256 * 4                                  # 256x256 tiles, four strips each
+    assert size(4, prm(2048, 4096, 50257)) == 2048 * strips * 8        # logsumexp
+    assert size(0, prm(2048, 4096, 50257)) == 0                        # no row op: nothing to keep
+    assert size(1, prm(2048, 4096, 50257)) <= 2048 * (50264 * 4 + strips * 8) + 256 + 50264 * 4     # softmax: parked
+
+
 def test_rows_far_apart_leave_the_tile_kernels():
     """The tile kernels address an operand row by a 32-bit byte offset from its tile's first row:
     rows of X or W 8 MiB apart or more are repacked (large problems) or go to the element-granular

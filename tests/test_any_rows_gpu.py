@@ -58,6 +58,61 @@ def test_row_operations_on_rows_of_any_width(dt, out, norm):
         H.check(w, got, gaux, ref, raux, f"any rows {M}x{K}x{N}+{pad}")
 
 
+@pytest.mark.parametrize("norm", [I.NORM_NONE, I.NORM_SOFTMAX, I.NORM_LAYERNORM, I.NORM_LOGSUMEXP])
+def test_stage_entry_points_in_the_room_asked_for(norm):
+    """Stage 1 alone leaves the final result of an odd width, bit for bit the one-call result, in a workspace
+    of exactly the size asked for (none at all without a row op)."""
+    for M, K, N in ((300, 1024, 2051), (70, 1001, 1001), (40, 1024, 2051)):
+        w = I.Workload(name=f"stage{norm}", M=M, K=K, N=N, in_dtype=I.BF16, out_dtype=I.BF16, act=I.ACT_SILU, norm=norm, eps=1e-5,
+                       dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, 1.0 / K ** 0.5), "b": None})
+        d = {k: H.to_device(v) for k, v in I.generate(w).items()}
+        want, waux = _run(w, d, 0)
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        aux = torch.full((M,), float("nan"), device="cuda") if norm == I.NORM_LOGSUMEXP else None
+        p = B.make_params(d["X"], d["W"], out, eps=w.eps, aux_out=aux)
+        n = B.fge_workspace_bytes(True, w.act, norm, p)
+        ws = torch.full((n + 1024,), 0xA5, dtype=torch.uint8, device="cuda")
+        if n:
+            p.workspace, p.workspace_bytes = ws.data_ptr(), n
+        B.fge_fused_tiles(d["X"], d["W"], None, w.act, norm, p, out)
+        assert not B.fge_fused_needs_finish(w.act, norm, p)
+        B.fge_fused_finish(w.act, norm, p, out)
+        torch.cuda.synchronize()
+        got = H.to_host_f64(out)
+        assert bool((ws[n:] == 0xA5).all())
+        if M > 64 and K % 8 == 0:
+            assert np.array_equal(got, want) and (aux is None or np.array_equal(H.to_host_f64(aux), waux))
+        else:                                          # (few rows, copied operands: the stages keep the element-granular product)
+            assert np.isfinite(got).all() and np.abs(got - want).max() <= 2.0 ** -6 * np.abs(want).max()
+
+
+def test_the_least_workspace_and_less():
+    """Copied operands and the row statistics are all the direct form needs of the workspace; with a byte less the
+    element-granular kernels run, with the fp32 rows those need."""
+    M, K, N = 333, 2049, 515
+    w = I.Workload(name="least", M=M, K=K, N=N, in_dtype=I.BF16, out_dtype=I.BF16, act=I.ACT_SILU, norm=I.NORM_LOGSUMEXP,
+                   dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, 1.0 / K ** 0.5), "b": None})
+    t = I.generate(w)
+    d = {k: H.to_device(v) for k, v in t.items()}
+    ref, raux = H.oracle_chain(w, t)
+    whole, waux = _run(w, d, 0)
+    up = lambda n: (n + 255) // 256 * 256
+    # X and W in rows of 2056 values, W to 516 rows; statistics of nine 64-column tiles, two strips each
+    least = up(M * 2056 * 2) + up(516 * 2056 * 2) + up(M * 18 * 8)
+    for n, same in ((least, True), (least - 1, False)):
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        aux = torch.full((M,), float("nan"), device="cuda")
+        p = B.make_params(d["X"], d["W"], out, aux_out=aux)
+        assert M * N * 4 < n < B.fge_workspace_bytes(True, w.act, w.norm, p)
+        ws = torch.full((n + 1024,), 0xA5, dtype=torch.uint8, device="cuda")
+        p.workspace, p.workspace_bytes = ws.data_ptr(), n
+        B.fused_gemm_epilogue(d["X"], d["W"], None, w.act, w.norm, p, out)
+        torch.cuda.synchronize()
+        assert bool((ws[n:] == 0xA5).all())
+        H.check(w, H.to_host_f64(out), H.to_host_f64(aux), ref, raux, f"{n} bytes")
+        assert np.array_equal(H.to_host_f64(aux), waux) == same
+
+
 @pytest.mark.parametrize("M", [7, 300])
 @pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LOGSUMEXP])
 def test_masked_columns_contribute_nothing(M, norm):
