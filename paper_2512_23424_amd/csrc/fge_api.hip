@@ -1317,8 +1317,10 @@ const char *fge_gated_tile_name(int act, int norm, const fge_params *p) {
 
 size_t fge_fault_word_offset(int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return (size_t)-1;
+    // (a workspace that lacks the few-row kernel's room sends the call to the tile kernels)
     const Skinny few = plan_skinny(p, norm, false);
-    if (few.use) return few.bytes() && skinny_in_kernel(p, norm) ? few.bytes() - 256 : (size_t)-1;
+    if (few.use && !(p->workspace && p->workspace_bytes < few.bytes()))
+        return few.bytes() && skinny_in_kernel(p, norm) ? few.bytes() - 256 : (size_t)-1;
     const Plan pl = make_plan(p, norm);
     return pl.coop ? pl.ws_stats + pl.ws_marks - 256 : (size_t)-1;
 }

@@ -262,6 +262,18 @@ def test_tile_choice_reads_the_search_table_and_respects_its_limits():
     assert B.fge_tile_name(True, 4, 3, f32) == B.fge_tile_name(True, 4, 3, _params(M=2048, N=4096, K=4096, ldx=4096, ldw=4096, ldo=4096, flags=B.FLAG_NO_TABLE))
 
 
+def test_fault_word_lies_inside_the_workspace():
+    """A few-row product in a workspace too small for its fp32 rows runs on the tile kernels, in two passes: no
+    fault word, rather than one behind the workspace's end."""
+    kw = dict(M=16, N=4096, K=4096, ldx=4096, ldw=4096, ldo=4096, in_dtype=1, out_dtype=1)
+    whole = B.fge_fault_word_offset(4, 3, _params(**kw))
+    room = 16 * 4096 * 4 + 1024 + 256                  # fp32 rows, 256 marks, the fault word
+    assert whole == room - 256
+    assert B.fge_fault_word_offset(4, 3, _params(**kw, workspace=FAKE, workspace_bytes=room)) == whole
+    assert B.fge_fault_word_offset(4, 3, _params(**kw, workspace=FAKE, workspace_bytes=room - 1)) is None
+    assert B.fge_fault_word_offset(4, 3, _params(**kw, workspace=FAKE, workspace_bytes=64 << 10)) is None
+
+
 def test_workspace_of_results_of_odd_width():
     """Odd-width results that the tile kernels store themselves, over operands they can stage where they lie, need
     room for the statistics of split rows, not for a copy of the result; parked rows need the fp32 rows beside them."""
