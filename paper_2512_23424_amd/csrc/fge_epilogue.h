@@ -240,7 +240,8 @@ struct TileEpilogue {
     }
 
     // Softmax / logsumexp, first step: every strip's maximum and the sum of its exponentials against
-    // that maximum (softmax: the exponentials take the values' place).  BOUNDED: see norm_group.  MASKED:
+    // that maximum (softmax: the exponentials take the values' place, but not in rows that ANY parks: their
+    // second pass forms them against the row's own maximum, with one rounding less).  BOUNDED: see norm_group.  MASKED:
     // columns may be masked, see `masked`; where the values are not needed any more (softmax; the cooperative
     // form's logsumexp has stored them) the differences are formed in place instead, a small branch in a kernel
     // that a second copy of this code slows down (16 x 2048 x 512 x 2048 softmax 150.6 -> 156.5 us).
@@ -274,7 +275,7 @@ struct TileEpilogue {
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
                 const float x = MASKED ? exp_diff(v[q][e], r) : exp_rel(v[q][e], r);
-                if constexpr (NORM == FGE_NORM_SOFTMAX) v[q][e] = x;
+                if (NORM == FGE_NORM_SOFTMAX && (!ANY || whole_row)) v[q][e] = x;
                 s += okc(e) ? x : 0.0f;
             }
             sum[q] = allreduce_lanes<OpSum, LPR>(s);

@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256) void finish_kernel(const RowArgs a) {
 // The same second pass for rows the tile kernel parked in fp32 (`in`, dense rows a.ldi apart, 16-byte
 // aligned, padded to whole groups of eight) because `out` has rows that start and end at any element and
 // its own type would round the parked values: eight columns per thread and step - two 16-byte loads, one unaligned
-// 16-byte store (32-bit results: two).  Softmax, LayerNorm, RMSNorm.  Bound by memory (6 bytes per value
+// 16-byte store (32-bit results: two).  Softmax (the values are parked, not their exponentials), LayerNorm, RMSNorm.  Bound by memory (6 bytes per value
 // with 16-bit results); WAVES as in finish_kernel.
 struct FinishAnyArgs {
     RowArgs r;
@@ -648,7 +648,7 @@ __global__ __launch_bounds__(256) void finish_any_kernel(const FinishAnyArgs f) 
         float s = 0.0f;
 #pragma unroll 8
         for (int t = lane; t < S; t += 64) s += wr[t].y * fast_exp(wr[t].x - ref);
-        scale = fast_rcp(allreduce64<OpSum>(s));
+        scale = 1.0f / allreduce64<OpSum>(s);
     } else if (a.norm == FGE_NORM_LAYERNORM) {
         float sm = 0.0f;
 #pragma unroll 8
@@ -676,9 +676,8 @@ __global__ __launch_bounds__(256) void finish_any_kernel(const FinishAnyArgs f) 
         Store<float>::unpack(*reinterpret_cast<const uint4 *>(in + c), v);
         Store<float>::unpack(*reinterpret_cast<const uint4 *>(in + c + 4), v + 4);
         if (a.norm == FGE_NORM_SOFTMAX) {
-            const float k = fast_exp(wr[c / SW].x - ref) * scale;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] *= k;
+            for (int e = 0; e < 8; ++e) v[e] = exp_diff(v[e], ref) * scale;
         } else {
             float g[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f}, b[8] = {};
             if (whole) {
