@@ -115,3 +115,26 @@ def test_a_wait_that_runs_out_poisons_the_rows(norm):
     ref, raux = H.oracle_chain(w, t)
     got, gaux = H.run_gpu(w, t, "fused", dev=d)
     H.check(w, got, gaux, ref, raux, "after an expired wait")
+
+
+@pytest.mark.parametrize("dt", [I.BF16, I.F16, I.F8E4M3])
+def test_sums_are_as_exact_as_those_of_k_slices(dt):
+    """fp32 results over a long K against float64, beside the same call in K slices of 64x64 tiles (which the forced
+    tile takes): the error, a matter of how long the chains of additions are, is no larger."""
+    for M, K, N in ((64, 8192, 2048), (1, 16384, 1024)):
+        g = torch.Generator(device="cuda").manual_seed(3)
+        tdt = {I.BF16: torch.bfloat16, I.F16: torch.float16, I.F8E4M3: torch.float8_e4m3fn}[dt]
+        X = torch.randn(M, K, generator=g, device="cuda").to(tdt)
+        W = torch.randn(N, K, generator=g, device="cuda").to(tdt)
+        ref = X.double() @ W.double().T
+        err = []
+        for flags in (0, 1 << 8):
+            out = torch.full((M, N), float("nan"), device="cuda")
+            p = B.make_params(X, W, out, flags=flags)
+            ws = torch.empty(B.fge_workspace_bytes(True, I.ACT_NONE, I.NORM_NONE, p), dtype=torch.uint8, device="cuda")
+            p.workspace, p.workspace_bytes = ws.data_ptr(), ws.numel()
+            B.fused_gemm_epilogue(X, W, None, I.ACT_NONE, I.NORM_NONE, p, out)
+            torch.cuda.synchronize()
+            err.append(float((out.double() - ref).norm() / ref.norm()))
+        print(f"dt {dt} {M}x{K}x{N}: few-row {err[0]:.3e}, K slices {err[1]:.3e}", flush=True)
+        assert err[0] <= 1.02 * err[1]                 # (the spread of either over seeds)
