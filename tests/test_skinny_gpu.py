@@ -120,8 +120,9 @@ def test_a_wait_that_runs_out_poisons_the_rows(norm):
 @pytest.mark.parametrize("dt", [I.BF16, I.F16, I.F8E4M3])
 def test_sums_are_as_exact_as_those_of_k_slices(dt):
     """fp32 results over a long K against float64, beside the same call in K slices of 64x64 tiles (which the forced
-    tile takes): the error, a matter of how long the chains of additions are, is no larger."""
-    for M, K, N in ((64, 8192, 2048), (1, 16384, 1024)):
+    tile takes): the error is a matter of how long the chains of additions are, which is its square root - 512 values
+    in either form at K = 8192; at 16384, where there are 16 slices and no more, 1024 against half a slice's 1024."""
+    for M, K, N, longer in ((64, 8192, 2048, 1), (16, 8192, 1024, 1), (1, 16384, 1024, 2)):
         g = torch.Generator(device="cuda").manual_seed(3)
         tdt = {I.BF16: torch.bfloat16, I.F16: torch.float16, I.F8E4M3: torch.float8_e4m3fn}[dt]
         X = torch.randn(M, K, generator=g, device="cuda").to(tdt)
@@ -137,4 +138,4 @@ def test_sums_are_as_exact_as_those_of_k_slices(dt):
             torch.cuda.synchronize()
             err.append(float((out.double() - ref).norm() / ref.norm()))
         print(f"dt {dt} {M}x{K}x{N}: few-row {err[0]:.3e}, K slices {err[1]:.3e}", flush=True)
-        assert err[0] <= 1.02 * err[1]                 # (the spread of either over seeds)
+        assert err[0] <= 1.02 * longer ** 0.5 * err[1]                 # (2 %: the spread of either over seeds)
