@@ -124,9 +124,7 @@ struct TileEpilogue {
     float scale, bias[NB];      // y = scale * acc + bias  (scale = post*alpha, bias = post*b)
     bool whole_row;
     bool bounded;               // clamp activation with a narrow range feeds softmax / logsumexp
-    bool masked;                // the bias may mask columns of the wave: a strip may have no other, and its exponentials
-                                // are taken of differences formed first, see exp_diff - one more operation per value,
-                                // so only here and with ANY
+    bool masked;                // the bias may mask columns of the wave (see strip_sums)
     bool defer_lse = false;     // whole-row logsumexp: park the strip pairs, the caller merges them later
     int lse_par = 0;            // exchange buffer the parked pairs of this tile go to
 
@@ -179,6 +177,8 @@ struct TileEpilogue {
     __device__ __forceinline__ int brow(int r) const { return (r >> 2) * 8 + h * 4 + (r & 3); }
     // tile row of pass q of a group whose first block starts at tile row grow0
     __device__ __forceinline__ int qrow(int grow0, int q) const { return grow0 + (q / NPB) * 32 + (q % NPB) * RPP + prow; }
+
+    __device__ __forceinline__ int norm() const { return NORM_CT >= 0 ? NORM_CT : a.norm; }
 
     template <int ACT> __device__ __forceinline__ void act_block(floatx16 (&blk)[NB]) {
 #pragma unroll
@@ -241,11 +241,14 @@ struct TileEpilogue {
 
     // Softmax / logsumexp, first step: every strip's maximum and the sum of its exponentials against
     // that maximum (softmax: the exponentials take the values' place, but not in rows that ANY parks: their
-    // second pass forms them against the row's own maximum, with one rounding less).  BOUNDED: see norm_group.  MASKED:
-    // columns may be masked, see `masked`; where the values are not needed any more (softmax; the cooperative
-    // form's logsumexp has stored them) the differences are formed in place instead, a small branch in a kernel
-    // that a second copy of this code slows down (16 x 2048 x 512 x 2048 softmax 150.6 -> 156.5 us).
-    template <int NORM, bool FULL, bool BOUNDED, bool MASKED>
+    // second pass forms them against the row's own maximum, with one rounding less).  BOUNDED: see norm_group.
+    // A strip may hold masked columns only, whatever value masks them:
+    //   logsumexp: from a maximum of 2^27 on the sum does not matter (its logarithm is less than half an ulp of the
+    //     maximum), it only has to be a number, and NaN for a NaN; -inf sums to zero;
+    //   softmax: the differences are formed first (exp_diff), in place - or, with ANY, throughout.
+    // Both where `masked` says so, with nothing per value elsewhere: a second copy of this code would slow the
+    // kernels down (16 x 2048 x 512 x 2048 softmax 150.6 -> 156.5 us).
+    template <int NORM, bool FULL, bool BOUNDED>
     __device__ __forceinline__ void strip_sums(float (&v)[NPG][VEC], float (&ml)[NPG], float (&sum)[NPG]) {
         auto okc = [&](int e) __attribute__((always_inline)) { return FULL || okv[ANY ? e : e >> 2]; };
 #pragma unroll
@@ -259,8 +262,9 @@ struct TileEpilogue {
                 ml[q] = allreduce_lanes<OpMax, LPR>(m);
             }
         }
-        constexpr bool IN_PLACE = !BOUNDED && !MASKED && (COOP || NORM == FGE_NORM_SOFTMAX);
-        if (IN_PLACE && masked) {
+        constexpr bool LSE = NORM == FGE_NORM_LOGSUMEXP && !BOUNDED, SOFTMAX = NORM == FGE_NORM_SOFTMAX && !BOUNDED;
+        constexpr float FAR = 1.0f * (1 << 27);
+        if (SOFTMAX && !ANY && masked) {
 #pragma unroll
             for (int q = 0; q < NPG; ++q) {
                 const float r = exp_ref(ml[q]);
@@ -268,17 +272,24 @@ struct TileEpilogue {
                 for (int e = 0; e < VEC; ++e) v[q][e] -= r;
             }
         }
+        const float most = LSE && masked ? 2.0f * FAR : __builtin_inff();
 #pragma unroll
         for (int q = 0; q < NPG; ++q) {
-            const float r = MASKED ? exp_ref(ml[q]) : IN_PLACE && masked ? 0.0f : -ml[q] * LOG2E;
+            const float r = SOFTMAX && ANY ? exp_ref(ml[q]) : SOFTMAX && masked ? 0.0f
+                            : LSE ? clamp_nc(-ml[q] * LOG2E, -most, most) : -ml[q] * LOG2E;
             float s = 0.0f;
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-                const float x = MASKED ? exp_diff(v[q][e], r) : exp_rel(v[q][e], r);
+                const float x = SOFTMAX && ANY ? exp_diff(v[q][e], r) : exp_rel(v[q][e], r);
                 if (NORM == FGE_NORM_SOFTMAX && (!ANY || whole_row)) v[q][e] = x;
                 s += okc(e) ? x : 0.0f;
             }
             sum[q] = allreduce_lanes<OpSum, LPR>(s);
+        }
+        if (LSE && masked) {
+#pragma unroll
+            for (int q = 0; q < NPG; ++q)
+                if (!(fabsf(ml[q]) < FAR) && sum[q] == sum[q]) sum[q] = ml[q] == OpMax::ident() ? 0.0f : 1.0f;
         }
     }
 
@@ -292,8 +303,7 @@ struct TileEpilogue {
         float s0[NPG], s1[NPG];
         if constexpr (NORM == FGE_NORM_SOFTMAX || NORM == FGE_NORM_LOGSUMEXP) {
             float ml[NPG];                            // strip maxima (or the common bound)
-            if (!BOUNDED && !ANY && !COOP && NORM == FGE_NORM_LOGSUMEXP && masked) strip_sums<NORM, FULL, false, true>(v, ml, s1);
-            else                                                                   strip_sums<NORM, FULL, BOUNDED, ANY>(v, ml, s1);
+            strip_sums<NORM, FULL, BOUNDED>(v, ml, s1);
 #pragma unroll
             for (int q = 0; q < NPG; ++q) s0[q] = mkeep[q] = ml[q];
             if (!whole_row) {
@@ -422,11 +432,15 @@ struct TileEpilogue {
     // (mkeep: the references the exponentials of a softmax / logsumexp group were taken against)
     template <bool FULL> __device__ __forceinline__ void norm_dispatch(float (&v)[NPG][VEC], int grow0, float (&mkeep)[NPG]) {
         if constexpr (NORM_CT >= 0) {
-            if constexpr (NORM_CT != FGE_NORM_NONE) norm_group<NORM_CT, FULL, BOUNDED_CT>(v, grow0, mkeep);
+            constexpr bool SUMS = NORM_CT == FGE_NORM_SOFTMAX || NORM_CT == FGE_NORM_LOGSUMEXP;
+            if constexpr (NORM_CT != FGE_NORM_NONE) {
+                if (SUMS && !BOUNDED_CT && ACT_CT < 0 && bounded) norm_group<NORM_CT, FULL, SUMS>(v, grow0, mkeep);
+                else                                              norm_group<NORM_CT, FULL, BOUNDED_CT>(v, grow0, mkeep);
+            }
             return;
         }
         if constexpr (COOP) {
-            switch (a.norm) {
+            switch (norm()) {
             case FGE_NORM_SOFTMAX:       norm_group<FGE_NORM_SOFTMAX, FULL, false>(v, grow0, mkeep); break;
             case FGE_NORM_LOGSUMEXP:     norm_group<FGE_NORM_LOGSUMEXP, FULL, false>(v, grow0, mkeep); break;
             case FGE_NORM_LAYERNORM:     norm_group<FGE_NORM_LAYERNORM, FULL, false>(v, grow0, mkeep); break;
@@ -434,7 +448,7 @@ struct TileEpilogue {
             }
             return;
         }
-        switch (a.norm + (bounded ? 8 : 0)) {
+        switch (norm() + (bounded ? 8 : 0)) {
         case FGE_NORM_NONE: case FGE_NORM_NONE + 8: break;
         case FGE_NORM_SOFTMAX:       norm_group<FGE_NORM_SOFTMAX, FULL, false>(v, grow0, mkeep); break;
         case FGE_NORM_SOFTMAX + 8:   norm_group<FGE_NORM_SOFTMAX, FULL, true>(v, grow0, mkeep); break;
@@ -544,13 +558,13 @@ struct TileEpilogue {
 #pragma unroll
         for (int w = 0; w < WAVES_N; ++w) e[w] = xch[row * WAVES_N + w];
         float o0, o1 = 0.0f;
-        if (a.norm == FGE_NORM_SOFTMAX || a.norm == FGE_NORM_LOGSUMEXP) {
+        if (norm() == FGE_NORM_SOFTMAX || norm() == FGE_NORM_LOGSUMEXP) {
             o0 = e[0].x;
 #pragma unroll
             for (int w = 1; w < WAVES_N; ++w) o0 = max_nc(o0, e[w].x);
 #pragma unroll
             for (int w = 0; w < WAVES_N; ++w) o1 += e[w].y * fast_exp(e[w].x - exp_ref(o0));   // empty and masked strips: 0 * exp(-inf)
-        } else if (a.norm == FGE_NORM_LAYERNORM) {
+        } else if (norm() == FGE_NORM_LAYERNORM) {
             const int nt = max(1, min(WAVES_N * WTN, a.N - n0));
             float sm = 0.0f;
 #pragma unroll
@@ -610,7 +624,7 @@ struct TileEpilogue {
         const int BN_ = WAVES_N * WTN;
         constexpr int CH = 8;                 // pairs fetched together (independent loads in flight)
         float o0, o1 = 0.0f;
-        if (a.norm == FGE_NORM_SOFTMAX || a.norm == FGE_NORM_LOGSUMEXP) {
+        if (norm() == FGE_NORM_SOFTMAX || norm() == FGE_NORM_LOGSUMEXP) {
             float m = OpMax::ident(), sum = 0.0f;
             for (int t0 = part; t0 < a.tiles_n; t0 += CH * TPR) {
                 float2 e[CH];
@@ -628,9 +642,9 @@ struct TileEpilogue {
             }
             o0 = allreduce_lanes<OpMax, TPR>(m);
             const float sden = allreduce_lanes<OpSum, TPR>(sum * fast_exp(m - exp_ref(o0)));
-            if (a.norm == FGE_NORM_SOFTMAX) o1 = fast_rcp(sden);
+            if (norm() == FGE_NORM_SOFTMAX) o1 = fast_rcp(sden);
             else if (part == 0 && tn == 0 && grow < a.M) a.aux[row_base + grow] = waited_ok ? o0 + __logf(sden) : __builtin_nanf("");
-        } else if (a.norm == FGE_NORM_LAYERNORM) {
+        } else if (norm() == FGE_NORM_LAYERNORM) {
             // two sweeps over the pairs: the mean first, then M2 about it
             const float inv_n = 1.0f / (float)a.N;
             float sm = 0.0f;
@@ -679,8 +693,8 @@ struct TileEpilogue {
             floatx4 g = {1.0f, 1.0f, 1.0f, 1.0f}, b = {0.0f, 0.0f, 0.0f, 0.0f};
             const int c = gcol + (e >> 2) * G4STEP;
             const bool ok = FULL || okv[ANY ? e : e >> 2];
-            if (a.norm != FGE_NORM_SOFTMAX && ok && a.gamma != nullptr) g = affine4<FULL>(a.gamma, c);
-            if (a.norm == FGE_NORM_LAYERNORM && ok && a.beta != nullptr) b = affine4<FULL>(a.beta, c);
+            if (norm() != FGE_NORM_SOFTMAX && ok && a.gamma != nullptr) g = affine4<FULL>(a.gamma, c);
+            if (norm() == FGE_NORM_LAYERNORM && ok && a.beta != nullptr) b = affine4<FULL>(a.beta, c);
             gam[e] = g[0]; gam[e + 1] = g[1]; gam[e + 2] = g[2]; gam[e + 3] = g[3];
             bet[e] = b[0]; bet[e + 1] = b[1]; bet[e + 2] = b[2]; bet[e + 3] = b[3];
         }
@@ -720,8 +734,8 @@ struct TileEpilogue {
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
                 static_for<0, G>([&]<int b>() __attribute__((always_inline)) { to_rows<b>(acc[g * G + b], vall[g]); });
                 const int grow0 = trow0 + g * G * 32;
-                if (a.norm == FGE_NORM_LOGSUMEXP) store_group<FULL_TILE>(vall[g], grow0);
                 norm_dispatch<FULL_TILE>(vall[g], grow0, mkeep[g]);
+                if (norm() == FGE_NORM_LOGSUMEXP) store_group<FULL_TILE>(vall[g], grow0);
             });
             // the affine vectors are the same for every group: fetched once, behind the wait
             float gam[VEC], bet[VEC];
@@ -731,11 +745,11 @@ struct TileEpilogue {
             const bool waited_ok = arrive_and_wait(rowblock, tid);
             float2 *fin = xch + tile_rows * WAVES_N;
             merge_tiles<NT / (MB * 32 * (NT / 64 / WAVES_N))>(tid, fin, waited_ok);
-            if (a.norm == FGE_NORM_LOGSUMEXP) return;
+            if (norm() == FGE_NORM_LOGSUMEXP) return;
             __syncthreads();
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
                 const int grow0 = trow0 + g * G * 32;
-                switch (a.norm) {
+                switch (norm()) {
                 case FGE_NORM_SOFTMAX:   finish_group<FGE_NORM_SOFTMAX>(vall[g], grow0, fin, mkeep[g], gam, bet); break;
                 case FGE_NORM_LAYERNORM: finish_group<FGE_NORM_LAYERNORM>(vall[g], grow0, fin, mkeep[g], gam, bet); break;
                 default:                 finish_group<FGE_NORM_RMSNORM>(vall[g], grow0, fin, mkeep[g], gam, bet); break;

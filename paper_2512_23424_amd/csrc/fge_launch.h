@@ -113,6 +113,48 @@ inline int resident_workgroups(const void *kernel, int threads) {
 template <typename InT> struct NarrowOut { typedef bf16_t type; };
 template <> struct NarrowOut<f16_t> { typedef f16_t type; };
 
+// The 256x256 tile, ordinary and cooperative launch: a kernel for every row op.  The four groups of a wave's rows
+// each pass over the code of all row ops and activations, and where one kernel holds all of them (90 to 105 KB) its
+// instructions arrive late, by an amount that any change of that code moves (bf16, ordinary: 8192 x 4096 x 4096 SiLU 212
+// to 217 us, 8192 x 64 x 4096 27.5 to 30.4 us).
+// STAGES: as for the tile kernel.  FULL (cooperative form): every tile lies inside the matrix, no guards.  All workgroups of
+// a cooperative grid must be resident at once; one that the device cannot hold that way is refused.
+template <typename InT, int STAGES>
+inline hipError_t launch_256(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
+    typedef typename NarrowOut<InT>::type NarrowT;
+#define FGE_256_KERNEL(OT, COOP, FULL, NORM)                                                    \
+    do {                                                                                        \
+        auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, FULL, false, false, STAGES, false, NORM>; \
+        if (COOP) {                                                                             \
+            static const int resident = resident_workgroups(reinterpret_cast<const void *>(kern), 512); \
+            if ((int)grid.x > resident) return hipErrorCooperativeLaunchTooLarge;               \
+        }                                                                                       \
+        hipLaunchKernelGGL(kern, grid, dim3(512), 0, s, a);                                     \
+    } while (0)
+#define FGE_256(COOP, FULL, NORM)                                                               \
+    do {                                                                                        \
+        if (out_dtype != FGE_F32) FGE_256_KERNEL(NarrowT, COOP, FULL, NORM);                    \
+        else                      FGE_256_KERNEL(float, COOP, FULL, NORM);                      \
+    } while (0)
+#define FGE_256_FORM(NORM)                                                                      \
+    do {                                                                                        \
+        if (!a.coop)                                FGE_256(false, false, NORM);                \
+        else if (a.M % 256 == 0 && a.N % 256 == 0)  FGE_256(true, true, NORM);                  \
+        else                                        FGE_256(true, false, NORM);                 \
+    } while (0)
+    switch (a.norm) {
+    case FGE_NORM_NONE:      FGE_256(false, false, FGE_NORM_NONE); break;
+    case FGE_NORM_SOFTMAX:   FGE_256_FORM(FGE_NORM_SOFTMAX); break;
+    case FGE_NORM_LAYERNORM: FGE_256_FORM(FGE_NORM_LAYERNORM); break;
+    case FGE_NORM_RMSNORM:   FGE_256_FORM(FGE_NORM_RMSNORM); break;
+    default:                 FGE_256_FORM(FGE_NORM_LOGSUMEXP); break;
+    }
+#undef FGE_256_FORM
+#undef FGE_256
+#undef FGE_256_KERNEL
+    return hipGetLastError();
+}
+
 template <typename InT, bool SPLIT>
 inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     typedef typename NarrowOut<InT>::type NarrowT;
@@ -128,23 +170,17 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
     // cooperative kernel of a tile.  All workgroups of the grid must be resident at once; a
     // launch that the device cannot hold that way is refused instead of being left to run into
     // its wait limit.
-#define FGE_LAUNCH_COOP2(BM, BN, WM, WN, OT, FULL)                                              \
+#define FGE_LAUNCH_COOP1(BM, BN, WM, WN, OT, NORM)                                              \
     do {                                                                                        \
-        auto kern = tile_kernel<InT, OT, BM, BN, WM, WN, true, FULL, SPLIT>;                    \
+        auto kern = tile_kernel<InT, OT, BM, BN, WM, WN, true, false, SPLIT, false, 0, false, NORM>; \
         static const int resident = resident_workgroups(reinterpret_cast<const void *>(kern), 64 * WM * WN); \
         if ((int)grid.x > resident) return hipErrorCooperativeLaunchTooLarge;                   \
         hipLaunchKernelGGL(kern, grid, dim3(64 * WM * WN), 0, s, a);                            \
     } while (0)
-    /* guard-free epilogue where every tile lies inside the matrix (256x256 tiles only) */      \
-#define FGE_LAUNCH_COOP1(BM, BN, WM, WN, OT)                                                    \
+#define FGE_LAUNCH_COOP(BM, BN, WM, WN, NORM)                                                   \
     do {                                                                                        \
-        if (BM == 256 && a.M % BM == 0 && a.N % BN == 0) FGE_LAUNCH_COOP2(BM, BN, WM, WN, OT, (BM == 256)); \
-        else                                             FGE_LAUNCH_COOP2(BM, BN, WM, WN, OT, false); \
-    } while (0)
-#define FGE_LAUNCH_COOP(BM, BN, WM, WN)                                                         \
-    do {                                                                                        \
-        if (out_dtype != FGE_F32)  FGE_LAUNCH_COOP1(BM, BN, WM, WN, NarrowT);                   \
-        else                       FGE_LAUNCH_COOP1(BM, BN, WM, WN, float);                     \
+        if (out_dtype != FGE_F32)  FGE_LAUNCH_COOP1(BM, BN, WM, WN, NarrowT, NORM);             \
+        else                       FGE_LAUNCH_COOP1(BM, BN, WM, WN, float, NORM);               \
     } while (0)
     // 128x128 tiles on eight waves with more stage buffers (one workgroup per CU), ordinary and cooperative launch
 #define FGE_LAUNCH_DEEP128(OT, WM, WN, STAGES)                                                  \
@@ -177,8 +213,13 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
     case TILE_64x512:  FGE_LAUNCH(64, 512, 1, 4); break;
     case TILE_128x128:
         if constexpr (BF || SPLIT) {
-            if (a.coop) FGE_LAUNCH_COOP(128, 128, 2, 2);
-            else        FGE_LAUNCH(128, 128, 2, 2);
+            // (a cooperative kernel for every row op, as for the 256x256 tile: fp32 16669 x 32 x 256 softmax 16.8 us
+            // with one for all)
+            if (!a.coop)                           FGE_LAUNCH(128, 128, 2, 2);
+            else if (a.norm == FGE_NORM_SOFTMAX)   FGE_LAUNCH_COOP(128, 128, 2, 2, FGE_NORM_SOFTMAX);
+            else if (a.norm == FGE_NORM_LAYERNORM) FGE_LAUNCH_COOP(128, 128, 2, 2, FGE_NORM_LAYERNORM);
+            else if (a.norm == FGE_NORM_RMSNORM)   FGE_LAUNCH_COOP(128, 128, 2, 2, FGE_NORM_RMSNORM);
+            else                                   FGE_LAUNCH_COOP(128, 128, 2, 2, FGE_NORM_LOGSUMEXP);
             break;
         }
         return hipErrorInvalidValue;
@@ -191,21 +232,19 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
         return hipErrorInvalidValue;
     case TILE_256x256:
         if constexpr (BF) {
-            if (a.coop) FGE_LAUNCH_COOP(256, 256, 2, 4);
-            else        FGE_LAUNCH(256, 256, 2, 4);
-            break;
+            return launch_256<InT, 0>(out_dtype, grid, s, a);
         }
         return hipErrorInvalidValue;
     case TILE_128x128_W8:
         if constexpr (SPLIT) {
-            if (a.coop) FGE_LAUNCH_COOP(128, 128, 2, 4);
+            if (a.coop) FGE_LAUNCH_COOP(128, 128, 2, 4, -1);
             else        FGE_LAUNCH(128, 128, 2, 4);
             break;
         }
         return hipErrorInvalidValue;
     case TILE_64x128:
         if constexpr (!BF) {
-            if (a.coop) FGE_LAUNCH_COOP(64, 128, 2, 2);
+            if (a.coop) FGE_LAUNCH_COOP(64, 128, 2, 2, -1);
             else        FGE_LAUNCH(64, 128, 2, 2);
             break;
         }
@@ -216,7 +255,6 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
 #undef FGE_LAUNCH_DEEP128
 #undef FGE_LAUNCH_COOP
 #undef FGE_LAUNCH_COOP1
-#undef FGE_LAUNCH_COOP2
     return hipGetLastError();
 }
 

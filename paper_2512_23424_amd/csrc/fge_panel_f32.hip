@@ -19,13 +19,23 @@ void launch(dim3 grid, hipStream_t s, const TileArgs &a) {
             return;
         }
     }
-    if (full) {
-        if (stream) hipLaunchKernelGGL((panel_kernel<OutT, true, true>), grid, block, 0, s, a);
-        else        hipLaunchKernelGGL((panel_kernel<OutT, true, false>), grid, block, 0, s, a);
-    } else {
-        if (stream) hipLaunchKernelGGL((panel_kernel<OutT, false, true>), grid, block, 0, s, a);
-        else        hipLaunchKernelGGL((panel_kernel<OutT, false, false>), grid, block, 0, s, a);
+    // else a kernel for every row op: one that holds the code of all of them spills registers (131072 x 32 x 364 SiLU
+    // logsumexp 77.9 to 80.3 us, now 66.9; 65536 x 64 x 384 softmax 42.6 to 44.3)
+#define FGE_PANEL(NORM)                                                                                                  \
+    do {                                                                                                                 \
+        if (full && stream) hipLaunchKernelGGL((panel_kernel<OutT, true, true, -1, NORM>), grid, block, 0, s, a);        \
+        else if (full)      hipLaunchKernelGGL((panel_kernel<OutT, true, false, -1, NORM>), grid, block, 0, s, a);       \
+        else if (stream)    hipLaunchKernelGGL((panel_kernel<OutT, false, true, -1, NORM>), grid, block, 0, s, a);       \
+        else                hipLaunchKernelGGL((panel_kernel<OutT, false, false, -1, NORM>), grid, block, 0, s, a);      \
+    } while (0)
+    switch (a.norm) {
+    case FGE_NORM_NONE:      FGE_PANEL(FGE_NORM_NONE); break;
+    case FGE_NORM_SOFTMAX:   FGE_PANEL(FGE_NORM_SOFTMAX); break;
+    case FGE_NORM_LAYERNORM: FGE_PANEL(FGE_NORM_LAYERNORM); break;
+    case FGE_NORM_RMSNORM:   FGE_PANEL(FGE_NORM_RMSNORM); break;
+    default:                 FGE_PANEL(FGE_NORM_LOGSUMEXP); break;
     }
+#undef FGE_PANEL
 }
 }  // namespace
 

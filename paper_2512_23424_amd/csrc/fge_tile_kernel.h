@@ -109,8 +109,9 @@ template <> struct Mma<float> {
 // split product has a mainloop of its own (operands are split on their way into LDS).
 // STAGES: 0 for the tile's usual number of stage buffers, else that many (see DEEP below).
 // ANY: N and the rows of the result are any number of elements (see TileEpilogue).
+// NORM_CT (>= 0): the row op, fixed at compile time.
 template <typename InT, typename OutT, int BM, int BN, int WAVES_M, int WAVES_N, bool COOP = false, bool FULL = false,
-          bool SPLIT = false, bool GATED = false, int STAGES = 0, bool ANY = false>
+          bool SPLIT = false, bool GATED = false, int STAGES = 0, bool ANY = false, int NORM_CT = -1>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (BM * BN <= 64 * 128 ? 2 : 1))
 void tile_kernel(const TileArgs a) {
     static_assert(!SPLIT || sizeof(InT) == 4, "only fp32 operands are split");
@@ -900,13 +901,13 @@ void tile_kernel(const TileArgs a) {
         });
         TileArgs ag = a;
         ag.act = FGE_ACT_NONE; ag.alpha = 1.0f; ag.post = 1.0f; ag.b = nullptr;
-        using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false>;
+        using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false, false, -1, NORM_CT>;
         static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= NST * STAGE, "store patches fit the panels");
         Epi epi(ag, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
                 wave_n, lane);
         epi.template tile<NT>(gated, wave_m * WTM, rowblock, tid);
     } else {
-        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, -1, false, false, ANY>;
+        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, NORM_CT, false, false, ANY>;
         constexpr int PATCH_BYTES = KSHARE ? OWN : Epi::PATCH_FLOATS * 4;
         static_assert(WAVES_M * WAVES_N * PATCH_BYTES <= NST * STAGE && Epi::PATCH_FLOATS * 4 <= PATCH_BYTES, "store patches fit the panels");
         Epi epi(a, out, xch, reinterpret_cast<float *>(smem + wave * PATCH_BYTES), BM, z, m0, n0, tn,
