@@ -45,6 +45,13 @@ inline const TileInfo &tile_info(int id) {
 // slower start and end are paid for (6144 x 304 x 528 bf16: 9.4 us without, 10.2 with it; 2048 x 624 x 1544
 // RMSNorm 16.5 / 17.3, 2048 x 1024 x 1544 18.4 / 18.0, 2048 x 2048 x 1544 26.1 / 24.3 us).
 inline bool long_k(int K, size_t esize) { return (size_t)K * esize >= 2048; }
+// K up to which the 256x256 tile and the gated form run the loop over k-steps: four K tiles of 64 16-bit values,
+// one of 128 8-bit ones.  The quadrants' loop copies two K tiles before it multiplies the first, which a short K does
+// not make up for (quadrants / k-steps, us; bf16 8192 x K x 4096, no row op: K = 64 24.9 / 24.0, 256 32.2 / 32.1, 384 38.6 / 39.5;
+// RMSNorm in one kernel: 128 45.7 / 44.7, 256 51.0 / 51.5, 512 62.5 / 63.6; softmax in 16 problems of 2048 x K x 2048: 128 103.8 /
+// 100.7, 256 115.4 / 114.8, 640 152.4 / 154.8; gated: 64 42.8 / 40.7, 256 62.6 / 60.9, 384 76.1 / 76.4, 640 98.4 / 102; E4M3: 128 23.3 / 22.5,
+// 144 26.2 / 27.0, 256 26.2 / 25.8, 384 28.6 / 29.2, RMSNorm 256 45.4 / 45.6).
+inline bool short_k(int K, size_t esize) { return (size_t)K * esize <= (esize == 2 ? 512 : 128); }
 // Wave strips across a tile.  any_rows: the forms for results of any width, which share out K always.
 inline int tile_strips(int tile, int K, size_t esize, bool any_rows) {
     return tile == TILE_128x128_S3 && (any_rows || long_k(K, esize)) ? 2 : tile_info(tile).waves_n;
@@ -112,6 +119,9 @@ inline int resident_workgroups(const void *kernel, int threads) {
 // The 16-bit output type that goes with an operand type (the other output type is fp32).
 template <typename InT> struct NarrowOut { typedef bf16_t type; };
 template <> struct NarrowOut<f16_t> { typedef f16_t type; };
+
+// 256x256 tiles and the gated form over a short K; defined in fge_tiles_short_*.hip.
+template <typename InT> hipError_t launch_short(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 
 // The 256x256 tile, ordinary and cooperative launch: a kernel for every row op.  The four groups of a wave's rows
 // each pass over the code of all row ops and activations, and where one kernel holds all of them (90 to 105 KB) its
@@ -232,6 +242,7 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
         return hipErrorInvalidValue;
     case TILE_256x256:
         if constexpr (BF) {
+            if (short_k(a.K, sizeof(InT))) return launch_short<InT>(false, out_dtype, grid, s, a);
             return launch_256<InT, 0>(out_dtype, grid, s, a);
         }
         return hipErrorInvalidValue;
@@ -262,6 +273,7 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
 template <typename InT>
 inline hipError_t launch_gated_any(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     typedef typename NarrowOut<InT>::type NarrowT;
+    if (short_k(a.K, sizeof(InT))) return launch_short<InT>(true, out_dtype, grid, s, a);
 #define FGE_GATED(OT, COOP)                                                                     \
     do {                                                                                        \
         auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, false, false, true>;             \
@@ -274,6 +286,25 @@ inline hipError_t launch_gated_any(int out_dtype, dim3 grid, hipStream_t s, cons
     if (out_dtype != FGE_F32) { if (a.coop) FGE_GATED(NarrowT, true); else FGE_GATED(NarrowT, false); }
     else                      { if (a.coop) FGE_GATED(float, true);   else FGE_GATED(float, false); }
 #undef FGE_GATED
+    return hipGetLastError();
+}
+// ... and those of both over a short K.
+template <typename InT>
+inline hipError_t launch_short_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
+    typedef typename NarrowOut<InT>::type NarrowT;
+    if (!gated) return launch_256<InT, 2>(out_dtype, grid, s, a);
+#define FGE_SHORT(OT, COOP)                                                                     \
+    do {                                                                                        \
+        auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, false, false, true, 2>;          \
+        if (COOP) {                                                                             \
+            static const int resident = resident_workgroups(reinterpret_cast<const void *>(kern), 512); \
+            if ((int)grid.x > resident) return hipErrorCooperativeLaunchTooLarge;               \
+        }                                                                                       \
+        hipLaunchKernelGGL(kern, grid, dim3(512), 0, s, a);                                     \
+    } while (0)
+    if (out_dtype != FGE_F32) { if (a.coop) FGE_SHORT(NarrowT, true); else FGE_SHORT(NarrowT, false); }
+    else                      { if (a.coop) FGE_SHORT(float, true);   else FGE_SHORT(float, false); }
+#undef FGE_SHORT
     return hipGetLastError();
 }
 // The half-tile configurations (TILE_128x256, TILE_256x128), ordinary or cooperative launch;

@@ -142,7 +142,10 @@ void tile_kernel(const TileArgs a) {
     // KSHARE (STAGES = 4): the same tiles for a longer K, with a mainloop of their own.  It starts and
     // ends more slowly (more copies in front of the first tile, the groups' sums behind the last), so the
     // launcher takes it from 2 KB of K on (see long_k).
-    static_assert(STAGES == 0 || ((STAGES == 3 || STAGES == 4) && !SPLIT && !GATED), "extra stage buffers: plain 16- and 8-bit tiles");
+    // STAGES = 2: the 256x256 tile (and the gated form) with the loop over k-steps in place of the quadrants,
+    // for a short K (see short_k).
+    static_assert(STAGES == 0 || (STAGES == 2 && BM == 256 && BN == 256) || ((STAGES == 3 || STAGES == 4) && !SPLIT && !GATED),
+                  "extra stage buffers: plain 16- and 8-bit tiles");
     constexpr bool KSHARE = STAGES == 4;
     constexpr bool DEEP = STAGES == 3 || (STAGES == 0 && BM == 64 && BN == 64 && !SPLIT && !COOP);
     // QUAD: the mainloop by output quadrants (see there); A buffers first, then B buffers, so that
@@ -224,18 +227,21 @@ void tile_kernel(const TileArgs a) {
     // Which rows a wave stages: rows w*8*A_LD .. of the A panel and w*8*B_LD .. of the B panel; QUAD:
     // 16 rows of each half of either panel.  A half of the A panel holds the upper (lower) 64 of
     // each wave's 128 rows, a half of the B panel the first (second) 32 of each wave's 64 columns -
-    // gated: 32 columns of the first product, the same 32 of the second.
+    // gated: 32 columns of the first product, the same 32 of the second.  (Gated without QUAD: the rows of W1,
+    // then those of W2.)
     // The lane at (row, physical chunk c) of the panel fetches global chunk c ^ swizzle(row): the
     // LDS image of a wave's 64 chunks is then the 1024 contiguous bytes a copy writes.
     const int ld_r = (tid & 63) >> 3, ld_c = tid & 7;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int PRE = 3072;                         // bytes the scalar bases start early (keeps lane offsets >= 0)
     constexpr int RUN = QUAD ? 2 : 4;
-    static_assert(!GATED || QUAD, "the gated form runs on the quadrant mainloop");
+    static_assert(!GATED || QUAD || BNO % (8 * B_LD) == 0, "a wave's B rows come from one matrix");
+    const bool second = GATED && !QUAD && wave_id * 8 * B_LD >= BNO;     // this wave stages rows of W2
     const unsigned char *Xt = reinterpret_cast<const unsigned char *>(X + (int64_t)m0 * a.ldx) - PRE;
-    const unsigned char *Wt = reinterpret_cast<const unsigned char *>(W + (int64_t)n0 * a.ldw) - PRE;
+    const unsigned char *W1t = reinterpret_cast<const unsigned char *>(W + (int64_t)n0 * a.ldw) - PRE;
     const unsigned char *W2t = GATED ? reinterpret_cast<const unsigned char *>(
-                                           reinterpret_cast<const InT *>(a.W2) + (int64_t)z * a.bsw + (int64_t)n0 * a.ldw) - PRE : Wt;
+                                           reinterpret_cast<const InT *>(a.W2) + (int64_t)z * a.bsw + (int64_t)n0 * a.ldw) - PRE : W1t;
+    const unsigned char *Wt = second ? W2t : W1t;
     // A copy's global address is a scalar base (first row of the tile, current k) plus the lane's
     // byte offset from it, which does not change along K: 32 bits (the host keeps tiles whose
     // rows span 2 GB or more off this kernel).
@@ -253,8 +259,8 @@ void tile_kernel(const TileArgs a) {
     for (int i = 0; i < B_LD; ++i) {
         const int in_half = wave_id * 16 + (i & 1) * 8 + ld_r;
         rowB[i] = QUAD ? (i >> 1) * 128 + in_half : wave_id * 8 * B_LD + i * 8 + ld_r;
-        const int row = GATED ? in_half                                                             // row of W (or of W2)
-                        : QUAD ? (in_half >> 5) * 64 + (i >> 1) * 32 + (in_half & 31) : rowB[i];
+        const int row = GATED && QUAD ? in_half                                                     // row of W (or of W2)
+                        : QUAD ? (in_half >> 5) * 64 + (i >> 1) * 32 + (in_half & 31) : rowB[i] - (second ? BNO : 0);
         gcB[i] = ld_c ^ swz(rowB[i]);
         oB[i] = (uint32_t)((int64_t)(min(n0 + row, a.w_rows - 1) - n0) * a.ldw + gcB[i] * CW) * (uint32_t)sizeof(InT) + PRE - (i % RUN) * 1024;
     }
@@ -295,7 +301,9 @@ void tile_kernel(const TileArgs a) {
     };
 
     // ---------------- fragment read plan
-    const int fa_row = wave_m * (QUAD ? 64 : WTM) + l32, fb_row = wave_n * (QUAD ? 32 : WTN) + l32;
+    // B fragment of column block j sits FB_STEP panel rows below block 0's (not QUAD)
+    constexpr int FB_STEP = GATED ? BNO : 32;
+    const int fa_row = wave_m * (QUAD ? 64 : WTM) + l32, fb_row = wave_n * (QUAD || GATED ? 32 : WTN) + l32;
     // chunk pair u (0..3) of a panel row: lanes 0-31 take chunk 2u, lanes 32-63 chunk 2u+1.
     // A k-step consumes FR pairs.  Which k land in which lane and slot does not matter as long
     // as both operands use the same assignment - the sum over k is complete either way.
@@ -755,7 +763,7 @@ void tile_kernel(const TileArgs a) {
                 if constexpr (F8) fa1[q][c] = v;
                 else              fr[t & 1][q][c] = v;
             } else {
-                fr[t & 1][q][c] = *reinterpret_cast<const u32x4 *>(sB + (q - MB) * 32 * ROWB + off);
+                fr[t & 1][q][c] = *reinterpret_cast<const u32x4 *>(sB + (q - MB) * FB_STEP * ROWB + off);
             }
         }
     };

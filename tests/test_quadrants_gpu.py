@@ -1,6 +1,7 @@
-"""The quadrant mainloop of the 256x256 tiles: two K tiles are in flight when a tile is multiplied,
+"""The two mainloops of the 256x256 tiles - by quadrants: two K tiles are in flight when a tile is multiplied,
 buffers and register sets change with the tile's parity, copies past the end move nothing and the
-chunks past K are zeroed by hand - exact integers over one to five K tiles, whole and partial."""
+chunks past K are zeroed by hand; by k-steps up to four K tiles of 16-bit operands (one of 8-bit ones): one K tile in flight, a
+partial one through registers.  Exact integers over one to eleven K tiles, whole and partial."""
 import numpy as np
 import pytest
 import torch
@@ -25,8 +26,18 @@ def _rounded(ref, dt):
 @pytest.mark.parametrize("gated", [False, True])
 def test_k_tiles_of_the_quadrant_mainloop(dt, out, gated):
     unit, tile_k = (16, 128) if dt == I.F8E4M3 else (8, 64)
-    for K in sorted({unit, tile_k - unit, tile_k, tile_k + unit, 2 * tile_k, 2 * tile_k + unit, 3 * tile_k,
-                     4 * tile_k - unit, 4 * tile_k, 5 * tile_k + unit}):
+    _sweep(dt, out, gated, sorted({unit, tile_k - unit, tile_k, tile_k + unit, 2 * tile_k, 2 * tile_k + unit, 3 * tile_k,
+                                   4 * tile_k - unit, 4 * tile_k, 5 * tile_k + unit}))
+
+
+@pytest.mark.parametrize("dt,out", [(I.BF16, I.F32), (I.BF16, I.BF16), (I.F16, I.F16)])
+@pytest.mark.parametrize("gated", [False, True])
+def test_k_tiles_around_and_past_the_line_between_the_loops(dt, out, gated):
+    _sweep(dt, out, gated, (4 * 64 + 8, 5 * 64 - 8, 5 * 64, 6 * 64 - 8, 6 * 64, 6 * 64 + 8, 7 * 64, 8 * 64 + 8, 9 * 64, 11 * 64 + 8))
+
+
+def _sweep(dt, out, gated, ks):
+    for K in ks:
         for M, N in ((260, 264), (530, 520)):
             w = I.Workload(name="quad", M=M, K=K, N=N, in_dtype=dt, out_dtype=out,
                            dist={"X": ("int", -2, 2), "W": ("int", -2, 2), "b": ("int", -3, 3)})
