@@ -107,9 +107,10 @@ typedef enum {
  *   other tiles did not arrive within about 2^20 polls) stores NaN for its rows - and NaN in
  *   aux_out for LOGSUMEXP - and sets the fault word (fge_fault_word_offset): the kernel always
  *   terminates and never stores values normalised with incomplete statistics.  (Products of at most
- *   64 rows finish their rows in the launch's last workgroups, which wait in the same bounded way
- *   for workgroups that started before them, so other launches cannot keep those from arriving;
- *   the flag moves the row operation to a second kernel there as well.)  The stage entry
+ *   64 rows finish their rows in the launch's last workgroups, which wait in the same bounded way for
+ *   all others.  Those are ahead of them in the order workgroups start in on each XCD, but other
+ *   launches may hold an XCD's share back while the last workgroups wait on another: set the flag
+ *   there too when launches may overlap; the row operation is then a second kernel.)  The stage entry
  *   points fge_fused_tiles / fge_fused_finish always take the two-pass form.
  *   FGE_FLAG_IEEE_FP32 : multiply fp32 operands with the fp32 matrix instruction.  Without it
  *   fp32 operands are multiplied on the bf16 matrix instruction after a split of each operand
@@ -243,7 +244,8 @@ size_t fge_fault_word_offset(int act, int norm, const fge_params *p);
  * applies scale, bias, activation and gate, and the row operation on that fp32 result - when
  * the workspace has the room, else the tile kernel.  fge_gated_workspace_bytes gives the
  * workspace either call needs; fge_gated_tile_name names what the fused call runs
- * ("partial_products_then_gate" for small problems, "unfused_sequence" for the fallback). */
+ * ("partial_products_then_gate" for small problems, "unfused_sequence" for the fallback; of at most 64
+ * rows see fge_few_rows). */
 int fused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, const float *b1,
                               const float *b2, int act, int norm, const fge_params *p, void *out,
                               void *stream);
@@ -268,9 +270,14 @@ int fge_fused_finish(int act, int norm, const fge_params *p, void *out, void *st
 int fge_fused_needs_finish(int act, int norm, const fge_params *p);
 /* Slices of K that fused_gemm_epilogue cuts these arguments into when the workspace has the
  * room (1: none; see FGE_FLAG_NO_SPLIT_K), negative on bad args; for a product the few-row kernel
- * takes, the slices it would be cut into otherwise.  The stage entry points fge_fused_tiles /
- * fge_fused_finish never slice. */
+ * takes (fge_few_rows), the slices it would be cut into otherwise.  The stage entry points
+ * fge_fused_tiles / fge_fused_finish never slice. */
 int fge_fused_k_slices(int act, int norm, const fge_params *p);
+/* 1 if fused_gemm_epilogue (gated != 0: fused_gated_gemm_epilogue) runs these arguments on the kernel
+ * for products of at most 64 rows, 0 if not, negative on bad args.  A workspace in p that lacks the room
+ * for it counts; none at all is taken for one of the size asked for.  The other reports
+ * (fge_fused_k_slices, fge_tile_name, fge_gated_tile_name) then name what would run otherwise. */
+int fge_few_rows(int gated, int act, int norm, const fge_params *p);
 
 /* Unfused K1: Y (rows x N, out_dtype, row stride ldo) = post_scale * (alpha * X.W^T + b). */
 int fge_gemm_bias(const void *X, const void *W, const float *b, const fge_params *p,
@@ -287,7 +294,7 @@ const char *fge_status_string(int status);
 int fge_last_hip_error(void);
 /* Name of the tile configuration the fused path picks for these arguments (static string,
  * e.g. "256x256_w2x4"); NULL on invalid arguments.  For reports and tests.  (Of a product the few-row
- * kernel takes: the configuration it would run on otherwise.) */
+ * kernel takes, see fge_few_rows: the configuration it would run on otherwise.) */
 const char *fge_tile_name(int fused, int act, int norm, const fge_params *p);
 
 #ifdef __cplusplus

@@ -74,6 +74,8 @@ def lib() -> ctypes.CDLL:
         L.fge_fused_finish.restype = ci
         L.fge_fused_needs_finish.argtypes = [ci, ci, pp]
         L.fge_fused_needs_finish.restype = ci
+        L.fge_few_rows.argtypes = [ci, ci, ci, pp]
+        L.fge_few_rows.restype = ci
         L.fge_fused_k_slices.argtypes = [ci, ci, pp]
         L.fge_fused_k_slices.restype = ci
         L.fge_gemm_bias.argtypes = [vp, vp, vp, pp, vp, vp]
@@ -215,6 +217,13 @@ def fge_fused_tiles(X, W, b, act, norm, p: FgeParams, out, stream=None) -> None:
 def fge_fused_finish(act, norm, p: FgeParams, out, stream=None) -> None:
     _check(lib().fge_fused_finish(_code(ACT, act), _code(NORM, norm), ctypes.byref(p), _ptr(out),
                                   _stream(stream)), "fge_fused_finish")
+
+
+def fge_few_rows(gated: bool, act, norm, p: FgeParams) -> bool:
+    rc = lib().fge_few_rows(int(bool(gated)), _code(ACT, act), _code(NORM, norm), ctypes.byref(p))
+    if rc < 0:
+        raise FgeError(-rc, "fge_few_rows")
+    return rc == 1
 
 
 def fge_fused_k_slices(act, norm, p: FgeParams) -> int:

@@ -1130,6 +1130,14 @@ int fge_fused_k_slices(int act, int norm, const fge_params *p) {
     return k_split(p, norm, make_plan(p, norm)).slices;
 }
 
+int fge_few_rows(int gated, int act, int norm, const fge_params *p) {
+    const int rc = check_common(p, act, norm, true);
+    if (rc) return -rc;
+    if (gated && !gated_fast(p, norm)) return 0;
+    const Skinny k = plan_skinny(p, norm, gated != 0);
+    return k.use && !(p->workspace && p->workspace_bytes < k.bytes()) ? 1 : 0;
+}
+
 int fused_gemm_epilogue(const void *X, const void *W, const float *b, int act, int norm,
                         const fge_params *p, void *out, void *stream) {
     return run_fused(X, W, b, act, norm, p, out, (hipStream_t)stream);

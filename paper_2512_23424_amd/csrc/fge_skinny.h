@@ -14,8 +14,9 @@
 //   * a row operation needs the whole row: the values go to an fp32 array in the workspace, and the
 //     last M workgroups of the launch (one row each) wait for all others' arrival marks and run the
 //     row op - or, where a launch may not wait (graph capture, FGE_FLAG_TWO_PASS), a second kernel
-//     does.  Workgroups start in index order, so the waiting ones have nobody behind them: they need
-//     not be resident together with the rest of the grid.
+//     does.  Workgroups start in index order on each XCD, so with the device to itself a launch's waiting
+//     workgroups have nobody behind them and need not be resident together with the rest of the grid.  A launch that
+//     fills an XCD meanwhile may hold some back: the wait is bounded, and ends in NaN rows and the fault word.
 #pragma once
 #include "fge_device.h"
 

@@ -262,6 +262,22 @@ def test_tile_choice_reads_the_search_table_and_respects_its_limits():
     assert B.fge_tile_name(True, 4, 3, f32) == B.fge_tile_name(True, 4, 3, _params(M=2048, N=4096, K=4096, ldx=4096, ldw=4096, ldo=4096, flags=B.FLAG_NO_TABLE))
 
 
+def test_few_row_report():
+    """Which calls the few-row kernel takes: at most 64 rows of 16- or 8-bit operands over a K of 1 KB and more,
+    unless a flag or the workspace keeps them on the tile kernels."""
+    def prm(M, K=4096, N=4096, dt=1, **kw):
+        return _params(M=M, N=N, K=K, ldx=K, ldw=K, ldo=N, in_dtype=dt, out_dtype=1 if dt == 3 else dt, **kw)
+    assert B.fge_few_rows(False, 4, 3, prm(16)) and B.fge_few_rows(True, 4, 3, prm(64)) and B.fge_few_rows(False, 4, 3, prm(16, dt=3))
+    assert not B.fge_few_rows(False, 4, 3, prm(65)) and not B.fge_few_rows(False, 4, 3, prm(16, dt=0))
+    assert not B.fge_few_rows(False, 4, 3, prm(16, K=504)) and B.fge_few_rows(False, 4, 3, prm(16, K=512))
+    assert not B.fge_few_rows(False, 4, 3, prm(16, flags=B.FLAG_NO_SPLIT_K)) and not B.fge_few_rows(False, 4, 3, prm(16, flags=1 << 8))
+    assert B.fge_few_rows(False, 4, 3, prm(16, flags=B.FLAG_TWO_PASS))                      # two launches of it
+    assert not B.fge_few_rows(False, 4, 3, prm(16, workspace=FAKE, workspace_bytes=1 << 16))
+    assert B.fge_few_rows(False, 4, 0, prm(16, workspace=FAKE, workspace_bytes=16))         # no row op: no workspace
+    with pytest.raises(B.FgeError):
+        B.fge_few_rows(False, 1, 1, _params(M=0))
+
+
 def test_fault_word_lies_inside_the_workspace():
     """A few-row product in a workspace too small for its fp32 rows runs on the tile kernels, in two passes: no
     fault word, rather than one behind the workspace's end."""

@@ -472,7 +472,7 @@ def test_graph_capture_and_replay():
     recorded arguments, so arrival marks could not tell one replay from the next).  Every
     replay - with eager work and synchronisations between them - reproduces the eager result."""
     for (dt, M, K, N) in [(I.BF16, 4100, 136, 4000), (I.F32, 2060, 100, 2040), (I.F32, 5000, 40, 328),
-                          (I.BF16, 24, 4096, 1024)]:          # the last one runs as a K-split (three kernels)
+                          (I.BF16, 24, 4096, 1024)]:          # the last one on the few-row kernel (a K-split: tests/test_k_share_gpu.py)
         w = I.Workload(name="graph", M=M, K=K, N=N, in_dtype=dt, out_dtype=dt, act=I.ACT_SILU,
                        norm=I.NORM_RMSNORM, eps=1e-5,
                        dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, 0.1 if K < 1024 else 0.02), "gamma": ("normal", 1.0, 0.1)})
