@@ -278,7 +278,7 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
         return TILE_256x256;
     // 128x128 tiles from 5/8 of the CUs on: one round of them (three stage buffers, see tile_args)
     // then beats the 64x64 tiles' several (640 x 4096 x 4096: 48.5 against 58.3 us; at 512 rows,
-    // 128 tiles, the 64x64 tiles still win with 38 us)
+    // 128 tiles, the 64x64 tiles still won with 38 us - both before either shared out K over its waves, 29 us now)
     if (fits(TILE_128x128) && count(TILE_128x128) * 8 >= num_cu() * 5) return TILE_128x128;
     return TILE_64x64;
 }

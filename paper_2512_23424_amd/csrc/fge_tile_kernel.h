@@ -491,10 +491,10 @@ void tile_kernel(const TileArgs a) {
     // issued no later than beta(kt-1), what is read between alpha(kt) and beta(kt+1) - A0 and the
     // second block of kt+1 - no later than alpha(kt-1): three pairs of copies are younger in both
     // cases, so the wait in front of a barrier is for all but the last six copies of the wave.
-    // Against the k-step order: 8192 x 4096 x 4096 SiLU + RMSNorm bf16 235.6 -> 224.8 us, 8-bit 131 ->
-    // 123 us, 16 x 2048 x 512 x 2048 softmax 148.9 -> 142.3 us, logits 2048 x 4096 x 50257 990 -> 922 us.
-    // What bounds it now is power: without copies, without barriers or without fragment reads the
-    // launch takes the same 365 K cycles, only at 1.8 to 2.3 GHz instead of 1.73.
+    // Against the k-step order: 8192 x 4096 x 4096 SiLU + RMSNorm bf16 240.9 -> 231.5 us, 8-bit 133.0 -> 127.1 us,
+    // 16 x 2048 x 512 x 2048 softmax 151.7 -> 149.0 us (short K keeps that order, see short_k).
+    // What is left: timing-only builds without copies, without barriers or without fragment reads take the same
+    // 365 K cycles, at 1.8 to 2.3 GHz instead of 1.73; a library's plain product of this shape takes 318 K.
     constexpr int NMQ = 2 * KS;                       // MFMAs per quadrant: k-steps x two row blocks
     constexpr int LASTK = NMQ - 2;                    // first MFMA of the last k-step
     const unsigned char *baseA = smem + fa_row * ROWB, *baseB = smem + B_AT + fb_row * ROWB;
@@ -641,8 +641,8 @@ void tile_kernel(const TileArgs a) {
     // (issued three tiles ago) and the fragment reads of tile kt have been waited for, so behind it
     // tile kt+1 is visible to every wave and buffer kt % 4 is free for the copy of tile kt+4.
     // 1000 x 4096 x 4096 fp16 46.3 -> 41.6 us, 256 x 4096 x 4096 bf16 21.0 -> 16.2 us; what is left is the copies'
-    // rate (L2 to LDS, about 85 GB/s per CU) and power: the MFMAs alone, without copies, reads or barriers,
-    // take 30 us of the former.
+    // rate (L2 to LDS, about 85 GB/s per CU); the MFMAs alone, without copies, reads or barriers, take 30 us of the
+    // former.
     static_assert(A_LD == 2 && B_LD == 2, "pairs of copies");
     constexpr int KG = 2;                             // K groups
     constexpr int WNG = 2, WMG = WAVES_M / KG;        // waves of a group across / down the tile
