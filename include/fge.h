@@ -128,6 +128,11 @@ typedef enum {
  *   smaller workspace (or none, where none is needed otherwise) the problem runs unsliced.
  *   Products of at most 64 rows of 16- or 8-bit operands (K of 1024 bytes and more) normally share
  *   out K inside a workgroup instead and need no slices; the flag keeps them on the tile kernels.
+ *   The last 256x256 tiles of a launch (gated: 256x128) that do not fill the device once more - all of a
+ *   problem that has few - are shared in the same way: two or four workgroups multiply a slice of K each, exchange
+ *   partial sums through the workspace and finish a part of the rows each.  They wait for each other like
+ *   the tiles of a row block (bounded, fault word, NaN); FGE_FLAG_NO_SPLIT_K and FGE_FLAG_TWO_PASS switch it off, a
+ *   captured stream and a workspace without the room do without.
  *   FGE_FLAG_TILE(t) : run the tile kernels with tile configuration t (an fge_tile) instead of
  *   the library's own choice - for tuning and tests.  A configuration without kernels for the
  *   operand type (or the narrow-K kernel outside K <= 64, N <= 512, fp32) yields
@@ -216,11 +221,12 @@ size_t fge_static_scratch_bytes(void);
 /* Device scratch is the caller's (the paper's kernels come with a host wrapper that owns all
  * buffers, Section 3.2, the Coder).  Bytes of workspace the fused (fused != 0) or unfused (fused == 0) path needs for these
  * arguments; 0 is a valid answer.  Returns (size_t)-1 when the arguments are invalid.  The fused
- * figure includes the room for the optional K slices (FGE_FLAG_NO_SPLIT_K); a smaller workspace
- * that still holds the row statistics of split rows is accepted and runs unsliced. */
+ * figure includes the room for the optional K slices and for the partial sums of shared tiles
+ * (FGE_FLAG_NO_SPLIT_K switches both off; up to 64 MiB); a smaller workspace that still holds the row
+ * statistics of split rows is accepted and runs without them. */
 size_t fge_workspace_bytes(int fused, int act, int norm, const fge_params *p);
 
-/* Where the one-kernel form of split rows reports a wait that ran out: byte offset into the
+/* Where the one-kernel form of split rows, or a launch with shared tiles, reports a wait that ran out: byte offset into the
  * workspace of an int32 that such a launch sets to 1 (it never clears it; the rows of the tiles
  * whose wait ran out are stored as NaN).  (size_t)-1 when fused_gemm_epilogue does not take that
  * form for these arguments.  A caller that wants the check clears the word before the call and

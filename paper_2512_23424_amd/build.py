@@ -17,6 +17,7 @@ OBJDIR = os.path.join(HERE, "_build")
 UNITS = ["fge_api.hip", "fge_tiles_f32.hip", "fge_tiles_f32s.hip", "fge_tiles_bf16.hip", "fge_tiles_f16.hip", "fge_tiles_f8.hip", "fge_panel_f32.hip", "fge_generic.hip", "fge_gated.hip", "fge_skinny.hip",
          "fge_tiles_half_bf16.hip", "fge_tiles_half_f16.hip", "fge_tiles_half_f8.hip",
          "fge_tiles_short_bf16.hip", "fge_tiles_short_f16.hip", "fge_tiles_short_f8.hip",
+         "fge_tiles_shared_bf16.hip", "fge_tiles_shared_f16.hip", "fge_tiles_shared_f8.hip",
          "fge_tiles_any_f32.hip", "fge_tiles_any_f32s.hip", "fge_tiles_any_bf16.hip", "fge_tiles_any_f16.hip", "fge_tiles_any_f8.hip"]
 HEADERS = ["fge_device.h", "fge_epilogue.h", "fge_tile_kernel.h", "fge_panel_kernel.h", "fge_rowops.h", "fge_skinny.h", "fge_launch.h", "fge_tile_table.h"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall", "-Wno-unused-function",

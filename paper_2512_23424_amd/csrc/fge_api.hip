@@ -279,8 +279,17 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
     // 128x128 tiles from 5/8 of the CUs on: one round of them (three stage buffers, see tile_args)
     // then beats the 64x64 tiles' several (640 x 4096 x 4096: 48.5 against 58.3 us; at 512 rows,
     // 128 tiles, the 64x64 tiles still won with 38 us - both before either shared out K over its waves, 29 us now)
-    if (fits(TILE_128x128) && count(TILE_128x128) * 8 >= num_cu() * 5) return TILE_128x128;
+    if (fits(TILE_128x128) && (count(TILE_128x128) * 8 >= num_cu() * 5 || count(TILE_64x64) > 2 * num_cu())) return TILE_128x128;
     return TILE_64x64;
+}
+
+// sharing: left-over tiles of 256x256 may be shared (see plan_share).  With a row of at least 8 KB and few of them (a
+// quarter of the CUs: up to four slices) that makes 256x256 tiles the better choice wherever there is a full round of them (4173 x 4096 x
+// 4096 RMSNorm, against the table's 128x256 tiles: bf16 189.6 -> 157.2 us, E4M3 107.3 -> 93.1; with 2 KB of K, 128x128 tiles, 68.8 -> 71.4).
+bool prefer_shared(const Problem &pr, int in_dtype) {
+    const int64_t tiles = (int64_t)((pr.M + 255) / 256) * ((pr.N + 255) / 256), left = tiles % num_cu();
+    return in_dtype != FGE_F32 && pr.batch == 1 && tiles > num_cu() && left > 0 && 4 * left <= num_cu() &&
+           (int64_t)pr.K * (int64_t)esize(in_dtype) >= 8192;
 }
 
 // two_pass: finish split rows with the second kernel even where the cooperative form exists
@@ -299,6 +308,9 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
               : forced_tile(p) >= 0 ? forced_tile(p)
                                     : pick_tile(pr, p->in_dtype, norm, (p->flags & FGE_FLAG_IEEE_FP32) != 0,
                                                 !(p->flags & FGE_FLAG_NO_TABLE));
+    if (force_tile < 0 && forced_tile(p) < 0 && !two_pass && !(p->flags & (FGE_FLAG_TWO_PASS | FGE_FLAG_NO_SPLIT_K)) &&
+        prefer_shared(pr, p->in_dtype))
+        pl.tile = TILE_256x256;
     // 16- and 8-bit 128x128 tiles, no more of them than CUs (however the tile was chosen): the form
     // on eight waves with three stage buffers - no second workgroup shares a CU, so a second K-tile
     // copy in flight and a second wave per SIMD hide the latencies instead (640 x 4096 x 4096: 43.2
@@ -391,6 +403,123 @@ KSplit k_split(const fge_params *p, int norm, const Plan &pl) {
     return ks;
 }
 
+// Shared tiles (256x256 tiles by output quadrants and the gated form, see the tile kernel): the tiles left
+// over when the others have filled the chip a whole number of times would take as long as a full round on
+// a part of the CUs; each is multiplied by two or four workgroups instead, a slice of K each (three, whose
+// parts of the rows are uneven, measured slower than two).
+struct Share {
+    int slices;                  // 0: no tile is shared
+    int left;                    // shared tiles
+    int from;                    // first of them (ordinary grid) / the round that shares its tiles (cooperative grid)
+    int k;                       // elements of K per slice
+    int grid;                    // workgroups of the launch
+    size_t ws_part, ws_marks;    // partial sums; their marks and, in the last 256 bytes, the fault word
+    size_t bytes() const { return ws_part + ws_marks; }
+};
+
+Share plan_share(const fge_params *p, const Plan &pl) {
+    Share sh{};
+    const size_t is = esize(p->in_dtype);
+    const bool gated = pl.tile == TILE_GATED;
+    if (pl.generic || p->in_dtype == FGE_F32 || (pl.tile != TILE_256x256 && !gated) || pl.pr.batch != 1) return sh;
+    if (g_out_rows != OUT_ALIGNED || short_k(pl.pr.K, is)) return sh;             // (no room is asked for there; another mainloop)
+    if (p->flags & (FGE_FLAG_NO_SPLIT_K | FGE_FLAG_TWO_PASS)) return sh;
+    const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
+    const int capacity = pl.coop ? num_cu() / pl.tiles_n * pl.tiles_n : num_cu();
+    const int left = (int)(tiles % capacity);
+    if (left == 0 || tiles > INT32_MAX / 2) return sh;
+    const int bk = (int)(128 / is), KT = (pl.pr.K + bk - 1) / bk;
+    // In K tiles: a slice, four for the start and the meeting, and the sums' way through memory (256 KB per tile and
+    // further slice: 0.06 each; 64 tiles over 16 K tiles take 22.2 us unshared, 19.4 in two slices, 31.2 in four).  Sharing
+    // that gains less than a K tile is left alone (16384 x 1704 x 1320, 128 tiles over 27: 93.9 -> 93.0 us).
+    // bf16, us, unshared -> shared: 4173 x 3192 x 512 76.1 -> 39.3, 6235 x 6096 x 3616 LayerNorm 360 -> 289, 8192 x 4096 x 4608 RMSNorm 329 ->
+    // 284 (E4M3 184 -> 166), gated 463 x 4096 x 4504 RMSNorm 75.1 -> 55.2.
+    double best = KT - 1;
+    int chunk = 0;
+    for (int S = 2; S <= 4 && S * left <= capacity; S += 2) {
+        const int c = (KT + S - 1) / S;
+        const double cost = c + 4 + 0.06 * left * (S - 1);
+        if ((KT + c - 1) / c != S) continue;             // (a slice would be empty)
+        if (cost < best) { best = cost; chunk = c; }
+    }
+    if (chunk == 0) return sh;
+    sh.slices = (KT + chunk - 1) / chunk;
+    sh.k = chunk * bk;
+    sh.left = left;
+    sh.from = pl.coop ? (int)(tiles / capacity) : (int)(tiles - left);
+    sh.grid = pl.coop ? (tiles > capacity ? capacity : left * sh.slices) : sh.from + left * sh.slices;
+    sh.ws_part = (size_t)sh.slices * left * (256 * 256 * sizeof(float));
+    sh.ws_marks = round256((size_t)sh.slices * left * (pl.coop ? 2 : 1) * sizeof(unsigned)) + 256;
+    return sh;
+}
+
+// Whether this call shares tiles: the workspace has the room behind what the plan itself needs.
+Share share_in(const fge_params *p, const Plan &pl) {
+    Share sh = plan_share(p, pl);
+    if (sh.slices && !(p->workspace && p->workspace_bytes >= pl.ws_stats + pl.ws_marks + sh.bytes())) sh = Share{};
+    return sh;
+}
+
+// Problems all of whose 256x256 (gated: 256x128) tiles are shared.  Rows that span several column tiles are
+// written in fp32, and a row kernel - one workgroup per row - turns them into the result: between workgroups that have
+// just exchanged sums, the exchange of row statistics costs more than that launch (gated 256 x 4096 x 2984
+// RMSNorm: 30.7 us so, 40.1 with the exchange, 34.9 as two products; 1000 x 2048 x 2984 38.8 and 43.3).
+struct SharedAll {
+    bool use;
+    fge_params q;                // the product and the activation: into `out`, or as fp32 rows into the workspace
+    Plan pl;
+    Share sh;
+    int norm;                    // ... and what its epilogue does of the row op
+    size_t ws_mid;               // bytes of the fp32 rows (0: none)
+    size_t bytes() const { return ws_mid + sh.bytes(); }
+};
+
+bool worth_sharing_all(const fge_params *p, int norm, const Plan &pl);
+
+SharedAll plan_shared_all(const fge_params *p, int norm, bool gated) {
+    SharedAll r{};
+    if (g_out_rows != OUT_ALIGNED || p->in_dtype == FGE_F32 || forced_tile(p) >= 0 || !vectorisable(p, norm, true)) return r;
+    const int tile = gated ? TILE_GATED : TILE_256x256;
+    r.q = *p;
+    r.pl = make_plan(p, FGE_NORM_NONE, true, tile);
+    if (!worth_sharing_all(p, norm, r.pl)) return r;
+    r.norm = r.pl.tiles_n == 1 ? norm : FGE_NORM_NONE;
+    if (norm != r.norm) {
+        if (p->N > MAX_ROWOP_N) return r;
+        r.ws_mid = round256((size_t)r.pl.pr.M * p->N * sizeof(float));
+        if (r.ws_mid > ((size_t)32 << 20)) return r;
+        r.q.out_dtype = FGE_F32;
+        r.q.M = r.pl.pr.M; r.q.batch = r.pl.pr.batch; r.q.ldx = r.pl.pr.ldx; r.q.ldo = p->N;
+        r.pl = make_plan(&r.q, FGE_NORM_NONE, true, tile);
+    }
+    r.sh = plan_share(&r.q, r.pl);
+    r.use = r.sh.slices && r.sh.from == 0;
+    return r;
+}
+
+// Whether that is the faster way (pl: the plan in these tiles).  A tile half of whose rows do not exist wastes its products: M > 128.
+// Gated: against two products in 64x64 tiles and a gate kernel, and against unshared gated tiles (bf16, us before -> shared):
+// 512 x 8192 x 2984 99.2 -> 54.2, 256 x 4096 x 5056 RMSNorm 55.9 -> 37.2, 512 x 2048 x 4096 36.3 -> 30.4; below the line 768 x 1024 x 600
+// 16.0 -> 18.3, 256 x 8192 x 600 31.2 -> 39.0, with the row kernel behind them 256 x 1024 x 4096 21.1 -> 22.0.
+// Plain: against 64x64 tiles and two 128x128 tiles per CU, which a long K keeps bound by operand traffic (768 x 8192 x 2048
+// 45.6 -> 41.0, 1000 x 8192 x 8192 129.6 -> 117.5, 1500 x 8192 x 4096 RMSNorm 115.8 -> 104.0; from half that K where the 128x128
+// tiles just miss one per CU: 4173 x 4096 x 1024 51.2 -> 44.4, but 2048 x 4096 x 4096 RMSNorm 72.2 -> 80.8).  One
+// 128x128 tile per CU is not beaten (1000 x 4096 x 4096 35.4 -> 43.4, 512 x 8192 x 8192 66.3 -> 69.4), nor are 8-bit operands at
+// the same K tiles (1500 x 8192 x 4096 52.3 -> 50.3 only).
+bool worth_sharing_all(const fge_params *p, int norm, const Plan &pl) {
+    const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n, row_bytes = (int64_t)pl.pr.K * (int64_t)esize(p->in_dtype);
+    if (pl.pr.M <= 128) return false;
+    if (pl.tile == TILE_GATED) {
+        const bool rows = norm != FGE_NORM_NONE && pl.tiles_n > 1;
+        return rows ? tiles >= 20 && tiles * row_bytes >= 80 << 10 : tiles >= 10 && tiles * row_bytes >= 40 << 10;
+    }
+    if (row_bytes < 8192) return false;
+    const int other = make_plan(p, norm).tile;
+    const bool longer = p->in_dtype != FGE_F8E4M3 && row_bytes >= 16384;
+    if (other == TILE_64x64) return longer && tiles >= 24;
+    return other == TILE_128x128 && (longer || tiles <= 100);
+}
+
 constexpr double REPACK_MIN_FLOP = 3.0e7;   // below this the element-granular product is as fast as four launches
 bool worth_repacking(const fge_params *p) { return 2.0 * (double)p->M * p->batch * p->N * p->K >= REPACK_MIN_FLOP; }
 
@@ -471,15 +600,21 @@ Repack plan_repack(const fge_params *p, int norm);
 // Workspace of the fused path: enough for either form of split rows, since a launch on a
 // stream under graph capture takes the two-pass form whatever the flags say - and for the
 // K-split where the one-call entry point would take it.
-size_t fused_workspace(const fge_params *p, int norm) {
+// (shared: with the room that shared tiles use, which no call insists on)
+size_t fused_workspace(const fge_params *p, int norm, bool shared) {
     const Plan p1 = make_plan(p, norm, false), p2 = make_plan(p, norm, true);
-    const size_t few = plan_skinny(p, norm, false).bytes();
+    const Skinny few_rows = plan_skinny(p, norm, false);
+    const size_t few = few_rows.bytes();
+    shared = shared && !few_rows.use;
     if (p1.generic) {                // room for the repacked operands where the problem is worth repacking
         const Repack rp = plan_repack(p, norm);
         if (rp.use && rp.staged()) return rp.bytes;
         return std::max({rp.use ? rp.bytes : 0, p1.ws_generic, few});
     }
-    return std::max({p1.ws_stats + p1.ws_marks, p2.ws_stats + p2.ws_marks, k_split(p, norm, p1).bytes(), few});
+    const SharedAll all = shared ? plan_shared_all(p, norm, false) : SharedAll{};
+    if (all.use) return std::max({p1.ws_stats + p1.ws_marks, p2.ws_stats + p2.ws_marks, all.bytes(), few});
+    return std::max({p1.ws_stats + p1.ws_marks + (shared ? plan_share(p, p1).bytes() : 0), p2.ws_stats + p2.ws_marks,
+                     k_split(p, norm, p1).bytes(), few});
 }
 
 // What the tile kernels need of it (the K-split is optional: without the room it is not taken).
@@ -492,9 +627,9 @@ size_t split_rows_workspace(const fge_params *p, int norm) {
 // The gated tile kernel takes 16-bit and 8-bit operands in shapes the vectorised kernels take.
 bool gated_fast(const fge_params *p, int norm) { return p->in_dtype != FGE_F32 && vectorisable(p, norm, true); }
 
-size_t gated_workspace(const fge_params *p, int norm) {
+size_t gated_workspace(const fge_params *p, int norm, bool shared = false) {
     const Plan p1 = make_plan(p, norm, false, TILE_GATED), p2 = make_plan(p, norm, true, TILE_GATED);
-    const size_t a = p1.ws_stats + p1.ws_marks, b = p2.ws_stats + p2.ws_marks;
+    const size_t a = p1.ws_stats + p1.ws_marks + (shared ? plan_share(p, p1).bytes() : 0), b = p2.ws_stats + p2.ws_marks;
     return a > b ? a : b;
 }
 
@@ -549,7 +684,7 @@ int static_scratch(void **ptr) {
 }
 
 TileArgs tile_args(const void *X, const void *W, const float *b, int act, int norm,
-                   const fge_params *p, const Plan &pl, void *out) {
+                   const fge_params *p, const Plan &pl, void *out, const Share &sh = Share{}) {
     TileArgs a{};
     a.X = X; a.W = W; a.b = b; a.gamma = p->gamma; a.beta = p->beta;
     a.out = out; a.aux = p->aux_out; a.ws = reinterpret_cast<float2 *>(p->workspace);
@@ -567,10 +702,25 @@ TileArgs tile_args(const void *X, const void *W, const float *b, int act, int no
     a.stream_out = (size_t)pl.pr.M * pl.pr.batch * pl.pr.N * esize(p->out_dtype) >= ((size_t)128 << 20);
     a.any_row = g_out_rows == OUT_ANY;
     a.coop = 0;
-    if (pl.coop && norm != FGE_NORM_NONE) {
+    a.share_from = pl.tiles_m * pl.tiles_n;
+    const bool coop = pl.coop && norm != FGE_NORM_NONE;
+    if (coop || sh.slices) {
+        a.gen = g_generation.fetch_add(1) + 1;
+        const bool expire = (p->flags & FGE_FLAG_TEST_EXPIRE_WAIT) != 0;
+        a.spin_limit = expire ? 1u : WAIT_POLLS;
+        a.withhold = expire ? 1 : 0;
+    }
+    if (sh.slices) {
+        char *base = static_cast<char *>(p->workspace) + pl.ws_stats + pl.ws_marks;
+        a.share = sh.slices; a.share_from = sh.from; a.share_k = sh.k;
+        a.part = reinterpret_cast<float *>(base);
+        a.part_marks = reinterpret_cast<unsigned *>(base + sh.ws_part);
+        a.share_arrive = a.part_marks + sh.slices * sh.left;
+        a.fault = reinterpret_cast<int *>(base + sh.bytes() - 256);
+    }
+    if (coop) {
         char *base = static_cast<char *>(p->workspace) + pl.ws_stats;
         a.coop = 1;
-        a.gen = g_generation.fetch_add(1) + 1;
         a.arrive = reinterpret_cast<unsigned *>(base);
         a.fault = reinterpret_cast<int *>(base + pl.ws_marks - 256);
         // staggered start of the row blocks (see the kernel): measured 1 to 7 % on problems whose
@@ -581,20 +731,20 @@ TileArgs tile_args(const void *X, const void *W, const float *b, int act, int no
         const int64_t row_blocks = (int64_t)pl.tiles_m * pl.pr.batch, per_round = pl.coop_grid / pl.tiles_n;
         a.stagger = pl.pr.K <= 2048 && row_blocks >= 3 * per_round ? 4 : 0;
         a.stagger_mask = 7;
-        const bool expire = (p->flags & FGE_FLAG_TEST_EXPIRE_WAIT) != 0;
-        a.spin_limit = expire ? 1u : WAIT_POLLS;
-        a.withhold = expire ? 1 : 0;
     }
     return a;
 }
 
-int launch_tiles(const TileArgs &a, const fge_params *p, const Plan &pl, hipStream_t s) {
+unsigned tile_grid(const TileArgs &a, const Plan &pl, const Share &sh) {
+    return sh.slices ? (unsigned)sh.grid : a.coop ? (unsigned)pl.coop_grid : (unsigned)(pl.tiles_m * pl.tiles_n);
+}
+
+int launch_tiles(const TileArgs &a, const fge_params *p, const Plan &pl, hipStream_t s, const Share &sh = Share{}) {
     if (pl.tile == TILE_PANEL) {
         const dim3 pgrid((unsigned)(pl.tiles_m < num_cu() ? pl.tiles_m : num_cu()));
         return hip_status(launch_panel_f32(p->out_dtype, pgrid, s, a));
     }
-    const dim3 grid(a.coop ? (unsigned)pl.coop_grid : (unsigned)(pl.tiles_m * pl.tiles_n), 1,
-                    a.coop ? 1u : (unsigned)pl.pr.batch);
+    const dim3 grid(tile_grid(a, pl, sh), 1, a.coop ? 1u : (unsigned)pl.pr.batch);
     if (g_out_rows != OUT_ALIGNED)
         return hip_status(p->in_dtype == FGE_BF16     ? launch_any_bf16(pl.tile, p->out_dtype, grid, s, a)
                           : p->in_dtype == FGE_F16    ? launch_any_f16(pl.tile, p->out_dtype, grid, s, a)
@@ -731,6 +881,28 @@ int run_skinny(const void *X, const void *W, const void *W2, const float *b, con
     return hip_status(launch_skinny_rows(p->in_dtype, W2 != nullptr, num_cu(), s, a));
 }
 
+int launch_gated(const fge_params *p, dim3 grid, hipStream_t s, const TileArgs &a) {
+    return hip_status(p->in_dtype == FGE_BF16  ? launch_gated_bf16(p->out_dtype, grid, s, a)
+                      : p->in_dtype == FGE_F16 ? launch_gated_f16(p->out_dtype, grid, s, a)
+                                               : launch_gated_f8(p->out_dtype, grid, s, a));
+}
+
+int run_shared_all(const void *X, const void *W, const void *W2, const float *b, const float *b2, int act, int norm,
+                   const fge_params *p, const SharedAll &r, void *out, hipStream_t s) {
+    char *ws = static_cast<char *>(p->workspace);
+    fge_params q = r.q;
+    q.workspace = ws + r.ws_mid;
+    q.workspace_bytes = p->workspace_bytes - r.ws_mid;
+    TileArgs a = tile_args(X, W, b, act, r.norm, &q, r.pl, r.ws_mid ? ws : out, r.sh);
+    a.W2 = W2; a.b2 = b2;
+    const int rc = W2 ? launch_gated(&q, dim3(tile_grid(a, r.pl, r.sh)), s, a) : launch_tiles(a, &q, r.pl, s, r.sh);
+    if (rc || !r.ws_mid) return rc;
+    q = *p;                                    // finished values: no scale, bias or activation is left
+    q.alpha = q.post_scale = 1.0f;
+    return finish_partials(ws, nullptr, nullptr, nullptr, FGE_ACT_NONE, norm, &q, make_plan(p, FGE_NORM_NONE, true, r.pl.tile), 1, 0,
+                           nullptr, out, s);
+}
+
 int run_fused(const void *X, const void *W, const float *b, int act, int norm, const fge_params *p, void *out,
               hipStream_t s);
 
@@ -798,7 +970,9 @@ Repack plan_repack(const fge_params *p, int norm) {
     r.off_b = r.off_w + wp;
     r.off_mid = r.off_b + (r.odd_out ? round256((size_t)r.Np * sizeof(float)) : 0);
     r.off_inner = r.off_mid + (r.odd_out ? round256((size_t)rows * r.Np * sizeof(float)) : 0);
-    r.need = r.bytes = r.off_inner + fused_workspace(&r.inner, r.odd_out ? FGE_NORM_NONE : norm);
+    const int inner_norm = r.odd_out ? FGE_NORM_NONE : norm;
+    r.need = r.off_inner + fused_workspace(&r.inner, inner_norm, false);
+    r.bytes = r.off_inner + fused_workspace(&r.inner, inner_norm, true);
     r.use = true;
     if (!r.odd_out || k_split(&r.inner, FGE_NORM_NONE, make_plan(&r.inner, FGE_NORM_NONE)).slices > 1) return r;
     const bool final_at_once = norm == FGE_NORM_NONE || norm == FGE_NORM_LOGSUMEXP;
@@ -813,7 +987,7 @@ Repack plan_repack(const fge_params *p, int norm) {
         const OutRows scope(OUT_ANY);
         const Plan pl = make_plan(&r.any_p, norm);
         r.any = !pl.generic && pl.strips <= MAX_SPLIT && (final_at_once || !pl.split);
-        if (r.any) need = r.off_b + fused_workspace(&r.any_p, norm);
+        if (r.any) need = r.off_b + fused_workspace(&r.any_p, norm, false);
     }
     if (!r.any && !final_at_once) {
         const int ld = (p->N + 7) / 8 * 8;
@@ -928,7 +1102,13 @@ int do_fused_tiles(const void *X, const void *W, const float *b, int act, int no
         if (k.use && (k.bytes() == 0 || (p->workspace && p->workspace_bytes >= k.bytes())))
             return run_skinny(X, W, nullptr, b, nullptr, act, norm, p, k, out, s);
     }
-    const Plan pl = make_plan(p, norm, !one_call || capturing(s));
+    const bool captured = capturing(s);
+    if (one_call && g_w_rows == 0 && !captured && p->in_dtype != FGE_F32) {
+        const SharedAll r = plan_shared_all(p, norm, false);
+        if (r.use && p->workspace && p->workspace_bytes >= r.bytes())
+            return run_shared_all(X, W, nullptr, b, nullptr, act, norm, p, r, out, s);
+    }
+    const Plan pl = make_plan(p, norm, !one_call || captured);
     if (plan_out) *plan_out = pl;
     if (pl.generic) {
         const Repack rp = plan_repack(p, norm);
@@ -960,7 +1140,8 @@ int do_fused_tiles(const void *X, const void *W, const float *b, int act, int no
         if (pl.strips > MAX_SPLIT) return FGE_ERR_UNSUPPORTED;
         if (!p->workspace || p->workspace_bytes < split_rows_workspace(p, norm)) return FGE_ERR_WORKSPACE;
     }
-    rc = launch_tiles(tile_args(X, W, b, act, norm, p, pl, out), p, pl, s);
+    const Share sh = one_call && !captured ? share_in(p, pl) : Share{};
+    rc = launch_tiles(tile_args(X, W, b, act, norm, p, pl, out, sh), p, pl, s, sh);
     if (rc == FGE_ERR_HIP && one_call && pl.coop && fge_last_hip_error() == (int)hipErrorCooperativeLaunchTooLarge) {
         const Plan p2 = make_plan(p, norm, true);
         if (plan_out) *plan_out = p2;
@@ -1165,7 +1346,7 @@ int fused_gemm_epilogue_static(const void *X, const void *W, const float *b, int
     q.workspace = nullptr;
     q.workspace_bytes = 0;
     // (the K slices and the fp32 rows of few-row products are optional: taken when their partial products fit the array as well)
-    if (need > 0 || k_split(p, norm, pl).slices > 1 || plan_skinny(p, norm, false).bytes() > 0) {
+    if (need > 0 || k_split(p, norm, pl).slices > 1 || plan_share(p, pl).slices || plan_skinny(p, norm, false).bytes() > 0) {
         void *sp = nullptr;
         if ((rc = static_scratch(&sp))) return rc;
         q.workspace = sp;
@@ -1276,6 +1457,12 @@ int fused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, con
     const Skinny few = plan_skinny(p, norm, true);
     if (few.use && (few.bytes() == 0 || (p->workspace && p->workspace_bytes >= few.bytes())))
         return run_skinny(X, W1, W2, b1, b2, act, norm, p, few, out, s);
+    const bool captured = capturing(s);
+    if (!captured) {
+        const SharedAll r = plan_shared_all(p, norm, true);
+        if (r.use && p->workspace && p->workspace_bytes >= r.bytes())
+            return run_shared_all(X, W1, W2, b1, b2, act, norm, p, r, out, s);
+    }
     const GatedSmall gs = gated_small(p, norm);
     if (gs.use && p->workspace && p->workspace_bytes >= gs.bytes()) {
         const int S = gs.ks.slices;
@@ -1286,19 +1473,17 @@ int fused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, con
         return finish_partials(part, part + gs.ks.ws_part, b1, b2, act, norm, p, gs.pl, S, slice,
                                part + 2 * gs.ks.ws_part, out, s);
     }
-    Plan pl = make_plan(p, norm, capturing(s), TILE_GATED);
+    Plan pl = make_plan(p, norm, captured, TILE_GATED);
     if (pl.split) {
         if (pl.strips > MAX_SPLIT) return FGE_ERR_UNSUPPORTED;
         if (!p->workspace || p->workspace_bytes < gated_workspace(p, norm)) return FGE_ERR_WORKSPACE;
     }
     for (int attempt = 0;; ++attempt) {
-        TileArgs a = tile_args(X, W1, b1, act, norm, p, pl, out);
+        const Share sh = attempt == 0 && !captured ? share_in(p, pl) : Share{};
+        TileArgs a = tile_args(X, W1, b1, act, norm, p, pl, out, sh);
         a.W2 = W2; a.b2 = b2;
-        const dim3 grid(a.coop ? (unsigned)pl.coop_grid : (unsigned)(pl.tiles_m * pl.tiles_n), 1,
-                        a.coop ? 1u : (unsigned)pl.pr.batch);
-        rc = hip_status(p->in_dtype == FGE_BF16  ? launch_gated_bf16(p->out_dtype, grid, s, a)
-                        : p->in_dtype == FGE_F16 ? launch_gated_f16(p->out_dtype, grid, s, a)
-                                                 : launch_gated_f8(p->out_dtype, grid, s, a));
+        const dim3 grid(tile_grid(a, pl, sh), 1, a.coop ? 1u : (unsigned)pl.pr.batch);
+        rc = launch_gated(p, grid, s, a);
         // a cooperative grid the device cannot hold is refused before anything runs: two-pass form
         if (attempt == 0 && rc == FGE_ERR_HIP && pl.coop && g_last_hip == (int)hipErrorCooperativeLaunchTooLarge) {
             pl = make_plan(p, norm, true, TILE_GATED);
@@ -1314,13 +1499,17 @@ size_t fge_gated_workspace_bytes(int fused, int act, int norm, const fge_params 
     if (check_common(p, act, norm, true)) return (size_t)-1;
     if (!fused || !gated_fast(p, norm)) return 2 * make_plan(p, norm).ws_buf;
     const GatedSmall gs = gated_small(p, norm);
-    return std::max({gated_workspace(p, norm), gs.use ? gs.bytes() : 0, plan_skinny(p, norm, true).bytes()});
+    const Skinny few = plan_skinny(p, norm, true);
+    const SharedAll all = plan_shared_all(p, norm, true);
+    // (a captured stream shares nothing and takes what else there is)
+    if (!few.use && all.use) return std::max({gated_workspace(p, norm), all.bytes(), gs.use ? gs.bytes() : 0});
+    return std::max({gated_workspace(p, norm, !few.use && !gs.use), gs.use ? gs.bytes() : 0, few.bytes()});
 }
 
 const char *fge_gated_tile_name(int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return nullptr;
     if (!gated_fast(p, norm)) return "unfused_sequence";
-    return gated_small(p, norm).use ? "partial_products_then_gate" : tile_info(TILE_GATED).name;
+    return !plan_shared_all(p, norm, true).use && gated_small(p, norm).use ? "partial_products_then_gate" : tile_info(TILE_GATED).name;
 }
 
 size_t fge_fault_word_offset(int act, int norm, const fge_params *p) {
@@ -1329,14 +1518,18 @@ size_t fge_fault_word_offset(int act, int norm, const fge_params *p) {
     const Skinny few = plan_skinny(p, norm, false);
     if (few.use && !(p->workspace && p->workspace_bytes < few.bytes()))
         return few.bytes() && skinny_in_kernel(p, norm) ? few.bytes() - 256 : (size_t)-1;
+    const SharedAll all = plan_shared_all(p, norm, false);
+    if (all.use && !(p->workspace && p->workspace_bytes < all.bytes())) return all.bytes() - 256;
     const Plan pl = make_plan(p, norm);
-    return pl.coop ? pl.ws_stats + pl.ws_marks - 256 : (size_t)-1;
+    if (pl.coop) return pl.ws_stats + pl.ws_marks - 256;
+    const Share sh = p->workspace ? share_in(p, pl) : plan_share(p, pl);      // (no workspace named: one of the size asked for)
+    return sh.slices ? pl.ws_stats + pl.ws_marks + sh.bytes() - 256 : (size_t)-1;
 }
 
 size_t fge_workspace_bytes(int fused, int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return (size_t)-1;
     const Plan pl = make_plan(p, norm);
-    return fused ? fused_workspace(p, norm) : pl.ws_buf * pl.n_bufs;
+    return fused ? fused_workspace(p, norm, true) : pl.ws_buf * pl.n_bufs;
 }
 
 const char *fge_status_string(int status) {
@@ -1359,7 +1552,7 @@ const char *fge_tile_name(int fused, int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return nullptr;
     const Plan pl = make_plan(p, fused ? norm : FGE_NORM_NONE);
     if (pl.generic) return fused && plan_repack(p, norm).use ? "repacked_operands" : "generic32x32_scalar";
-    const TileInfo &ti = tile_info(pl.tile);
+    const TileInfo &ti = tile_info(fused && plan_shared_all(p, norm, false).use ? (int)TILE_256x256 : pl.tile);
     return p->in_dtype == FGE_F32 && !(p->flags & FGE_FLAG_IEEE_FP32) ? ti.name_split : ti.name;
 }
 

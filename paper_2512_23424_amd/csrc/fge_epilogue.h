@@ -50,7 +50,14 @@ struct TileArgs {
     int any_row;                // rows of `out` start and end at any element (stored 16 bytes at a time all the same, unaligned)
     int stagger, stagger_mask;  // cooperative form: row block rb of the first round starts (rb & mask) * stagger * 1024 clocks late
     unsigned spin_limit;        // polls after which a wait gives up
-    int withhold;               // tests only: column tile 0 never marks itself as arrived
+    int withhold;               // tests only: column tile 0 never marks itself as arrived (shared tiles: slice 1 of the first)
+    // Shared tiles (256x256 and gated tiles): the last ones of a launch, too few to fill the chip, are each
+    // multiplied by `share` workgroups, a slice of share_k of K each (0 or 1: none are shared).
+    // share_from: the first shared tile (ordinary grid; tiles_m * tiles_n: none), or the round that shares its tiles (cooperative grid)
+    int share, share_from, share_k;
+    float *part;                // [shared tiles][share][256 * 256] partial sums
+    unsigned *part_marks;       // [shared tiles][share]: gen once they are there
+    unsigned *share_arrive;     // cooperative grid: [row blocks of that round][share][tiles_n] arrival marks
 };
 
 // OutT: storage type of out.  MB x NB: 32x32 accumulator blocks per wave.  WAVES_N: waves
@@ -74,7 +81,8 @@ struct TileArgs {
 // fp32 kernels 3 to 7 % - and the rows of `out` may start anywhere (a.any_row).  Ordinary launches only.
 template <typename OutT, int MB, int NB, int WAVES_N, int PATCH_ROWS, bool JOINT, bool WAIT_VM, bool COOP = false,
           bool FULL_TILE = false, bool STREAM_OUT = false, int ACT_CT = -1, int NORM_CT = -1, bool BOUNDED_CT = false,
-          bool PLAIN_ACC = false, bool ANY = false>
+          bool PLAIN_ACC = false, bool ANY = false,
+          bool SHARED = false>
 struct TileEpilogue {
     static constexpr int WTN = NB * 32;               // columns of a wave strip
     // Patch layout.  A patch row is written 32 columns at a time by the lanes 0-31 (row R) and
@@ -126,6 +134,10 @@ struct TileEpilogue {
     bool bounded;               // clamp activation with a narrow range feeds softmax / logsumexp
     bool masked;                // the bias may mask columns of the wave (see strip_sums)
     bool defer_lse = false;     // whole-row logsumexp: park the strip pairs, the caller merges them later
+    // SHARED (see the tile kernel):
+    unsigned mine = ~0u;        // the groups of the wave's rows to be finished here (the others are another workgroup's)
+    bool sums_ok = true;        // the accumulators hold whole sums
+    unsigned *row_marks = nullptr;   // arrival marks of this part of the row block
     int lse_par = 0;            // exchange buffer the parked pairs of this tile go to
 
     __device__ __forceinline__ TileEpilogue(const TileArgs &a_, OutT *out_, float2 *xch_, float *patch_,
@@ -552,6 +564,7 @@ struct TileEpilogue {
     // Merging pairs: (m, s): m = max, s = sum s_i exp(m_i - m);  (mean, M2) with counts n_i:
     // mean = sum n_i mean_i / n, M2 = sum M2_i + n_i (mean_i - mean)^2;  (sum of squares, -): sum.
 
+    __device__ __forceinline__ bool is_mine(int row) const { return !SHARED || mine >> (row % (MB * 32) / 32) & 1; }   // tile row `row`
     // step 2: tile row `row` (one thread each)
     __device__ __forceinline__ void merge_strips(int row) {
         float2 e[WAVES_N];
@@ -580,7 +593,7 @@ struct TileEpilogue {
 #pragma unroll
             for (int w = 0; w < WAVES_N; ++w) o0 += e[w].x;
         }
-        if (m0 + row < a.M) put_pair(a.ws + (row_base + m0 + row) * a.tiles_n + tn, o0, o1);
+        if (m0 + row < a.M && is_mine(row)) put_pair(a.ws + (row_base + m0 + row) * a.tiles_n + tn, o0, o1);
     }
 
     // step 3.  Only correct when all tiles of the row block are in flight at once (the caller's
@@ -593,10 +606,11 @@ struct TileEpilogue {
         // visible to the whole device, and the barrier orders every wave's drain before the mark
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();                                        // (also: the strip pairs in xch are consumed)
-        unsigned *marks = a.arrive + (int64_t)rowblock * a.tiles_n;
+        unsigned *marks = SHARED ? row_marks : a.arrive + (int64_t)rowblock * a.tiles_n;
         // (withhold: host-side tests make the waits of a row block run out by keeping back the
         // mark of its first column tile)
-        if (tid == 0 && !(a.withhold && tn == 0))
+        // (a tile whose own sums are incomplete withholds its mark: all rows of the block become NaN)
+        if (tid == 0 && (!SHARED || sums_ok) && !(a.withhold && tn == 0))
             __hip_atomic_store(marks + tn, a.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (tid < 64) {
             bool ok = true;
@@ -643,7 +657,7 @@ struct TileEpilogue {
             o0 = allreduce_lanes<OpMax, TPR>(m);
             const float sden = allreduce_lanes<OpSum, TPR>(sum * fast_exp(m - exp_ref(o0)));
             if (norm() == FGE_NORM_SOFTMAX) o1 = fast_rcp(sden);
-            else if (part == 0 && tn == 0 && grow < a.M) a.aux[row_base + grow] = waited_ok ? o0 + __logf(sden) : __builtin_nanf("");
+            else if (part == 0 && tn == 0 && grow < a.M && is_mine(row)) a.aux[row_base + grow] = waited_ok ? o0 + __logf(sden) : __builtin_nanf("");
         } else if (norm() == FGE_NORM_LAYERNORM) {
             // two sweeps over the pairs: the mean first, then M2 about it
             const float inv_n = 1.0f / (float)a.N;
@@ -732,6 +746,7 @@ struct TileEpilogue {
             // (logsumexp leaves the activated values as they are: stored right away)
             float vall[MB / G][NPG][VEC], mkeep[MB / G][NPG];
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
+                if (SHARED && !(mine >> g & 1)) return;
                 static_for<0, G>([&]<int b>() __attribute__((always_inline)) { to_rows<b>(acc[g * G + b], vall[g]); });
                 const int grow0 = trow0 + g * G * 32;
                 norm_dispatch<FULL_TILE>(vall[g], grow0, mkeep[g]);
@@ -748,6 +763,7 @@ struct TileEpilogue {
             if (norm() == FGE_NORM_LOGSUMEXP) return;
             __syncthreads();
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
+                if (SHARED && !(mine >> g & 1)) return;
                 const int grow0 = trow0 + g * G * 32;
                 switch (norm()) {
                 case FGE_NORM_SOFTMAX:   finish_group<FGE_NORM_SOFTMAX>(vall[g], grow0, fin, mkeep[g], gam, bet); break;
@@ -759,6 +775,7 @@ struct TileEpilogue {
         } else {
             auto body = [&]<bool FULL>() __attribute__((always_inline)) {
                 static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
+                    if (SHARED && !(mine >> g & 1)) return;
                     float v[NPG][VEC], mkeep[NPG];
                     static_for<0, G>([&]<int b>() __attribute__((always_inline)) { to_rows<b>(acc[g * G + b], v); });
                     const int grow0 = trow0 + g * G * 32;

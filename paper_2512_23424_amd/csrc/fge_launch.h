@@ -123,18 +123,21 @@ template <> struct NarrowOut<f16_t> { typedef f16_t type; };
 // 256x256 tiles and the gated form over a short K; defined in fge_tiles_short_*.hip.
 template <typename InT> hipError_t launch_short(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 
+// ... and with shared tiles (a.share); defined in fge_tiles_shared_*.hip.
+template <typename InT> hipError_t launch_shared(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
+
 // The 256x256 tile, ordinary and cooperative launch: a kernel for every row op.  The four groups of a wave's rows
 // each pass over the code of all row ops and activations, and where one kernel holds all of them (90 to 105 KB) its
 // instructions arrive late, by an amount that any change of that code moves (bf16, ordinary: 8192 x 4096 x 4096 SiLU 212
 // to 217 us, 8192 x 64 x 4096 27.5 to 30.4 us).
 // STAGES: as for the tile kernel.  FULL (cooperative form): every tile lies inside the matrix, no guards.  All workgroups of
 // a cooperative grid must be resident at once; one that the device cannot hold that way is refused.
-template <typename InT, int STAGES>
+template <typename InT, int STAGES, bool SHARED = false>
 inline hipError_t launch_256(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     typedef typename NarrowOut<InT>::type NarrowT;
 #define FGE_256_KERNEL(OT, COOP, FULL, NORM)                                                    \
     do {                                                                                        \
-        auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, FULL, false, false, STAGES, false, NORM>; \
+        auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, FULL, false, false, STAGES, false, NORM, SHARED>; \
         if (COOP) {                                                                             \
             static const int resident = resident_workgroups(reinterpret_cast<const void *>(kern), 512); \
             if ((int)grid.x > resident) return hipErrorCooperativeLaunchTooLarge;               \
@@ -149,7 +152,7 @@ inline hipError_t launch_256(int out_dtype, dim3 grid, hipStream_t s, const Tile
 #define FGE_256_FORM(NORM)                                                                      \
     do {                                                                                        \
         if (!a.coop)                                FGE_256(false, false, NORM);                \
-        else if (a.M % 256 == 0 && a.N % 256 == 0)  FGE_256(true, true, NORM);                  \
+        else if (!SHARED && a.M % 256 == 0 && a.N % 256 == 0)  FGE_256(true, !SHARED, NORM);    \
         else                                        FGE_256(true, false, NORM);                 \
     } while (0)
     switch (a.norm) {
@@ -243,6 +246,7 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
     case TILE_256x256:
         if constexpr (BF) {
             if (short_k(a.K, sizeof(InT))) return launch_short<InT>(false, out_dtype, grid, s, a);
+            if (a.share) return launch_shared<InT>(false, out_dtype, grid, s, a);
             return launch_256<InT, 0>(out_dtype, grid, s, a);
         }
         return hipErrorInvalidValue;
@@ -271,12 +275,12 @@ inline hipError_t launch_tile_any(int tile, int out_dtype, dim3 grid, hipStream_
 
 // The gated tile kernel (16-bit and 8-bit operands), ordinary and cooperative launch: a kernel for every row op, as
 // for the plain 256x256 tile (bf16 8192 x 384 x 4096 SiLU RMSNorm 106.9 us with one for all, 101.0 so; at K = 4096 439.8 and 432.4).
-template <typename InT, int STAGES>
+template <typename InT, int STAGES, bool SHARED = false>
 inline hipError_t launch_gated_form(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     typedef typename NarrowOut<InT>::type NarrowT;
 #define FGE_GATED_KERNEL(OT, COOP, NORM)                                                        \
     do {                                                                                        \
-        auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, false, false, true, STAGES, false, NORM>; \
+        auto kern = tile_kernel<InT, OT, 256, 256, 2, 4, COOP, false, false, true, STAGES, false, NORM, SHARED>; \
         if (COOP) {                                                                             \
             static const int resident = resident_workgroups(reinterpret_cast<const void *>(kern), 512); \
             if ((int)grid.x > resident) return hipErrorCooperativeLaunchTooLarge;               \
@@ -307,12 +311,18 @@ inline hipError_t launch_gated_form(int out_dtype, dim3 grid, hipStream_t s, con
 }
 template <typename InT>
 inline hipError_t launch_gated_any(int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
+    if (a.share) return launch_shared<InT>(true, out_dtype, grid, s, a);
     return short_k(a.K, sizeof(InT)) ? launch_short<InT>(true, out_dtype, grid, s, a) : launch_gated_form<InT, 0>(out_dtype, grid, s, a);
 }
 // ... and the 256x256 tile, plain and gated, over a short K.
 template <typename InT>
 inline hipError_t launch_short_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     return gated ? launch_gated_form<InT, 2>(out_dtype, grid, s, a) : launch_256<InT, 2>(out_dtype, grid, s, a);
+}
+// ... and with shared tiles.
+template <typename InT>
+inline hipError_t launch_shared_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
+    return gated ? launch_gated_form<InT, 0, true>(out_dtype, grid, s, a) : launch_256<InT, 0, true>(out_dtype, grid, s, a);
 }
 // The half-tile configurations (TILE_128x256, TILE_256x128), ordinary or cooperative launch;
 // defined in fge_tiles_half.hip.

@@ -29,12 +29,13 @@ namespace fge {
 // robin, so ids congruent mod 8 share an L2; give each XCD one contiguous range of logical
 // tiles, then walk that range in groups of `group_m` row tiles, column-tile major inside a
 // group, so the tiles resident on one XCD at a time share few X and W panels.
-__device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, int group_m,
-                                            int &tm, int &tn) {
-    const int nt = tiles_m * tiles_n;
-    const int q = nt >> 3, rem = nt & 7;
+__device__ __forceinline__ int xcd_order(int bid, int count) {
+    const int q = count >> 3, rem = count & 7;
     const int xcd = bid & 7, slot = bid >> 3;
-    const int logical = xcd * q + (xcd < rem ? xcd : rem) + slot;
+    return xcd * q + (xcd < rem ? xcd : rem) + slot;
+}
+__device__ __forceinline__ void tile_coords(int logical, int tiles_m, int tiles_n, int group_m,
+                                            int &tm, int &tn) {
     const int per_group = group_m * tiles_n;
     const int g = logical / per_group;
     const int first_m = g * group_m;
@@ -110,8 +111,11 @@ template <> struct Mma<float> {
 // STAGES: 0 for the tile's usual number of stage buffers, else that many (see DEEP below).
 // ANY: N and the rows of the result are any number of elements (see TileEpilogue).
 // NORM_CT (>= 0): the row op, fixed at compile time.
+// SHARED: some of the launch's tiles are shared between workgroups (see the end of the quadrants' loop).  A kernel of its
+// own: the registers it takes cost launches that share nothing up to 1.5 % (8192 x 4096 x 4096, RMSNorm: gated 451.7 -> 457.7, E4M3 123.1 ->
+// 125.0 us).
 template <typename InT, typename OutT, int BM, int BN, int WAVES_M, int WAVES_N, bool COOP = false, bool FULL = false,
-          bool SPLIT = false, bool GATED = false, int STAGES = 0, bool ANY = false, int NORM_CT = -1>
+          bool SPLIT = false, bool GATED = false, int STAGES = 0, bool ANY = false, int NORM_CT = -1, bool SHARED = false>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, (BM * BN <= 64 * 128 ? 2 : 1))
 void tile_kernel(const TileArgs a) {
     static_assert(!SPLIT || sizeof(InT) == 4, "only fp32 operands are split");
@@ -150,6 +154,7 @@ void tile_kernel(const TileArgs a) {
     constexpr bool DEEP = STAGES == 3 || (STAGES == 0 && BM == 64 && BN == 64 && !SPLIT && !COOP);
     // QUAD: the mainloop by output quadrants (see there); A buffers first, then B buffers, so that
     // every fragment read is a lane address plus an immediate offset
+    static_assert(!SHARED || (BM == 256 && BN == 256 && STAGES == 0 && !FULL), "shared tiles: the quadrants' loop");
     constexpr bool QUAD = BM == 256 && BN == 256 && NT == 512 && MB == 4 && NB == 2 && !SPLIT && STAGES == 0;
     constexpr int A_STEP = QUAD ? BM * ROWB : STAGE, B_STEP = QUAD ? BN * ROWB : STAGE;    // bytes between stage buffers
     constexpr int B_AT = QUAD ? 2 * BM * ROWB : BM * ROWB;                                 // first B buffer
@@ -175,14 +180,23 @@ void tile_kernel(const TileArgs a) {
     const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
     const int h = lane >> 5, l32 = lane & 31;
     int tm, tn, z, rowblock;
+    // Shared tiles (QUAD): this workgroup's slice of K, the tile's place among the shared ones (-1: not shared)
+    // and its row block's
+    [[maybe_unused]] int slice = 0, shared_at = -1, shared_at_rb = 0;
     if constexpr (COOP) {
         constexpr int PW = 4;
-        const int G = gridDim.x, q = G >> 3, rem = G & 7;
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        const int s = xcd * q + (xcd < rem ? xcd : rem) + slot;
+        const int G = gridDim.x;
+        int s = xcd_order(blockIdx.x, G);
         const int rpr = G / a.tiles_n;                                   // row blocks per round
         const int R = min(rpr, a.tiles_m * a.batch - round * rpr);       // ... in this round
-        if (R <= 0 || s >= R * a.tiles_n) break;
+        if (R <= 0) break;
+        if constexpr (SHARED) {
+            if (round == a.share_from && s < R * a.tiles_n * a.share) {
+                slice = s / (R * a.tiles_n);
+                shared_at = s -= slice * R * a.tiles_n;
+            }
+        }
+        if (s >= R * a.tiles_n) break;
         const int full = a.tiles_n / PW, panel = s / (R * PW);
         int rb;
         if (panel < full) {
@@ -195,6 +209,7 @@ void tile_kernel(const TileArgs a) {
             tn = full * PW + w % wd;
         }
         rowblock = round * rpr + rb;
+        if constexpr (SHARED) shared_at_rb = rb;
         z = rowblock / a.tiles_m;
         tm = rowblock - z * a.tiles_m;
         // Staggered start: the row blocks of the first round begin a little apart (all column
@@ -206,14 +221,31 @@ void tile_kernel(const TileArgs a) {
         }
     } else {
         if (round > 0) break;
-        tile_coords(blockIdx.x, a.tiles_m, a.tiles_n, a.group_m, tm, tn);
+        int logical;
+        if constexpr (SHARED) {
+            const int left = a.tiles_m * a.tiles_n - a.share_from, e = (int)blockIdx.x - a.share_from;
+            if (e < 0) {
+                logical = xcd_order(blockIdx.x, a.share_from);
+            } else {
+                const int g = e / left;
+                slice = g;
+                shared_at = xcd_order(e - g * left, left);
+                logical = a.share_from + shared_at;
+            }
+        } else {
+            logical = xcd_order(blockIdx.x, a.tiles_m * a.tiles_n);
+        }
+        tile_coords(logical, a.tiles_m, a.tiles_n, a.group_m, tm, tn);
         z = blockIdx.z;
         rowblock = z * a.tiles_m + tm;
     }
     const int m0 = tm * BM, n0 = tn * BNO;
+    // k range of this workgroup: all of K, or its slice (whole K tiles; the last one takes the rest)
+    const int k_from = SHARED && shared_at >= 0 ? slice * a.share_k : 0;
+    const int K = SHARED && shared_at >= 0 ? min(a.K - k_from, a.share_k) : a.K;
 
-    const InT *X = reinterpret_cast<const InT *>(a.X) + (int64_t)z * a.bsx;
-    const InT *W = reinterpret_cast<const InT *>(a.W) + (int64_t)z * a.bsw;
+    const InT *X = reinterpret_cast<const InT *>(a.X) + (int64_t)z * a.bsx + k_from;
+    const InT *W = reinterpret_cast<const InT *>(a.W) + (int64_t)z * a.bsw + k_from;
     OutT *out = reinterpret_cast<OutT *>(a.out) + (int64_t)z * a.bso;
 
     // ---------------- global -> LDS staging plan
@@ -240,7 +272,7 @@ void tile_kernel(const TileArgs a) {
     const unsigned char *Xt = reinterpret_cast<const unsigned char *>(X + (int64_t)m0 * a.ldx) - PRE;
     const unsigned char *W1t = reinterpret_cast<const unsigned char *>(W + (int64_t)n0 * a.ldw) - PRE;
     const unsigned char *W2t = GATED ? reinterpret_cast<const unsigned char *>(
-                                           reinterpret_cast<const InT *>(a.W2) + (int64_t)z * a.bsw + (int64_t)n0 * a.ldw) - PRE : W1t;
+                                           reinterpret_cast<const InT *>(a.W2) + (int64_t)z * a.bsw + k_from + (int64_t)n0 * a.ldw) - PRE : W1t;
     const unsigned char *Wt = second ? W2t : W1t;
     // A copy's global address is a scalar base (first row of the tile, current k) plus the lane's
     // byte offset from it, which does not change along K: 32 bits (the host keeps tiles whose
@@ -311,6 +343,10 @@ void tile_kernel(const TileArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) fsw[u] = ((2 * u + h) ^ swz(l32)) << 4;
 
+    unsigned mine = ~0u;                              // the groups of a wave's rows that this workgroup finishes
+    bool sums_ok = true;                              // (a shared tile whose other slices never came: false)
+    [[maybe_unused]] unsigned *row_marks = nullptr;   // cooperative form: the marks to leave and wait for
+    if constexpr (SHARED) row_marks = a.arrive + (int64_t)rowblock * a.tiles_n;
     floatx16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -514,8 +550,8 @@ void tile_kernel(const TileArgs a) {
     // under a lane mask: all lanes for a whole tile, the lanes whose chunk lies inside K for the partial
     // one (the others' LDS chunks are zeroed by hand), none past the last tile - the instruction
     // is still issued and counted then, so the waits in front of the barriers hold for every tile.
-    const int KF = a.K / BK, KT = (a.K + BK - 1) / BK;
-    const uint64_t part[2] = {__ballot(KF * BK + gcA[0] * CW < a.K), __ballot(KF * BK + gcA[1] * CW < a.K)};
+    const int KF = K / BK, KT = (K + BK - 1) / BK;
+    const uint64_t part[2] = {__ballot(KF * BK + gcA[0] * CW < K), __ballot(KF * BK + gcA[1] * CW < K)};
     auto lanes = [&](int kt, int i) __attribute__((always_inline)) -> uint64_t { return kt < KF ? ~0ull : kt < KT ? part[i] : 0ull; };
     // copies of half `half` of the A panel / of column block `col` of the B panel of tile kt
     auto copy_a = [&](int par, int half, int kt, int i) __attribute__((always_inline)) {
@@ -529,7 +565,7 @@ void tile_kernel(const TileArgs a) {
         unsigned char *dst = smem + wave_id * 2048 + lane * 16;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            if (KF * BK + gcA[i] * CW >= a.K)
+            if (KF * BK + gcA[i] * CW >= K)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
                     *reinterpret_cast<u32x4 *>(dst + par * A_STEP + half * 128 * ROWB + i * 1024) = none;
@@ -627,6 +663,75 @@ void tile_kernel(const TileArgs a) {
         if (++kt == KT) break;
     }
     __syncthreads();                                  // the epilogue reuses the panel memory
+    // ---------------- shared tiles: the slices' sums meet.  The tiles of a launch that do not fill the chip once
+    // more (its last round) are each multiplied by S = `share` workgroups, a slice of K each (S = 2 or 4).  Of the four groups
+    // of 32 rows every wave has summed, slice s keeps group s (with two slices s and s + 2): it leaves the other groups' sums in the workspace, in the order the lanes hold them (every access of a
+    // wave is 1 KB in one piece), adds what the other slices left for its own, in the order of the slices, and takes
+    // only those rows through the epilogue - which is thereby shared out as well.  Stores and loads of the
+    // sums and of the marks are device-scope (the sc1 bit), as in the exchange of row statistics, and like that exchange this one
+    // needs the launch's last workgroups (no more of them than CUs) in flight at once and has a bounded wait.
+    // (A single workgroup that adds all slices' sums and finishes the tile alone waits 8 us for each 256 KB: 4173 x 3192 x 512
+    // 62 us in two slices and in three, 68 in four; shared out 50, 47 and 39.)
+    if constexpr (SHARED) if (shared_at >= 0) {
+        constexpr int DEVICE = 16, GROUP_BYTES = BM * BN * 4 / MB;       // sc1
+        const int S = a.share;
+        const int at = wave * (NB * 4096) + lane * 16;
+        auto sums = [&](int sl, int g) __attribute__((always_inline)) {
+            return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char *>(a.part) + (int64_t)((shared_at * S + sl) * MB + g) * GROUP_BYTES,
+                                                     0, GROUP_BYTES, 0x00027000);
+        };
+        mine = S == 2 ? 5u << slice : 1u << slice;
+        static_for<0, MB>([&]<int g>() __attribute__((always_inline)) {
+            if (mine >> g & 1) return;
+            const auto dst = sums(slice, g);
+#pragma unroll
+            for (int k = 0; k < NB * 4; ++k) {
+                const floatx16 &v = acc[g][k / 4];
+                const int r = k % 4 * 4;
+                const u32x4 w = {as_u32(v[r]), as_u32(v[r + 1]), as_u32(v[r + 2]), as_u32(v[r + 3])};
+                __builtin_amdgcn_raw_buffer_store_b128(w, dst, at, k * 1024, DEVICE);
+            }
+        });
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        unsigned *marks = a.part_marks + shared_at * S;
+        if (tid == 0 && !(a.withhold && slice == 1 && shared_at == 0))
+            __hip_atomic_store(marks + slice, a.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid < 64) {
+            bool ok = true;
+            if (tid < S) {
+                unsigned spins = 0;
+                while (__hip_atomic_load(marks + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.gen) {
+                    __builtin_amdgcn_s_sleep(2);
+                    if (++spins > a.spin_limit) { ok = false; break; }
+                }
+            }
+            const bool all_ok = __all(ok);
+            if (!ok) *a.fault = 1;
+            if (tid == 0) xch[0].x = all_ok ? 0.0f : 1.0f;
+        }
+        __syncthreads();
+        sums_ok = xch[0].x == 0.0f;
+        for (int sl = 0; sl < S; ++sl) {
+            if (sl == slice) continue;
+            static_for<0, MB>([&]<int g>() __attribute__((always_inline)) {
+                if (!(mine >> g & 1)) return;
+                const auto src = sums(sl, g);
+#pragma unroll
+                for (int k = 0; k < NB * 4; ++k) {
+                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(src, at, k * 1024, DEVICE);
+                    floatx16 &v = acc[g][k / 4];
+                    const int r = k % 4 * 4;
+                    v[r] += as_f32(w.x); v[r + 1] += as_f32(w.y); v[r + 2] += as_f32(w.z); v[r + 3] += as_f32(w.w);
+                }
+            });
+        }
+        __syncthreads();                              // xch has been read
+        if constexpr (COOP) {                         // the row block's marks: the same slice of its other tiles
+            const int rb_slice = (shared_at_rb * S + slice) * a.tiles_n;
+            row_marks = a.share_arrive + rb_slice;
+        }
+    }
     } else if constexpr (KSHARE) {
     // ---------------- mainloop, small tiles with a long K: waves share out K, copies run three K tiles ahead, fragments one
     // What bounds these tiles is LDS: every operand value is read once per wave that multiplies it.  So the
@@ -902,25 +1007,46 @@ void tile_kernel(const TileArgs a) {
         floatx16 gated[MB][1];
         dispatch_act(a.act, [&]<int ACT>() __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
+            for (int i = 0; i < MB; ++i) {
+                if (SHARED && !COOP && !(mine >> i & 1)) continue;      // (in the cooperative form the test costs 128 spilled registers)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     gated[i][0][r] = activate<ACT>(scale * acc[i][0][r] + bias1, a.lo, a.hi) * (scale * acc[i][1][r] + bias2);
+            }
         });
         TileArgs ag = a;
         ag.act = FGE_ACT_NONE; ag.alpha = 1.0f; ag.post = 1.0f; ag.b = nullptr;
-        using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false, false, -1, NORM_CT>;
+        using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false, false, -1, NORM_CT, false, false, false, SHARED>;
         static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= NST * STAGE, "store patches fit the panels");
         Epi epi(ag, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
                 wave_n, lane);
+        if constexpr (SHARED) { epi.sums_ok = sums_ok; epi.mine = mine; epi.row_marks = row_marks; }
         epi.template tile<NT>(gated, wave_m * WTM, rowblock, tid);
     } else {
-        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, NORM_CT, false, false, ANY>;
+        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, NORM_CT, false, false, ANY, SHARED>;
         constexpr int PATCH_BYTES = KSHARE ? OWN : Epi::PATCH_FLOATS * 4;
         static_assert(WAVES_M * WAVES_N * PATCH_BYTES <= NST * STAGE && Epi::PATCH_FLOATS * 4 <= PATCH_BYTES, "store patches fit the panels");
         Epi epi(a, out, xch, reinterpret_cast<float *>(smem + wave * PATCH_BYTES), BM, z, m0, n0, tn,
                 wave_n, lane);
+        if constexpr (SHARED) { epi.sums_ok = sums_ok; epi.mine = mine; epi.row_marks = row_marks; }
         epi.template tile<NT>(acc, wave_m * WTM, rowblock, tid);
+    }
+    if constexpr (SHARED && !COOP) {
+        if (!sums_ok) {                               // incomplete sums: NaN in their place (COOP: see arrive_and_wait)
+            const float nan = __builtin_nanf("");
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            for (int i = tid; i < BM * BNO; i += NT) {
+                const int row = m0 + i / BNO, col = n0 + i % BNO;
+                if ((mine >> (i / BNO % WTM / 32) & 1) && row < a.M && col < a.N) Store<OutT>::put(out + (int64_t)row * a.ldo + col, nan);
+            }
+            for (int i = tid; i < BM * WAVES_N; i += NT) {
+                const int row = m0 + i / WAVES_N;
+                if (a.norm == FGE_NORM_NONE || row >= a.M || !(mine >> (i / WAVES_N % WTM / 32) & 1)) continue;
+                if (a.tiles_n > 1)                        a.ws[(int64_t)row * (a.tiles_n * WAVES_N) + tn * WAVES_N + i % WAVES_N] = make_float2(nan, nan);
+                else if (a.norm == FGE_NORM_LOGSUMEXP)    a.aux[row] = nan;
+            }
+        }
     }
     if constexpr (COOP) __syncthreads();             // patches are panel memory of the next tile
     }

@@ -1,0 +1,144 @@
+"""Tiles shared between workgroups (the last, partial round of 256x256 and gated tiles; all tiles of a problem that has
+few of them): each workgroup multiplies a slice of K, the sums meet in the workspace, and every slice finishes a
+part of the rows.  Slices that end inside a K tile, two and four of them, ragged rows and columns, whole rounds in front,
+every row op in each of its forms, and the ways around sharing."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2512_23424_amd import binding as B
+from paper_2512_23424_amd import inputs as I
+from tests import _harness as H
+
+pytestmark = pytest.mark.gpu
+FLAG_256 = (3 + 1) << 8                     # FGE_FLAG_TILE(FGE_TILE_256x256)
+NORMS = [I.NORM_NONE, I.NORM_SOFTMAX, I.NORM_LAYERNORM, I.NORM_RMSNORM, I.NORM_LOGSUMEXP]
+
+
+def _workload(dt, M, K, N, act, norm, odt=None):
+    f8 = dt == I.F8E4M3
+    return I.Workload(name=f"shared{act}{norm}", M=M, K=K, N=N, in_dtype=dt, out_dtype=odt or (I.BF16 if f8 else dt), act=act, norm=norm,
+                      alpha=K ** -0.5 if f8 else 0.5, post_scale=1.5, clamp_lo=-1.0, clamp_hi=2.0, eps=1e-5,
+                      dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, 1.0 if f8 else K ** -0.5), "b": ("uniform", -0.5, 0.5),
+                            "gamma": ("normal", 1.0, 0.1), "beta": ("normal", 0.0, 0.1)})
+
+
+def _shares(w, d, flags):
+    """The plan of a call without row op or of rows in one piece shares tiles exactly when it names a fault word."""
+    p = B.make_params(d["X"], d["W"], torch.empty(w.M, w.N, dtype=H.tdtype(w.out_dtype), device="cuda"), flags=flags)
+    return B.fge_fault_word_offset(w.act, w.norm, p) is not None
+
+
+def _gated(w, t, d, flags=0, ws_bytes=None):
+    f = {k: I.as_f64(v) for k, v in t.items()}
+    ref, raux = O.gated_chain(f["X"], f["W"], f["W2"], f["b"], f["b2"], f["gamma"], f["beta"], alpha=w.alpha, post_scale=w.post_scale,
+                              act=w.act, clamp_lo=w.clamp_lo, clamp_hi=w.clamp_hi, norm=w.norm, eps=w.eps)
+    out = torch.full((w.M, w.N), float("nan"), dtype=H.tdtype(w.out_dtype), device="cuda")
+    aux = torch.full((w.M,), float("nan"), device="cuda") if w.norm == I.NORM_LOGSUMEXP else None
+    p = B.make_params(d["X"], d["W"], out, alpha=w.alpha, post_scale=w.post_scale, clamp_lo=w.clamp_lo, clamp_hi=w.clamp_hi, eps=w.eps,
+                      gamma=d["gamma"], beta=d["beta"], aux_out=aux, flags=flags)
+    n = ws_bytes or B.fge_gated_workspace_bytes(True, w.act, w.norm, p)
+    raw = torch.full((n + 1024,), 0xA5, dtype=torch.uint8, device="cuda")
+    p.workspace, p.workspace_bytes = raw.data_ptr(), n
+    B.fused_gated_gemm_epilogue(d["X"], d["W"], d["W2"], d["b"], d["b2"], w.act, w.norm, p, out)
+    torch.cuda.synchronize()
+    assert bool((raw[n:] == 0xA5).all()), "the call wrote past the end of its workspace"
+    return H.to_host_f64(out), None if aux is None else H.to_host_f64(aux), ref, raux
+
+
+@pytest.mark.parametrize("dt,out", [(I.BF16, I.F32), (I.F16, I.F32), (I.F8E4M3, I.F32)])
+@pytest.mark.parametrize("gated", [False, True])
+def test_slices_give_exact_sums(dt, out, gated):
+    """Small integers: the sums are exact whatever their order.  4 to 9 tiles, KT K tiles of which the last may be partial."""
+    unit, tile_k = (16, 128) if dt == I.F8E4M3 else (8, 64)
+    for K in (10 * tile_k, 11 * tile_k - unit, 12 * tile_k + unit, 16 * tile_k, 18 * tile_k + unit):
+        for M, N in ((260, 264), (530, 520)):
+            w = I.Workload(name="shared", M=M, K=K, N=N, in_dtype=dt, out_dtype=out,
+                           dist={"X": ("int", -2, 2), "W": ("int", -2, 2), "b": ("int", -3, 3)})
+            t = I.generate_gated(w) if gated else I.generate(w)
+            d = {k: H.to_device(v) for k, v in t.items()}
+            if gated:
+                got, _, ref, _ = _gated(w, t, d)
+            else:
+                assert _shares(w, d, FLAG_256) and not _shares(w, d, FLAG_256 | B.FLAG_NO_SPLIT_K)
+                ref, _ = H.oracle_chain(w, t)
+                got, _ = H.run_gpu(w, t, "fused", dev=d, flags=FLAG_256)
+            assert np.array_equal(got, ref), f"K={K} M={M} N={N}: {int((got != ref).sum())} mismatches"
+
+
+@pytest.mark.parametrize("M,N", [(4300, 4096), (5000, 1000)])       # 16 tiles left (four slices); no whole round, 80 tiles (two slices)
+@pytest.mark.parametrize("norm", NORMS)
+def test_whole_rounds_in_front(norm, M, N):
+    w = _workload(I.BF16, M, 2056, N, I.ACT_SILU, norm)
+    t = I.generate(w)
+    ref, raux = H.oracle_chain(w, t)
+    for flags in (FLAG_256, FLAG_256 | B.FLAG_NO_SPLIT_K):
+        got, gaux = H.run_gpu(w, t, "fused", flags=flags)
+        H.check(w, got, gaux, ref, raux, f"flags={flags}")
+
+
+@pytest.mark.parametrize("dt", [I.BF16, I.F16, I.F8E4M3])
+@pytest.mark.parametrize("norm", NORMS)
+def test_all_tiles_shared(dt, norm):
+    """Few tiles over a long K: the row op in the tile (one column tile) or in a kernel over fp32 rows."""
+    for M, K, N in ((300, 4104, 1400), (140, 8200, 2104)) if dt != I.F8E4M3 else ((300, 8208, 1400),):
+        w = _workload(dt, M, K, N, I.ACT_SILU, norm)
+        t = I.generate_gated(w)
+        d = {k: H.to_device(v) for k, v in t.items()}
+        got, gaux, ref, raux = _gated(w, t, d)
+        H.check(w, got, gaux, ref, raux, "gated")
+        got, gaux, _, _ = _gated(w, t, d, flags=B.FLAG_NO_SPLIT_K)
+        H.check(w, got, gaux, ref, raux, "gated, not shared")
+    for M, K, N in ((520, 8200, 3080), (2100, 640, 248)):
+        if dt == I.F8E4M3:
+            K *= 2
+        w = _workload(dt, M, K, N, I.ACT_GELU_ERF, norm, odt=None if N > 256 else I.F32)
+        t = I.generate(w)
+        ref, raux = H.oracle_chain(w, t)
+        got, gaux = H.run_gpu(w, t, "fused", flags=0 if N > 256 else FLAG_256)
+        H.check(w, got, gaux, ref, raux, "plain")
+
+
+@pytest.mark.parametrize("norm", [I.NORM_NONE, I.NORM_RMSNORM])
+def test_an_expired_wait_leaves_nan(norm):
+    """Slice 1 of the first shared tile (and, for split rows, every first column tile) keeps its mark back and waits end after
+    one poll: NaN, never partial sums; all else is right."""
+    w = _workload(I.BF16, 4300, 1032, 4096, I.ACT_RELU, norm)
+    t = I.generate(w)
+    ref, _ = H.oracle_chain(w, t)
+    got, _ = H.run_gpu(w, t, "fused", flags=FLAG_256 | B.FLAG_TEST_EXPIRE_WAIT, expect_fault=True)
+    ok = np.isfinite(got)
+    assert not ok.all()
+    den = np.maximum(np.abs(ref), H.C.row_floor(ref))
+    assert (np.abs(got - ref)[ok] / den[ok]).max(initial=0.0) <= 2e-2
+    got, _ = H.run_gpu(w, t, "fused", flags=FLAG_256)
+    H.check(w, got, None, ref, None, "after an expired wait")
+
+
+def test_without_the_room_and_under_capture():
+    """A workspace that holds the statistics alone, and a captured stream, run without sharing."""
+    w = _workload(I.BF16, 300, 4104, 1400, I.ACT_SILU, I.NORM_RMSNORM)
+    t = I.generate_gated(w)
+    d = {k: H.to_device(v) for k, v in t.items()}
+    got, _, ref, _ = _gated(w, t, d, ws_bytes=1 << 17)
+    H.check(w, got, None, ref, None, "small workspace")
+    out = torch.full((w.M, w.N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    p = B.make_params(d["X"], d["W"], out, alpha=w.alpha, post_scale=w.post_scale, eps=w.eps, gamma=d["gamma"], beta=d["beta"])
+    n = B.fge_gated_workspace_bytes(True, w.act, w.norm, p)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    p.workspace, p.workspace_bytes = ws.data_ptr(), n
+    call = lambda: B.fused_gated_gemm_epilogue(d["X"], d["W"], d["W2"], d["b"], d["b2"], w.act, w.norm, p, out)
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(3):
+        out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        H.check(w, H.to_host_f64(out), None, ref, None, "replay")
+        call()
+        torch.cuda.synchronize()
+        H.check(w, H.to_host_f64(out), None, ref, None, "eager")
