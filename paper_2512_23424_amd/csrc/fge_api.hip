@@ -763,6 +763,37 @@ int launch_tiles(const TileArgs &a, const fge_params *p, const Plan &pl, hipStre
     return hip_status(e);
 }
 
+// Results of any width in 256x256 tiles (whose launches ask for no room to share tiles in): the columns whose tiles would be left over
+// behind whole rounds of the chip are a launch of their own, in 128x128 tiles, at most one per CU.  That takes
+// half of a round's time (bf16, us: 2048 x 4096 x 50257 logsumexp, 40 of 1576 tiles, 745.6 -> 718.7; 1570 x 3352 x 20221
+// 259.0 -> 239.9; E4M3 2048 x 4096 x 50257 367.7 -> 356.7; 2048 x 1024 x 50257 267.3 -> 263.5); a shorter K keeps one launch.  Both tiles have strips of 64 columns, so the row statistics do not tell them apart.
+int first_tail_column(const fge_params *p, const Plan &pl) {
+    if (pl.tile != TILE_256x256 || pl.pr.batch != 1 || !long_k(pl.pr.K, esize(p->in_dtype)) || forced_tile(p) >= 0) return 0;
+    const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
+    const int whole = (int)(tiles / num_cu() * num_cu() / pl.tiles_m);             // column tiles of the whole rounds
+    if (whole == 0 || whole == pl.tiles_n) return 0;
+    const int64_t tail = (int64_t)((pl.pr.M + 127) / 128) * ((pl.pr.N - whole * 256 + 127) / 128);
+    return tail <= num_cu() ? whole * 256 : 0;
+}
+
+int launch_any_width(const void *X, const void *W, const float *b, int act, int norm, const fge_params *p, Plan &pl, void *out, hipStream_t s) {
+    const int at = first_tail_column(p, pl);
+    if (at == 0) return launch_tiles(tile_args(X, W, b, act, norm, p, pl, out), p, pl, s);
+    fge_params q = *p, r = *p;
+    q.N = at;
+    r.N = p->N - at;
+    Plan pq = make_plan(&q, norm, true, TILE_256x256), pr = make_plan(&r, norm, true, TILE_128x128_S3);
+    TileArgs a = tile_args(X, W, b, act, norm, &q, pq, out);
+    TileArgs c = tile_args(X, static_cast<const char *>(W) + (int64_t)at * pl.pr.ldw * (int64_t)esize(p->in_dtype), b ? b + at : nullptr, act, norm,
+                           &r, pr, static_cast<char *>(out) + (int64_t)at * (int64_t)esize(p->out_dtype));
+    if (norm != FGE_NORM_NONE) {
+        a.strips = c.strips = pl.strips = pq.tiles_n * pq.waves_n + pr.tiles_n * pr.waves_n;     // (no more than before)
+        c.ws += pq.tiles_n * pq.waves_n;
+    }
+    const int rc = launch_tiles(a, &q, pq, s);
+    return rc ? rc : launch_tiles(c, &r, pr, s);
+}
+
 RowArgs row_args(const void *in, void *out, int act, int norm, const fge_params *p, const Plan &pl) {
     RowArgs r{};
     r.in = in; r.out = out; r.gamma = p->gamma; r.beta = p->beta; r.aux = p->aux_out;
@@ -1019,8 +1050,8 @@ int run_parked(const void *X, const void *W, const float *b, int act, int norm, 
     q.workspace = ws + rp.off_parked;
     q.workspace_bytes = p->workspace_bytes - rp.off_parked;
     const OutRows scope(OUT_PADDED);
-    const Plan pl = plan_parked(&q, norm);
-    const int rc = launch_tiles(tile_args(X, W, b, act, norm, &q, pl, ws + rp.off_b), &q, pl, s);
+    Plan pl = plan_parked(&q, norm);
+    const int rc = launch_any_width(X, W, b, act, norm, &q, pl, ws + rp.off_b, s);
     if (rc) return rc;
     FinishAnyArgs f{row_args(ws + rp.off_b, out, act, norm, &q, pl), q.ldo};
     f.r.M = p->M; f.r.batch = p->batch; f.r.ldo = p->ldo; f.r.bso = p->batch > 1 ? p->batch_stride_o : 0;
@@ -1139,6 +1170,12 @@ int do_fused_tiles(const void *X, const void *W, const float *b, int act, int no
     if (pl.split) {
         if (pl.strips > MAX_SPLIT) return FGE_ERR_UNSUPPORTED;
         if (!p->workspace || p->workspace_bytes < split_rows_workspace(p, norm)) return FGE_ERR_WORKSPACE;
+    }
+    if (g_out_rows == OUT_ANY) {
+        Plan any = pl;
+        rc = launch_any_width(X, W, b, act, norm, p, any, out, s);
+        if (plan_out) *plan_out = any;
+        return rc;
     }
     const Share sh = one_call && !captured ? share_in(p, pl) : Share{};
     rc = launch_tiles(tile_args(X, W, b, act, norm, p, pl, out, sh), p, pl, s, sh);

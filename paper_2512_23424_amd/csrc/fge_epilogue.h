@@ -57,6 +57,7 @@ struct TileArgs {
     int share, share_from, share_k;
     float *part;                // [shared tiles][share][256 * 256] partial sums
     unsigned *part_marks;       // [shared tiles][share]: gen once they are there
+    int strips;                 // ANY: strip pairs per row in ws where that is not tiles_n * waves across (0: it is)
     unsigned *share_arrive;     // cooperative grid: [row blocks of that round][share][tiles_n] arrival marks
 };
 
@@ -165,7 +166,7 @@ struct TileEpilogue {
             rsel[0] = pcol;                  rsel[1] = pcol + G4STEP;
         }
         xch_par = 0;
-        whole_row = a.tiles_n == 1;
+        whole_row = a.tiles_n == 1 && !(ANY && a.strips);
         // (not in the cooperative form, whose registers are too scarce for two more variants)
         bounded = !COOP && a.act == FGE_ACT_CLAMP && a.hi - a.lo <= 64.0f;
         bool far = false;
@@ -209,7 +210,7 @@ struct TileEpilogue {
         } else {
             const int grow = m0 + qrow(grow0, q);
             if (sub == 0 && (FULL || grow < a.M))
-                a.ws[(row_base + grow) * (a.tiles_n * WAVES_N) + tn * WAVES_N + wave_n] = make_float2(s0, s1);
+                a.ws[(row_base + grow) * (ANY && a.strips ? a.strips : a.tiles_n * WAVES_N) + tn * WAVES_N + wave_n] = make_float2(s0, s1);
         }
     }
     // Cooperative form: the pairs travel between workgroups of one launch, possibly on different

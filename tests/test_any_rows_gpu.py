@@ -138,3 +138,19 @@ def test_masked_columns_contribute_nothing(M, norm):
     else:
         assert torch.allclose(out.double().cpu(), torch.softmax(ref, 1), rtol=2 ** -7, atol=1e-9)   # one bf16 rounding
         assert bool((out[:, 64:330] == 0).all())
+
+
+@pytest.mark.parametrize("dt", [I.BF16, I.F8E4M3])
+@pytest.mark.parametrize("norm", [I.NORM_NONE, I.NORM_SOFTMAX, I.NORM_LAYERNORM, I.NORM_RMSNORM, I.NORM_LOGSUMEXP])
+def test_columns_behind_whole_rounds_are_a_launch_of_their_own(dt, norm):
+    """17 x 17 tiles of 256x256: 15 column tiles are a whole round, the other columns (259, the last ones alone in their tile)
+    run in 128x128 tiles; the statistics of a row come from both."""
+    K = 1032 if dt == I.BF16 else 2064
+    w = I.Workload(name=f"tail{norm}", M=4300, K=K, N=4099, in_dtype=dt, out_dtype=I.BF16, act=I.ACT_SILU, norm=norm, eps=1e-5,
+                   alpha=1.0 if dt == I.BF16 else K ** -0.5,
+                   dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, K ** -0.5 if dt == I.BF16 else 1.0), "b": ("uniform", -0.5, 0.5),
+                         "gamma": ("normal", 1.0, 0.1), "beta": ("normal", 0.0, 0.1)})
+    t = I.generate(w)
+    got, gaux = H.run_gpu(w, t, "fused")
+    ref, raux = H.oracle_chain(w, t)
+    H.check(w, got, gaux, ref, raux, "columns behind whole rounds")
