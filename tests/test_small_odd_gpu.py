@@ -1,0 +1,35 @@
+"""Small products of odd extents (element-granular product: 32x32 tiles, 128 k at a time, shared out by four waves): exact integers
+around the K tile and the waves' parts of it, around the output tile, and with strides."""
+import numpy as np
+import pytest
+
+from paper_2512_23424_amd import binding as B
+from paper_2512_23424_amd import inputs as I
+from tests import _harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dt", [I.F32, I.BF16, I.F16, I.F8E4M3])
+def test_exact_sums(dt):
+    for M, N in ((1, 33), (31, 31), (33, 65), (70, 97)):
+        for K in (1, 3, 31, 33, 127, 129, 161, 255, 257, 429):
+            w = I.Workload(name="odd", M=M, K=K, N=N, in_dtype=dt, out_dtype=I.F32, act=I.ACT_RELU,
+                           dist={"X": ("int", -2, 2), "W": ("int", -2, 2), "b": ("int", -3, 3)})
+            t = I.generate(w)
+            ref, _ = H.oracle_chain(w, t)
+            got, _ = H.run_gpu(w, t, "fused")
+            assert np.array_equal(got, ref), f"K={K} M={M} N={N}: {int((got != ref).sum())} mismatches"
+
+
+@pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LAYERNORM])
+def test_fp32_precision(norm):
+    """fp32 products and sums: the gate of the fp32 instruction."""
+    w = I.Workload(name="odd32", M=365, K=429, N=33, act=I.ACT_SILU, norm=norm, eps=1e-5,
+                   dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, 429 ** -0.5), "b": ("uniform", -0.5, 0.5),
+                         "gamma": ("normal", 1.0, 0.1), "beta": ("normal", 0.0, 0.1)})
+    t = I.generate(w)
+    ref, raux = H.oracle_chain(w, t)
+    got, gaux = H.run_gpu(w, t, "fused")
+    assert B.fge_tile_name(True, w.act, norm, B.make_params(*(H.to_device(t[k]) for k in "XW"), H.to_device(got.astype(np.float32)))) == "generic32x32_scalar"
+    assert H.C.max_rel_err(got, ref) <= 2e-5
