@@ -423,6 +423,7 @@ Share plan_share(const fge_params *p, const Plan &pl) {
     const bool gated = pl.tile == TILE_GATED;
     if (pl.generic || p->in_dtype == FGE_F32 || (pl.tile != TILE_256x256 && !gated) || pl.pr.batch != 1) return sh;
     if (g_out_rows != OUT_ALIGNED || short_k(pl.pr.K, is)) return sh;             // (no room is asked for there; another mainloop)
+    if (gated && pl.coop) return sh;                       // (the cooperative gated form has no kernels that share: see launch_shared_any)
     if (p->flags & (FGE_FLAG_NO_SPLIT_K | FGE_FLAG_TWO_PASS)) return sh;
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
     const int capacity = pl.coop ? num_cu() / pl.tiles_n * pl.tiles_n : num_cu();
