@@ -292,6 +292,18 @@ bool prefer_shared(const Problem &pr, int in_dtype) {
            (int64_t)pr.K * (int64_t)esize(in_dtype) >= 8192;
 }
 
+// fp32 rows of 65 to 256 columns over K <= 64: where the narrow-K kernel (four or two waves across) takes the place of the general tiles.
+// Against two column tiles and their exchange it wins from its first rows on, against whole rows in one tile where the
+// output stream is long (us, general tiles -> narrow-K; K = 44: 131072 x 252 RMSNorm 66.4 -> 41.4, 45815 x 200 softmax 30.8 -> 20.4, no row op
+// 18.1 -> 14.5, 9000 x 128 softmax 13.1 -> 8.9).  Elsewhere it does not: no row op, 9000 x 252 7.2 -> 7.7 (K = 64: 9.5); rows of up
+// to 128 columns in one 128x128 tile, 45815 x 128 softmax 15.3 -> 15.8, 131072 x 96 over K = 16 22.7 -> 25.6 (over 44 they gain again).
+bool narrow_rows(const Problem &pr, int in_dtype, int norm, bool ieee_fp32) {
+    if (in_dtype != FGE_F32 || ieee_fp32 || pr.K > 64 || pr.N <= 64 || pr.N > 256 || pr.batch != 1 || pr.M < PANEL_MIN_ROWS) return false;
+    if (pr.N > 128) return norm != FGE_NORM_NONE || pr.M >= 32768;
+    const int64_t whole = (pr.M + 127) / 128;          // 128x128 tiles; below 5/8 of the CUs 64x64 tiles would run, two to a row
+    return (pr.M >= 131072 && pr.K > 32) || (norm != FGE_NORM_NONE && whole * 8 < (int64_t)num_cu() * 5);
+}
+
 // two_pass: finish split rows with the second kernel even where the cooperative form exists
 // (asked for by flag, or the stream is being captured into a graph).
 Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_tile = -1) {
@@ -311,6 +323,8 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
     if (force_tile < 0 && forced_tile(p) < 0 && !two_pass && !(p->flags & (FGE_FLAG_TWO_PASS | FGE_FLAG_NO_SPLIT_K)) &&
         prefer_shared(pr, p->in_dtype))
         pl.tile = TILE_256x256;
+    if (force_tile < 0 && forced_tile(p) < 0 && g_out_rows == OUT_ALIGNED && narrow_rows(pr, p->in_dtype, norm, (p->flags & FGE_FLAG_IEEE_FP32) != 0))
+        pl.tile = TILE_PANEL;
     // 16- and 8-bit 128x128 tiles, no more of them than CUs (however the tile was chosen): the form
     // on eight waves with three stage buffers - no second workgroup shares a CU, so a second K-tile
     // copy in flight and a second wave per SIMD hide the latencies instead (640 x 4096 x 4096: 43.2
@@ -1590,7 +1604,10 @@ const char *fge_tile_name(int fused, int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return nullptr;
     const Plan pl = make_plan(p, fused ? norm : FGE_NORM_NONE);
     if (pl.generic) return fused && plan_repack(p, norm).use ? "repacked_operands" : "generic32x32_scalar";
-    const TileInfo &ti = tile_info(fused && plan_shared_all(p, norm, false).use ? (int)TILE_256x256 : pl.tile);
+    // (rows of up to 256 columns over a short K go by the name of the general tile whose place the narrow-K kernel takes)
+    const bool narrow = pl.tile == TILE_PANEL && p->N <= 256 && forced_tile(p) < 0;
+    const TileInfo &ti = tile_info(fused && plan_shared_all(p, norm, false).use ? (int)TILE_256x256
+                                   : narrow ? rule_tile(pl.pr, p->in_dtype, false) : pl.tile);
     return p->in_dtype == FGE_F32 && !(p->flags & FGE_FLAG_IEEE_FP32) ? ti.name_split : ti.name;
 }
 

@@ -1,4 +1,5 @@
-// Narrow-K whole-row kernel for fp32 operands: K <= 64, N <= 512, many rows.
+// Narrow-K whole-row kernel for fp32 operands: K <= 64, N <= 512, many rows.  (What follows describes rows of
+// 257 to 512 columns; for narrower ones see PanelShape.)
 //
 // Such a problem is bound by the output stream (every row reads K*4 bytes and writes N*4), so
 // the kernel is organised around HBM, not around the matrix cores:
@@ -42,33 +43,36 @@ __device__ __forceinline__ void mfma_bf16(const u32x4 &a, const u32x4 &b, floatx
                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-struct PanelShape {
-    static constexpr int BM = 64, BN = 512, WAVES_N = 8, MB = 2, NB = 2, KMAX = 64;
-    static constexpr int THREADS = 64 * WAVES_N;
+// WAVES_N waves of 64 columns side by side: 8 for rows of 257 to 512 columns; 4 and 2 for rows of up to 256 and 128, the
+// other waves taking further rows of the tile (32 each, so that two workgroups' worth of LDS images and patches is not exceeded).
+template <int WAVES_N_> struct PanelShape {
+    static constexpr int WAVES_N = WAVES_N_, WAVES_M = 8 / WAVES_N, MB = WAVES_N == 8 ? 2 : 1, NB = 2, KMAX = 64;
+    static constexpr int BM = WAVES_M * MB * 32, BN = WAVES_N * 64, THREADS = 512;
 };
 
-// FULL: M is a multiple of 64 and N == 512, so the epilogue needs no row or column guards.
+// FULL: M is a multiple of BM and N == BN, so the epilogue needs no row or column guards.
 // STREAM: the output is larger than the last-level cache and is stored with the streaming hint.
 // ACT_CT / NORM_CT / BOUNDED_CT: the chain fixed at compile time (see TileEpilogue), -1 to take
 // it from the arguments.
-template <typename OutT, bool FULL, bool STREAM, int ACT_CT = -1, int NORM_CT = -1, bool BOUNDED_CT = false>
-__global__ __launch_bounds__(PanelShape::THREADS)
+template <typename Shape, typename OutT, bool FULL, bool STREAM, int ACT_CT = -1, int NORM_CT = -1, bool BOUNDED_CT = false>
+__global__ __launch_bounds__(Shape::THREADS)
 void panel_kernel(const TileArgs a) {
-    constexpr int BM = PanelShape::BM, WAVES_N = PanelShape::WAVES_N;
-    constexpr int MB = PanelShape::MB, NB = PanelShape::NB, NT = PanelShape::THREADS;
+    constexpr int BM = Shape::BM, WAVES_N = Shape::WAVES_N;
+    constexpr int MB = Shape::MB, NB = Shape::NB, NT = Shape::THREADS;
+    constexpr int RPT = BM * 8 / NT;                  // rows of an X tile a thread fetches 8 values of, 64 apart
     constexpr int WTN = NB * 32;
     constexpr int SROWB = 128;                        // LDS bytes per row of a bf16 image: 64 values
     constexpr int SIMG = BM * SROWB;                  // 8 KB; an X buffer is the image of the high
     constexpr int XBUF = 2 * SIMG;                    // parts followed by the image of the low parts
     using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 16, false, false, false, FULL, STREAM, ACT_CT, NORM_CT, BOUNDED_CT, true>;
-    static_assert(NT == BM * 8, "one thread per (row, 8 values of k) of an X tile");
+    static_assert(NT == 512 && BM % 64 == 0, "a thread per 8 values of k of a row, 64 rows at a time");
 
     __shared__ __attribute__((aligned(16))) unsigned char xs[2 * XBUF];
     __shared__ __attribute__((aligned(16))) float2 xch[2 * BM * WAVES_N];
     __shared__ __attribute__((aligned(16))) float patches[(NT / 64) * Epi::PATCH_FLOATS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wave_n = wave;
+    const int wave_n = wave % WAVES_N, trow0 = wave / WAVES_N * (MB * 32);
     const int h = lane >> 5, l32 = lane & 31;
     const float *X = reinterpret_cast<const float *>(a.X);
     const float *W = reinterpret_cast<const float *>(a.W);
@@ -108,38 +112,44 @@ void panel_kernel(const TileArgs a) {
     // banks.  Values past K are zero.
     const int s_row = tid >> 3, s_c = tid & 7;
     const int s_off = s_row * SROWB + ((s_c ^ ((s_row >> 1) & 7)) << 4);
-    floatx4 xin[2];
+    floatx4 xin[RPT][2];
     auto load_x = [&](int m0) __attribute__((always_inline)) {
-        const float *g = X + (int64_t)min(m0 + s_row, a.M - 1) * a.ldx + s_c * 8;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            xin[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (s_c * 8 + 4 * c < a.K) xin[c] = *reinterpret_cast<const floatx4 *>(g + 4 * c);
+        for (int i = 0; i < RPT; ++i) {
+            const float *g = X + (int64_t)min(m0 + s_row + i * 64, a.M - 1) * a.ldx + s_c * 8;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                xin[i][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (s_c * 8 + 4 * c < a.K) xin[i][c] = *reinterpret_cast<const floatx4 *>(g + 4 * c);
+            }
         }
     };
     auto park_x = [&](int buf) __attribute__((always_inline)) {
-        const float f[8] = {xin[0][0], xin[0][1], xin[0][2], xin[0][3], xin[1][0], xin[1][1], xin[1][2], xin[1][3]};
-        u32x4 hi, lo;
-        split_bf16x8(f, hi, lo);
-        *reinterpret_cast<u32x4 *>(xs + buf * XBUF + s_off) = hi;
-        *reinterpret_cast<u32x4 *>(xs + buf * XBUF + SIMG + s_off) = lo;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const float f[8] = {xin[i][0][0], xin[i][0][1], xin[i][0][2], xin[i][0][3], xin[i][1][0], xin[i][1][1], xin[i][1][2], xin[i][1][3]};
+            u32x4 hi, lo;
+            split_bf16x8(f, hi, lo);
+            *reinterpret_cast<u32x4 *>(xs + buf * XBUF + s_off + i * 64 * SROWB) = hi;
+            *reinterpret_cast<u32x4 *>(xs + buf * XBUF + SIMG + s_off + i * 64 * SROWB) = lo;
+        }
     };
 
-    // A fragment (i, t): row i*32 + l32, k = 16t + 8h .. +7 = chunk 2t + h of that row
+    // A fragment (i, t): row trow0 + i*32 + l32, k = 16t + 8h .. +7 = chunk 2t + h of that row
     int fa_off[MB][4];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            fa_off[i][t] = (i * 32 + l32) * SROWB + (((2 * t + h) ^ ((l32 >> 1) & 7)) << 4);
+            fa_off[i][t] = (trow0 + i * 32 + l32) * SROWB + (((2 * t + h) ^ ((l32 >> 1) & 7)) << 4);
 
     Epi epi(a, out, xch, patches + wave * Epi::PATCH_FLOATS, BM, 0, 0, 0, 0, wave_n, lane);
 
-    // ---------------- persistent loop over 64-row tiles.  At the top of an iteration the tile is
+    // ---------------- persistent loop over the row tiles.  At the top of an iteration the tile is
     // parked in LDS buffer `buf` and the registers hold the values of the next tile, fetched a
     // whole iteration ago; they are parked behind this tile's product, and the fetch of the tile
     // after next follows at once, still ahead of this tile's stores.
-    const int ntiles = a.tiles_m;
+    const int ntiles = (a.M + BM - 1) / BM;
     int tile = blockIdx.x;
     if (tile < ntiles) {
         load_x(tile * BM);
@@ -191,7 +201,7 @@ void panel_kernel(const TileArgs a) {
         __builtin_amdgcn_sched_barrier(0);
         epi.m0 = tile * BM;
         epi.lse_par = buf;
-        epi.template tile<NT>(acc, 0, 0, tid);
+        epi.template tile<NT>(acc, trow0, 0, tid);
     }
     if (epi.defer_lse && it > 0) {
         __syncthreads();
