@@ -5,7 +5,8 @@
 //
 //   generic_gemm_kernel : dst = act(post*(alpha*X.W^T + b))   32x32 tile, LDS staged, fp32 matrix instruction
 //   generic_act_kernel  : dst = act(src) [* second operand]   elementwise
-//   generic_row_kernel  : out = rowop(src)                    one wave per row, passes over src
+//   any_row_kernel      : out = rowop(src)                    rows of up to 8192 columns, in registers
+//   generic_row_kernel  : out = rowop(src)                    wider rows: one wave per row, passes over src
 //   splitk_sum_kernel   : dst = act(post*(alpha*sum_s P_s + b))  the slices of a K-split product, summed in slice order
 //   pad_rows_kernel     : dense copy of a matrix with K padded by zeros to whole 16-byte chunks
 //                         (and zero rows appended): what makes an operand with odd extents or
@@ -99,6 +100,124 @@ __global__ __launch_bounds__(256) void generic_act_kernel(const GenArgs a) {
             Store<T>::put(reinterpret_cast<T *>(a.dst) + off, v);
         }
     });
+}
+
+// The same on rows that registers hold (up to 8192 columns): WAVES waves per row, NCH chunks of CW values per lane, loaded and
+// stored 16 bytes at a time at any alignment and read once.  (The kernel below reads a value at a time, three times over; us, with it
+// -> so, floor at a large copy's 5.8 TB/s: bf16 65536 x 4095 RMSNorm 520.6 -> 306.2 / 185, 65536 x 2047 softmax 356.7 -> 171.8 / 93, fp32 65536 x 2047
+// LayerNorm 436.9 -> 201.6 / 185, 9000 x 8191 RMSNorm 275.1 -> 110.7 / 102, f16 4000 x 8191 logsumexp 120.8 -> 34.5 / 23.  What is left in 16
+// bits is the rows' halves of sectors, written by two workgroups.)
+template <typename SrcT, typename OutT, int WAVES, int NCH>
+__global__ __launch_bounds__(256) void any_row_kernel(const GenArgs a) {
+    constexpr int CW = Store<OutT>::CW, SL = CW / Store<SrcT>::CW;      // values per chunk; loads per chunk
+    static_assert(SL >= 1, "source no narrower than the result");
+    constexpr int TEAM = 64 * WAVES;
+    __shared__ float red[2][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int member = WAVES == 1 ? lane : (int)threadIdx.x;
+    const int64_t rowg = WAVES == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x;
+    if (rowg >= (int64_t)a.batch * a.M) return;                       // wave-uniform (WAVES = 4: never)
+    const SrcT *src = row_ptr<SrcT>(a.X, rowg, a.M, a.ldx, a.bsx);
+    OutT *out = const_cast<OutT *>(row_ptr<OutT>(a.dst, rowg, a.M, a.ldd, a.bsd));
+    const float inv_n = 1.0f / (float)a.N;
+    int turn = 0;
+    auto reduce = [&]<typename Op>(Op, float v) __attribute__((always_inline)) {
+        v = allreduce64<Op>(v);
+        if constexpr (WAVES > 1) {
+            if (lane == 0) red[turn][wave] = v;
+            __syncthreads();
+            v = Op::f(Op::f(red[turn][0], red[turn][1]), Op::f(red[turn][2], red[turn][3]));
+            turn ^= 1;
+        }
+        return v;
+    };
+    float v[NCH][CW];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int j0 = (c * TEAM + member) * CW;
+        if (j0 + CW <= a.N) {
+#pragma unroll
+            for (int l = 0; l < SL; ++l) {
+                typedef typename Store<SrcT>::any16 chunk_t;
+                const u32x4 u = *reinterpret_cast<const chunk_t *>(src + j0 + l * Store<SrcT>::CW);
+                Store<SrcT>::unpack(make_uint4(u.x, u.y, u.z, u.w), v[c] + l * Store<SrcT>::CW);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < CW; ++e) v[c][e] = j0 + e < a.N ? Store<SrcT>::get(src + j0 + e) : 0.0f;
+        }
+    }
+    auto each = [&](auto &&f) __attribute__((always_inline)) {           // f(value, column) for the row's own values
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < CW; ++e) {
+                const int j = (c * TEAM + member) * CW + e;
+                if (j < a.N) f(v[c][e], j);
+            }
+    };
+    // f(value, gamma, beta): the vectors start on 16-byte boundaries, and so do a chunk's parts of them
+    auto part = [&](const float *p, int j, float none) __attribute__((always_inline)) {
+        floatx4 r = {none, none, none, none};
+        if (p == nullptr) return r;
+        if (j + 4 <= a.N) return *reinterpret_cast<const floatx4 *>(p + j);
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (j + e < a.N) r[e] = p[j + e];
+        return r;
+    };
+    auto affine = [&](auto &&f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < CW; e += 4) {
+                const int j = (c * TEAM + member) * CW + e;
+                const floatx4 g = part(a.gamma, j, 1.0f), b = part(a.norm == FGE_NORM_LAYERNORM ? a.beta : nullptr, j, 0.0f);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f(v[c][e + i], g[i], b[i]);
+            }
+    };
+    if (a.norm == FGE_NORM_SOFTMAX || a.norm == FGE_NORM_LOGSUMEXP) {
+        float m = OpMax::ident();
+        each([&](float &x, int) __attribute__((always_inline)) { m = max_nc(m, x); });
+        m = reduce(OpMax{}, m);
+        float s = 0.0f;
+        if (a.norm == FGE_NORM_SOFTMAX) {
+            each([&](float &x, int) __attribute__((always_inline)) { x = fast_exp(x - m); s += x; });
+            const float inv = 1.0f / reduce(OpSum{}, s);
+            each([&](float &x, int) __attribute__((always_inline)) { x *= inv; });
+        } else {
+            each([&](float &x, int) __attribute__((always_inline)) { s += fast_exp(x - m); });
+            s = reduce(OpSum{}, s);
+            if (member == 0) a.aux[rowg] = m + __logf(s);
+            if (reinterpret_cast<const void *>(src) == reinterpret_cast<const void *>(out)) return;
+        }
+    } else if (a.norm == FGE_NORM_LAYERNORM) {
+        float s = 0.0f, d2 = 0.0f;
+        each([&](float &x, int) __attribute__((always_inline)) { s += x; });
+        const float mean = reduce(OpSum{}, s) * inv_n;
+        each([&](float &x, int) __attribute__((always_inline)) { x -= mean; d2 += x * x; });
+        const float rstd = rsqrtf(reduce(OpSum{}, d2) * inv_n + a.eps);
+        affine([&](float &x, float g, float b) __attribute__((always_inline)) { x = x * rstd * g + b; });
+    } else if (a.norm == FGE_NORM_RMSNORM) {
+        float s = 0.0f;
+        each([&](float &x, int) __attribute__((always_inline)) { s += x * x; });
+        const float rr = rsqrtf(reduce(OpSum{}, s) * inv_n + a.eps);
+        affine([&](float &x, float g, float) __attribute__((always_inline)) { x *= rr * g; });
+    }
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int j0 = (c * TEAM + member) * CW;
+        if (j0 + CW <= a.N) {
+            const uint4 u = Store<OutT>::pack(v[c]);
+            const u32x4 w = {u.x, u.y, u.z, u.w};
+            *reinterpret_cast<typename Store<OutT>::any16 *>(out + j0) = w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < CW; ++e)
+                if (j0 + e < a.N) Store<OutT>::put(out + j0 + e, v[c][e]);
+        }
+    }
 }
 
 // src: rows x N of SrcT (row stride lds, batch stride bss); out: rows x N of OutT (ldd, bsd).
@@ -421,6 +540,30 @@ hipError_t launch_generic_row(int src_dtype, int out_dtype, hipStream_t s, const
         else if (out_dtype == FGE_F16) FGE_ROW(f16_t);
         else                           FGE_ROW(float);
 #undef FGE_ROW
+        return hipGetLastError();
+    }
+    // rows that registers hold: one wave per row of up to 2048 (fp32: 1024) columns where there are enough rows for that, else four
+    if (a.N <= 8192 && rows <= INT32_MAX && (src_dtype == FGE_F32 || src_dtype == out_dtype)) {
+#define FGE_ANY_ROW(ST, OT, W, C) hipLaunchKernelGGL((any_row_kernel<ST, OT, W, C>), dim3((unsigned)(W == 1 ? (rows + 3) / 4 : rows)), block, 0, s, a)
+#define FGE_ANY_ROWS(ST, OT)                                                                               \
+        do {                                                                                               \
+            constexpr int PER = 256 * Store<OT>::CW;                                                       \
+            const bool waves = rows >= 1024;                                                               \
+            if (waves && a.N <= PER / 4)          FGE_ANY_ROW(ST, OT, 1, 1);                               \
+            else if (waves && a.N <= PER / 2)     FGE_ANY_ROW(ST, OT, 1, 2);                               \
+            else if (waves && a.N <= PER)         FGE_ANY_ROW(ST, OT, 1, 4);                               \
+            else if (a.N <= PER)                  FGE_ANY_ROW(ST, OT, 4, 1);                               \
+            else if (a.N <= 2 * PER)              FGE_ANY_ROW(ST, OT, 4, 2);                               \
+            else if (a.N <= 4 * PER)              FGE_ANY_ROW(ST, OT, 4, 4);                               \
+            else if constexpr (sizeof(OT) == 4)   FGE_ANY_ROW(ST, OT, 4, 8);                               \
+        } while (0)
+        if (src_dtype == FGE_F32 && out_dtype == FGE_BF16)     FGE_ANY_ROWS(float, bf16_t);
+        else if (src_dtype == FGE_F32 && out_dtype == FGE_F16) FGE_ANY_ROWS(float, f16_t);
+        else if (src_dtype == FGE_F32)                         FGE_ANY_ROWS(float, float);
+        else if (out_dtype == FGE_BF16)                        FGE_ANY_ROWS(bf16_t, bf16_t);
+        else                                                   FGE_ANY_ROWS(f16_t, f16_t);
+#undef FGE_ANY_ROWS
+#undef FGE_ANY_ROW
         return hipGetLastError();
     }
     if (src_dtype == FGE_F32) {

@@ -2,6 +2,7 @@
 around the K tile and the waves' parts of it, around the output tile, and with strides."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2512_23424_amd import binding as B
 from paper_2512_23424_amd import inputs as I
@@ -33,3 +34,39 @@ def test_fp32_precision(norm):
     got, gaux = H.run_gpu(w, t, "fused")
     assert B.fge_tile_name(True, w.act, norm, B.make_params(*(H.to_device(t[k]) for k in "XW"), H.to_device(got.astype(np.float32)))) == "generic32x32_scalar"
     assert H.C.max_rel_err(got, ref) <= 2e-5
+
+
+@pytest.mark.parametrize("dt", [I.F32, I.BF16, I.F16])
+@pytest.mark.parametrize("norm", [I.NORM_SOFTMAX, I.NORM_LAYERNORM, I.NORM_RMSNORM, I.NORM_LOGSUMEXP])
+def test_row_operations_of_odd_width(dt, norm):
+    """fge_row_op on rows that start and end at any element: widths around the chunks of a lane, a wave and a workgroup, few rows and
+    many, out of place and in place."""
+    td = H.tdtype(dt)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    for M, N in ((3, 1), (5, 255), (1030, 257), (1030, 511), (1500, 513), (1030, 1029), (40, 1025), (40, 2049), (9, 4097), (5, 8191)):
+        A = (torch.randn(M, N, generator=g, device="cuda") * 2).to(td)
+        gamma = 1 + 0.1 * torch.randn(N + 3, generator=g, device="cuda")[:N]
+        beta = 0.1 * torch.randn(N + 3, generator=g, device="cuda")[:N]
+        x = A.double()
+        raux = torch.logsumexp(x, 1)
+        if norm == I.NORM_SOFTMAX:
+            ref = torch.softmax(x, 1)
+        elif norm == I.NORM_LAYERNORM:
+            ref = (x - x.mean(1, keepdim=True)) / (x.var(1, unbiased=False, keepdim=True) + 1e-5).sqrt() * gamma.double() + beta.double()
+        elif norm == I.NORM_RMSNORM:
+            ref = x / ((x * x).mean(1, keepdim=True) + 1e-5).sqrt() * gamma.double()
+        else:
+            ref = x
+        for inplace in (False, True):
+            src = A.clone()
+            out = src if inplace else torch.full_like(A, float("nan"))
+            aux = torch.full((M,), float("nan"), device="cuda") if norm == I.NORM_LOGSUMEXP else None
+            p = B.make_params(None, None, out, eps=1e-5, gamma=gamma, beta=beta, aux_out=aux)
+            B.fge_row_op(src, norm, p, out)
+            torch.cuda.synchronize()
+            # one rounding to the result's type on top of fp32 arithmetic
+            tol = {I.F32: 2e-5, I.BF16: 2.0 ** -8, I.F16: 2.0 ** -10}[dt]
+            den = ref.abs().maximum(ref.abs().mean(1, keepdim=True))
+            assert float(((out.double() - ref).abs() / den).max()) <= tol, (M, N, inplace)
+            if aux is not None:
+                assert float((aux.double() - raux).abs().max()) <= 1e-4
