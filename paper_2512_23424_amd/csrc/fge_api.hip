@@ -494,6 +494,7 @@ bool worth_sharing_all(const fge_params *p, int norm, const Plan &pl);
 SharedAll plan_shared_all(const fge_params *p, int norm, bool gated) {
     SharedAll r{};
     if (g_out_rows != OUT_ALIGNED || p->in_dtype == FGE_F32 || forced_tile(p) >= 0 || !vectorisable(p, norm, true)) return r;
+    if (!gated && (int64_t)p->K * (int64_t)esize(p->in_dtype) < 8192) return r;          // (see worth_sharing_all: the cheap refusal first)
     const int tile = gated ? TILE_GATED : TILE_256x256;
     r.q = *p;
     r.pl = make_plan(p, FGE_NORM_NONE, true, tile);

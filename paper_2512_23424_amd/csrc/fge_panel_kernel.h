@@ -44,7 +44,7 @@ __device__ __forceinline__ void mfma_bf16(const u32x4 &a, const u32x4 &b, floatx
 }
 
 // WAVES_N waves of 64 columns side by side: 8 for rows of 257 to 512 columns; 4 and 2 for rows of up to 256 and 128, the
-// other waves taking further rows of the tile (32 each, so that two workgroups' worth of LDS images and patches is not exceeded).
+// other waves taking further rows of the tile (32 each: a tile of 64 and of 128 rows, 32 and 64 KB of X images).
 template <int WAVES_N_> struct PanelShape {
     static constexpr int WAVES_N = WAVES_N_, WAVES_M = 8 / WAVES_N, MB = WAVES_N == 8 ? 2 : 1, NB = 2, KMAX = 64;
     static constexpr int BM = WAVES_M * MB * 32, BN = WAVES_N * 64, THREADS = 512;
@@ -72,7 +72,8 @@ void panel_kernel(const TileArgs a) {
     __shared__ __attribute__((aligned(16))) float patches[(NT / 64) * Epi::PATCH_FLOATS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wave_n = wave % WAVES_N, trow0 = wave / WAVES_N * (MB * 32);
+    const int wave_n = Shape::WAVES_M == 1 ? wave : wave % WAVES_N;
+    const int trow0 = Shape::WAVES_M == 1 ? 0 : wave / WAVES_N * (MB * 32);
     const int h = lane >> 5, l32 = lane & 31;
     const float *X = reinterpret_cast<const float *>(a.X);
     const float *W = reinterpret_cast<const float *>(a.W);

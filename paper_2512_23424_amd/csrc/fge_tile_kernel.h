@@ -154,7 +154,7 @@ void tile_kernel(const TileArgs a) {
     constexpr bool DEEP = STAGES == 3 || (STAGES == 0 && BM == 64 && BN == 64 && !SPLIT && !COOP);
     // QUAD: the mainloop by output quadrants (see there); A buffers first, then B buffers, so that
     // every fragment read is a lane address plus an immediate offset
-    static_assert(!SHARED || (BM == 256 && BN == 256 && STAGES == 0 && !FULL), "shared tiles: the quadrants' loop");
+    static_assert(!SHARED || (BM == 256 && BN == 256 && STAGES == 0 && !FULL && !(GATED && COOP)), "shared tiles: the quadrants' loop");
     constexpr bool QUAD = BM == 256 && BN == 256 && NT == 512 && MB == 4 && NB == 2 && !SPLIT && STAGES == 0;
     constexpr int A_STEP = QUAD ? BM * ROWB : STAGE, B_STEP = QUAD ? BN * ROWB : STAGE;    // bytes between stage buffers
     constexpr int B_AT = QUAD ? 2 * BM * ROWB : BM * ROWB;                                 // first B buffer
@@ -1008,7 +1008,7 @@ void tile_kernel(const TileArgs a) {
         dispatch_act(a.act, [&]<int ACT>() __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
-                if (SHARED && !COOP && !(mine >> i & 1)) continue;      // (in the cooperative form the test costs 128 spilled registers)
+                if (SHARED && !(mine >> i & 1)) continue;
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     gated[i][0][r] = activate<ACT>(scale * acc[i][0][r] + bias1, a.lo, a.hi) * (scale * acc[i][1][r] + bias2);
