@@ -284,9 +284,10 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
 }
 
 // sharing: left-over tiles of 256x256 may be shared (see plan_share).  With a row of at least 8 KB and few of them (a
-// quarter of the CUs: up to four slices) that makes 256x256 tiles the better choice wherever there is a full round of them (4173 x 4096 x
-// 4096 RMSNorm, against the table's 128x256 tiles: bf16 189.6 -> 157.2 us, E4M3 107.3 -> 93.1; with 2 KB of K, 128x128 tiles, 68.8 -> 71.4).
-bool prefer_shared(const Problem &pr, int in_dtype) {
+// quarter of the CUs: up to four slices) that makes 256x256 tiles the better choice wherever there is a full round of them.  Without a
+// row op only: tiles that exchange row statistics are not shared.
+bool prefer_shared(const Problem &pr, int in_dtype, int norm) {
+    if (norm != FGE_NORM_NONE) return false;
     const int64_t tiles = (int64_t)((pr.M + 255) / 256) * ((pr.N + 255) / 256), left = tiles % num_cu();
     return in_dtype != FGE_F32 && pr.batch == 1 && tiles > num_cu() && left > 0 && 4 * left <= num_cu() &&
            (int64_t)pr.K * (int64_t)esize(in_dtype) >= 8192;
@@ -321,7 +322,7 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
                                     : pick_tile(pr, p->in_dtype, norm, (p->flags & FGE_FLAG_IEEE_FP32) != 0,
                                                 !(p->flags & FGE_FLAG_NO_TABLE));
     if (force_tile < 0 && forced_tile(p) < 0 && !two_pass && !(p->flags & (FGE_FLAG_TWO_PASS | FGE_FLAG_NO_SPLIT_K)) &&
-        prefer_shared(pr, p->in_dtype))
+        prefer_shared(pr, p->in_dtype, norm))
         pl.tile = TILE_256x256;
     if (force_tile < 0 && forced_tile(p) < 0 && g_out_rows == OUT_ALIGNED && narrow_rows(pr, p->in_dtype, norm, (p->flags & FGE_FLAG_IEEE_FP32) != 0))
         pl.tile = TILE_PANEL;
@@ -424,7 +425,7 @@ KSplit k_split(const fge_params *p, int norm, const Plan &pl) {
 struct Share {
     int slices;                  // 0: no tile is shared
     int left;                    // shared tiles
-    int from;                    // first of them (ordinary grid) / the round that shares its tiles (cooperative grid)
+    int from;                    // first of them
     int k;                       // elements of K per slice
     int grid;                    // workgroups of the launch
     size_t ws_part, ws_marks;    // partial sums; their marks and, in the last 256 bytes, the fault word
@@ -437,18 +438,16 @@ Share plan_share(const fge_params *p, const Plan &pl) {
     const bool gated = pl.tile == TILE_GATED;
     if (pl.generic || p->in_dtype == FGE_F32 || (pl.tile != TILE_256x256 && !gated) || pl.pr.batch != 1) return sh;
     if (g_out_rows != OUT_ALIGNED || short_k(pl.pr.K, is)) return sh;             // (no room is asked for there; another mainloop)
-    if (gated && pl.coop) return sh;                       // (the cooperative gated form has no kernels that share: see launch_shared_any)
+    if (pl.coop) return sh;                                // (no cooperative kernel shares: see launch_shared_any)
     if (p->flags & (FGE_FLAG_NO_SPLIT_K | FGE_FLAG_TWO_PASS)) return sh;
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-    const int capacity = pl.coop ? num_cu() / pl.tiles_n * pl.tiles_n : num_cu();
-    const int left = (int)(tiles % capacity);
+    const int capacity = num_cu(), left = (int)(tiles % capacity);
     if (left == 0 || tiles > INT32_MAX / 2) return sh;
     const int bk = (int)(128 / is), KT = (pl.pr.K + bk - 1) / bk;
     // In K tiles: a slice, four for the start and the meeting, and the sums' way through memory (256 KB per tile and
     // further slice: 0.06 each; 64 tiles over 16 K tiles take 22.2 us unshared, 19.4 in two slices, 31.2 in four).  Sharing
     // that gains less than a K tile is left alone (16384 x 1704 x 1320, 128 tiles over 27: 93.9 -> 93.0 us).
-    // bf16, us, unshared -> shared: 4173 x 3192 x 512 76.1 -> 39.3, 6235 x 6096 x 3616 LayerNorm 360 -> 289, 8192 x 4096 x 4608 RMSNorm 329 ->
-    // 284 (E4M3 184 -> 166), gated 463 x 4096 x 4504 RMSNorm 75.1 -> 55.2.
+    // bf16, us, unshared -> shared: 4173 x 3192 x 512 76.1 -> 39.3, gated 463 x 4096 x 4504 RMSNorm 75.1 -> 55.2.
     double best = KT - 1;
     int chunk = 0;
     for (int S = 2; S <= 4 && S * left <= capacity; S += 2) {
@@ -461,10 +460,10 @@ Share plan_share(const fge_params *p, const Plan &pl) {
     sh.slices = (KT + chunk - 1) / chunk;
     sh.k = chunk * bk;
     sh.left = left;
-    sh.from = pl.coop ? (int)(tiles / capacity) : (int)(tiles - left);
-    sh.grid = pl.coop ? (tiles > capacity ? capacity : left * sh.slices) : sh.from + left * sh.slices;
+    sh.from = (int)(tiles - left);
+    sh.grid = sh.from + left * sh.slices;
     sh.ws_part = (size_t)sh.slices * left * (256 * 256 * sizeof(float));
-    sh.ws_marks = round256((size_t)sh.slices * left * (pl.coop ? 2 : 1) * sizeof(unsigned)) + 256;
+    sh.ws_marks = round256((size_t)sh.slices * left * sizeof(unsigned)) + 256;
     return sh;
 }
 
@@ -731,7 +730,6 @@ TileArgs tile_args(const void *X, const void *W, const float *b, int act, int no
         a.share = sh.slices; a.share_from = sh.from; a.share_k = sh.k;
         a.part = reinterpret_cast<float *>(base);
         a.part_marks = reinterpret_cast<unsigned *>(base + sh.ws_part);
-        a.share_arrive = a.part_marks + sh.slices * sh.left;
         a.fault = reinterpret_cast<int *>(base + sh.bytes() - 256);
     }
     if (coop) {

@@ -53,12 +53,11 @@ struct TileArgs {
     int withhold;               // tests only: column tile 0 never marks itself as arrived (shared tiles: slice 1 of the first)
     // Shared tiles (256x256 and gated tiles): the last ones of a launch, too few to fill the chip, are each
     // multiplied by `share` workgroups, a slice of share_k of K each (0 or 1: none are shared).
-    // share_from: the first shared tile (ordinary grid; tiles_m * tiles_n: none), or the round that shares its tiles (cooperative grid)
+    // share_from: the first shared tile (tiles_m * tiles_n: none)
     int share, share_from, share_k;
     float *part;                // [shared tiles][share][256 * 256] partial sums
     unsigned *part_marks;       // [shared tiles][share]: gen once they are there
     int strips;                 // ANY: strip pairs per row in ws where that is not tiles_n * waves across (0: it is)
-    unsigned *share_arrive;     // cooperative grid: [row blocks of that round][share][tiles_n] arrival marks
 };
 
 // OutT: storage type of out.  MB x NB: 32x32 accumulator blocks per wave.  WAVES_N: waves
@@ -137,8 +136,6 @@ struct TileEpilogue {
     bool defer_lse = false;     // whole-row logsumexp: park the strip pairs, the caller merges them later
     // SHARED (see the tile kernel):
     unsigned mine = ~0u;        // the groups of the wave's rows to be finished here (the others are another workgroup's)
-    bool sums_ok = true;        // the accumulators hold whole sums
-    unsigned *row_marks = nullptr;   // arrival marks of this part of the row block
     int lse_par = 0;            // exchange buffer the parked pairs of this tile go to
 
     __device__ __forceinline__ TileEpilogue(const TileArgs &a_, OutT *out_, float2 *xch_, float *patch_,
@@ -565,7 +562,6 @@ struct TileEpilogue {
     // Merging pairs: (m, s): m = max, s = sum s_i exp(m_i - m);  (mean, M2) with counts n_i:
     // mean = sum n_i mean_i / n, M2 = sum M2_i + n_i (mean_i - mean)^2;  (sum of squares, -): sum.
 
-    __device__ __forceinline__ bool is_mine(int row) const { return !SHARED || mine >> (row % (MB * 32) / 32) & 1; }   // tile row `row`
     // step 2: tile row `row` (one thread each)
     __device__ __forceinline__ void merge_strips(int row) {
         float2 e[WAVES_N];
@@ -594,7 +590,7 @@ struct TileEpilogue {
 #pragma unroll
             for (int w = 0; w < WAVES_N; ++w) o0 += e[w].x;
         }
-        if (m0 + row < a.M && is_mine(row)) put_pair(a.ws + (row_base + m0 + row) * a.tiles_n + tn, o0, o1);
+        if (m0 + row < a.M) put_pair(a.ws + (row_base + m0 + row) * a.tiles_n + tn, o0, o1);
     }
 
     // step 3.  Only correct when all tiles of the row block are in flight at once (the caller's
@@ -607,11 +603,10 @@ struct TileEpilogue {
         // visible to the whole device, and the barrier orders every wave's drain before the mark
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();                                        // (also: the strip pairs in xch are consumed)
-        unsigned *marks = SHARED ? row_marks : a.arrive + (int64_t)rowblock * a.tiles_n;
+        unsigned *marks = a.arrive + (int64_t)rowblock * a.tiles_n;
         // (withhold: host-side tests make the waits of a row block run out by keeping back the
         // mark of its first column tile)
-        // (a tile whose own sums are incomplete withholds its mark: all rows of the block become NaN)
-        if (tid == 0 && (!SHARED || sums_ok) && !(a.withhold && tn == 0))
+        if (tid == 0 && !(a.withhold && tn == 0))
             __hip_atomic_store(marks + tn, a.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (tid < 64) {
             bool ok = true;
@@ -658,7 +653,7 @@ struct TileEpilogue {
             o0 = allreduce_lanes<OpMax, TPR>(m);
             const float sden = allreduce_lanes<OpSum, TPR>(sum * fast_exp(m - exp_ref(o0)));
             if (norm() == FGE_NORM_SOFTMAX) o1 = fast_rcp(sden);
-            else if (part == 0 && tn == 0 && grow < a.M && is_mine(row)) a.aux[row_base + grow] = waited_ok ? o0 + __logf(sden) : __builtin_nanf("");
+            else if (part == 0 && tn == 0 && grow < a.M) a.aux[row_base + grow] = waited_ok ? o0 + __logf(sden) : __builtin_nanf("");
         } else if (norm() == FGE_NORM_LAYERNORM) {
             // two sweeps over the pairs: the mean first, then M2 about it
             const float inv_n = 1.0f / (float)a.N;

@@ -123,7 +123,7 @@ template <> struct NarrowOut<f16_t> { typedef f16_t type; };
 // 256x256 tiles and the gated form over a short K; defined in fge_tiles_short_*.hip.
 template <typename InT> hipError_t launch_short(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 
-// ... and with shared tiles (a.share); defined in fge_tiles_shared_*.hip.
+// ... and with shared tiles (a.share; ordinary launches); defined in fge_tiles_shared_*.hip.
 template <typename InT> hipError_t launch_shared(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a);
 
 // The 256x256 tile, ordinary and cooperative launch: a kernel for every row op.  The four groups of a wave's rows
@@ -151,8 +151,9 @@ inline hipError_t launch_256(int out_dtype, dim3 grid, hipStream_t s, const Tile
     } while (0)
 #define FGE_256_FORM(NORM)                                                                      \
     do {                                                                                        \
-        if (!a.coop)                                FGE_256(false, false, NORM);                \
-        else if (!SHARED && a.M % 256 == 0 && a.N % 256 == 0)  FGE_256(true, !SHARED, NORM);    \
+        if constexpr (SHARED)                       FGE_256(false, false, NORM);                \
+        else if (!a.coop)                           FGE_256(false, false, NORM);                \
+        else if (a.M % 256 == 0 && a.N % 256 == 0)  FGE_256(true, true, NORM);                  \
         else                                        FGE_256(true, false, NORM);                 \
     } while (0)
     switch (a.norm) {
@@ -320,11 +321,12 @@ template <typename InT>
 inline hipError_t launch_short_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     return gated ? launch_gated_form<InT, 2>(out_dtype, grid, s, a) : launch_256<InT, 2>(out_dtype, grid, s, a);
 }
-// ... and with shared tiles; gated ones in ordinary launches only.  (A launch of the cooperative gated form with shared tiles has
-// faulted, cause not found: 2048 x 6888 x 4272 bf16 RMSNorm, one whole round and 34 tiles in four slices.)
+// ... and with shared tiles, in ordinary launches only.  (A launch of the cooperative gated form with shared tiles has
+// faulted, cause not found: 2048 x 6888 x 4272 bf16 RMSNorm, one whole round and 34 tiles in four slices.  No cooperative
+// kernel shares tiles, the plain ones included, which had the same code.)
 template <typename InT>
 inline hipError_t launch_shared_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
-    if (gated && a.coop) return hipErrorInvalidValue;
+    if (a.coop) return hipErrorInvalidValue;
     return gated ? launch_gated_form<InT, 0, true>(out_dtype, grid, s, a) : launch_256<InT, 0, true>(out_dtype, grid, s, a);
 }
 // The half-tile configurations (TILE_128x256, TILE_256x128), ordinary or cooperative launch;

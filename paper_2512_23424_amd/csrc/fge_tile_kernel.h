@@ -111,7 +111,7 @@ template <> struct Mma<float> {
 // STAGES: 0 for the tile's usual number of stage buffers, else that many (see DEEP below).
 // ANY: N and the rows of the result are any number of elements (see TileEpilogue).
 // NORM_CT (>= 0): the row op, fixed at compile time.
-// SHARED: some of the launch's tiles are shared between workgroups (see the end of the quadrants' loop).  A kernel of its
+// SHARED: the last of an ordinary launch's tiles are shared between workgroups (see the end of the quadrants' loop).  A kernel of its
 // own: the registers it takes cost launches that share nothing up to 1.5 % (8192 x 4096 x 4096, RMSNorm: gated 451.7 -> 457.7, E4M3 123.1 ->
 // 125.0 us).
 template <typename InT, typename OutT, int BM, int BN, int WAVES_M, int WAVES_N, bool COOP = false, bool FULL = false,
@@ -154,7 +154,7 @@ void tile_kernel(const TileArgs a) {
     constexpr bool DEEP = STAGES == 3 || (STAGES == 0 && BM == 64 && BN == 64 && !SPLIT && !COOP);
     // QUAD: the mainloop by output quadrants (see there); A buffers first, then B buffers, so that
     // every fragment read is a lane address plus an immediate offset
-    static_assert(!SHARED || (BM == 256 && BN == 256 && STAGES == 0 && !FULL && !(GATED && COOP)), "shared tiles: the quadrants' loop");
+    static_assert(!SHARED || (BM == 256 && BN == 256 && STAGES == 0 && !COOP), "shared tiles: the quadrants' loop, ordinary launches");
     constexpr bool QUAD = BM == 256 && BN == 256 && NT == 512 && MB == 4 && NB == 2 && !SPLIT && STAGES == 0;
     constexpr int A_STEP = QUAD ? BM * ROWB : STAGE, B_STEP = QUAD ? BN * ROWB : STAGE;    // bytes between stage buffers
     constexpr int B_AT = QUAD ? 2 * BM * ROWB : BM * ROWB;                                 // first B buffer
@@ -181,22 +181,14 @@ void tile_kernel(const TileArgs a) {
     const int h = lane >> 5, l32 = lane & 31;
     int tm, tn, z, rowblock;
     // Shared tiles (QUAD): this workgroup's slice of K, the tile's place among the shared ones (-1: not shared)
-    // and its row block's
-    [[maybe_unused]] int slice = 0, shared_at = -1, shared_at_rb = 0;
+    [[maybe_unused]] int slice = 0, shared_at = -1;
     if constexpr (COOP) {
         constexpr int PW = 4;
         const int G = gridDim.x;
-        int s = xcd_order(blockIdx.x, G);
+        const int s = xcd_order(blockIdx.x, G);
         const int rpr = G / a.tiles_n;                                   // row blocks per round
         const int R = min(rpr, a.tiles_m * a.batch - round * rpr);       // ... in this round
-        if (R <= 0) break;
-        if constexpr (SHARED) {
-            if (round == a.share_from && s < R * a.tiles_n * a.share) {
-                slice = s / (R * a.tiles_n);
-                shared_at = s -= slice * R * a.tiles_n;
-            }
-        }
-        if (s >= R * a.tiles_n) break;
+        if (R <= 0 || s >= R * a.tiles_n) break;
         const int full = a.tiles_n / PW, panel = s / (R * PW);
         int rb;
         if (panel < full) {
@@ -209,7 +201,6 @@ void tile_kernel(const TileArgs a) {
             tn = full * PW + w % wd;
         }
         rowblock = round * rpr + rb;
-        if constexpr (SHARED) shared_at_rb = rb;
         z = rowblock / a.tiles_m;
         tm = rowblock - z * a.tiles_m;
         // Staggered start: the row blocks of the first round begin a little apart (all column
@@ -345,8 +336,6 @@ void tile_kernel(const TileArgs a) {
 
     unsigned mine = ~0u;                              // the groups of a wave's rows that this workgroup finishes
     bool sums_ok = true;                              // (a shared tile whose other slices never came: false)
-    [[maybe_unused]] unsigned *row_marks = nullptr;   // cooperative form: the marks to leave and wait for
-    if constexpr (SHARED) row_marks = a.arrive + (int64_t)rowblock * a.tiles_n;
     floatx16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -727,10 +716,6 @@ void tile_kernel(const TileArgs a) {
             });
         }
         __syncthreads();                              // xch has been read
-        if constexpr (COOP) {                         // the row block's marks: the same slice of its other tiles
-            const int rb_slice = (shared_at_rb * S + slice) * a.tiles_n;
-            row_marks = a.share_arrive + rb_slice;
-        }
     }
     } else if constexpr (KSHARE) {
     // ---------------- mainloop, small tiles with a long K: waves share out K, copies run three K tiles ahead, fragments one
@@ -1020,7 +1005,7 @@ void tile_kernel(const TileArgs a) {
         static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= NST * STAGE, "store patches fit the panels");
         Epi epi(ag, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
                 wave_n, lane);
-        if constexpr (SHARED) { epi.sums_ok = sums_ok; epi.mine = mine; epi.row_marks = row_marks; }
+        if constexpr (SHARED) epi.mine = mine;
         epi.template tile<NT>(gated, wave_m * WTM, rowblock, tid);
     } else {
         using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, NORM_CT, false, false, ANY, SHARED>;
@@ -1028,11 +1013,11 @@ void tile_kernel(const TileArgs a) {
         static_assert(WAVES_M * WAVES_N * PATCH_BYTES <= NST * STAGE && Epi::PATCH_FLOATS * 4 <= PATCH_BYTES, "store patches fit the panels");
         Epi epi(a, out, xch, reinterpret_cast<float *>(smem + wave * PATCH_BYTES), BM, z, m0, n0, tn,
                 wave_n, lane);
-        if constexpr (SHARED) { epi.sums_ok = sums_ok; epi.mine = mine; epi.row_marks = row_marks; }
+        if constexpr (SHARED) epi.mine = mine;
         epi.template tile<NT>(acc, wave_m * WTM, rowblock, tid);
     }
-    if constexpr (SHARED && !COOP) {
-        if (!sums_ok) {                               // incomplete sums: NaN in their place (COOP: see arrive_and_wait)
+    if constexpr (SHARED) {
+        if (!sums_ok) {                               // incomplete sums: NaN in their place
             const float nan = __builtin_nanf("");
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();

@@ -314,3 +314,20 @@ def test_rows_far_apart_leave_the_tile_kernels():
     assert name(512, (8 << 20) // 2) == "repacked_operands"
     assert name(64, (8 << 20) // 2) == "generic32x32_scalar"
 
+
+
+@pytest.mark.parametrize("dt", [1, 2, 3])
+@pytest.mark.parametrize("norm", [1, 2, 3, 4])
+def test_tiles_that_exchange_row_statistics_are_not_shared(dt, norm):
+    """Row blocks finished inside the tile kernel (a fault word is named) behind whole rounds of 256x256 tiles: no room for partial
+    sums is asked for, whatever is left over, and the tile is the one that is taken without sharing."""
+    FLAG_256 = (3 + 1) << 8
+    for M, K, N in ((4300, 2064, 4096), (4173, 8192, 4096), (6235, 6096, 3616), (8192, 4096, 4608)):
+        q = dict(M=M, N=N, K=K, ldx=K, ldw=K, ldo=N, in_dtype=dt, out_dtype=1 if dt == 3 else dt)
+        for flags in (0, FLAG_256):
+            p, plain = _params(**q, flags=flags), _params(**q, flags=flags | B.FLAG_NO_SPLIT_K)
+            exchanged = B.fge_fault_word_offset(1, norm, plain) is not None
+            assert exchanged or flags == 0 or norm == 4        # (logsumexp over more than 16 column tiles takes a second pass)
+            if exchanged:
+                assert B.fge_workspace_bytes(True, 1, norm, p) == B.fge_workspace_bytes(True, 1, norm, plain)
+                assert B.fge_tile_name(True, 1, norm, p) == B.fge_tile_name(True, 1, norm, plain)
