@@ -129,10 +129,10 @@ typedef enum {
  *   Products of at most 64 rows of 16- or 8-bit operands (K of 1024 bytes and more) normally share
  *   out K inside a workgroup instead and need no slices; the flag keeps them on the tile kernels.
  *   The last 256x256 tiles of a launch (gated: 256x128) that do not fill the device once more - all of a
- *   problem that has few - are shared in the same way: two or four workgroups multiply a slice of K each, exchange
- *   partial sums through the workspace and finish a part of the rows each.  They wait for each other like
- *   the tiles of a row block (bounded, fault word, NaN); FGE_FLAG_NO_SPLIT_K and FGE_FLAG_TWO_PASS switch it off, a
- *   captured stream and a workspace without the room do without.
+ *   problem that has few - are shared: two or four workgroups multiply a slice of K each and leave
+ *   partial sums in the workspace, which a second launch adds and finishes.  No workgroup waits for another
+ *   in this form; rows that are finished by such a wait (split rows, without FGE_FLAG_TWO_PASS) share no tiles.
+ *   FGE_FLAG_NO_SPLIT_K and FGE_FLAG_TWO_PASS switch it off, a captured stream and a workspace without the room do without.
  *   FGE_FLAG_TILE(t) : run the tile kernels with tile configuration t (an fge_tile) instead of
  *   the library's own choice - for tuning and tests.  A configuration without kernels for the
  *   operand type (or the narrow-K kernel outside K <= 64, N <= 512, fp32) yields
@@ -222,11 +222,12 @@ size_t fge_static_scratch_bytes(void);
  * buffers, Section 3.2, the Coder).  Bytes of workspace the fused (fused != 0) or unfused (fused == 0) path needs for these
  * arguments; 0 is a valid answer.  Returns (size_t)-1 when the arguments are invalid.  The fused
  * figure includes the room for the optional K slices and for the partial sums of shared tiles
- * (FGE_FLAG_NO_SPLIT_K switches both off; up to 64 MiB); a smaller workspace that still holds the row
+ * (FGE_FLAG_NO_SPLIT_K switches both off; at most 64 MiB of sums, and with a row op behind a problem all of
+ * whose tiles are shared up to 32 MiB of fp32 rows); a smaller workspace that still holds the row
  * statistics of split rows is accepted and runs without them. */
 size_t fge_workspace_bytes(int fused, int act, int norm, const fge_params *p);
 
-/* Where the one-kernel form of split rows, or a launch with shared tiles, reports a wait that ran out: byte offset into the
+/* Where the one-kernel form of split rows reports a wait that ran out: byte offset into the
  * workspace of an int32 that such a launch sets to 1 (it never clears it; the rows of the tiles
  * whose wait ran out are stored as NaN).  (size_t)-1 when fused_gemm_epilogue does not take that
  * form for these arguments.  A caller that wants the check clears the word before the call and

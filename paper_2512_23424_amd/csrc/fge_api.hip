@@ -418,18 +418,52 @@ KSplit k_split(const fge_params *p, int norm, const Plan &pl) {
     return ks;
 }
 
+// The gated tile kernel takes 16-bit and 8-bit operands in shapes the vectorised kernels take.
+bool gated_fast(const fge_params *p, int norm) { return p->in_dtype != FGE_F32 && vectorisable(p, norm, true); }
+
+// Gated form of a small problem with a long K: the gated tile kernel has 256-row tiles only, and
+// with a handful of them most of the chip idles (16 x 4096 x 4096: 84 us, against 52 us for the
+// unfused sequence).  Such a problem runs like a K-split instead: both products as fp32 partial
+// products (one slice if K is not worth cutting), one kernel that adds the slices and applies
+// scale, bias, activation and the gate in fp32, then the row op.
+struct GatedSmall {
+    bool use;
+    Plan pl;                     // plan of one plain product of this shape
+    KSplit ks;                   // slices of each product; ws_part bytes per product
+    size_t bytes() const { return 2 * ks.ws_part + ks.ws_mid; }
+};
+
+GatedSmall gated_small(const fge_params *p, int norm) {
+    GatedSmall g{false, make_plan(p, norm), {1, 0, 0}};
+    const Plan &pl = g.pl;
+    if (!gated_fast(p, norm) || pl.generic || pl.pr.batch != 1 || pl.tile == TILE_PANEL || pl.pr.K < 1024) return g;
+    if (norm != FGE_NORM_NONE && pl.pr.N > MAX_ROWOP_N) return g;
+    const TileInfo &gt = tile_info(TILE_GATED);
+    const int64_t gated_tiles = (int64_t)((pl.pr.M + gt.bm - 1) / gt.bm) * ((pl.pr.N + gt.bn - 1) / gt.bn);
+    // from about 96 of its tiles on the gated kernel is the faster one, and so it is when one plain
+    // product alone has more 64x64 tiles than two per CU (256 x 4096 x 11008: 86 against 117 us)
+    if (gated_tiles * 8 > num_cu() * 3 || pl.tile != TILE_64x64 || (int64_t)pl.tiles_m * pl.tiles_n > 2 * num_cu()) return g;
+    g.ks = k_split(p, norm, pl);
+    if (g.ks.slices == 1) {
+        const size_t one = round256((size_t)pl.pr.M * pl.pr.N * sizeof(float));
+        g.ks.ws_part = one;
+        g.ks.ws_mid = norm == FGE_NORM_NONE ? 0 : one;
+    }
+    g.use = true;
+    return g;
+}
+
 // Shared tiles (256x256 tiles by output quadrants and the gated form, see the tile kernel): the tiles left
 // over when the others have filled the chip a whole number of times would take as long as a full round on
-// a part of the CUs; each is multiplied by two or four workgroups instead, a slice of K each (three, whose
-// parts of the rows are uneven, measured slower than two).
+// a part of the CUs; each is multiplied by two or four workgroups instead, a slice of K each, and a second launch
+// (shared_finish_kernel) adds their sums.
 struct Share {
     int slices;                  // 0: no tile is shared
     int left;                    // shared tiles
     int from;                    // first of them
     int k;                       // elements of K per slice
     int grid;                    // workgroups of the launch
-    size_t ws_part, ws_marks;    // partial sums; their marks and, in the last 256 bytes, the fault word
-    size_t bytes() const { return ws_part + ws_marks; }
+    size_t ws_part;              // bytes of the partial sums
 };
 
 Share plan_share(const fge_params *p, const Plan &pl) {
@@ -444,15 +478,18 @@ Share plan_share(const fge_params *p, const Plan &pl) {
     const int capacity = num_cu(), left = (int)(tiles % capacity);
     if (left == 0 || tiles > INT32_MAX / 2) return sh;
     const int bk = (int)(128 / is), KT = (pl.pr.K + bk - 1) / bk;
-    // In K tiles: a slice, four for the start and the meeting, and the sums' way through memory (256 KB per tile and
-    // further slice: 0.06 each; 64 tiles over 16 K tiles take 22.2 us unshared, 19.4 in two slices, 31.2 in four).  Sharing
-    // that gains less than a K tile is left alone (16384 x 1704 x 1320, 128 tiles over 27: 93.9 -> 93.0 us).
-    // bf16, us, unshared -> shared: 4173 x 3192 x 512 76.1 -> 39.3, gated 463 x 4096 x 4504 RMSNorm 75.1 -> 55.2.
-    double best = KT - 1;
+    // (few gated tiles over a short K, whose epilogue is half a plain tile's: 500 x 1000 x 2048 22.0 -> 25.8 us)
+    if (gated && tiles == left && KT < 24) return sh;
+    // In K tiles (0.9 us): a slice; 0.8 per slice for the second launch; 0.05 per tile and slice for their 256 KB of sums on
+    // the way out and back, and 0.09 more for each beyond the 128 that the L2s hold.  Unshared -> two slices, four (bf16, us): 16 tiles
+    // over 16 K tiles 24.5 -> 21.1, 23.0, over 64 67.0 -> 40.1, 29.0; 64 over 16 25.3 -> 25.4, 43.5, over 64 68.0 -> 47.9, 58.5; 128 over
+    // 32 41.8 -> 52.2, over 128 135.0 -> 124.3; behind a whole round, 16 over 64 173.0 -> 146.9, 135.7, 128 over 64 186.7 -> 181.1; E4M3
+    // alike.  A tenth of K has to be gained: with all CUs busy the clock is lower, and 64 over 16 or 128 over 64 give nothing.
+    double best = 0.9 * KT;
     int chunk = 0;
     for (int S = 2; S <= 4 && S * left <= capacity; S += 2) {
-        const int c = (KT + S - 1) / S;
-        const double cost = c + 4 + 0.06 * left * (S - 1);
+        const int c = (KT + S - 1) / S, blocks = left * S;
+        const double cost = c + 0.8 * S + 0.05 * blocks + 0.09 * std::max(0, blocks - 128);
         if ((KT + c - 1) / c != S) continue;             // (a slice would be empty)
         if (cost < best) { best = cost; chunk = c; }
     }
@@ -463,21 +500,18 @@ Share plan_share(const fge_params *p, const Plan &pl) {
     sh.from = (int)(tiles - left);
     sh.grid = sh.from + left * sh.slices;
     sh.ws_part = (size_t)sh.slices * left * (256 * 256 * sizeof(float));
-    sh.ws_marks = round256((size_t)sh.slices * left * sizeof(unsigned)) + 256;
     return sh;
 }
 
 // Whether this call shares tiles: the workspace has the room behind what the plan itself needs.
 Share share_in(const fge_params *p, const Plan &pl) {
     Share sh = plan_share(p, pl);
-    if (sh.slices && !(p->workspace && p->workspace_bytes >= pl.ws_stats + pl.ws_marks + sh.bytes())) sh = Share{};
+    if (sh.slices && !(p->workspace && p->workspace_bytes >= pl.ws_stats + sh.ws_part)) sh = Share{};
     return sh;
 }
 
 // Problems all of whose 256x256 (gated: 256x128) tiles are shared.  Rows that span several column tiles are
-// written in fp32, and a row kernel - one workgroup per row - turns them into the result: between workgroups that have
-// just exchanged sums, the exchange of row statistics costs more than that launch (gated 256 x 4096 x 2984
-// RMSNorm: 30.7 us so, 40.1 with the exchange, 34.9 as two products; 1000 x 2048 x 2984 38.8 and 43.3).
+// written in fp32, and a row kernel - one workgroup per row - turns them into the result.
 struct SharedAll {
     bool use;
     fge_params q;                // the product and the activation: into `out`, or as fp32 rows into the workspace
@@ -485,7 +519,7 @@ struct SharedAll {
     Share sh;
     int norm;                    // ... and what its epilogue does of the row op
     size_t ws_mid;               // bytes of the fp32 rows (0: none)
-    size_t bytes() const { return ws_mid + sh.bytes(); }
+    size_t bytes() const { return ws_mid + sh.ws_part; }
 };
 
 bool worth_sharing_all(const fge_params *p, int norm, const Plan &pl);
@@ -493,7 +527,7 @@ bool worth_sharing_all(const fge_params *p, int norm, const Plan &pl);
 SharedAll plan_shared_all(const fge_params *p, int norm, bool gated) {
     SharedAll r{};
     if (g_out_rows != OUT_ALIGNED || p->in_dtype == FGE_F32 || forced_tile(p) >= 0 || !vectorisable(p, norm, true)) return r;
-    if (!gated && (int64_t)p->K * (int64_t)esize(p->in_dtype) < 8192) return r;          // (see worth_sharing_all: the cheap refusal first)
+    if ((int64_t)p->K * (int64_t)esize(p->in_dtype) < (gated ? 24 * 128 : 16384)) return r;          // (see worth_sharing_all: the cheap refusal first)
     const int tile = gated ? TILE_GATED : TILE_256x256;
     r.q = *p;
     r.pl = make_plan(p, FGE_NORM_NONE, true, tile);
@@ -513,26 +547,28 @@ SharedAll plan_shared_all(const fge_params *p, int norm, bool gated) {
 }
 
 // Whether that is the faster way (pl: the plan in these tiles).  A tile half of whose rows do not exist wastes its products: M > 128.
-// Gated: against two products in 64x64 tiles and a gate kernel, and against unshared gated tiles (bf16, us before -> shared):
-// 512 x 8192 x 2984 99.2 -> 54.2, 256 x 4096 x 5056 RMSNorm 55.9 -> 37.2, 512 x 2048 x 4096 36.3 -> 30.4; below the line 768 x 1024 x 600
-// 16.0 -> 18.3, 256 x 8192 x 600 31.2 -> 39.0, with the row kernel behind them 256 x 1024 x 4096 21.1 -> 22.0.
-// Plain: against 64x64 tiles and two 128x128 tiles per CU, which a long K keeps bound by operand traffic (768 x 8192 x 2048
-// 45.6 -> 41.0, 1000 x 8192 x 8192 129.6 -> 117.5, 1500 x 8192 x 4096 RMSNorm 115.8 -> 104.0; from half that K where the 128x128
-// tiles just miss one per CU: 4173 x 4096 x 1024 51.2 -> 44.4, but 2048 x 4096 x 4096 RMSNorm 72.2 -> 80.8).  One
-// 128x128 tile per CU is not beaten (1000 x 4096 x 4096 35.4 -> 43.4, 512 x 8192 x 8192 66.3 -> 69.4), nor are 8-bit operands at
-// the same K tiles (1500 x 8192 x 4096 52.3 -> 50.3 only).
+// Gated (bf16, us before -> shared, T the tiles): against both products cut into slices of K, or in one round of 64x64 tiles over a row
+// of less than 10 KB (6 with a partial K tile, which costs them 3 us), and a gate kernel: 512 x 2048 x 3072 (T = 48) 33.9 -> 29.1, 256 x 4096 x 3072 (24) 32.8 -> 30.5, below the line 512 x 2048 x
+// 2048 (32) 23.6 -> 25.5, 400 x 4096 x 640 (10) 25.5 -> 26.7; with the row kernel behind them 256 x 8192 x 3072 (24) 58.4 -> 49.1, 1024 x
+// 4096 x 1280 (40) 53.2 -> 42.2, below the line 256 x 2048 x 4096 (32) 26.1 -> 30.8, 400 x 4096 x 2048 (32) 34.6 -> 36.2.  Against whole
+// products otherwise and unshared gated tiles from a part of that on: 256 x 2056 x 4104 42.9 -> 28.2, 1000 x 4104 x 640 45.6 -> 34.0, RMSNorm
+// 463 x 4096 x 4504 74.0 -> 56.3, 500 x 3080 x 1280 38.8 -> 33.1, 256 x 1544 x 4104 39.5 -> 32.1; over 16 K tiles they lose (1000 x 1000 x 1280
+// 22.3 -> 24.5).
+// Plain: against two 128x128 tiles per CU, which a long K keeps bound by operand traffic (1500 x 8192 x 3072 96.1 -> 87.8, RMSNorm 96.6 ->
+// 92.3; 1024 x 8192 x 6144 102.8 -> 96.1, RMSNorm 110.6 -> 107.2; 128 tiles 119.9 -> 118.7, RMSNorm 127.4 -> 133.6; 3/4 of that K 69.5 -> 69.5
+// and 76.8 -> 77.9; 32 tiles, against 64x64 ones, 48.2 -> 50.0).  8-bit operands lose (1500 x 8192 x 4096 51.4 -> 56.6).
 bool worth_sharing_all(const fge_params *p, int norm, const Plan &pl) {
     const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n, row_bytes = (int64_t)pl.pr.K * (int64_t)esize(p->in_dtype);
     if (pl.pr.M <= 128) return false;
     if (pl.tile == TILE_GATED) {
         const bool rows = norm != FGE_NORM_NONE && pl.tiles_n > 1;
-        return rows ? tiles >= 20 && tiles * row_bytes >= 80 << 10 : tiles >= 10 && tiles * row_bytes >= 40 << 10;
+        if (row_bytes < 24 * 128 || tiles < (rows ? 20 : 10) || tiles * row_bytes < (rows ? 96 << 10 : 80 << 10)) return false;
+        if (tiles >= 20 && tiles * row_bytes >= (rows ? 320 << 10 : 160 << 10)) return true;
+        const GatedSmall other = gated_small(p, norm);
+        const bool one_round = (int64_t)other.pl.tiles_m * other.pl.tiles_n <= num_cu();
+        return !other.use || (other.ks.slices == 1 && !(one_round && row_bytes < (row_bytes % 128 ? 6 << 10 : 10 << 10)));
     }
-    if (row_bytes < 8192) return false;
-    const int other = make_plan(p, norm).tile;
-    const bool longer = p->in_dtype != FGE_F8E4M3 && row_bytes >= 16384;
-    if (other == TILE_64x64) return longer && tiles >= 24;
-    return other == TILE_128x128 && (longer || tiles <= 100);
+    return p->in_dtype != FGE_F8E4M3 && row_bytes >= 16384 && tiles >= 64 && tiles <= 100 && make_plan(p, norm).tile == TILE_128x128;
 }
 
 constexpr double REPACK_MIN_FLOP = 3.0e7;   // below this the element-granular product is as fast as four launches
@@ -628,7 +664,7 @@ size_t fused_workspace(const fge_params *p, int norm, bool shared) {
     }
     const SharedAll all = shared ? plan_shared_all(p, norm, false) : SharedAll{};
     if (all.use) return std::max({p1.ws_stats + p1.ws_marks, p2.ws_stats + p2.ws_marks, all.bytes(), few});
-    return std::max({p1.ws_stats + p1.ws_marks + (shared ? plan_share(p, p1).bytes() : 0), p2.ws_stats + p2.ws_marks,
+    return std::max({p1.ws_stats + p1.ws_marks + (shared ? plan_share(p, p1).ws_part : 0), p2.ws_stats + p2.ws_marks,
                      k_split(p, norm, p1).bytes(), few});
 }
 
@@ -639,12 +675,9 @@ size_t split_rows_workspace(const fge_params *p, int norm) {
     return a > b ? a : b;
 }
 
-// The gated tile kernel takes 16-bit and 8-bit operands in shapes the vectorised kernels take.
-bool gated_fast(const fge_params *p, int norm) { return p->in_dtype != FGE_F32 && vectorisable(p, norm, true); }
-
 size_t gated_workspace(const fge_params *p, int norm, bool shared = false) {
     const Plan p1 = make_plan(p, norm, false, TILE_GATED), p2 = make_plan(p, norm, true, TILE_GATED);
-    const size_t a = p1.ws_stats + p1.ws_marks + (shared ? plan_share(p, p1).bytes() : 0), b = p2.ws_stats + p2.ws_marks;
+    const size_t a = p1.ws_stats + p1.ws_marks + (shared ? plan_share(p, p1).ws_part : 0), b = p2.ws_stats + p2.ws_marks;
     return a > b ? a : b;
 }
 
@@ -718,23 +751,14 @@ TileArgs tile_args(const void *X, const void *W, const float *b, int act, int no
     a.any_row = g_out_rows == OUT_ANY;
     a.coop = 0;
     a.share_from = pl.tiles_m * pl.tiles_n;
-    const bool coop = pl.coop && norm != FGE_NORM_NONE;
-    if (coop || sh.slices) {
-        a.gen = g_generation.fetch_add(1) + 1;
-        const bool expire = (p->flags & FGE_FLAG_TEST_EXPIRE_WAIT) != 0;
-        a.spin_limit = expire ? 1u : WAIT_POLLS;
-        a.withhold = expire ? 1 : 0;
-    }
     if (sh.slices) {
-        char *base = static_cast<char *>(p->workspace) + pl.ws_stats + pl.ws_marks;
         a.share = sh.slices; a.share_from = sh.from; a.share_k = sh.k;
-        a.part = reinterpret_cast<float *>(base);
-        a.part_marks = reinterpret_cast<unsigned *>(base + sh.ws_part);
-        a.fault = reinterpret_cast<int *>(base + sh.bytes() - 256);
+        a.part = reinterpret_cast<float *>(static_cast<char *>(p->workspace) + pl.ws_stats);
     }
-    if (coop) {
+    if (pl.coop && norm != FGE_NORM_NONE) {
         char *base = static_cast<char *>(p->workspace) + pl.ws_stats;
         a.coop = 1;
+        a.gen = g_generation.fetch_add(1) + 1;
         a.arrive = reinterpret_cast<unsigned *>(base);
         a.fault = reinterpret_cast<int *>(base + pl.ws_marks - 256);
         // staggered start of the row blocks (see the kernel): measured 1 to 7 % on problems whose
@@ -745,6 +769,9 @@ TileArgs tile_args(const void *X, const void *W, const float *b, int act, int no
         const int64_t row_blocks = (int64_t)pl.tiles_m * pl.pr.batch, per_round = pl.coop_grid / pl.tiles_n;
         a.stagger = pl.pr.K <= 2048 && row_blocks >= 3 * per_round ? 4 : 0;
         a.stagger_mask = 7;
+        const bool expire = (p->flags & FGE_FLAG_TEST_EXPIRE_WAIT) != 0;
+        a.spin_limit = expire ? 1u : WAIT_POLLS;
+        a.withhold = expire ? 1 : 0;
     }
     return a;
 }
@@ -1462,38 +1489,6 @@ int unfused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, c
     return do_rownorm(A, norm, p, out, s);
 }
 
-// Gated form of a small problem with a long K: the gated tile kernel has 256-row tiles only, and
-// with a handful of them most of the chip idles (16 x 4096 x 4096: 84 us, against 52 us for the
-// unfused sequence).  Such a problem runs like a K-split instead: both products as fp32 partial
-// products (one slice if K is not worth cutting), one kernel that adds the slices and applies
-// scale, bias, activation and the gate in fp32, then the row op.
-struct GatedSmall {
-    bool use;
-    Plan pl;                     // plan of one plain product of this shape
-    KSplit ks;                   // slices of each product; ws_part bytes per product
-    size_t bytes() const { return 2 * ks.ws_part + ks.ws_mid; }
-};
-
-GatedSmall gated_small(const fge_params *p, int norm) {
-    GatedSmall g{false, make_plan(p, norm), {1, 0, 0}};
-    const Plan &pl = g.pl;
-    if (!gated_fast(p, norm) || pl.generic || pl.pr.batch != 1 || pl.tile == TILE_PANEL || pl.pr.K < 1024) return g;
-    if (norm != FGE_NORM_NONE && pl.pr.N > MAX_ROWOP_N) return g;
-    const TileInfo &gt = tile_info(TILE_GATED);
-    const int64_t gated_tiles = (int64_t)((pl.pr.M + gt.bm - 1) / gt.bm) * ((pl.pr.N + gt.bn - 1) / gt.bn);
-    // from about 96 of its tiles on the gated kernel is the faster one, and so it is when one plain
-    // product alone has more 64x64 tiles than two per CU (256 x 4096 x 11008: 86 against 117 us)
-    if (gated_tiles * 8 > num_cu() * 3 || pl.tile != TILE_64x64 || (int64_t)pl.tiles_m * pl.tiles_n > 2 * num_cu()) return g;
-    g.ks = k_split(p, norm, pl);
-    if (g.ks.slices == 1) {
-        const size_t one = round256((size_t)pl.pr.M * pl.pr.N * sizeof(float));
-        g.ks.ws_part = one;
-        g.ks.ws_mid = norm == FGE_NORM_NONE ? 0 : one;
-    }
-    g.use = true;
-    return g;
-}
-
 int fused_gated_gemm_epilogue(const void *X, const void *W1, const void *W2, const float *b1, const float *b2,
                               int act, int norm, const fge_params *p, void *out, void *stream) {
     int rc = check_common(p, act, norm, true);
@@ -1569,12 +1564,11 @@ size_t fge_fault_word_offset(int act, int norm, const fge_params *p) {
     const Skinny few = plan_skinny(p, norm, false);
     if (few.use && !(p->workspace && p->workspace_bytes < few.bytes()))
         return few.bytes() && skinny_in_kernel(p, norm) ? few.bytes() - 256 : (size_t)-1;
+    // (a problem all of whose tiles are shared takes launches that wait for nothing)
     const SharedAll all = plan_shared_all(p, norm, false);
-    if (all.use && !(p->workspace && p->workspace_bytes < all.bytes())) return all.bytes() - 256;
+    if (all.use && !(p->workspace && p->workspace_bytes < all.bytes())) return (size_t)-1;
     const Plan pl = make_plan(p, norm);
-    if (pl.coop) return pl.ws_stats + pl.ws_marks - 256;
-    const Share sh = p->workspace ? share_in(p, pl) : plan_share(p, pl);      // (no workspace named: one of the size asked for)
-    return sh.slices ? pl.ws_stats + pl.ws_marks + sh.bytes() - 256 : (size_t)-1;
+    return pl.coop ? pl.ws_stats + pl.ws_marks - 256 : (size_t)-1;
 }
 
 size_t fge_workspace_bytes(int fused, int act, int norm, const fge_params *p) {

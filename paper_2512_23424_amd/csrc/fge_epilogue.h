@@ -50,13 +50,12 @@ struct TileArgs {
     int any_row;                // rows of `out` start and end at any element (stored 16 bytes at a time all the same, unaligned)
     int stagger, stagger_mask;  // cooperative form: row block rb of the first round starts (rb & mask) * stagger * 1024 clocks late
     unsigned spin_limit;        // polls after which a wait gives up
-    int withhold;               // tests only: column tile 0 never marks itself as arrived (shared tiles: slice 1 of the first)
+    int withhold;               // tests only: column tile 0 never marks itself as arrived
     // Shared tiles (256x256 and gated tiles): the last ones of a launch, too few to fill the chip, are each
     // multiplied by `share` workgroups, a slice of share_k of K each (0 or 1: none are shared).
     // share_from: the first shared tile (tiles_m * tiles_n: none)
     int share, share_from, share_k;
     float *part;                // [shared tiles][share][256 * 256] partial sums
-    unsigned *part_marks;       // [shared tiles][share]: gen once they are there
     int strips;                 // ANY: strip pairs per row in ws where that is not tiles_n * waves across (0: it is)
 };
 
@@ -81,8 +80,7 @@ struct TileArgs {
 // fp32 kernels 3 to 7 % - and the rows of `out` may start anywhere (a.any_row).  Ordinary launches only.
 template <typename OutT, int MB, int NB, int WAVES_N, int PATCH_ROWS, bool JOINT, bool WAIT_VM, bool COOP = false,
           bool FULL_TILE = false, bool STREAM_OUT = false, int ACT_CT = -1, int NORM_CT = -1, bool BOUNDED_CT = false,
-          bool PLAIN_ACC = false, bool ANY = false,
-          bool SHARED = false>
+          bool PLAIN_ACC = false, bool ANY = false>
 struct TileEpilogue {
     static constexpr int WTN = NB * 32;               // columns of a wave strip
     // Patch layout.  A patch row is written 32 columns at a time by the lanes 0-31 (row R) and
@@ -134,8 +132,6 @@ struct TileEpilogue {
     bool bounded;               // clamp activation with a narrow range feeds softmax / logsumexp
     bool masked;                // the bias may mask columns of the wave (see strip_sums)
     bool defer_lse = false;     // whole-row logsumexp: park the strip pairs, the caller merges them later
-    // SHARED (see the tile kernel):
-    unsigned mine = ~0u;        // the groups of the wave's rows to be finished here (the others are another workgroup's)
     int lse_par = 0;            // exchange buffer the parked pairs of this tile go to
 
     __device__ __forceinline__ TileEpilogue(const TileArgs &a_, OutT *out_, float2 *xch_, float *patch_,
@@ -742,7 +738,6 @@ struct TileEpilogue {
             // (logsumexp leaves the activated values as they are: stored right away)
             float vall[MB / G][NPG][VEC], mkeep[MB / G][NPG];
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
-                if (SHARED && !(mine >> g & 1)) return;
                 static_for<0, G>([&]<int b>() __attribute__((always_inline)) { to_rows<b>(acc[g * G + b], vall[g]); });
                 const int grow0 = trow0 + g * G * 32;
                 norm_dispatch<FULL_TILE>(vall[g], grow0, mkeep[g]);
@@ -759,7 +754,6 @@ struct TileEpilogue {
             if (norm() == FGE_NORM_LOGSUMEXP) return;
             __syncthreads();
             static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
-                if (SHARED && !(mine >> g & 1)) return;
                 const int grow0 = trow0 + g * G * 32;
                 switch (norm()) {
                 case FGE_NORM_SOFTMAX:   finish_group<FGE_NORM_SOFTMAX>(vall[g], grow0, fin, mkeep[g], gam, bet); break;
@@ -771,7 +765,6 @@ struct TileEpilogue {
         } else {
             auto body = [&]<bool FULL>() __attribute__((always_inline)) {
                 static_for<0, MB / G>([&]<int g>() __attribute__((always_inline)) {
-                    if (SHARED && !(mine >> g & 1)) return;
                     float v[NPG][VEC], mkeep[NPG];
                     static_for<0, G>([&]<int b>() __attribute__((always_inline)) { to_rows<b>(acc[g * G + b], v); });
                     const int grow0 = trow0 + g * G * 32;

@@ -321,13 +321,35 @@ template <typename InT>
 inline hipError_t launch_short_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     return gated ? launch_gated_form<InT, 2>(out_dtype, grid, s, a) : launch_256<InT, 2>(out_dtype, grid, s, a);
 }
-// ... and with shared tiles, in ordinary launches only.  (A launch of the cooperative gated form with shared tiles has
+// ... and with shared tiles, in ordinary launches only: the tiles, then the sums of the shared ones.  (A launch of the cooperative gated form with shared tiles has
 // faulted, cause not found: 2048 x 6888 x 4272 bf16 RMSNorm, one whole round and 34 tiles in four slices.  No cooperative
 // kernel shares tiles, the plain ones included, which had the same code.)
 template <typename InT>
 inline hipError_t launch_shared_any(bool gated, int out_dtype, dim3 grid, hipStream_t s, const TileArgs &a) {
     if (a.coop) return hipErrorInvalidValue;
-    return gated ? launch_gated_form<InT, 0, true>(out_dtype, grid, s, a) : launch_256<InT, 0, true>(out_dtype, grid, s, a);
+    const hipError_t e = gated ? launch_gated_form<InT, 0, true>(out_dtype, grid, s, a) : launch_256<InT, 0, true>(out_dtype, grid, s, a);
+    if (e != hipSuccess) return e;
+    typedef typename NarrowOut<InT>::type NarrowT;
+    const dim3 quarters((grid.x - (unsigned)a.share_from) / (unsigned)a.share * 4);
+#define FGE_SHARED_FINISH(NORM)                                                                                     \
+    do {                                                                                                            \
+        if (out_dtype != FGE_F32) {                                                                                 \
+            if (gated) hipLaunchKernelGGL((shared_finish_kernel<NarrowT, true, NORM>), quarters, dim3(512), 0, s, a);  \
+            else       hipLaunchKernelGGL((shared_finish_kernel<NarrowT, false, NORM>), quarters, dim3(512), 0, s, a); \
+        } else {                                                                                                    \
+            if (gated) hipLaunchKernelGGL((shared_finish_kernel<float, true, NORM>), quarters, dim3(512), 0, s, a);    \
+            else       hipLaunchKernelGGL((shared_finish_kernel<float, false, NORM>), quarters, dim3(512), 0, s, a);   \
+        }                                                                                                           \
+    } while (0)
+    switch (a.norm) {
+    case FGE_NORM_NONE:      FGE_SHARED_FINISH(FGE_NORM_NONE); break;
+    case FGE_NORM_SOFTMAX:   FGE_SHARED_FINISH(FGE_NORM_SOFTMAX); break;
+    case FGE_NORM_LAYERNORM: FGE_SHARED_FINISH(FGE_NORM_LAYERNORM); break;
+    case FGE_NORM_RMSNORM:   FGE_SHARED_FINISH(FGE_NORM_RMSNORM); break;
+    default:                 FGE_SHARED_FINISH(FGE_NORM_LOGSUMEXP); break;
+    }
+#undef FGE_SHARED_FINISH
+    return hipGetLastError();
 }
 // The half-tile configurations (TILE_128x256, TILE_256x128), ordinary or cooperative launch;
 // defined in fge_tiles_half.hip.

@@ -99,6 +99,9 @@ template <> struct Mma<float> {
     }
 };
 
+// Partial sums of shared tiles: floats of a tile (256 x 256 sums) and of a wave's 32 rows x 64 columns.
+constexpr int SHARED_TILE = 256 * 256, SHARED_WAVE = 32 * 64;
+
 // FULL: M and N are multiples of BM and BN - the epilogue then runs without row or column guards.
 // Tiles of up to 64x128 are meant to run two workgroups per CU (second launch bound: waves per
 // SIMD), which caps their registers at 256.
@@ -111,7 +114,7 @@ template <> struct Mma<float> {
 // STAGES: 0 for the tile's usual number of stage buffers, else that many (see DEEP below).
 // ANY: N and the rows of the result are any number of elements (see TileEpilogue).
 // NORM_CT (>= 0): the row op, fixed at compile time.
-// SHARED: the last of an ordinary launch's tiles are shared between workgroups (see the end of the quadrants' loop).  A kernel of its
+// SHARED: the last of an ordinary launch's tiles are shared between workgroups (see the end of the quadrants' loop).  Kernels of their
 // own: the registers it takes cost launches that share nothing up to 1.5 % (8192 x 4096 x 4096, RMSNorm: gated 451.7 -> 457.7, E4M3 123.1 ->
 // 125.0 us).
 template <typename InT, typename OutT, int BM, int BN, int WAVES_M, int WAVES_N, bool COOP = false, bool FULL = false,
@@ -334,8 +337,6 @@ void tile_kernel(const TileArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) fsw[u] = ((2 * u + h) ^ swz(l32)) << 4;
 
-    unsigned mine = ~0u;                              // the groups of a wave's rows that this workgroup finishes
-    bool sums_ok = true;                              // (a shared tile whose other slices never came: false)
     floatx16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -652,70 +653,21 @@ void tile_kernel(const TileArgs a) {
         if (++kt == KT) break;
     }
     __syncthreads();                                  // the epilogue reuses the panel memory
-    // ---------------- shared tiles: the slices' sums meet.  The tiles of a launch that do not fill the chip once
-    // more (its last round) are each multiplied by S = `share` workgroups, a slice of K each (S = 2 or 4).  Of the four groups
-    // of 32 rows every wave has summed, slice s keeps group s (with two slices s and s + 2): it leaves the other groups' sums in the workspace, in the order the lanes hold them (every access of a
-    // wave is 1 KB in one piece), adds what the other slices left for its own, in the order of the slices, and takes
-    // only those rows through the epilogue - which is thereby shared out as well.  Stores and loads of the
-    // sums and of the marks are device-scope (the sc1 bit), as in the exchange of row statistics, and like that exchange this one
-    // needs the launch's last workgroups (no more of them than CUs) in flight at once and has a bounded wait.
-    // (A single workgroup that adds all slices' sums and finishes the tile alone waits 8 us for each 256 KB: 4173 x 3192 x 512
-    // 62 us in two slices and in three, 68 in four; shared out 50, 47 and 39.)
+    // ---------------- shared tiles: the tiles of a launch that do not fill the chip once more (its last round) are each
+    // multiplied by S = `share` workgroups, a slice of K each.  Their sums go to the workspace as the lanes hold them, by
+    // row blocks of 32 (every access of a wave is 1 KB in one piece), and shared_finish_kernel - the next launch on
+    // the stream, so nobody waits for anybody - adds them and runs the epilogue.
     if constexpr (SHARED) if (shared_at >= 0) {
-        constexpr int DEVICE = 16, GROUP_BYTES = BM * BN * 4 / MB;       // sc1
-        const int S = a.share;
-        const int at = wave * (NB * 4096) + lane * 16;
-        auto sums = [&](int sl, int g) __attribute__((always_inline)) {
-            return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char *>(a.part) + (int64_t)((shared_at * S + sl) * MB + g) * GROUP_BYTES,
-                                                     0, GROUP_BYTES, 0x00027000);
-        };
-        mine = S == 2 ? 5u << slice : 1u << slice;
-        static_for<0, MB>([&]<int g>() __attribute__((always_inline)) {
-            if (mine >> g & 1) return;
-            const auto dst = sums(slice, g);
+        float *part = a.part + (int64_t)(shared_at * a.share + slice) * SHARED_TILE + (wave_m * MB * WAVES_N + wave_n) * SHARED_WAVE + lane * 4;
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int k = 0; k < NB * 4; ++k) {
-                const floatx16 &v = acc[g][k / 4];
+                const floatx16 &v = acc[i][k / 4];
                 const int r = k % 4 * 4;
-                const u32x4 w = {as_u32(v[r]), as_u32(v[r + 1]), as_u32(v[r + 2]), as_u32(v[r + 3])};
-                __builtin_amdgcn_raw_buffer_store_b128(w, dst, at, k * 1024, DEVICE);
+                *reinterpret_cast<floatx4 *>(part + i * WAVES_N * SHARED_WAVE + k * 256) = floatx4{v[r], v[r + 1], v[r + 2], v[r + 3]};
             }
-        });
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        unsigned *marks = a.part_marks + shared_at * S;
-        if (tid == 0 && !(a.withhold && slice == 1 && shared_at == 0))
-            __hip_atomic_store(marks + slice, a.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (tid < 64) {
-            bool ok = true;
-            if (tid < S) {
-                unsigned spins = 0;
-                while (__hip_atomic_load(marks + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.gen) {
-                    __builtin_amdgcn_s_sleep(2);
-                    if (++spins > a.spin_limit) { ok = false; break; }
-                }
-            }
-            const bool all_ok = __all(ok);
-            if (!ok) *a.fault = 1;
-            if (tid == 0) xch[0].x = all_ok ? 0.0f : 1.0f;
-        }
-        __syncthreads();
-        sums_ok = xch[0].x == 0.0f;
-        for (int sl = 0; sl < S; ++sl) {
-            if (sl == slice) continue;
-            static_for<0, MB>([&]<int g>() __attribute__((always_inline)) {
-                if (!(mine >> g & 1)) return;
-                const auto src = sums(sl, g);
-#pragma unroll
-                for (int k = 0; k < NB * 4; ++k) {
-                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(src, at, k * 1024, DEVICE);
-                    floatx16 &v = acc[g][k / 4];
-                    const int r = k % 4 * 4;
-                    v[r] += as_f32(w.x); v[r + 1] += as_f32(w.y); v[r + 2] += as_f32(w.z); v[r + 3] += as_f32(w.w);
-                }
-            });
-        }
-        __syncthreads();                              // xch has been read
+        return;
     }
     } else if constexpr (KSHARE) {
     // ---------------- mainloop, small tiles with a long K: waves share out K, copies run three K tiles ahead, fragments one
@@ -992,48 +944,85 @@ void tile_kernel(const TileArgs a) {
         floatx16 gated[MB][1];
         dispatch_act(a.act, [&]<int ACT>() __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < MB; ++i) {
-                if (SHARED && !(mine >> i & 1)) continue;
+            for (int i = 0; i < MB; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     gated[i][0][r] = activate<ACT>(scale * acc[i][0][r] + bias1, a.lo, a.hi) * (scale * acc[i][1][r] + bias2);
-            }
         });
         TileArgs ag = a;
         ag.act = FGE_ACT_NONE; ag.alpha = 1.0f; ag.post = 1.0f; ag.b = nullptr;
-        using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false, false, -1, NORM_CT, false, false, false, SHARED>;
+        using Epi = TileEpilogue<OutT, MB, 1, WAVES_N, 32, false, false, COOP, false, false, -1, NORM_CT>;
         static_assert(WAVES_M * WAVES_N * Epi::PATCH_FLOATS * 4 <= NST * STAGE, "store patches fit the panels");
         Epi epi(ag, out, xch, reinterpret_cast<float *>(smem) + wave * Epi::PATCH_FLOATS, BM, z, m0, n0, tn,
                 wave_n, lane);
-        if constexpr (SHARED) epi.mine = mine;
         epi.template tile<NT>(gated, wave_m * WTM, rowblock, tid);
     } else {
-        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, NORM_CT, false, false, ANY, SHARED>;
+        using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 32, JOINT, false, COOP, FULL, false, -1, NORM_CT, false, false, ANY>;
         constexpr int PATCH_BYTES = KSHARE ? OWN : Epi::PATCH_FLOATS * 4;
         static_assert(WAVES_M * WAVES_N * PATCH_BYTES <= NST * STAGE && Epi::PATCH_FLOATS * 4 <= PATCH_BYTES, "store patches fit the panels");
         Epi epi(a, out, xch, reinterpret_cast<float *>(smem + wave * PATCH_BYTES), BM, z, m0, n0, tn,
                 wave_n, lane);
-        if constexpr (SHARED) epi.mine = mine;
         epi.template tile<NT>(acc, wave_m * WTM, rowblock, tid);
     }
-    if constexpr (SHARED) {
-        if (!sums_ok) {                               // incomplete sums: NaN in their place
-            const float nan = __builtin_nanf("");
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            for (int i = tid; i < BM * BNO; i += NT) {
-                const int row = m0 + i / BNO, col = n0 + i % BNO;
-                if ((mine >> (i / BNO % WTM / 32) & 1) && row < a.M && col < a.N) Store<OutT>::put(out + (int64_t)row * a.ldo + col, nan);
-            }
-            for (int i = tid; i < BM * WAVES_N; i += NT) {
-                const int row = m0 + i / WAVES_N;
-                if (a.norm == FGE_NORM_NONE || row >= a.M || !(mine >> (i / WAVES_N % WTM / 32) & 1)) continue;
-                if (a.tiles_n > 1)                        a.ws[(int64_t)row * (a.tiles_n * WAVES_N) + tn * WAVES_N + i % WAVES_N] = make_float2(nan, nan);
-                else if (a.norm == FGE_NORM_LOGSUMEXP)    a.aux[row] = nan;
-            }
-        }
-    }
     if constexpr (COOP) __syncthreads();             // patches are panel memory of the next tile
+    }
+}
+
+// Shared tiles (SHARED above), second launch: adds the slices' sums, in slice order, and runs the epilogue.  A quarter of a
+// tile - 64 rows - per workgroup, so that even a dozen tiles reach a good part of the chip; what bounds it is the sums' way
+// from the caches (64 KB per slice and quarter), all of them requested at once.
+template <typename OutT, bool GATED, int NORM_CT>
+__global__ __launch_bounds__(512) void shared_finish_kernel(const TileArgs a) {
+    constexpr int WAVES_N = 4, NB = 2, BM = 64, NT = 512;
+    using Epi = TileEpilogue<OutT, 1, GATED ? 1 : NB, WAVES_N, 32, false, false, false, false, false, -1, NORM_CT>;
+    __shared__ __attribute__((aligned(16))) float patches[8 * Epi::PATCH_FLOATS];
+    __shared__ __attribute__((aligned(16))) float2 xch[2 * BM * WAVES_N];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
+    const int at = blockIdx.x >> 2, quarter = blockIdx.x & 3;
+    int tm, tn;
+    tile_coords(a.share_from + at, a.tiles_m, a.tiles_n, a.group_m, tm, tn);
+    const int m0 = tm * 256 + quarter * BM, n0 = tn * (GATED ? 128 : 256);
+    if (m0 >= a.M) return;
+    const float *part = a.part + (int64_t)at * a.share * SHARED_TILE + ((quarter * 2 + wave_m) * WAVES_N + wave_n) * SHARED_WAVE + lane * 4;
+    floatx16 acc[1][NB];
+    auto sum = [&]<int S>() __attribute__((always_inline)) {
+        floatx4 v[S][NB * 4];
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int k = 0; k < NB * 4; ++k) v[s][k] = *reinterpret_cast<const floatx4 *>(part + (int64_t)s * SHARED_TILE + k * 256);
+#pragma unroll
+        for (int k = 0; k < NB * 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float x = v[0][k][e];
+#pragma unroll
+                for (int s = 1; s < S; ++s) x += v[s][k][e];
+                acc[0][k / 4][k % 4 * 4 + e] = x;
+            }
+    };
+    if (a.share == 2) sum.template operator()<2>();
+    else              sum.template operator()<4>();
+    OutT *out = reinterpret_cast<OutT *>(a.out);
+    float *patch = patches + wave * Epi::PATCH_FLOATS;
+    if constexpr (GATED) {
+        const int col = n0 + wave_n * 32 + (lane & 31);
+        const float scale = a.post * a.alpha;
+        const float bias1 = (a.b != nullptr && col < a.N) ? a.post * a.b[col] : 0.0f;
+        const float bias2 = (a.b2 != nullptr && col < a.N) ? a.post * a.b2[col] : 0.0f;
+        floatx16 gated[1][1];
+        dispatch_act(a.act, [&]<int ACT>() __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                gated[0][0][r] = activate<ACT>(scale * acc[0][0][r] + bias1, a.lo, a.hi) * (scale * acc[0][1][r] + bias2);
+        });
+        TileArgs ag = a;
+        ag.act = FGE_ACT_NONE; ag.alpha = 1.0f; ag.post = 1.0f; ag.b = nullptr;
+        Epi epi(ag, out, xch, patch, BM, 0, m0, n0, tn, wave_n, lane);
+        epi.template tile<NT>(gated, wave_m * 32, 0, tid);
+    } else {
+        Epi epi(a, out, xch, patch, BM, 0, m0, n0, tn, wave_n, lane);
+        epi.template tile<NT>(acc, wave_m * 32, 0, tid);
     }
 }
 

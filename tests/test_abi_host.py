@@ -331,3 +331,14 @@ def test_tiles_that_exchange_row_statistics_are_not_shared(dt, norm):
             if exchanged:
                 assert B.fge_workspace_bytes(True, 1, norm, p) == B.fge_workspace_bytes(True, 1, norm, plain)
                 assert B.fge_tile_name(True, 1, norm, p) == B.fge_tile_name(True, 1, norm, plain)
+
+
+def test_calls_without_row_op_wait_for_no_other_workgroup():
+    """No fault word, with whatever workspace: their launches, shared tiles included, depend on nothing in flight beside them."""
+    for dt in (1, 2, 3):
+        for M, K, N in ((8192, 4096, 4608), (4173, 3200, 512), (1000, 8192, 8192), (300, 4096, 4096), (65, 8192, 8192)):
+            for flags in (0, (3 + 1) << 8):
+                p = _params(M=M, N=N, K=K, ldx=K, ldw=K, ldo=N, in_dtype=dt, out_dtype=1 if dt == 3 else dt, flags=flags)
+                assert B.fge_fault_word_offset(1, 0, p) is None
+                p.workspace, p.workspace_bytes = FAKE, B.fge_workspace_bytes(True, 1, 0, p)
+                assert B.fge_fault_word_offset(1, 0, p) is None
