@@ -283,16 +283,6 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
     return TILE_64x64;
 }
 
-// sharing: left-over tiles of 256x256 may be shared (see plan_share).  With a row of at least 8 KB and few of them (a
-// quarter of the CUs: up to four slices) that makes 256x256 tiles the better choice wherever there is a full round of them.  Without a
-// row op only: tiles that exchange row statistics are not shared.
-bool prefer_shared(const Problem &pr, int in_dtype, int norm) {
-    if (norm != FGE_NORM_NONE) return false;
-    const int64_t tiles = (int64_t)((pr.M + 255) / 256) * ((pr.N + 255) / 256), left = tiles % num_cu();
-    return in_dtype != FGE_F32 && pr.batch == 1 && tiles > num_cu() && left > 0 && 4 * left <= num_cu() &&
-           (int64_t)pr.K * (int64_t)esize(in_dtype) >= 8192;
-}
-
 // fp32 rows of 65 to 256 columns over K <= 64: where the narrow-K kernel (four or two waves across) takes the place of the general tiles.
 // Against two column tiles and their exchange it wins from its first rows on, against whole rows in one tile where the
 // output stream is long (us, general tiles -> narrow-K; K = 44: 131072 x 252 RMSNorm 66.4 -> 41.4, 45815 x 200 softmax 30.8 -> 20.4, no row op
@@ -321,9 +311,6 @@ Plan make_plan(const fge_params *p, int norm, bool two_pass = false, int force_t
               : forced_tile(p) >= 0 ? forced_tile(p)
                                     : pick_tile(pr, p->in_dtype, norm, (p->flags & FGE_FLAG_IEEE_FP32) != 0,
                                                 !(p->flags & FGE_FLAG_NO_TABLE));
-    if (force_tile < 0 && forced_tile(p) < 0 && !two_pass && !(p->flags & (FGE_FLAG_TWO_PASS | FGE_FLAG_NO_SPLIT_K)) &&
-        prefer_shared(pr, p->in_dtype, norm))
-        pl.tile = TILE_256x256;
     if (force_tile < 0 && forced_tile(p) < 0 && g_out_rows == OUT_ALIGNED && narrow_rows(pr, p->in_dtype, norm, (p->flags & FGE_FLAG_IEEE_FP32) != 0))
         pl.tile = TILE_PANEL;
     // 16- and 8-bit 128x128 tiles, no more of them than CUs (however the tile was chosen): the form

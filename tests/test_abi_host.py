@@ -322,7 +322,7 @@ def test_tiles_that_exchange_row_statistics_are_not_shared(dt, norm):
     """Row blocks finished inside the tile kernel (a fault word is named) behind whole rounds of 256x256 tiles: no room for partial
     sums is asked for, whatever is left over, and the tile is the one that is taken without sharing."""
     FLAG_256 = (3 + 1) << 8
-    for M, K, N in ((4300, 2064, 4096), (4173, 8192, 4096), (6235, 6096, 3616), (8192, 4096, 4608)):
+    for M, K, N in ((4300, 2064, 4096), (4173, 4096, 4096), (4173, 8192, 4096), (6235, 6096, 3616), (8192, 4096, 4608)):
         q = dict(M=M, N=N, K=K, ldx=K, ldw=K, ldo=N, in_dtype=dt, out_dtype=1 if dt == 3 else dt)
         for flags in (0, FLAG_256):
             p, plain = _params(**q, flags=flags), _params(**q, flags=flags | B.FLAG_NO_SPLIT_K)
