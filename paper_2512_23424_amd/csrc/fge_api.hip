@@ -285,8 +285,8 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
 
 // fp32 rows of 65 to 256 columns over K <= 64: where the narrow-K kernel (four or two waves across) takes the place of the general tiles.
 // Against two column tiles and their exchange it wins from its first rows on, against whole rows in one tile where the
-// output stream is long (us, general tiles -> narrow-K; K = 44: 131072 x 252 RMSNorm 66.4 -> 41.4, 45815 x 200 softmax 30.8 -> 20.4, no row op
-// 18.1 -> 14.5, 9000 x 128 softmax 13.1 -> 8.9).  Elsewhere it does not: no row op, 9000 x 252 7.2 -> 7.7 (K = 64: 9.5); rows of up
+// output stream is long (us, general tiles -> narrow-K; K = 44: 131072 x 252 RMSNorm 66.4 -> 42.7, 45815 x 200 softmax 30.8 -> 20.4, no row op
+// 18.1 -> 15.4, 9000 x 128 softmax 13.1 -> 8.7).  Elsewhere it does not: no row op, 9000 x 252 7.2 -> 7.7 (K = 64: 9.5); rows of up
 // to 128 columns in one 128x128 tile, 45815 x 128 softmax 15.3 -> 15.8, 131072 x 96 over K = 16 22.7 -> 25.6 (over 44 they gain again).
 bool narrow_rows(const Problem &pr, int in_dtype, int norm, bool ieee_fp32) {
     if (in_dtype != FGE_F32 || ieee_fp32 || pr.K > 64 || pr.N <= 64 || pr.N > 256 || pr.batch != 1 || pr.M < PANEL_MIN_ROWS) return false;

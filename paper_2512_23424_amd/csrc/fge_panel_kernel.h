@@ -1,5 +1,5 @@
 // Narrow-K whole-row kernel for fp32 operands: K <= 64, N <= 512, many rows.  (What follows describes rows of
-// 257 to 512 columns; for narrower ones see PanelShape.)
+// 257 to 512 columns; for narrower ones see PanelShape and its FOLD.)
 //
 // Such a problem is bound by the output stream (every row reads K*4 bytes and writes N*4), so
 // the kernel is organised around HBM, not around the matrix cores:
@@ -48,6 +48,10 @@ __device__ __forceinline__ void mfma_bf16(const u32x4 &a, const u32x4 &b, floatx
 template <int WAVES_N_> struct PanelShape {
     static constexpr int WAVES_N = WAVES_N_, WAVES_M = 8 / WAVES_N, MB = WAVES_N == 8 ? 2 : 1, NB = 2, KMAX = 64;
     static constexpr int BM = WAVES_M * MB * 32, BN = WAVES_N * 64, THREADS = 512;
+    // Scale and bias folded into W and the accumulators' start.  Accumulators that start from a large bias round every one of
+    // their 12 sums at its magnitude, so narrower rows, whose general tiles add it once at the end, do as those do (a
+    // common bias of 100, LayerNorm: 2.9 times the error folded).
+    static constexpr bool FOLD = WAVES_N == 8;
 };
 
 // FULL: M is a multiple of BM and N == BN, so the epilogue needs no row or column guards.
@@ -64,7 +68,7 @@ void panel_kernel(const TileArgs a) {
     constexpr int SROWB = 128;                        // LDS bytes per row of a bf16 image: 64 values
     constexpr int SIMG = BM * SROWB;                  // 8 KB; an X buffer is the image of the high
     constexpr int XBUF = 2 * SIMG;                    // parts followed by the image of the low parts
-    using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 16, false, false, false, FULL, STREAM, ACT_CT, NORM_CT, BOUNDED_CT, true>;
+    using Epi = TileEpilogue<OutT, MB, NB, WAVES_N, 16, false, false, false, FULL, STREAM, ACT_CT, NORM_CT, BOUNDED_CT, Shape::FOLD>;
     static_assert(NT == 512 && BM % 64 == 0, "a thread per 8 values of k of a row, 64 rows at a time");
 
     __shared__ __attribute__((aligned(16))) unsigned char xs[2 * XBUF];
@@ -81,15 +85,15 @@ void panel_kernel(const TileArgs a) {
 
     // ---------------- W fragments of this wave's 64 columns, split once, kept in registers
     // fragment (j, t): column wave_n*64 + j*32 + l32, k = 16t + 8h .. +7
-    // scaled by post*alpha on the way in; the accumulators start from post*b (column l32 of block j
+    // FOLD: scaled by post*alpha on the way in; the accumulators start from post*b (column l32 of block j
     // in every register of the block), so that they end as post*(alpha*x.w + b)
-    const float wscale = a.post * a.alpha;
+    const float wscale = Shape::FOLD ? a.post * a.alpha : 1.0f;
     u32x4 whi[NB][4], wlo[NB][4];
     float binit[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int col = wave_n * WTN + j * 32 + l32;
-        binit[j] = (a.b != nullptr && col < a.N) ? a.post * a.b[col] : 0.0f;
+        binit[j] = (Shape::FOLD && a.b != nullptr && col < a.N) ? a.post * a.b[col] : 0.0f;
         const float *wr = W + (int64_t)min(col, a.w_rows - 1) * a.ldw;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {

@@ -8,6 +8,7 @@ from tests import _harness as H
 
 pytestmark = pytest.mark.gpu
 FLAG_PANEL = (4 + 1) << 8                   # FGE_FLAG_TILE(FGE_TILE_PANEL)
+FLAG_64 = (0 + 1) << 8                      # FGE_FLAG_TILE(FGE_TILE_64x64)
 
 
 @pytest.mark.parametrize("out", [I.F32, I.BF16])
@@ -35,3 +36,21 @@ def test_row_operations(norm, act):
         ref, raux = H.oracle_chain(w, t)
         got, gaux = H.run_gpu(w, t, "fused")
         H.check(w, got, gaux, ref, raux, "narrow rows")
+
+
+@pytest.mark.parametrize("norm", [I.NORM_NONE, I.NORM_LAYERNORM])
+@pytest.mark.parametrize("M,K,N", [(40000, 64, 252), (33000, 36, 192), (4100, 64, 128)])
+def test_a_large_bias_costs_no_precision(norm, M, K, N):
+    """A bias of 100 on every column and an uneven scale: the error is that of the general tiles, which add the bias once.  (Both errors are
+    sums of the same kind over 500000 values and more; their ratio is 1 within a few per cent, and 2.9 where every partial sum
+    is rounded at the bias's magnitude.)"""
+    w = I.Workload(name="bias", M=M, K=K, N=N, act=I.ACT_NONE, norm=norm, alpha=0.7, post_scale=1.3, eps=1e-5,
+                   dist={"X": ("normal", 0.0, 1.0), "W": ("normal", 0.0, K ** -0.5), "b": ("uniform", 99.5, 100.5),
+                         "gamma": ("normal", 1.0, 0.1), "beta": ("normal", 0.0, 0.1)})
+    t = I.generate(w)
+    ref, _ = H.oracle_chain(w, t)
+    errors = []
+    for flags in (FLAG_PANEL, FLAG_64):
+        got, _ = H.run_gpu(w, t, "fused", flags=flags)
+        errors.append(float(np.sqrt(np.mean((got - ref) ** 2))))
+    assert errors[0] <= 1.2 * errors[1], errors
