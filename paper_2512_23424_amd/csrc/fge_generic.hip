@@ -542,16 +542,17 @@ hipError_t launch_generic_row(int src_dtype, int out_dtype, hipStream_t s, const
 #undef FGE_ROW
         return hipGetLastError();
     }
-    // rows that registers hold: one wave per row of up to 2048 (fp32: 1024) columns where there are enough rows for that, else four
-    if (a.N <= 8192 && rows <= INT32_MAX && (src_dtype == FGE_F32 || src_dtype == out_dtype)) {
+    // rows that registers hold: one wave per row of up to 2048 (fp32: 1024) columns where there are enough rows for that, else four -
+    // a workgroup of 256 per row, up to the 2^32 work items that the runtime launches
+    const bool one_wave = rows >= 1024 && a.N <= (out_dtype == FGE_F32 ? 1024 : 2048);
+    if (a.N <= 8192 && (one_wave || rows < (1 << 24)) && (src_dtype == FGE_F32 || src_dtype == out_dtype)) {
 #define FGE_ANY_ROW(ST, OT, W, C) hipLaunchKernelGGL((any_row_kernel<ST, OT, W, C>), dim3((unsigned)(W == 1 ? (rows + 3) / 4 : rows)), block, 0, s, a)
 #define FGE_ANY_ROWS(ST, OT)                                                                               \
         do {                                                                                               \
             constexpr int PER = 256 * Store<OT>::CW;                                                       \
-            const bool waves = rows >= 1024;                                                               \
-            if (waves && a.N <= PER / 4)          FGE_ANY_ROW(ST, OT, 1, 1);                               \
-            else if (waves && a.N <= PER / 2)     FGE_ANY_ROW(ST, OT, 1, 2);                               \
-            else if (waves && a.N <= PER)         FGE_ANY_ROW(ST, OT, 1, 4);                               \
+            if (one_wave && a.N <= PER / 4)       FGE_ANY_ROW(ST, OT, 1, 1);                               \
+            else if (one_wave && a.N <= PER / 2)  FGE_ANY_ROW(ST, OT, 1, 2);                               \
+            else if (one_wave)                    FGE_ANY_ROW(ST, OT, 1, 4);                               \
             else if (a.N <= PER)                  FGE_ANY_ROW(ST, OT, 4, 1);                               \
             else if (a.N <= 2 * PER)              FGE_ANY_ROW(ST, OT, 4, 2);                               \
             else if (a.N <= 4 * PER)              FGE_ANY_ROW(ST, OT, 4, 4);                               \

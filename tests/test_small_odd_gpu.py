@@ -70,3 +70,25 @@ def test_row_operations_of_odd_width(dt, norm):
             assert float(((out.double() - ref).abs() / den).max()) <= tol, (M, N, inplace)
             if aux is not None:
                 assert float((aux.double() - raux).abs().max()) <= 1e-4
+
+
+def test_more_rows_than_workgroups_of_four_waves():
+    """2^24 rows of more columns than one wave takes: a workgroup of 256 per row would pass the 2^32 work items a launch may have."""
+    M, N = 1 << 24, 2049
+    if torch.cuda.mem_get_info()[0] < M * N * 2 + (4 << 30):
+        pytest.skip("needs 73 GB of device memory")
+    A = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    A.fill_(0.5)
+    rows = torch.tensor([0, 1, 12345, (1 << 23) + 7, M - 2, M - 1], device="cuda")
+    A[rows] = (torch.randn(len(rows), N, generator=torch.Generator(device="cuda").manual_seed(5), device="cuda") * 2).to(torch.bfloat16)
+    ref = torch.logsumexp(A[rows].double(), 1)
+    aux = torch.full((M,), float("nan"), device="cuda")
+    p = B.make_params(None, None, A, aux_out=aux)
+    B.fge_row_op(A, I.NORM_LOGSUMEXP, p, A)
+    torch.cuda.synchronize()
+    assert float((aux[rows].double() - ref).abs().max()) <= 1e-4          # fp32 arithmetic on values near 10
+    others = torch.ones(M, dtype=torch.bool, device="cuda")
+    others[rows] = False
+    assert float((aux[others] - (0.5 + float(np.log(N)))).abs().max()) <= 1e-4
+    del A
+    torch.cuda.empty_cache()
