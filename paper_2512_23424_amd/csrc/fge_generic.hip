@@ -119,6 +119,8 @@ __global__ __launch_bounds__(256) void any_row_kernel(const GenArgs a) {
     if (rowg >= (int64_t)a.batch * a.M) return;                       // wave-uniform (WAVES = 4: never)
     const SrcT *src = row_ptr<SrcT>(a.X, rowg, a.M, a.ldx, a.bsx);
     OutT *out = const_cast<OutT *>(row_ptr<OutT>(a.dst, rowg, a.M, a.ldd, a.bsd));
+    const bool in_place = reinterpret_cast<const void *>(src) == reinterpret_cast<const void *>(out);
+    if (a.norm == FGE_NORM_NONE && in_place) return;                  // nothing to do: no value is written back
     const float inv_n = 1.0f / (float)a.N;
     int turn = 0;
     auto reduce = [&]<typename Op>(Op, float v) __attribute__((always_inline)) {
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(256) void any_row_kernel(const GenArgs a) {
             each([&](float &x, int) __attribute__((always_inline)) { s += fast_exp(x - m); });
             s = reduce(OpSum{}, s);
             if (member == 0) a.aux[rowg] = m + __logf(s);
-            if (reinterpret_cast<const void *>(src) == reinterpret_cast<const void *>(out)) return;
+            if (in_place) return;
         }
     } else if (a.norm == FGE_NORM_LAYERNORM) {
         float s = 0.0f, d2 = 0.0f;

@@ -92,3 +92,13 @@ def test_more_rows_than_workgroups_of_four_waves():
     assert float((aux[others] - (0.5 + float(np.log(N)))).abs().max()) <= 1e-4
     del A
     torch.cuda.empty_cache()
+
+
+def test_no_row_op_in_place_leaves_every_byte():
+    """Signalling NaNs included: there is nothing to write back."""
+    A = torch.arange(-(1 << 15), 1 << 15, device="cuda").to(torch.int16)[:4 * 16381].reshape(4, 16381)[:, :4095].contiguous()
+    A[1, 7] = 0x7F81                        # a signalling NaN in bf16 and in fp16
+    out = A.clone().view(torch.bfloat16)
+    B.fge_row_op(out, I.NORM_NONE, B.make_params(None, None, out), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), A)
