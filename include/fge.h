@@ -301,8 +301,8 @@ const char *fge_status_string(int status);
 int fge_last_hip_error(void);
 /* Name of the tile configuration the fused path picks for these arguments (static string,
  * e.g. "256x256_w2x4"); NULL on invalid arguments.  For reports and tests.  (Of a product the few-row
- * kernel takes, see fge_few_rows, and of fp32 rows of up to 256 columns over K <= 64, which the narrow-K kernel
- * takes where it is faster: the configuration they would run on otherwise.) */
+ * kernel takes, see fge_few_rows: the configuration it would run on otherwise.)  A workspace in p that lacks the room
+ * a configuration needs counts; none at all is taken for one of the size asked for. */
 const char *fge_tile_name(int fused, int act, int norm, const fge_params *p);
 
 #ifdef __cplusplus

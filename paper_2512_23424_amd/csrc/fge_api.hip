@@ -1542,7 +1542,10 @@ size_t fge_gated_workspace_bytes(int fused, int act, int norm, const fge_params 
 const char *fge_gated_tile_name(int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return nullptr;
     if (!gated_fast(p, norm)) return "unfused_sequence";
-    return !plan_shared_all(p, norm, true).use && gated_small(p, norm).use ? "partial_products_then_gate" : tile_info(TILE_GATED).name;
+    const SharedAll all = plan_shared_all(p, norm, true);
+    const GatedSmall gs = gated_small(p, norm);
+    const auto room = [&](size_t bytes) { return !(p->workspace && p->workspace_bytes < bytes); };     // (none named: the size asked for)
+    return !(all.use && room(all.bytes())) && gs.use && room(gs.bytes()) ? "partial_products_then_gate" : tile_info(TILE_GATED).name;
 }
 
 size_t fge_fault_word_offset(int act, int norm, const fge_params *p) {
@@ -1584,10 +1587,11 @@ const char *fge_tile_name(int fused, int act, int norm, const fge_params *p) {
     if (check_common(p, act, norm, true)) return nullptr;
     const Plan pl = make_plan(p, fused ? norm : FGE_NORM_NONE);
     if (pl.generic) return fused && plan_repack(p, norm).use ? "repacked_operands" : "generic32x32_scalar";
-    // (rows of up to 256 columns over a short K go by the name of the general tile whose place the narrow-K kernel takes)
-    const bool narrow = pl.tile == TILE_PANEL && p->N <= 256 && forced_tile(p) < 0;
-    const TileInfo &ti = tile_info(fused && plan_shared_all(p, norm, false).use ? (int)TILE_256x256
-                                   : narrow ? rule_tile(pl.pr, p->in_dtype, false) : pl.tile);
+    if (pl.tile == TILE_PANEL)       // (eight, four or two waves across: see launch_panel_f32)
+        return pl.pr.N > 256 ? tile_info(TILE_PANEL).name : pl.pr.N > 128 ? "panel64x256_w2x4_splitbf16" : "panel128x128_w4x2_splitbf16";
+    // (no workspace named: one of the size asked for)
+    const SharedAll all = fused ? plan_shared_all(p, norm, false) : SharedAll{};
+    const TileInfo &ti = tile_info(all.use && !(p->workspace && p->workspace_bytes < all.bytes()) ? (int)TILE_256x256 : pl.tile);
     return p->in_dtype == FGE_F32 && !(p->flags & FGE_FLAG_IEEE_FP32) ? ti.name_split : ti.name;
 }
 

@@ -116,8 +116,9 @@ def test_status_strings_and_tile_names():
     assert B.fge_tile_name(True, 5, 4, _params(M=262144, N=512, ldo=512, flags=B.FLAG_IEEE_FP32)) == "64x128_w2x2"
     assert B.fge_tile_name(True, 5, 4, _params(M=262144, N=512, ldo=512)) == "panel64x512_w1x8_splitbf16"
     assert B.fge_tile_name(True, 5, 4, _params(M=1000, N=512, ldo=512)) == "64x64_w2x2_splitbf16"     # few tiles
-    assert B.fge_tile_name(True, 5, 4, _params(M=262144, N=256, ldo=256)) == "128x128_w2x2_splitbf16"  # row too narrow for it
-    assert B.fge_tile_name(True, 5, 4, _params(M=8192, N=256, ldo=256)) == "64x64_w2x2_splitbf16"      # fewer 128x128 tiles than CUs
+    assert B.fge_tile_name(True, 5, 4, _params(M=262144, N=256, ldo=256)) == "panel64x256_w2x4_splitbf16"     # four waves across
+    assert B.fge_tile_name(True, 5, 4, _params(M=262144, N=256, K=68, ldx=68, ldw=68, ldo=256)) == "128x128_w2x2_splitbf16"  # K too long for it
+    assert B.fge_tile_name(True, 5, 4, _params(M=8192, N=256, K=68, ldx=68, ldw=68, ldo=256)) == "64x64_w2x2_splitbf16"      # fewer 128x128 tiles than CUs
     huge = _params(M=4096, N=4096, K=4096, ldx=4096, ldw=4096, ldo=4096)
     assert B.fge_tile_name(True, 2, 2, huge) == "128x128_w2x2_splitbf16"
     huge.flags = B.FLAG_IEEE_FP32
@@ -342,3 +343,35 @@ def test_calls_without_row_op_wait_for_no_other_workgroup():
                 assert B.fge_fault_word_offset(1, 0, p) is None
                 p.workspace, p.workspace_bytes = FAKE, B.fge_workspace_bytes(True, 1, 0, p)
                 assert B.fge_fault_word_offset(1, 0, p) is None
+
+
+def test_which_rows_the_narrow_k_kernel_takes():
+    """fp32, K <= 64: both sides of every line of the choice, by the name that is reported."""
+    def name(M, N, K=44, norm=2, flags=0):
+        n = B.fge_tile_name(True, 1, norm, _params(M=M, N=N, K=K, ldx=K, ldw=K, ldo=N, flags=flags))
+        return n.split("_")[0] if n.startswith("panel") else "general"
+    assert name(5000, 260) == name(5000, 512) == "panel64x512" and name(5000, 516) == "general"
+    assert name(5000, 256) == name(4096, 132) == "panel64x256" and name(4095, 256) == "general"
+    assert name(5000, 128) == name(5000, 68) == "panel128x128" and name(5000, 64) == "general"
+    assert name(5000, 256, K=64) == "panel64x256" and name(5000, 256, K=68) == "general"
+    assert name(5000, 256, flags=B.FLAG_IEEE_FP32) == "general"
+    # no row op: from 32768 rows of more than 128 columns on
+    assert name(32768, 256, norm=0) == "panel64x256" and name(32767, 256, norm=0) == "general"
+    # up to 128 columns: with a row op below 160 tiles of 128 rows; from 131072 rows on if K > 32
+    assert name(159 * 128, 128) == "panel128x128" and name(159 * 128 + 1, 128) == "general"
+    assert name(131072, 128) == name(131072, 128, norm=0) == "panel128x128" and name(131071, 128) == "general"
+    assert name(131072, 128, K=32) == "general" and name(131072, 128, K=36) == "panel128x128"
+
+
+def test_names_follow_the_workspace():
+    """A call all of whose tiles would be shared, and a gated one, with the room asked for and without."""
+    p = _params(M=1500, N=3072, K=8192, ldx=8192, ldw=8192, ldo=3072, in_dtype=1, out_dtype=1)
+    assert B.fge_tile_name(True, 1, 0, p) == "256x256_w2x4"
+    p.workspace, p.workspace_bytes = FAKE, B.fge_workspace_bytes(True, 1, 0, p)
+    assert B.fge_tile_name(True, 1, 0, p) == "256x256_w2x4"
+    p.workspace_bytes -= 256
+    assert B.fge_tile_name(True, 1, 0, p) == "128x128_w2x2"
+    p = _params(M=256, N=3072, K=4096, ldx=4096, ldw=4096, ldo=3072, in_dtype=1, out_dtype=1)
+    assert B.fge_gated_tile_name(4, 0, p) == "gated256x128_w2x4"
+    p.workspace, p.workspace_bytes = FAKE, B.fge_gated_workspace_bytes(True, 4, 0, p) - 256
+    assert B.fge_gated_tile_name(4, 0, p) == "partial_products_then_gate"
