@@ -278,7 +278,9 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
         return TILE_256x256;
     // 128x128 tiles from 5/8 of the CUs on: one round of them (three stage buffers, see tile_args)
     // then beats the 64x64 tiles' several (640 x 4096 x 4096: 48.5 against 58.3 us; at 512 rows,
-    // 128 tiles, the 64x64 tiles still won with 38 us - both before either shared out K over its waves, 29 us now)
+    // 128 tiles, the 64x64 tiles still won with 38 us - both before either shared out K over its waves, 29 us now) - and
+    // from half of them on where the 64x64 tiles would be more than two per CU (130 to 159 of the 128x128 tiles, K of 256 to
+    // 8192, with and without a row op: 0.71 to 0.94 of the time in 16 bits, 0.73 to 1.01 in 8; 1152 x 2048 x 2048 RMSNorm: bf16 and E4M3 0.85 and 0.83)
     if (fits(TILE_128x128) && (count(TILE_128x128) * 8 >= num_cu() * 5 || count(TILE_64x64) > 2 * num_cu())) return TILE_128x128;
     return TILE_64x64;
 }
