@@ -23,27 +23,30 @@ template <typename T> __device__ __forceinline__ const T *row_ptr(const void *ba
 }
 
 // A 32x32 tile of outputs per workgroup.  Small problems of odd extents are its work, so what bounds it is a chain of
-// memory latencies along K: 128 k are fetched at a time, one K tile ahead in registers, and the four waves share out each
+// memory latencies along K: KT = 128 k are fetched at a time, one K tile ahead in registers, and the four waves share out each
 // K tile (32 k each, fp32 matrix instruction) and add their sums in LDS.  (32 k at a time, nothing
 // ahead, an FMA per value read from LDS: 365 x 429 x 32 SiLU LayerNorm 35.8 us, now 12.1;
-// 17 x 500 x 33 34.9 and 8.7, 40 x 64 x 47 LayerNorm 9.9 and 8.8.)
-template <typename InT, typename DstT>
+// 17 x 500 x 33 34.9 and 8.7, 40 x 64 x 47 LayerNorm 9.9 and 8.8.)  A K of up to 32 or 64 is one tile of that many k: staging 128
+// cost calls of a few microseconds up to a third (bf16 2 x 17 x 47 logsumexp, with 128 -> now -> with that former kernel: 7.3, 5.2, 5.6).
+template <typename InT, typename DstT, int KT>
 __global__ __launch_bounds__(256) void generic_gemm_kernel(const GenArgs a) {
-    constexpr int T = 32, KT = 128, LD = KT + 4, RPT = T * KT / 256;     // LD: rows 16-byte aligned, four banks apart
-    __shared__ __attribute__((aligned(16))) float xs[T * LD], ws[T * LD];
+    constexpr int T = 32, LD = KT + 4, STEP = 256 / KT, RPT = T / STEP;   // LD: rows 16-byte aligned, four banks apart
+    constexpr int PANELS = 2 * T * LD, SUMS = 4 * T * T;
+    __shared__ __attribute__((aligned(16))) float xs[PANELS > SUMS ? PANELS : SUMS];
+    float *ws = xs + T * LD;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
     const int n0 = blockIdx.x * T, m0 = blockIdx.y * T, z = blockIdx.z;
     const InT *X = reinterpret_cast<const InT *>(a.X) + (int64_t)z * a.bsx;
     const InT *W = reinterpret_cast<const InT *>(a.W);
-    const int lk = tid & (KT - 1), lr = tid >> 7;                    // this thread's k and first row of a K tile
-    float xr[RPT], wr[RPT];
+    const int lk = tid & (KT - 1), lr = tid / KT;                    // this thread's k and first row of a K tile
+    InT xr[RPT], wr[RPT];                                            // as they lie in memory: a conversion behind each load would wait for it
     auto fetch = [&](int k0) __attribute__((always_inline)) {
         const int k = k0 + lk;
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-            const int r = lr + 2 * i;
-            xr[i] = (m0 + r < a.M && k < a.K) ? Store<InT>::get(X + (int64_t)(m0 + r) * a.ldx + k) : 0.0f;
-            wr[i] = (n0 + r < a.N && k < a.K) ? Store<InT>::get(W + (int64_t)(n0 + r) * a.ldw + k) : 0.0f;
+            const int r = lr + STEP * i;
+            xr[i] = (m0 + r < a.M && k < a.K) ? X[(int64_t)(m0 + r) * a.ldx + k] : InT{};
+            wr[i] = (n0 + r < a.N && k < a.K) ? W[(int64_t)(n0 + r) * a.ldw + k] : InT{};
         }
     };
     floatx16 acc;
@@ -53,19 +56,19 @@ __global__ __launch_bounds__(256) void generic_gemm_kernel(const GenArgs a) {
     for (int k0 = 0; k0 < a.K; k0 += KT) {
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-            xs[(lr + 2 * i) * LD + lk] = xr[i];
-            ws[(lr + 2 * i) * LD + lk] = wr[i];
+            xs[(lr + STEP * i) * LD + lk] = Store<InT>::get(&xr[i]);
+            ws[(lr + STEP * i) * LD + lk] = Store<InT>::get(&wr[i]);
         }
         __syncthreads();
         if (k0 + KT < a.K) fetch(k0 + KT);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {                                // lanes 0-31: k 8u .. 8u+3 of the wave's 32, lanes 32-63: the next four
-            const int at = l32 * LD + wave * 32 + u * 8 + h * 4;
+        for (int u = 0; u < KT / 32; ++u) {                          // lanes 0-31: k 8u .. 8u+3 of the wave's, lanes 32-63: the next four
+            const int at = l32 * LD + wave * (KT / 4) + u * 8 + h * 4;
             Mma<float>::run(*reinterpret_cast<const u32x4 *>(xs + at), *reinterpret_cast<const u32x4 *>(ws + at), acc);
         }
         __syncthreads();
     }
-    // the waves' sums: [wave][row][column], 32 floats a row, in xs (16 KB of its 16.5)
+    // the waves' sums: [wave][row][column], 32 floats a row, in the panels' place
 #pragma unroll
     for (int r = 0; r < 16; ++r) xs[wave * T * T + ((r >> 2) * 8 + h * 4 + (r & 3)) * T + l32] = acc[r];
     __syncthreads();
@@ -498,16 +501,23 @@ hipError_t launch_splitk_sum(int dst_dtype, hipStream_t s, const GenArgs &a) {
 
 hipError_t launch_generic_gemm(int in_dtype, int dst_dtype, hipStream_t s, const GenArgs &a) {
     const dim3 grid((unsigned)((a.N + 31) / 32), (unsigned)((a.M + 31) / 32), (unsigned)a.batch), block(256);
+#define FGE_GGK(InT, NarrowT, KT)                                                                      \
+    do {                                                                                               \
+        if (dst_dtype != FGE_F32) hipLaunchKernelGGL((generic_gemm_kernel<InT, NarrowT, KT>), grid, block, 0, s, a); \
+        else                      hipLaunchKernelGGL((generic_gemm_kernel<InT, float, KT>), grid, block, 0, s, a);   \
+    } while (0)
 #define FGE_GG(InT, NarrowT)                                                                           \
     do {                                                                                               \
-        if (dst_dtype != FGE_F32) hipLaunchKernelGGL((generic_gemm_kernel<InT, NarrowT>), grid, block, 0, s, a); \
-        else                      hipLaunchKernelGGL((generic_gemm_kernel<InT, float>), grid, block, 0, s, a);   \
+        if (a.K <= 32)      FGE_GGK(InT, NarrowT, 32);                                                 \
+        else if (a.K <= 64) FGE_GGK(InT, NarrowT, 64);                                                 \
+        else                FGE_GGK(InT, NarrowT, 128);                                                \
     } while (0)
     if (in_dtype == FGE_BF16)     FGE_GG(bf16_t, bf16_t);
     else if (in_dtype == FGE_F16) FGE_GG(f16_t, f16_t);
     else if (in_dtype == FGE_F8E4M3) FGE_GG(f8_t, bf16_t);
     else                          FGE_GG(float, bf16_t);
 #undef FGE_GG
+#undef FGE_GGK
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Small products of odd extents (element-granular product: 32x32 tiles, 128 k at a time, shared out by four waves): exact integers
+"""Small products of odd extents (element-granular product: 32x32 tiles, 128 k at a time or all of a K of up to 32 or 64, shared out by four waves): exact integers
 around the K tile and the waves' parts of it, around the output tile, and with strides."""
 import numpy as np
 import pytest
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dt", [I.F32, I.BF16, I.F16, I.F8E4M3])
 def test_exact_sums(dt):
     for M, N in ((1, 33), (31, 31), (33, 65), (70, 97)):
-        for K in (1, 3, 31, 33, 127, 129, 161, 255, 257, 429):
+        for K in (1, 3, 31, 32, 33, 63, 64, 65, 127, 129, 161, 255, 257, 429):
             w = I.Workload(name="odd", M=M, K=K, N=N, in_dtype=dt, out_dtype=I.F32, act=I.ACT_RELU,
                            dist={"X": ("int", -2, 2), "W": ("int", -2, 2), "b": ("int", -3, 3)})
             t = I.generate(w)
