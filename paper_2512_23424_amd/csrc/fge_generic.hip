@@ -5,8 +5,8 @@
 //
 //   generic_gemm_kernel : dst = act(post*(alpha*X.W^T + b))   32x32 tile, LDS staged, fp32 matrix instruction
 //   generic_act_kernel  : dst = act(src) [* second operand]   elementwise
-//   any_row_kernel      : out = rowop(src)                    rows of up to 8192 columns, in registers
-//   generic_row_kernel  : out = rowop(src)                    wider rows: one wave per row, passes over src
+//   any_row_kernel      : out = rowop(src)                    rows of up to 8192 columns but the shortest, in registers
+//   generic_row_kernel  : out = rowop(src)                    other rows: one wave per row, passes over src
 //   splitk_sum_kernel   : dst = act(post*(alpha*sum_s P_s + b))  the slices of a K-split product, summed in slice order
 //   pad_rows_kernel     : dense copy of a matrix with K padded by zeros to whole 16-byte chunks
 //                         (and zero rows appended): what makes an operand with odd extents or
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void generic_act_kernel(const GenArgs a) {
     });
 }
 
-// The same on rows that registers hold (up to 8192 columns): WAVES waves per row, NCH chunks of CW values per lane, loaded and
+// The same on rows that registers hold (see launch_generic_row): WAVES waves per row, NCH chunks of CW values per lane, loaded and
 // stored 16 bytes at a time at any alignment and read once.  (The kernel below reads a value at a time, three times over; us, with it
 // -> so, floor at a large copy's 5.8 TB/s: bf16 65536 x 4095 RMSNorm 520.6 -> 306.2 / 185, 65536 x 2047 softmax 356.7 -> 171.8 / 93, fp32 65536 x 2047
 // LayerNorm 436.9 -> 201.6 / 185, 9000 x 8191 RMSNorm 275.1 -> 110.7 / 102, f16 4000 x 8191 logsumexp 120.8 -> 34.5 / 23.  What is left in 16
@@ -148,8 +148,11 @@ __global__ __launch_bounds__(256) void any_row_kernel(const GenArgs a) {
                 Store<SrcT>::unpack(make_uint4(u.x, u.y, u.z, u.w), v[c] + l * Store<SrcT>::CW);
             }
         } else {
+            SrcT tail[CW];                                           // (converted behind all the loads: each conversion waits for its own)
 #pragma unroll
-            for (int e = 0; e < CW; ++e) v[c][e] = j0 + e < a.N ? Store<SrcT>::get(src + j0 + e) : 0.0f;
+            for (int e = 0; e < CW; ++e) tail[e] = j0 + e < a.N ? src[j0 + e] : SrcT{};
+#pragma unroll
+            for (int e = 0; e < CW; ++e) v[c][e] = Store<SrcT>::get(tail + e);
         }
     }
     auto each = [&](auto &&f) __attribute__((always_inline)) {           // f(value, column) for the row's own values
@@ -554,10 +557,17 @@ hipError_t launch_generic_row(int src_dtype, int out_dtype, hipStream_t s, const
 #undef FGE_ROW
         return hipGetLastError();
     }
-    // rows that registers hold: one wave per row of up to 2048 (fp32: 1024) columns where there are enough rows for that, else four -
-    // a workgroup of 256 per row, up to the 2^32 work items that the runtime launches
-    const bool one_wave = rows >= 1024 && a.N <= (out_dtype == FGE_F32 ? 1024 : 2048);
-    if (a.N <= 8192 && (one_wave || rows < (1 << 24)) && (src_dtype == FGE_F32 || src_dtype == out_dtype)) {
+    // rows that registers hold: one wave per row of up to 512 (fp32: 256) columns, and of up to 2048 (1024) where there are enough rows for
+    // that, else four - a workgroup of 256 per row, up to the 2^32 work items that the runtime launches.  Shorter rows, a few chunks of
+    // 16 bytes, leave most of a wave idle there and go to the kernel with a value per lane (us, it -> so; bf16 259888 x 21 RMSNorm 47.6 -> 96.8,
+    // 571 x 51 LayerNorm 2.5 -> 3.2, 300278 x 125 softmax 96.2 -> 133.6, f16 144010 x 153 softmax 59.9 -> 54.4, 75705 x 195 LayerNorm 38.0 -> 32.2;
+    // fp32 146555 x 63 RMSNorm 29.1 -> 37.7, 827238 x 75 softmax 320.6 -> 258.0).  RMSNorm, whose values the other kernel reads
+    // only twice, stays there longer (f16 195097 x 223 72.6 -> 89.8, bf16 211448 x 287 91.3 -> 99.7, fp32 997414 x 79 287.2 -> 326.6).
+    const int per_wave = out_dtype == FGE_F32 ? 1024 : 2048;
+    const bool rms = a.norm == FGE_NORM_RMSNORM;
+    const int least = out_dtype == FGE_F32 ? (rms ? 96 : 64) : (rms ? 320 : 192);
+    const bool one_wave = a.N <= per_wave / 4 || (rows >= 1024 && a.N <= per_wave);
+    if (a.N > least && a.N <= 8192 && (one_wave || rows < (1 << 24)) && (src_dtype == FGE_F32 || src_dtype == out_dtype)) {
 #define FGE_ANY_ROW(ST, OT, W, C) hipLaunchKernelGGL((any_row_kernel<ST, OT, W, C>), dim3((unsigned)(W == 1 ? (rows + 3) / 4 : rows)), block, 0, s, a)
 #define FGE_ANY_ROWS(ST, OT)                                                                               \
         do {                                                                                               \

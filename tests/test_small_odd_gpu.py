@@ -43,7 +43,7 @@ def test_row_operations_of_odd_width(dt, norm):
     many, out of place and in place."""
     td = H.tdtype(dt)
     g = torch.Generator(device="cuda").manual_seed(3)
-    for M, N in ((3, 1), (5, 255), (1030, 257), (1030, 511), (1500, 513), (1030, 1029), (40, 1025), (40, 2049), (9, 4097), (5, 8191)):
+    for M, N in ((3, 1), (40, 63), (1030, 65), (40, 97), (1030, 193), (40, 319), (1030, 321), (5, 255), (1030, 257), (1030, 511), (1500, 513), (1030, 1029), (40, 1025), (40, 2049), (9, 4097), (5, 8191)):
         A = (torch.randn(M, N, generator=g, device="cuda") * 2).to(td)
         gamma = 1 + 0.1 * torch.randn(N + 3, generator=g, device="cuda")[:N]
         beta = 0.1 * torch.randn(N + 3, generator=g, device="cuda")[:N]
