@@ -288,13 +288,23 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
 // fp32 rows of 65 to 256 columns over K <= 64: where the narrow-K kernel (four or two waves across) takes the place of the general tiles.
 // Against two column tiles and their exchange it wins from its first rows on, against whole rows in one tile where the
 // output stream is long (us, general tiles -> narrow-K; K = 44: 131072 x 252 RMSNorm 66.4 -> 42.7, 45815 x 200 softmax 30.8 -> 20.4, no row op
-// 18.1 -> 15.4, 9000 x 128 softmax 13.1 -> 8.7).  Elsewhere it does not: no row op, 9000 x 252 7.2 -> 7.7 (K = 64: 9.5); rows of up
-// to 128 columns in one 128x128 tile, 45815 x 128 softmax 15.3 -> 15.8, 131072 x 96 over K = 16 22.7 -> 25.6 (over 44 they gain again).
+// 18.1 -> 15.4, 9000 x 128 softmax 13.1 -> 8.7).  Elsewhere it does not (5136 calls in turn, K of 4 to 64; kernel over general tiles): no row op,
+// 32768 rows 1.06 to 1.12, 53000 to 62000 over K <= 32 1.00 to 1.07; over whole K tiles of the general kernels, K = 32 and 64, which they do not
+// mask: 16500 to 24576 rows of 192 to 256 columns 0.98 to 1.08, logsumexp to 8192 rows 1.00 to 1.19, the others over K = 64 to 5000 rows 0.92 to
+// 1.09; up to 128 columns, to 8192 rows 0.92 to 1.10 (K = 64 1.28), 20480 to 131071 in one 128x128 tile, 45815 x 128 softmax 15.3 -> 15.8, beyond them over
+// K = 64 with a row op 0.95 to 1.06, over K <= 32 131072 x 96 22.7 -> 25.6.
+// (Of the 3950 such calls that take the kernel by these lines one loses 3 %.)
 bool narrow_rows(const Problem &pr, int in_dtype, int norm, bool ieee_fp32) {
     if (in_dtype != FGE_F32 || ieee_fp32 || pr.K > 64 || pr.N <= 64 || pr.N > 256 || pr.batch != 1 || pr.M < PANEL_MIN_ROWS) return false;
-    if (pr.N > 128) return norm != FGE_NORM_NONE || pr.M >= 32768;
+    const bool lse = norm == FGE_NORM_LOGSUMEXP, full = pr.K == 64;
+    if (pr.N > 128) {
+        if (norm == FGE_NORM_NONE) return pr.M > 65536 || (pr.K > 32 && pr.M > 32768);
+        if (pr.K % 32 != 0) return true;
+        return pr.M > (lse ? 8192 : full ? 5000 : 0) && (pr.M <= 16384 || pr.M > 24576);
+    }
     const int64_t whole = (pr.M + 127) / 128;          // 128x128 tiles; below 5/8 of the CUs 64x64 tiles would run, two to a row
-    return (pr.M >= 131072 && pr.K > 32) || (norm != FGE_NORM_NONE && whole * 8 < (int64_t)num_cu() * 5);
+    if (norm != FGE_NORM_NONE && whole * 8 < (int64_t)num_cu() * 5) return pr.M > (full ? (lse ? 16384 : 9000) : lse ? 8192 : 5000);
+    return pr.K > 32 && pr.M >= (full && norm != FGE_NORM_NONE ? 262144 : 131072);
 }
 
 // two_pass: finish split rows with the second kernel even where the cooperative form exists
