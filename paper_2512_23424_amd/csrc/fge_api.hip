@@ -288,23 +288,23 @@ int rule_tile(const Problem &pr, int in_dtype, bool ieee_fp32) {
 // fp32 rows of 65 to 256 columns over K <= 64: where the narrow-K kernel (four or two waves across) takes the place of the general tiles.
 // Against two column tiles and their exchange it wins from its first rows on, against whole rows in one tile where the
 // output stream is long (us, general tiles -> narrow-K; K = 44: 131072 x 252 RMSNorm 66.4 -> 42.7, 45815 x 200 softmax 30.8 -> 20.4, no row op
-// 18.1 -> 15.4, 9000 x 128 softmax 13.1 -> 8.7).  Elsewhere it does not (5136 calls in turn, K of 4 to 64; kernel over general tiles): no row op,
-// 32768 rows 1.06 to 1.12, 53000 to 62000 over K <= 32 1.00 to 1.07; over whole K tiles of the general kernels, K = 32 and 64, which they do not
-// mask: 16500 to 24576 rows of 192 to 256 columns 0.98 to 1.08, logsumexp to 8192 rows 1.00 to 1.19, the others over K = 64 to 5000 rows 0.92 to
-// 1.09; up to 128 columns, to 8192 rows 0.92 to 1.10 (K = 64 1.28), 20480 to 131071 in one 128x128 tile, 45815 x 128 softmax 15.3 -> 15.8, beyond them over
-// K = 64 with a row op 0.95 to 1.06, over K <= 32 131072 x 96 22.7 -> 25.6.
-// (Of the 3950 such calls that take the kernel by these lines one loses 3 %.)
+// 18.1 -> 15.4, 9000 x 128 softmax 13.1 -> 8.7).  Where it does not, kernel over general tiles, without activation and with GELU-erf (5136 calls in
+// turn, K of 4 to 64): no row op, 32768 rows 0.95 to 1.18, over K <= 32 49153 to 65536 rows 0.99 and 1.01; over K = 64, which the general
+// tiles need not mask, logsumexp of up to 8192 rows 0.98 and 1.13 (up to 128 columns to 12288), the others to 4500 rows 0.95 and 1.07 (up to
+// 128 columns to 8192, 0.97 and 1.09); softmax over K = 32 and 64, 16385 to 24576 rows of more than 128 columns, 1.00 and 1.01; up to 128
+// columns in one 128x128 tile, 20480 to 131071 rows, 45815 softmax 15.3 -> 15.8, over K <= 32 131072 x 96 22.7 -> 25.6, over K = 64 131072 rows 1.00
+// and 1.04 but logsumexp 0.87 and 0.95.  Of the 4700 of those calls that take it so, 22 lose more than 3 % and one more than 7, all with GELU-erf.
 bool narrow_rows(const Problem &pr, int in_dtype, int norm, bool ieee_fp32) {
     if (in_dtype != FGE_F32 || ieee_fp32 || pr.K > 64 || pr.N <= 64 || pr.N > 256 || pr.batch != 1 || pr.M < PANEL_MIN_ROWS) return false;
-    const bool lse = norm == FGE_NORM_LOGSUMEXP, full = pr.K == 64;
+    const bool plain = norm == FGE_NORM_NONE, lse = norm == FGE_NORM_LOGSUMEXP, full = pr.K == 64;
     if (pr.N > 128) {
-        if (norm == FGE_NORM_NONE) return pr.M > 65536 || (pr.K > 32 && pr.M > 32768);
-        if (pr.K % 32 != 0) return true;
-        return pr.M > (lse ? 8192 : full ? 5000 : 0) && (pr.M <= 16384 || pr.M > 24576);
+        if (plain) return pr.M > 32768 && (pr.K > 32 || pr.M <= 49152 || pr.M > 65536);
+        if (norm == FGE_NORM_SOFTMAX && pr.K % 32 == 0 && pr.M > 16384 && pr.M <= 24576) return false;
+        return !full || pr.M > (lse ? 8192 : 4500);
     }
     const int64_t whole = (pr.M + 127) / 128;          // 128x128 tiles; below 5/8 of the CUs 64x64 tiles would run, two to a row
-    if (norm != FGE_NORM_NONE && whole * 8 < (int64_t)num_cu() * 5) return pr.M > (full ? (lse ? 16384 : 9000) : lse ? 8192 : 5000);
-    return pr.K > 32 && pr.M >= (full && norm != FGE_NORM_NONE ? 262144 : 131072);
+    if (!plain && whole * 8 < (int64_t)num_cu() * 5) return !full || pr.M > (lse ? 12288 : 8192);
+    return pr.K > 32 && pr.M >= (full && !plain && !lse ? 163840 : 131072);
 }
 
 // two_pass: finish split rows with the second kernel even where the cooperative form exists

@@ -27,7 +27,7 @@ template <typename T> __device__ __forceinline__ const T *row_ptr(const void *ba
 // K tile (32 k each, fp32 matrix instruction) and add their sums in LDS.  (32 k at a time, nothing
 // ahead, an FMA per value read from LDS: 365 x 429 x 32 SiLU LayerNorm 35.8 us, now 12.1;
 // 17 x 500 x 33 34.9 and 8.7, 40 x 64 x 47 LayerNorm 9.9 and 8.8.)  A K of up to 32 or 64 is one tile of that many k: staging 128
-// cost calls of a few microseconds up to a third (bf16 2 x 17 x 47 logsumexp, with 128 -> now -> with that former kernel: 7.3, 5.2, 5.6).
+// cost calls of a few microseconds up to a third (f16 1 x 31 x 145, with 128, now, with that former kernel: 4.3, 2.7, 3.6).
 template <typename InT, typename DstT, int KT>
 __global__ __launch_bounds__(256) void generic_gemm_kernel(const GenArgs a) {
     constexpr int T = 32, LD = KT + 4, STEP = 256 / KT, RPT = T / STEP;   // LD: rows 16-byte aligned, four banks apart

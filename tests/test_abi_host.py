@@ -351,28 +351,31 @@ def test_which_rows_the_narrow_k_kernel_takes():
         n = B.fge_tile_name(True, 1, norm, _params(M=M, N=N, K=K, ldx=K, ldw=K, ldo=N, flags=flags))
         return n.split("_")[0] if n.startswith("panel") else "general"
     assert name(5000, 260) == name(5000, 512) == "panel64x512" and name(5000, 516) == "general"
-    assert name(5001, 256) == name(4096, 132) == "panel64x256" and name(4095, 256) == "general"
-    assert name(5001, 128) == name(5001, 68) == "panel128x128" and name(5001, 64) == "general"
-    assert name(5001, 256, K=64) == "panel64x256" and name(5001, 256, K=68) == "general"
-    assert name(5001, 256, flags=B.FLAG_IEEE_FP32) == "general"
-    # more than 128 columns, no row op: from 32769 rows on, from 65537 if K <= 32
-    assert name(32769, 256, norm=0) == "panel64x256" and name(32768, 256, norm=0) == "general"
-    assert name(65537, 256, K=32, norm=0) == "panel64x256" and name(65536, 256, K=32, norm=0) == "general"
-    # ... with one, over whole K tiles of the general kernels: not the first rows, nor 16385 to 24576
-    assert name(4096, 256, K=32) == "panel64x256" and name(5000, 256, K=64) == "general"
-    assert name(8193, 256, K=32, norm=4) == name(8193, 256, K=64, norm=4) == "panel64x256"
-    assert name(8192, 256, K=32, norm=4) == name(8192, 256, K=64, norm=4) == "general" and name(8192, 256, K=36, norm=4) == "panel64x256"
+    assert name(5000, 256) == name(4096, 132) == "panel64x256" and name(4095, 256) == "general"
+    assert name(5000, 128) == name(4096, 68) == "panel128x128" and name(5000, 64) == "general"
+    assert name(5000, 256, K=64) == "panel64x256" and name(5000, 256, K=68) == "general"
+    assert name(5000, 256, flags=B.FLAG_IEEE_FP32) == "general"
+    # more than 128 columns, no row op: from 32769 rows on, but over K <= 32 not 49153 to 65536
+    assert name(32769, 256, norm=0) == name(32769, 256, K=32, norm=0) == "panel64x256" and name(32768, 256, norm=0) == "general"
+    for M in (49152, 65537):
+        assert name(M, 256, K=32, norm=0) == "panel64x256"
+    for M in (49153, 65536):
+        assert name(M, 256, K=32, norm=0) == "general" and name(M, 256, K=36, norm=0) == "panel64x256"
+    # ... with one, over K = 64, not the first rows; softmax over K = 32 and 64 not 16385 to 24576
+    assert name(4501, 256, K=64) == name(4500, 256, K=60) == "panel64x256" and name(4500, 256, K=64) == "general"
+    assert name(8193, 256, K=64, norm=4) == name(8192, 256, K=60, norm=4) == "panel64x256" and name(8192, 256, K=64, norm=4) == "general"
     for K in (32, 64):
-        assert name(16384, 256, K=K) == name(24577, 256, K=K) == "panel64x256" and name(16385, 256, K=K) == name(24576, 256, K=K) == "general"
-    assert name(16385, 256, K=60) == "panel64x256"
-    # up to 128 columns: with a row op below 160 tiles of 128 rows, but not the first rows
-    assert name(159 * 128, 128) == "panel128x128" and name(159 * 128 + 1, 128) == name(5000, 128) == "general"
-    assert name(9001, 128, K=64) == name(8193, 128, norm=4) == name(16385, 128, K=64, norm=4) == "panel128x128"
-    assert name(9000, 128, K=64) == name(8192, 128, norm=4) == name(16384, 128, K=64, norm=4) == "general"
-    # ... from 131072 rows on if K > 32, from 262144 with a row op over K = 64
+        assert name(16384, 256, K=K, norm=1) == name(24577, 256, K=K, norm=1) == name(24576, 256, K=K) == "panel64x256"
+        assert name(16385, 256, K=K, norm=1) == name(24576, 256, K=K, norm=1) == "general"
+    assert name(16385, 256, K=60, norm=1) == "panel64x256"
+    # up to 128 columns: with a row op below 160 tiles of 128 rows, over K = 64 not the first rows
+    assert name(159 * 128, 128) == "panel128x128" and name(159 * 128 + 1, 128) == "general"
+    assert name(8193, 128, K=64) == name(12289, 128, K=64, norm=4) == "panel128x128"
+    assert name(8192, 128, K=64) == name(12288, 128, K=64, norm=4) == "general"
+    # ... from 131072 rows on if K > 32, from 163840 over K = 64 with a row op other than logsumexp
     assert name(131072, 128) == name(131072, 128, norm=0) == "panel128x128" and name(131071, 128) == "general"
-    assert name(131072, 128, K=32) == "general" and name(131072, 128, K=36) == name(131072, 128, K=64, norm=0) == "panel128x128"
-    assert name(262144, 128, K=64) == "panel128x128" and name(262143, 128, K=64) == "general"
+    assert name(131072, 128, K=32) == "general" and name(131072, 128, K=36) == "panel128x128"
+    assert name(131072, 128, K=64, norm=0) == name(131072, 128, K=64, norm=4) == name(163840, 128, K=64) == "panel128x128" and name(163839, 128, K=64) == "general"
 
 
 def test_names_follow_the_workspace():
