@@ -52,8 +52,8 @@
  * 16-byte units and runs the fast kernels on those (fge_tile_name reports "repacked_operands";
  * when the result's own extents or strides are odd too, it passes through fp32 rows of padded
  * width and an element-granular row kernel); small problems, the stage entry points, the unfused
- * sequence and calls whose workspace only covers it run element-granular kernels (plain fp32 FMA,
- * not tuned; "generic32x32_scalar").  out must not alias X or W.
+ * sequence and calls whose workspace only covers it run element-granular kernels (fp32 products
+ * and sums; "generic32x32_scalar").  out must not alias X or W.
  */
 #ifndef FGE_H
 #define FGE_H
@@ -246,7 +246,7 @@ size_t fge_fault_word_offset(int act, int norm, const fge_params *p);
  * the unfused sequence: two GEMMs into the workspace (fp32 operands always on the fp32 matrix
  * instruction here: the gate multiplies two products and their errors), the gate as an
  * elementwise kernel, the row operation.  A small problem with a long K (at most 96 of the gated
- * kernel's 256 x 128 tiles, K >= 1024) runs as fp32 partial products of both GEMMs instead (K cut
+ * kernel's 256 x 128 tiles, K >= 1024) whose tiles are not shared runs as fp32 partial products of both GEMMs instead (K cut
  * into slices where fused_gemm_epilogue would cut it), one kernel that adds the slices and
  * applies scale, bias, activation and gate, and the row operation on that fp32 result - when
  * the workspace has the room, else the tile kernel.  fge_gated_workspace_bytes gives the
